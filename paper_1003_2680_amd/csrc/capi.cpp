@@ -320,6 +320,7 @@ int gen_level_noise(Run& r, int only_level = -1, int only_slot = 0) {
 BotArgs make_botargs(Hierarchy& h) {
   BotArgs a{};
   const bool f32 = refined(h);
+  const size_t ts = f32 ? sizeof(float) : sizeof(double);
   a.nlev = (int)h.lv.size() - h.bottom;
   a.level0 = h.bottom;
   a.nu1 = h.prm.nu1;
@@ -329,7 +330,7 @@ BotArgs make_botargs(Hierarchy& h) {
   for (int i = 0; i < a.nlev; ++i) {
     const Level& v = h.lv[h.bottom + i];
     int sy, sz;
-    bot_strides(v.kind, v.nx, v.ny, sy, sz);
+    bot_strides(v.kind, v.nx, v.ny, ts, sy, sz);
     BotLevel& bl = a.lv[i];
     bl.nx = v.nx;
     bl.ny = v.ny;
@@ -342,12 +343,12 @@ BotArgs make_botargs(Hierarchy& h) {
     bl.zt = v.zt_d;
     bl.bfac = v.bfac_d;
     a.lds_off[i] = off;
-    off += 3 * (int)bot_field_elems(v.kind, v.nx, v.ny, v.nz);
+    off += (int)bot_level_elems(v.kind, v.nx, v.ny, v.nz, ts);
   }
   for (int i = 0; i < a.nlev; ++i) {
     const Level& v = h.lv[h.bottom + i];
     a.tab_off[i] = off;
-    if (v.kind == KIND_BLOCK) off += v.nz * 10 + (v.nz / 2) * 192;
+    if (v.kind == KIND_BLOCK) off += (int)bot_table_elems(v.nz);
   }
   Level& b0 = h.lv[h.bottom];
   a.b_in = f32 ? (const void*)b0.bf : (const void*)b0.b;

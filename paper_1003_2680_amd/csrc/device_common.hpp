@@ -12,11 +12,6 @@ constexpr int TPB = 256;
 
 __device__ __forceinline__ int wrapm(int v, int n) { return v < 0 ? v + n : (v >= n ? v - n : v); }
 
-// padded LDS strides (doubles) of an nx x ny x nz field
-__host__ __device__ inline int lds_sy(int nx) { return nx + 2; }
-__host__ __device__ inline int lds_sz(int nx, int ny) { return ny * (nx + 2) + 1; }
-__host__ __device__ inline int lds_field(int nx, int ny, int nz) { return nz * lds_sz(nx, ny); }
-
 // Quotient and remainder by d, using a shift when d is a power of two (lg2 >= 0).
 __device__ __forceinline__ uint32_t udiv(uint32_t a, uint32_t d, int lg2) {
   return lg2 >= 0 ? (a >> lg2) : a / d;
@@ -165,38 +160,6 @@ __device__ __forceinline__ void gal_plane_pair(const T* __restrict__ P, int sy, 
   q1 = o1 + dpp_xor2(p1);
 }
 
-// UNROLL_Z: all five planes in flight at once (global-memory operands, where load latency
-// dominates); otherwise one plane at a time (LDS operands, fewer registers).
-template <typename T, bool UNROLL_Z = false>
-__device__ __forceinline__ T gal_apply(const T* __restrict__ X, int sy, int sz, const T* s1d,
-                                       const T* __restrict__ zt, int nx, int ny, int nz, int cx,
-                                       int cy, int cz) {
-  const T* zr = zt + cz * 10;
-  int xs[5], ys[5];
-#pragma unroll
-  for (int d = 0; d < 5; ++d) {
-    xs[d] = wrapm(cx + d - 2, nx);
-    ys[d] = wrapm(cy + d - 2, ny);
-  }
-  T acc0 = 0, acc1 = 0;
-  auto plane = [&](int dz) {
-    int zz = cz + dz - 2;
-    zz = zz < 0 ? 0 : (zz >= nz ? nz - 1 : zz);
-    T p1;
-    const T p0 = gal_plane<T>(X + (size_t)zz * sz, sy, xs, ys, s1d, p1);
-    acc0 = fma(zr[dz], p0, acc0);
-    acc1 = fma(zr[5 + dz], p1, acc1);
-  };
-  if constexpr (UNROLL_Z) {
-#pragma unroll
-    for (int dz = 0; dz < 5; ++dz) plane(dz);
-  } else {
-#pragma unroll 1
-    for (int dz = 0; dz < 5; ++dz) plane(dz);
-  }
-  return acc0 + acc1;
-}
-
 // The two z-layers of a 2x2x2 block see six Galerkin planes between them; lane kz of a block
 // reduces planes 3kz .. 3kz+2 (q) and receives its partner's three (o).  The cell's own
 // window of five planes (dz = 0 .. 4, i.e. planes kz .. kz+4) is then one select per entry
@@ -210,82 +173,6 @@ __device__ __forceinline__ void plane_window(int kz, const T (&q)[3], const T (&
   w[2] = kz ? q[0] : q[2];
   w[3] = kz ? q[1] : o[0];
   w[4] = kz ? q[2] : o[1];
-}
-
-// Block heat-bath lane: lane k (0..7) of 2x2x2 block (bx,by,bz) returns its new value
-//   x_B[k] = sum_j A_BB^-1[k][j] rhs_j + sqrt(kT) sum_j L_BB^-T[k][j] n_j,
-//   rhs_j  = b_j - (A x)_j + sum_i A_BB[j][i] x_B[i]   (= b_j - A_{j,rest} x_rest).
-// The eight lanes of a block must be consecutive lanes of one wave (shuffle width 8) and all
-// lanes of the wave must call this together; inactive lanes pass active = false.
-// The lane's noise comes from a pregenerated field Z (natural layout of the level, one value
-// per cell and sweep): the block's normals already multiplied by sqrt(kT) L_BB^-T.
-template <typename T, bool NOISE>
-__device__ __forceinline__ T block_lane(const T* __restrict__ X, int sy, int sz,
-                                        const T* __restrict__ Bv, const T* s1d,
-                                        const T* __restrict__ zt, const T* __restrict__ bfac,
-                                        int nx, int ny, int nz, int bx, int by, int bz, int k,
-                                        bool active, const T* __restrict__ Z,
-                                        uint32_t& cell_out) {
-  const int cx = 2 * bx + (k & 1);
-  const int cy = 2 * by + ((k >> 1) & 1);
-  const int cz = 2 * bz + (k >> 2);
-  const uint32_t cell = (uint32_t)cz * sz + (uint32_t)cy * sy + cx;
-  cell_out = cell;
-  T ax = 0, xk = 0, bk = 0, nrm = 0;
-  if (active) {
-    if (NOISE) nrm = Z[((uint32_t)cz * ny + cy) * nx + cx];
-    xk = X[cell];
-    bk = Bv[cell];
-  }
-  {
-    // The block's two z-layers reach the same six planes 2bz-2 .. 2bz+3 (clamped at the
-    // walls, where their factors vanish): lane kz reduces planes 3kz .. 3kz+2 and trades them
-    // with its partner lane ^ 4.  Every lane takes part (the shuffles need the partner).
-    const int kz = k >> 2;
-    int xs[5];
-#pragma unroll
-    for (int d = 0; d < 5; ++d) xs[d] = wrapm(cx + d - 2, nx);
-    const int ky = (k >> 1) & 1;
-    int rows[3];
-#pragma unroll
-    for (int i = 0; i < 3; ++i) rows[i] = wrapm(cy + (ky ? 2 - i : i - 2), ny);
-    T q0[3], q1[3];
-#pragma unroll
-    for (int j = 0; j < 3; ++j) {
-      int pz = 2 * bz - 2 + 3 * kz + j;
-      pz = pz < 0 ? 0 : (pz >= nz ? nz - 1 : pz);
-      gal_plane_pair<T>(X + (size_t)pz * sz, sy, xs, rows, s1d, q0[j], q1[j]);
-    }
-    T o0[3], o1[3], w0[5], w1[5];
-#pragma unroll
-    for (int j = 0; j < 3; ++j) {
-      o0[j] = __shfl_xor(q0[j], 4, 8);
-      o1[j] = __shfl_xor(q1[j], 4, 8);
-    }
-    plane_window(kz, q0, o0, w0);
-    plane_window(kz, q1, o1, w1);
-    if (active) {
-      const T* zr = zt + cz * 10;
-      T acc0 = 0, acc1 = 0;
-#pragma unroll
-      for (int dz = 0; dz < 5; ++dz) {
-        acc0 = fma(zr[dz], w0[dz], acc0);
-        acc1 = fma(zr[5 + dz], w1[dz], acc1);
-      }
-      ax = acc0 + acc1;
-    }
-  }
-  // x_B + A_BB^-1 (b_B - (A x)_B) equals A_BB^-1 (b_B - A_B,rest x_rest): the block's own
-  // coupling cancels, so only the residual needs to be shared across the block's lanes
-  const T* F = bfac + (size_t)(active ? bz : 0) * 192;
-  const T res = bk - ax;
-  T v0 = xk, v1 = NOISE ? nrm : T(0);
-#pragma unroll
-  for (int j = 0; j < 8; j += 2) {
-    v0 = fma(F[k * 8 + j], __shfl(res, j, 8), v0);
-    v1 = fma(F[k * 8 + j + 1], __shfl(res, j + 1, 8), v1);
-  }
-  return v0 + v1;
 }
 
 // b_c = P^T r at coarse cell (X,Y,Z): 4x4x4 fine window 2J-1..2J+2 per axis, weights

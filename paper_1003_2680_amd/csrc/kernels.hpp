@@ -41,7 +41,7 @@ struct NoiseGenArgs {
 constexpr int kMaxBotLevels = 6;
 struct BotLevel {
   int nx, ny, nz, kind;
-  int sy, sz;          // LDS strides: padded for block levels, natural for the coarsest
+  int sy, sz;          // LDS strides of x: padded for block levels, natural for the coarsest
   const void* noise;   // T: pregenerated noise of this level [slot][ncomp][N] (block levels)
   double s1d[20];      // 1D stencils (m_x, a_x, m_y, a_y), offsets -2..2
   const void* zt;      // T: [nz][10]
@@ -58,24 +58,34 @@ struct BotArgs {
   const double* w;     // coarsest L_c^-1
 };
 
-// LDS strides of a bottom level: on the block levels rows are padded by 2 elements and
-// planes to the first count that is 16 mod 32 elements, which spreads a wave's reads of one
-// window offset (8 cells x 8 blocks, the two z-layers of a block three planes apart) over the
-// 64 banks; the coarsest stays natural.
-inline void bot_strides(int kind, int nx, int ny, int& sy, int& sz) {
+// LDS strides of a bottom level's x: on the block levels rows hold two halo cells per side (the
+// periodic copies) and two more of padding (2 mod 4 elements in all), and planes are padded so
+// that the lanes served together fall on different banks of the 32 four-byte ones.  FP64 reads
+// are served sixteen lanes at a time (two neighbouring blocks: x steps 0, 1, 4, 5; the y-partners
+// an odd number of rows apart, the z-partners three planes), which need distinct elements mod
+// 16: planes of 8 mod 16.  FP32 reads are served 32 lanes at a time: planes of 16 mod 32, which
+// put the z-partners of FP64 on one bank (a third of the LDS time of the 16^3 .. 4^3 bottom, 109
+// against 92 us; FP32 with planes of 8 mod 16 82 against 77 us).  The coarsest stays natural, as
+// do b and the scratch field of every level.
+constexpr int kBotHalo = 2;
+inline void bot_strides(int kind, int nx, int ny, size_t elem, int& sy, int& sz) {
   if (kind == KIND_BLOCK) {
-    sy = nx + 2;
-    sz = ny * sy + (48 - (ny * sy) % 32) % 32;
+    sy = nx + 2 * kBotHalo + 2;
+    const int p = ny * sy;
+    sz = elem == 8 ? p + (24 - p % 16) % 16 : p + (48 - p % 32) % 32;
   } else {
     sy = nx;
     sz = nx * ny;
   }
 }
-inline size_t bot_field_elems(int kind, int nx, int ny, int nz) {
+// elements of a level's fields: x in these strides, b and scratch natural
+inline size_t bot_level_elems(int kind, int nx, int ny, int nz, size_t elem) {
   int sy, sz;
-  bot_strides(kind, nx, ny, sy, sz);
-  return (size_t)nz * sz;
+  bot_strides(kind, nx, ny, elem, sy, sz);
+  return (size_t)nz * sz + 2 * (size_t)nx * ny * nz;
 }
+// elements of a block level's tables (z-factors and A_BB^-1)
+inline size_t bot_table_elems(int nz) { return (size_t)nz * 10 + (size_t)(nz / 2) * 64; }
 
 template <typename T>
 hipError_t launch_rb_pass(T* xc, const T* xo, const T* bc, int nx, int ny, int nz, int ncomp,

@@ -1,5 +1,5 @@
-// Galerkin-level kernels: 2x2x2 block heat bath, residual, restriction, prolongation, the
-// coarsest exact draw, and the LDS-resident bottom of the V-cycle.
+// Galerkin-level kernels: 2x2x2 block heat bath, residual, restriction, prolongation and the
+// coarsest exact draw (the LDS-resident bottom of the V-cycle is in kernels_bottom.hip).
 //
 // Sec. "Stochastic Multigrid Methods": the coarse operators are Galerkin, A^(l+1) = P^T A^(l) P,
 // which makes them 81-point (level 1) and 125-point (deeper) stencils.  Two cells of one
@@ -547,209 +547,6 @@ __global__ __launch_bounds__(TPB) void k_coarsest(T* __restrict__ xg, const T* _
   xg[(size_t)comp * n + row] = (T)acc;
 }
 
-// ----------------------------------------------------------------------------- bottom of the V
-// One work-group per component runs every level from the bottom level down to the coarsest
-// and back up, with x, b and a scratch field of each level in LDS; only b of the bottom level
-// comes from global memory and only its x goes back.  Colour passes are separated by
-// work-group barriers instead of kernel launches.  The coarsest draw is FP64 in every mode.
-constexpr int BOT_TPB = 512;
-
-template <typename T, bool NOISE>
-__device__ __forceinline__ void bot_block_pass(T* X, const T* Bv, const BotLevel& L, const T* tab,
-                                               int colour, const T* Z) {
-  // the 1D stencils are the same for every lane: scalar loads from the level descriptor
-  T s1d[20];
-#pragma unroll
-  for (int q = 0; q < 20; ++q) s1d[q] = (T)L.s1d[q];
-  const T* zt = tab;
-  const T* bfac = tab + L.nz * 10;
-  const int nbx2 = L.nx / 4, nby2 = L.ny / 4;
-  const int nbzc = (L.nz / 2 + 1 - (colour >> 2)) / 2;
-  const int total = nbx2 * nby2 * nbzc * 8;
-#pragma unroll 1
-  for (int base = 0; base < total; base += BOT_TPB) {
-    const int t = base + (int)threadIdx.x;
-    const bool active = t < total;
-    const int k = t & 7;
-    const int blk = active ? (t >> 3) : 0;
-    const int i = blk % nbx2;
-    const int rest = blk / nbx2;
-    const int j = rest % nby2;
-    const int l = rest / nby2;
-    uint32_t cell;
-    const T v = block_lane<T, NOISE>(X, L.sy, L.sz, Bv, s1d, zt, bfac, L.nx, L.ny, L.nz,
-                                     2 * i + (colour & 1), 2 * j + ((colour >> 1) & 1),
-                                     2 * l + (colour >> 2), k, active, Z, cell);
-    if (active) X[cell] = v;
-  }
-  __syncthreads();
-}
-
-template <typename T, bool NOISE>
-__device__ __forceinline__ void bot_sweep(T* X, const T* Bv, const BotLevel& L, const T* tab,
-                                          int slot, bool post, int ncomp, uint32_t comp) {
-  const int n = L.nx * L.ny * L.nz;
-  const T* Z = NOISE ? (const T*)L.noise + ((size_t)slot * ncomp + comp) * n : nullptr;
-#pragma unroll 1
-  for (int t = 0; t < 8; ++t) {
-    const int colour = post ? 7 - t : t;
-    bot_block_pass<T, NOISE>(X, Bv, L, tab, colour, Z);
-  }
-}
-
-__device__ __forceinline__ int bot_pos(const BotLevel& L, int q) {
-  const int x = q % L.nx, r = q / L.nx;
-  const int y = r % L.ny, z = r / L.ny;
-  return z * L.sz + y * L.sy + x;
-}
-
-template <typename T, bool NOISE>
-__device__ __forceinline__ void bottom_body(const BotArgs& a, const uint32_t comp,
-                                            const NoiseArgs& na) {
-  extern __shared__ char smraw[];
-  T* sm = reinterpret_cast<T*>(smraw);
-  const int tid = threadIdx.x;
-  const BotLevel& L0 = a.lv[0];
-  const int n0 = L0.nx * L0.ny * L0.nz;
-  const int f0 = L0.nz * L0.sz;
-  for (int q = tid; q < f0; q += BOT_TPB) sm[a.lds_off[0] + q] = T(0);
-  __syncthreads();
-  for (int q = tid; q < n0; q += BOT_TPB)
-    sm[a.lds_off[0] + f0 + bot_pos(L0, q)] = ((const T*)a.b_in)[(size_t)comp * n0 + q];
-  // operator tables of the block levels: [zt nz*10][bfac nz/2*192] at tab_off[i]
-  for (int i = 0; i < a.nlev; ++i) {
-    if (a.lv[i].kind != KIND_BLOCK) continue;
-    const int nz = a.lv[i].nz;
-    T* t = sm + a.tab_off[i];
-    const T* zt = (const T*)a.lv[i].zt;
-    const T* bf = (const T*)a.lv[i].bfac;
-    for (int q = tid; q < nz * 10; q += BOT_TPB) t[q] = zt[q];
-    for (int q = tid; q < (nz / 2) * 192; q += BOT_TPB) t[nz * 10 + q] = bf[q];
-  }
-  __syncthreads();
-  int last = a.nlev - 1;
-  for (int i = 0; i < a.nlev; ++i) {
-    const BotLevel& L = a.lv[i];
-    const int level = a.level0 + i;
-    const int n = L.nx * L.ny * L.nz;
-    const int f = L.nz * L.sz;
-    T* xi = sm + a.lds_off[i];
-    T* bi = xi + f;
-    T* ri = bi + f;
-    if (L.kind == KIND_CHOL) {
-      // exact draw x = A_c^-1 b + sqrt(kT) L_c^-T n (natural layout on this level)
-      if (NOISE) {
-        const uint32_t sid = (uint32_t)level | (1u << 24);
-        for (int q = tid; 2 * q < n; q += BOT_TPB) {
-          double z0, z1;
-          normal_pair(na, sid, comp, (uint32_t)q, z0, z1);
-          ri[2 * q] = (T)z0;
-          if (2 * q + 1 < n) ri[2 * q + 1] = (T)z1;
-        }
-        __syncthreads();
-      }
-      // G lanes per row (a power of two, G <= 32) split the columns, so that every lane has
-      // only n/G loads of the dense factors in its chain; their sums meet by shuffles
-      int G = 1;
-      while (G < 32 && 2 * G * n <= BOT_TPB) G *= 2;
-      const int part = tid % G;
-      for (int row = tid / G; row < n; row += BOT_TPB / G) {
-        double acc = 0.0, an = 0.0;
-        for (int jj = part; jj < n; jj += G) {
-          acc = fma(a.ainv[(size_t)jj * n + row], (double)bi[jj], acc);
-          if (NOISE && jj >= row) an = fma(a.w[(size_t)jj * n + row], (double)ri[jj], an);
-        }
-        for (int off = G / 2; off >= 1; off >>= 1) {
-          acc += __shfl_xor(acc, off, G);
-          if (NOISE) an += __shfl_xor(an, off, G);
-        }
-        if (NOISE) acc = fma(na.sqkT, an, acc);
-        if (part == 0) xi[row] = (T)acc;
-      }
-      __syncthreads();
-      last = i;
-      break;
-    }
-    const T* tab = sm + a.tab_off[i];
-    for (int s = 0; s < a.nu1; ++s)
-      bot_sweep<T, NOISE>(xi, bi, L, tab, s, false, a.ncomp, comp);
-    if (i == a.nlev - 1) {
-      // smoothing-only coarsest level: the post-sweeps follow at once
-      for (int s = 0; s < a.nu2; ++s)
-        bot_sweep<T, NOISE>(xi, bi, L, tab, a.nu1 + s, true, a.ncomp, comp);
-      last = i;
-      break;
-    }
-    // b_{i+1} = P^T (b_i - A_i x_i), x_{i+1} = 0
-    {
-      T s1d[20];
-#pragma unroll
-      for (int q = 0; q < 20; ++q) s1d[q] = (T)L.s1d[q];
-      for (int q = tid; q < n; q += BOT_TPB) {
-        const int x = q % L.nx, y = (q / L.nx) % L.ny, z = q / (L.nx * L.ny);
-        const int p = z * L.sz + y * L.sy + x;
-        ri[p] = bi[p] - gal_apply<T>(xi, L.sy, L.sz, s1d, tab, L.nx, L.ny, L.nz, x, y, z);
-      }
-    }
-    __syncthreads();
-    const BotLevel& C = a.lv[i + 1];
-    const int nc = C.nx * C.ny * C.nz;
-    const int fc = C.nz * C.sz;
-    T* xc = sm + a.lds_off[i + 1];
-    for (int q = tid; q < fc; q += BOT_TPB) xc[q] = T(0);
-    for (int q = tid; q < nc; q += BOT_TPB) {
-      const int X = q % C.nx, Y = (q / C.nx) % C.ny, Z = q / (C.nx * C.ny);
-      xc[fc + Z * C.sz + Y * C.sy + X] = restrict_at<T>(ri, L.sy, L.sz, L.nx, L.ny, L.nz, X, Y, Z);
-    }
-    __syncthreads();
-  }
-  for (int i = last - 1; i >= 0; --i) {
-    const BotLevel& L = a.lv[i];
-    const BotLevel& C = a.lv[i + 1];
-    const int n = L.nx * L.ny * L.nz;
-    T* xi = sm + a.lds_off[i];
-    const T* xc = sm + a.lds_off[i + 1];
-    for (int q = tid; q < n; q += BOT_TPB) {
-      const int x = q % L.nx, y = (q / L.nx) % L.ny, z = q / (L.nx * L.ny);
-      xi[z * L.sz + y * L.sy + x] += prolong_at<T>(xc, C.sy, C.sz, x, y, z, C.nx, C.ny, C.nz);
-    }
-    __syncthreads();
-    for (int s = 0; s < a.nu2; ++s)
-      bot_sweep<T, NOISE>(xi, xi + L.nz * L.sz, L, sm + a.tab_off[i], a.nu1 + s, true, a.ncomp,
-                          comp);
-  }
-  for (int q = tid; q < n0; q += BOT_TPB)
-    ((T*)a.x_out)[(size_t)comp * n0 + q] = sm[a.lds_off[0] + bot_pos(L0, q)];
-}
-
-// One hierarchy, one work-group per component.
-template <typename T, bool NOISE>
-__global__ __launch_bounds__(BOT_TPB) void k_bottom(const BotArgs* __restrict__ ap, int c0,
-                                                    NoiseArgs na) {
-  bottom_body<T, NOISE>(*ap, c0 + (int)blockIdx.x, na);
-}
-
-// Several hierarchies (of any sizes) in one launch: work-group w runs component wg >> 16 of
-// item wg & 0xffff, with that item's level descriptors and noise keys, so the latency-bound
-// bottoms of uneven instances overlap instead of running one launch after another.
-template <typename T, bool NOISE>
-__global__ __launch_bounds__(BOT_TPB) void k_bottom_multi(BotMultiArgs m) {
-  const uint32_t w = m.wg[blockIdx.x];
-  const BotMultiItem& it = m.it[w & 0xffffu];
-  NoiseArgs na;
-  na.k0 = it.k0;
-  na.k1 = it.k1;
-  na.sid = 0;
-  na.c2 = it.c2;
-  na.c3 = it.c3;
-  na.sqkT = it.sqkT;
-  na.chains = it.chains;
-  na.comps_per_chain = it.cpc;
-  na.cpc_magic = it.cpc_magic;
-  na.bm = m.bm;
-  bottom_body<T, NOISE>(*it.args, w >> 16, na);
-}
-
 }  // namespace
 
 template <typename T, int TI, int TJ>
@@ -1014,44 +811,6 @@ hipError_t launch_level_noise(const NoiseGenArgs& a, const NoiseArgs& na, hipStr
   return hipGetLastError();
 }
 
-template <typename T>
-hipError_t launch_bottom(const BotArgs* a, int ncomp, int c0, size_t lds, bool noise,
-                         const NoiseArgs& na, hipStream_t s) {
-  static bool attr_set = false;
-  if (!attr_set) {
-    hipError_t e = hipFuncSetAttribute((const void*)k_bottom<T, true>,
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
-    if (e == hipSuccess)
-      e = hipFuncSetAttribute((const void*)k_bottom<T, false>,
-                              hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
-    if (e != hipSuccess) return e;
-    attr_set = true;
-  }
-  if (noise) k_bottom<T, true><<<ncomp, BOT_TPB, lds, s>>>(a, c0, na);
-  else k_bottom<T, false><<<ncomp, BOT_TPB, lds, s>>>(a, c0, na);
-  return hipGetLastError();
-}
-
-template <typename T>
-hipError_t launch_bottom_multi(const BotMultiArgs& m, int nwg, size_t lds, bool noise,
-                               hipStream_t s) {
-  static bool attr_set = false;
-  if (!attr_set) {
-    hipError_t e = hipFuncSetAttribute((const void*)k_bottom_multi<T, true>,
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
-    if (e == hipSuccess)
-      e = hipFuncSetAttribute((const void*)k_bottom_multi<T, false>,
-                              hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
-    if (e != hipSuccess) return e;
-    attr_set = true;
-  }
-  if (nwg <= 0) return hipSuccess;
-  if (nwg > kBotMultiWG || m.nitems > kBotMultiItems) return hipErrorInvalidValue;
-  if (noise) k_bottom_multi<T, true><<<nwg, BOT_TPB, lds, s>>>(m);
-  else k_bottom_multi<T, false><<<nwg, BOT_TPB, lds, s>>>(m);
-  return hipGetLastError();
-}
-
 #define SMG_INST(T)                                                                            \
   template hipError_t launch_block_pass<T>(T*, const T*, const T*, const T*, const T*, int, int, \
                                            int, int, int, const T*, int, hipStream_t);          \
@@ -1067,10 +826,7 @@ hipError_t launch_bottom_multi(const BotMultiArgs& m, int nwg, size_t lds, bool 
   template hipError_t launch_prolong<T>(T*, const T*, int, int, int, int, hipStream_t);         \
   template hipError_t launch_coarsest<T>(T*, const T*, const double*, const double*, int, int,  \
                                          bool, const NoiseArgs&, hipStream_t);                  \
-  template hipError_t launch_level_noise<T>(const NoiseGenArgs&, const NoiseArgs&, hipStream_t); \
-  template hipError_t launch_bottom<T>(const BotArgs*, int, int, size_t, bool,                 \
-                                       const NoiseArgs&, hipStream_t);                           \
-  template hipError_t launch_bottom_multi<T>(const BotMultiArgs&, int, size_t, bool, hipStream_t);
+  template hipError_t launch_level_noise<T>(const NoiseGenArgs&, const NoiseArgs&, hipStream_t);
 SMG_INST(double)
 SMG_INST(float)
 #undef SMG_INST

@@ -422,8 +422,8 @@ int build_plan(const smg_grid_desc& d, const smg_cycle_params& p, Hierarchy& h, 
     size_t lds = 0;
     for (int m = l; m < L; ++m) {
       const Level& v = h.lv[m];
-      lds += 3 * bot_field_elems(v.kind, v.nx, v.ny, v.nz) * ts;
-      if (v.kind == KIND_BLOCK) lds += ((size_t)v.nz * 10 + (size_t)(v.nz / 2) * 192) * ts;
+      lds += bot_level_elems(v.kind, v.nx, v.ny, v.nz, ts) * ts;
+      if (v.kind == KIND_BLOCK) lds += bot_table_elems(v.nz) * ts;
     }
     if (lds <= kBottomLdsMax && L - l <= kBottomLevelsMax) {
       h.bottom = l;
