@@ -342,6 +342,8 @@ BotArgs make_botargs(Hierarchy& h) {
     for (int q = 0; q < 20; ++q) bl.s1d[q] = v.s1d.empty() ? 0.0 : v.s1d[q];
     bl.zt = v.zt_d;
     bl.bfac = v.bfac_d;
+    bl.xg = f32 ? (void*)v.xf : (void*)v.x;
+    bl.bg = f32 ? (void*)v.bf : (void*)v.b;
     a.lds_off[i] = off;
     off += (int)bot_level_elems(v.kind, v.nx, v.ny, v.nz, ts);
   }
@@ -358,15 +360,31 @@ BotArgs make_botargs(Hierarchy& h) {
   return a;
 }
 
-// Every level from h.bottom down, in one launch (LDS-resident, one work-group per component).
+// The bottom's block levels are in front of a coarsest draw that takes a launch of its own.
+bool splits_bottom(const Hierarchy& h) {
+  return h.wide_coarsest && h.lv[h.bottom].kind == KIND_BLOCK;
+}
+
+// Every level from h.bottom down: in one launch (LDS-resident, one work-group per component), or
+// in two around the coarsest draw's own where that level is large; a bottom that is the coarsest
+// level alone is that draw.
 template <typename T>
 int bottom_cycle(Run& r) {
   Hierarchy& h = *r.h;
   NoiseArgs na = make_noise(r, 0, 0, 0, KIND_SMOOTH_NOISE);
   na.comp0 = 0;  // this kernel numbers components absolutely (from c0)
+  const int last = (int)h.lv.size() - 1;
   TimedScope ts(h, r.s, SMG_TIMED_BOTTOM, 1);
   SMG_TRY(ts.rc);
-  SMG_HIP(launch_bottom<T>(h.botargs_d, r.nc, r.c0, h.bottom_lds, r.noise, na, r.s));
+  if (h.lv[h.bottom].kind == KIND_CHOL) {
+    SMG_TRY(coarsest_step<T>(r, last));
+  } else if (splits_bottom(h)) {
+    SMG_HIP(launch_bottom<T>(h.botargs_d, r.nc, r.c0, h.bottom_lds, r.noise, BOT_DOWN, na, r.s));
+    SMG_TRY(coarsest_step<T>(r, last));
+    SMG_HIP(launch_bottom<T>(h.botargs_d, r.nc, r.c0, h.bottom_lds, r.noise, BOT_UP, na, r.s));
+  } else {
+    SMG_HIP(launch_bottom<T>(h.botargs_d, r.nc, r.c0, h.bottom_lds, r.noise, BOT_WHOLE, na, r.s));
+  }
   return ts.close();
 }
 
@@ -617,7 +635,8 @@ int full_cycle(Run& r, bool residual_ready = false) {
 
 // The LDS-resident bottoms of every run that has one, in as few launches as possible (one per
 // sweep precision and noise setting, up to kBotMultiItems hierarchies and kBotMultiWG
-// components each; a run with more components takes a launch of its own).
+// components each; a run with more components takes launches of its own).  Runs with a wide
+// coarsest draw go down with the others, make their draws in a launch each, and go up together.
 int batch_bottoms(const std::vector<Run*>& runs) {
   for (int f32 = 0; f32 < 2; ++f32)
     for (int nz = 0; nz < 2; ++nz) {
@@ -639,15 +658,8 @@ int batch_bottoms(const std::vector<Run*>& runs) {
         lds = 0;
         return SMG_OK;
       };
-      for (Run* r : runs) {
+      auto add = [&](Run* r, int part) -> int {
         Hierarchy& h = *r->h;
-        if (!split_bottom(h) || (int)refined(h) != f32 || (int)r->noise != nz) continue;
-        if (r->nc > kBotMultiWG) {  // more components than one launch holds: its own launch
-          Run ri = *r;
-          ri.has_b0 = ri.has_b0 || refined(h);
-          SMG_TRY(f32 ? bottom_cycle<float>(ri) : bottom_cycle<double>(ri));
-          continue;
-        }
         if (m.nitems == kBotMultiItems || nwg + r->nc > kBotMultiWG) SMG_TRY(flush());
         const NoiseArgs na = make_noise(*r, 0, 0, 0, KIND_SMOOTH_NOISE);
         BotMultiItem& it = m.it[m.nitems];
@@ -659,6 +671,7 @@ int batch_bottoms(const std::vector<Run*>& runs) {
         it.chains = na.chains;
         it.cpc = na.comps_per_chain;
         it.cpc_magic = na.cpc_magic;
+        it.part = part;
         it.sqkT = na.sqkT;
         // the bottom numbers components absolutely (its noise keys take the chain table as is)
         for (int c = r->c0; c < r->c0 + r->nc; ++c)
@@ -666,7 +679,28 @@ int batch_bottoms(const std::vector<Run*>& runs) {
         ++m.nitems;
         lds = std::max(lds, h.bottom_lds);
         s = r->s;
+        return SMG_OK;
+      };
+      std::vector<Run*> wide;
+      for (Run* r : runs) {
+        Hierarchy& h = *r->h;
+        if (!split_bottom(h) || (int)refined(h) != f32 || (int)r->noise != nz) continue;
+        if (r->nc > kBotMultiWG || h.lv[h.bottom].kind == KIND_CHOL) {  // launches of its own
+          Run ri = *r;
+          ri.has_b0 = ri.has_b0 || refined(h);
+          SMG_TRY(f32 ? bottom_cycle<float>(ri) : bottom_cycle<double>(ri));
+          continue;
+        }
+        const bool w = splits_bottom(h);
+        if (w) wide.push_back(r);
+        SMG_TRY(add(r, w ? BOT_DOWN : BOT_WHOLE));
       }
+      SMG_TRY(flush());
+      for (Run* r : wide) {
+        const int last = (int)r->h->lv.size() - 1;
+        SMG_TRY(f32 ? coarsest_step<float>(*r, last) : coarsest_step<double>(*r, last));
+      }
+      for (Run* r : wide) SMG_TRY(add(r, BOT_UP));
       SMG_TRY(flush());
     }
   return SMG_OK;

@@ -46,7 +46,12 @@ struct BotLevel {
   double s1d[20];      // 1D stencils (m_x, a_x, m_y, a_y), offsets -2..2
   const void* zt;      // T: [nz][10]
   const void* bfac;    // T: [nz/2][3][64]
+  void* xg;            // T [ncomp][n]: the level's x and b in memory, where the two parts of a
+  void* bg;            // split bottom leave and find them
 };
+// What a bottom launch runs: everything, or the two halves around a coarsest draw that the whole
+// chip makes (launch_coarsest): down to its right-hand side, and up from its result.
+enum BotPart { BOT_WHOLE = 0, BOT_DOWN = 1, BOT_UP = 2 };
 struct BotArgs {
   int nlev, level0, nu1, nu2, ncomp;
   BotLevel lv[kMaxBotLevels];
@@ -212,7 +217,7 @@ hipError_t launch_level_noise(const NoiseGenArgs& a, const NoiseArgs& na, hipStr
 // `a` points to a BotArgs in device memory; the launch runs components c0 .. c0+ncomp-1 (one
 // work-group each; the noise is keyed by those absolute component numbers)
 template <typename T>
-hipError_t launch_bottom(const BotArgs* a, int ncomp, int c0, size_t lds, bool noise,
+hipError_t launch_bottom(const BotArgs* a, int ncomp, int c0, size_t lds, bool noise, int part,
                          const NoiseArgs& na, hipStream_t s);
 // The bottoms of several hierarchies in one launch (kernel arguments only): item i brings its
 // device BotArgs and its noise keys; work-group w runs component wg[w] >> 16 of item
@@ -224,6 +229,7 @@ struct BotMultiItem {
   uint32_t k0, k1, c2, c3;   // as NoiseArgs
   const ChainKey* chains;
   uint32_t cpc, cpc_magic;
+  int part;                  // BotPart
   double sqkT;
 };
 struct BotMultiArgs {

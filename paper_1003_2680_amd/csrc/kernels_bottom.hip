@@ -421,13 +421,38 @@ __device__ __forceinline__ void bot_residual(T* R, const T* X, const T* B, const
 
 template <typename T, bool NOISE>
 __device__ __forceinline__ void bottom_body(const BotArgs& a, const uint32_t comp,
-                                            const NoiseArgs& na) {
+                                            const NoiseArgs& na, int part) {
   extern __shared__ char smraw[];
   T* sm = reinterpret_cast<T*>(smraw);
   const int tid = threadIdx.x;
   const BotLevel& L0 = a.lv[0];
   const int n0 = L0.nx * L0.ny * L0.nz;
-  {
+  // element of the LDS field x for the natural index q of level L, halo copies beside it
+  auto place = [](const BotLevel& L, int q, int& x) {
+    int y, z, r;
+    divmod_uniform(q, L.nx, r, x);
+    divmod_uniform(r, L.ny, z, y);
+    return z * L.sz + y * L.sy + x + (L.kind == KIND_BLOCK ? kBotHalo : 0);
+  };
+  if (part == BOT_UP) {  // x and b of every block level, and the coarsest x, as BOT_DOWN left them
+    for (int i = 0; i < a.nlev; ++i) {
+      const BotLevel& L = a.lv[i];
+      const int n = L.nx * L.ny * L.nz;
+      T* xi = sm + a.lds_off[i];
+      const gptr<T> xg = global_ptr<T>(L.xg) + (size_t)comp * n;
+      const gptr<T> bg = global_ptr<T>(L.bg) + (size_t)comp * n;
+      for (int q = tid; q < n; q += BOT_TPB) {
+        int x;
+        const int p = place(L, q, x);
+        if (L.kind == KIND_BLOCK) {
+          bot_store(xi, p, x, L.nx, (T)xg[q]);
+          xi[L.nz * L.sz + q] = bg[q];
+        } else {
+          xi[p] = xg[q];
+        }
+      }
+    }
+  } else {
     T* x0 = sm + a.lds_off[0];
     for (int q = tid; q < L0.nz * L0.sz; q += BOT_TPB) x0[q] = T(0);
     T* b0 = x0 + L0.nz * L0.sz;
@@ -445,7 +470,7 @@ __device__ __forceinline__ void bottom_body(const BotArgs& a, const uint32_t com
       for (int q = tid; q < nz * 10; q += BOT_TPB) t[q] = zt[q];
       for (int q = tid; q < (nz / 2) * 64; q += BOT_TPB)
         t[nz * 10 + q] = bf[(q >> 6) * 192 + (q & 63)];
-    } else if (NOISE) {
+    } else if (NOISE && part == BOT_WHOLE) {
       const int n = L.nx * L.ny * L.nz;
       T* ri = sm + a.lds_off[i] + 2 * n;
       const uint32_t sid = (uint32_t)(a.level0 + i) | (1u << 24);
@@ -459,13 +484,18 @@ __device__ __forceinline__ void bottom_body(const BotArgs& a, const uint32_t com
   }
   __syncthreads();
   int last = a.nlev - 1;
-  for (int i = 0; i < a.nlev; ++i) {
+  for (int i = 0; i < a.nlev && part != BOT_UP; ++i) {
     const BotLevel& L = a.lv[i];
     const int n = L.nx * L.ny * L.nz;
     T* xi = sm + a.lds_off[i];
     T* bi = xi + L.nz * L.sz;
     T* ri = bi + n;
+    if (part == BOT_DOWN && i > 0) {
+      T* bg = (T*)L.bg + (size_t)comp * n;
+      for (int q = tid; q < n; q += BOT_TPB) bg[q] = bi[q];
+    }
     if (L.kind == KIND_CHOL) {
+      if (part == BOT_DOWN) return;
       // exact draw x = A_c^-1 b + sqrt(kT) L_c^-T n (natural layout on this level).  G lanes
       // per row (a power of two, G <= 32) split the columns, so that every lane has only n/G
       // loads of the dense factors in its chain; their sums meet by shuffles
@@ -501,6 +531,13 @@ __device__ __forceinline__ void bottom_body(const BotArgs& a, const uint32_t com
       last = i;
       break;
     }
+    if (part == BOT_DOWN) {
+      T* xg = (T*)L.xg + (size_t)comp * n;
+      for (int q = tid; q < n; q += BOT_TPB) {
+        int x;
+        xg[q] = xi[place(L, q, x)];
+      }
+    }
     // b_{i+1} = P^T (b_i - A_i x_i), x_{i+1} = 0
     bot_residual<T>(ri, xi, bi, L, tab);
     __syncthreads();
@@ -534,12 +571,9 @@ __device__ __forceinline__ void bottom_body(const BotArgs& a, const uint32_t com
     bot_sweeps<T, NOISE>(xi, xi + L.nz * L.sz, L, sm + a.tab_off[i], a.nu1, a.nu2, true,
                          global_ptr<T>(L.noise) + (size_t)comp * n, (size_t)a.ncomp * n);
   }
-  const int halo = L0.kind == KIND_BLOCK ? kBotHalo : 0;
   for (int q = tid; q < n0; q += BOT_TPB) {
-    int x, y, z, r;
-    divmod_uniform(q, L0.nx, r, x);
-    divmod_uniform(r, L0.ny, z, y);
-    ((T*)a.x_out)[(size_t)comp * n0 + q] = sm[a.lds_off[0] + z * L0.sz + y * L0.sy + x + halo];
+    int x;
+    ((T*)a.x_out)[(size_t)comp * n0 + q] = sm[a.lds_off[0] + place(L0, q, x)];
   }
 }
 
@@ -547,8 +581,8 @@ __device__ __forceinline__ void bottom_body(const BotArgs& a, const uint32_t com
 template <typename T, bool NOISE>
 __global__ __launch_bounds__(BOT_TPB)
 __attribute__((amdgpu_waves_per_eu(2, 2))) void k_bottom(const BotArgs* __restrict__ ap, int c0,
-                                                    NoiseArgs na) {
-  bottom_body<T, NOISE>(*ap, c0 + (int)blockIdx.x, na);
+                                                    int part, NoiseArgs na) {
+  bottom_body<T, NOISE>(*ap, c0 + (int)blockIdx.x, na, part);
 }
 
 // Several hierarchies (of any sizes) in one launch: work-group w runs component wg >> 16 of
@@ -570,13 +604,13 @@ __attribute__((amdgpu_waves_per_eu(2, 2))) void k_bottom_multi(BotMultiArgs m) {
   na.comps_per_chain = it.cpc;
   na.cpc_magic = it.cpc_magic;
   na.bm = m.bm;
-  bottom_body<T, NOISE>(*it.args, w >> 16, na);
+  bottom_body<T, NOISE>(*it.args, w >> 16, na, it.part);
 }
 
 }  // namespace
 
 template <typename T>
-hipError_t launch_bottom(const BotArgs* a, int ncomp, int c0, size_t lds, bool noise,
+hipError_t launch_bottom(const BotArgs* a, int ncomp, int c0, size_t lds, bool noise, int part,
                          const NoiseArgs& na, hipStream_t s) {
   static bool attr_set = false;
   if (!attr_set) {
@@ -588,8 +622,8 @@ hipError_t launch_bottom(const BotArgs* a, int ncomp, int c0, size_t lds, bool n
     if (e != hipSuccess) return e;
     attr_set = true;
   }
-  if (noise) k_bottom<T, true><<<ncomp, BOT_TPB, lds, s>>>(a, c0, na);
-  else k_bottom<T, false><<<ncomp, BOT_TPB, lds, s>>>(a, c0, na);
+  if (noise) k_bottom<T, true><<<ncomp, BOT_TPB, lds, s>>>(a, c0, part, na);
+  else k_bottom<T, false><<<ncomp, BOT_TPB, lds, s>>>(a, c0, part, na);
   return hipGetLastError();
 }
 
@@ -614,7 +648,7 @@ hipError_t launch_bottom_multi(const BotMultiArgs& m, int nwg, size_t lds, bool 
 }
 
 #define SMG_INST(T)                                                                  \
-  template hipError_t launch_bottom<T>(const BotArgs*, int, int, size_t, bool,       \
+  template hipError_t launch_bottom<T>(const BotArgs*, int, int, size_t, bool, int,  \
                                        const NoiseArgs&, hipStream_t);               \
   template hipError_t launch_bottom_multi<T>(const BotMultiArgs&, int, size_t, bool, \
                                              hipStream_t);

@@ -515,36 +515,79 @@ __global__ __launch_bounds__(TPB) void k_prolong(T* __restrict__ x, const T* __r
       prolong_at<T>(e + (size_t)comp * Nc, nxc, nxc * nyc, xf, yf, zf, nxc, nyc, nzf >> 1);
 }
 
-// x = A_c^-1 b (+ sqrt(kT) L_c^-T n) in FP64: rows split over work-groups; each work-group
-// stages b and the whole noise vector in LDS.
-template <typename T, bool NOISE>
-__global__ __launch_bounds__(TPB) void k_coarsest(T* __restrict__ xg, const T* __restrict__ bg,
-                                                   const double* __restrict__ ainv,
-                                                   const double* __restrict__ w, int n,
-                                                   NoiseArgs na) {
-  extern __shared__ double sh[];
-  const uint32_t comp = blockIdx.y;
-  const T* B = bg + (size_t)comp * n;
-  for (int i = threadIdx.x; i < n; i += TPB) sh[i] = (double)B[i];
-  if (NOISE) {
-    for (int q = threadIdx.x; 2 * q < n; q += TPB) {
-      double z0, z1;
-      normal_pair(na, na.sid, comp, (uint32_t)q, z0, z1);
-      sh[n + 2 * q] = z0;
-      if (2 * q + 1 < n) sh[n + 2 * q + 1] = z1;
+// x = A_c^-1 b (+ sqrt(kT) L_c^-T n) in FP64.  A work-group owns CO_ROWS rows of C components
+// and splits the columns over CO_TPB / CO_ROWS lanes per row, so that the dense factors (the
+// bound: 12 n^2 bytes, from L2 or memory) are read by the whole chip, in 128-byte segments, with
+// eight loads per lane in flight; the components of a group share every factor element.  b and
+// the normals that the rows need (columns from the first row on: L_c^-T is upper triangular) are
+// staged in LDS.  A lane's columns and the order of the sums do not depend on the grid, so a
+// component's draw is the same bits in any launch.
+// One work-group per component took 3469 us at n = 2160 (inside the bottom kernel) and 140-230
+// us at n = 512; one thread per row over n / 256 work-groups 40 us at n = 256 (eight components).
+constexpr int CO_ROWS = 16, CO_TPB = 512, CO_PARTS = CO_TPB / CO_ROWS;
+
+template <typename T, bool NOISE, int C>
+__global__ __launch_bounds__(CO_TPB) void k_coarsest(T* __restrict__ xg,
+                                                      const T* __restrict__ bg,
+                                                      const double* __restrict__ ainv,
+                                                      const double* __restrict__ w, int n,
+                                                      int ncomp, NoiseArgs na) {
+  extern __shared__ double sh[];  // b [C][n], normals [C][n]; then the partial sums
+  const int comp0 = blockIdx.y * C;
+  const int nc = min(C, ncomp - comp0);
+  const int row0 = blockIdx.x * CO_ROWS;
+  for (int c = 0; c < nc; ++c) {
+    const T* B = bg + (size_t)(comp0 + c) * n;
+    for (int i = threadIdx.x; i < n; i += CO_TPB) sh[c * n + i] = (double)B[i];
+    if (NOISE) {
+      double* Z = sh + (C + c) * n;
+      for (int q = row0 / 2 + threadIdx.x; 2 * q < n; q += CO_TPB) {
+        double z0, z1;
+        normal_pair(na, na.sid, comp0 + c, (uint32_t)q, z0, z1);
+        Z[2 * q] = z0;
+        if (2 * q + 1 < n) Z[2 * q + 1] = z1;
+      }
     }
   }
+  for (int c = nc; c < C; ++c)  // components past the last: zeros, so that the sums need no test
+    for (int i = threadIdx.x; i < n; i += CO_TPB) sh[c * n + i] = sh[(C + c) * n + i] = 0.0;
   __syncthreads();
-  const int row = blockIdx.x * TPB + threadIdx.x;
-  if (row >= n) return;
-  double acc = 0.0;
-  for (int jj = 0; jj < n; ++jj) acc = fma(ainv[(size_t)jj * n + row], sh[jj], acc);
-  if (NOISE) {
-    double an = 0.0;
-    for (int jj = row; jj < n; ++jj) an = fma(w[(size_t)jj * n + row], sh[n + jj], an);
-    acc = fma(na.sqkT, an, acc);
+  const int r = threadIdx.x % CO_ROWS, part = threadIdx.x / CO_ROWS;
+  const int row = row0 + r, rl = min(row, n - 1);
+  double acc[C], an[C];
+#pragma unroll
+  for (int c = 0; c < C; ++c) acc[c] = an[c] = 0.0;
+#pragma unroll 8
+  for (int jj = part; jj < n; jj += CO_PARTS) {
+    const double a = ainv[(size_t)jj * n + rl];
+#pragma unroll
+    for (int c = 0; c < C; ++c) acc[c] = fma(a, sh[c * n + jj], acc[c]);
   }
-  xg[(size_t)comp * n + row] = (T)acc;
+  if (NOISE) {
+    // from the lane's first column at or after row0; entries above the diagonal row are zero
+#pragma unroll 8
+    for (int jj = row0 + (part - row0 % CO_PARTS + CO_PARTS) % CO_PARTS; jj < n; jj += CO_PARTS) {
+      const double a = jj >= rl ? w[(size_t)jj * n + rl] : 0.0;
+#pragma unroll
+      for (int c = 0; c < C; ++c) an[c] = fma(a, sh[(C + c) * n + jj], an[c]);
+    }
+  }
+  __syncthreads();  // every read of b and the normals is done: the sums take their place
+#pragma unroll
+  for (int c = 0; c < C; ++c) {
+    double v = NOISE ? fma(na.sqkT, an[c], acc[c]) : acc[c];
+    v += __shfl_xor(v, 16, 64);
+    v += __shfl_xor(v, 32, 64);
+    if ((threadIdx.x & 63) < CO_ROWS) sh[(c * (CO_TPB / 64) + threadIdx.x / 64) * CO_ROWS + r] = v;
+  }
+  __syncthreads();
+  const int c = threadIdx.x / CO_ROWS;
+  if (c < nc && row < n) {
+    double v = 0.0;
+#pragma unroll
+    for (int q = 0; q < CO_TPB / 64; ++q) v += sh[(c * (CO_TPB / 64) + q) * CO_ROWS + r];
+    xg[(size_t)(comp0 + c) * n + row] = (T)v;
+  }
 }
 
 }  // namespace
@@ -786,14 +829,25 @@ hipError_t launch_prolong(T* x, const T* e, int nxf, int nyf, int nzf, int ncomp
   return hipGetLastError();
 }
 
+template <typename T, int C>
+hipError_t launch_coarsest_c(T* x, const T* b, const double* ainv, const double* w, int n,
+                             int ncomp, bool noise, const NoiseArgs& na, hipStream_t s) {
+  dim3 grid((n + CO_ROWS - 1) / CO_ROWS, (ncomp + C - 1) / C);
+  const size_t sums = (size_t)C * (CO_TPB / 64) * CO_ROWS;
+  const size_t lds = std::max((size_t)2 * C * n, sums) * sizeof(double);
+  if (noise) k_coarsest<T, true, C><<<grid, CO_TPB, lds, s>>>(x, b, ainv, w, n, ncomp, na);
+  else k_coarsest<T, false, C><<<grid, CO_TPB, lds, s>>>(x, b, ainv, w, n, ncomp, na);
+  return hipGetLastError();
+}
+
 template <typename T>
 hipError_t launch_coarsest(T* x, const T* b, const double* ainv, const double* w, int n,
                            int ncomp, bool noise, const NoiseArgs& na, hipStream_t s) {
-  dim3 grid(blocks_for(n), ncomp);
-  size_t lds = (size_t)(noise ? 2 : 1) * n * sizeof(double);
-  if (noise) k_coarsest<T, true><<<grid, TPB, lds, s>>>(x, b, ainv, w, n, na);
-  else k_coarsest<T, false><<<grid, TPB, lds, s>>>(x, b, ainv, w, n, na);
-  return hipGetLastError();
+  if (n > 4096) return hipErrorInvalidValue;  // 64 KB of LDS for one component
+  // four components per work-group once that still leaves work for the chip: a quarter of the
+  // factor traffic, while four components' b and normals fit 64 KB
+  if (ncomp >= 8 && n <= 1024) return launch_coarsest_c<T, 4>(x, b, ainv, w, n, ncomp, noise, na, s);
+  return launch_coarsest_c<T, 1>(x, b, ainv, w, n, ncomp, noise, na, s);
 }
 
 template <typename T>

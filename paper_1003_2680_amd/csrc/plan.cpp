@@ -145,6 +145,12 @@ size_t align_up(size_t v) { return (v + 255) & ~size_t(255); }
 constexpr int64_t kBottomCells = 4096;
 constexpr size_t kBottomLdsMax = 160 * 1024;
 constexpr int kBottomLevelsMax = 6;
+// Coarsest levels of at least this many unknowns are drawn by a launch of their own over the whole
+// chip, between two halves of the bottom launch, instead of by the bottom's one work-group: two
+// launches more (about 9 us a cycle) against a dense product whose time there grows with n^2.
+// Whole cycles, one work-group / own launch: n = 128 203 / 212 us, n = 216 228 / 226 us (16
+// components 310 / 290), n = 256 120 / 105 us, n = 512 192 / 129 us (16 components 299 / 146).
+constexpr int kWideCoarsest = 192;
 
 // The dense factors of the coarsest level depend only on the finest grid, h and the depth (the
 // Galerkin recurrences are fixed by them), not on the component count, the sweeps or the
@@ -431,6 +437,7 @@ int build_plan(const smg_grid_desc& d, const smg_cycle_params& p, Hierarchy& h, 
     }
     break;
   }
+  h.wide_coarsest = h.bottom >= 0 && h.nc >= kWideCoarsest;
   if (h.nc > 0) {
     h.off_ainv = take((size_t)h.nc * h.nc * sizeof(double));
     h.off_w = take((size_t)h.nc * h.nc * sizeof(double));

@@ -57,6 +57,7 @@ struct Hierarchy {
   std::vector<Level> lv;
   int bottom = -1;               // first level handled by the LDS-resident bottom kernel
   size_t bottom_lds = 0;         // its LDS bytes
+  bool wide_coarsest = false;    // the coarsest draw is a launch of its own (see plan.cpp)
   bool use_bottom = true;        // false: run those levels with one launch per pass instead
   int block_tile = SMG_TILE_AUTO;  // tile shape of the block-pass launches
   bool block_pairs = true;         // two block colours per launch where the level allows

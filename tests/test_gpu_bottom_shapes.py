@@ -14,6 +14,7 @@ import numpy as np
 import pytest
 
 from oracle.mg import StochasticMG
+from oracle.philox import PhiloxNoise
 
 torch = pytest.importorskip("torch")
 pytestmark = pytest.mark.gpu
@@ -47,3 +48,37 @@ def test_bottom_shape_against_oracle(dims, levels, coarsest, precision):
         assert np.max(np.abs(got - ref)) <= 1e-12 * np.max(np.abs(ref))
     else:
         assert np.linalg.norm(got - ref) <= 1e-4 * np.linalg.norm(ref)
+
+
+# Coarsest levels drawn by a launch of their own (192 unknowns and more): below a block level, alone
+# under level 0, sizes that are no multiple of the 16 rows of a work-group (216, 525, 2160), and
+# component counts below, at and just above groups of four (eight and more share the factors).
+@pytest.mark.parametrize("dims,levels,ncomp", [
+    ((32, 32, 32), 3, 1), ((32, 32, 32), 3, 9), ((48, 48, 48), 4, 8), ((30, 14, 10), 2, 11),
+    ((36, 20, 24), 2, 2), ((16, 16, 12), 2, 3),
+])
+@pytest.mark.parametrize("precision", ["fp64", "fp32_refined"])
+def test_wide_coarsest_against_oracle(dims, levels, ncomp, precision):
+    from paper_1003_2680_amd.api import Hierarchy
+    print("[gpu-case] wide coarsest %s L=%d nc=%d %s" % (dims, levels, ncomp, precision), flush=True)
+    H = Hierarchy(*dims, ncomp=ncomp, kT=0.7, levels=levels, coarsest_max=4096,
+                  precision=precision)
+    got = H.sample(2, 7, first_cycle=1)[0].cpu().numpy().reshape(2, ncomp, -1)
+    mg = StochasticMG(*dims, kT=0.7, levels=levels, coarsest_max=4096)
+    zero = np.zeros(mg.levels[0].n)
+    for c in sorted({0, ncomp // 2, ncomp - 1}):
+        x = zero.copy()
+        for k in range(2):
+            x = mg.vcycle(x, zero, PhiloxNoise(7), 1 + k, c)
+            if precision == "fp64":
+                assert np.max(np.abs(got[k, c] - x)) <= 1e-12 * np.max(np.abs(x)), (c, k)
+            else:
+                assert np.linalg.norm(got[k, c] - x) <= 1e-4 * np.linalg.norm(x), (c, k)
+    f = torch.randn(H.shape, dtype=torch.float64, device=H.device,
+                    generator=torch.Generator(device=H.device).manual_seed(5))
+    u, cycles, relres = H.solve(f, rtol=1e-12)
+    ref, _, _ = mg.solve(f[-1].cpu().numpy().ravel(), rtol=1e-13)
+    # both relative residuals are at most 1e-12: the solutions differ by the operator's condition
+    # number (lambda from 12 / h^2 down to that of the lowest mode) times their sum
+    cond = 12.0 / (4.0 * np.sin(np.pi / (2 * dims[2])) ** 2)
+    assert np.linalg.norm(u[-1].cpu().numpy().ravel() - ref) <= 2e-12 * cond * np.linalg.norm(ref)
