@@ -1,0 +1,192 @@
+// The 2x2x2 block heat bath of a Galerkin level on cells held in LDS, shared by every kernel that
+// makes block passes, so that a cell's new value is the same bits in each of them.
+//
+// A = a_z (x) m_y (x) m_x + m_z (x) (a_y (x) m_x + m_y (x) a_x) with symmetric 5-point periodic 1D
+// stencils s1d = (m_x, a_x, m_y, a_y) (offsets -2..2, uniform over the level) and the wall-axis
+// rows zt[z] = (a_z[z][z + dz], m_z[z][z + dz]).  The eight lanes of a block are consecutive, lane
+// bits kx, ky, kz from the lowest (neighbouring lanes touch neighbouring cells in memory; with kx
+// as the highest bit the FP64 single-colour pass of 256x256x128 took 38 instead of 31 us): both
+// exchanges of partial sums (y-partner lane ^ 2, z-partner lane ^ 4) and the eight-value sum of the
+// block solve are DPP moves, never LDS permutes.
+#pragma once
+
+#include <hip/hip_runtime.h>
+
+namespace smg {
+
+// v of another lane of the same eight: quad_perm moves for lane ^ 1, ^ 2, ^ 3 and the mirror of
+// the eight lanes for lane ^ 7 (lane ^ 4 is ^ 3 of it).
+constexpr int DPP_XOR1 = 0xB1, DPP_XOR2 = 0x4E, DPP_XOR3 = 0x1B, DPP_XOR7 = 0x141;
+template <int CTRL>
+__device__ __forceinline__ double dpp_lane(double v) {
+  const long long u = __double_as_longlong(v);
+  const int lo = __builtin_amdgcn_mov_dpp((int)u, CTRL, 0xf, 0xf, false);
+  const int hi = __builtin_amdgcn_mov_dpp((int)(u >> 32), CTRL, 0xf, 0xf, false);
+  return __longlong_as_double(((long long)hi << 32) | (unsigned)lo);
+}
+template <int CTRL>
+__device__ __forceinline__ float dpp_lane(float v) {
+  return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), CTRL, 0xf, 0xf, false));
+}
+
+// Sum over the four lanes l, l ^ 16, l ^ 32, l ^ 48 (the same bits in each of them).
+__device__ __forceinline__ unsigned lane_pairs16(unsigned v, unsigned& other) {
+  const auto r = __builtin_amdgcn_permlane16_swap(v, v, false, false);
+  other = r[1];
+  return r[0];
+}
+__device__ __forceinline__ unsigned lane_pairs32(unsigned v, unsigned& other) {
+  const auto r = __builtin_amdgcn_permlane32_swap(v, v, false, false);
+  other = r[1];
+  return r[0];
+}
+__device__ __forceinline__ double sum_rows(double v) {
+  auto join = [](unsigned lo, unsigned hi) {
+    return __longlong_as_double(((long long)hi << 32) | lo);
+  };
+  long long u = __double_as_longlong(v);
+  unsigned l1, h1;
+  unsigned l0 = lane_pairs16((unsigned)u, l1), h0 = lane_pairs16((unsigned)(u >> 32), h1);
+  v = join(l0, h0) + join(l1, h1);
+  u = __double_as_longlong(v);
+  l0 = lane_pairs32((unsigned)u, l1);
+  h0 = lane_pairs32((unsigned)(u >> 32), h1);
+  return join(l0, h0) + join(l1, h1);
+}
+__device__ __forceinline__ float sum_rows(float v) {
+  unsigned a, b;
+  a = lane_pairs16(__float_as_uint(v), b);
+  v = __uint_as_float(a) + __uint_as_float(b);
+  a = lane_pairs32(__float_as_uint(v), b);
+  return __uint_as_float(a) + __uint_as_float(b);
+}
+
+// What a lane keeps over the passes of one block layer.  Of the layer's six planes 2 bz - 2 ..
+// 2 bz + 3 the lanes of cell layer kz reduce planes 3 kz + m, m = 0 .. 2: all three (SPLIT 1) or,
+// where a level leaves lanes idle, one each (SPLIT 4: m = s, the fourth lane with zero factors).
+// po: element offset of each plane; the plane's z-factors for the lane's own cell and for its
+// z-partner's; the lane's row of A_BB^-1 in the order of the lanes ^ m.
+template <typename T, int SPLIT>
+struct BlockWeights {
+  static constexpr int P = SPLIT == 4 ? 1 : 3;
+  int po[P];
+  T own0[P], own1[P], oth0[P], oth1[P], F[8];
+};
+// The device table of a block layer bz (kBlockRow values): A_BB^-1 with entry m of row k that of
+// cell k ^ m, cells k = kx + 2 ky + 4 kz; L_BB^-T; and at kBlockZ the packed z-factors of the two
+// cell layers kz, own0, own1, oth0, oth1 of planes m = 0 .. 2 and a zero each.
+constexpr int kBlockRow = 192, kBlockZ = 128;
+// Fp, Zp: a layer's A_BB^-1 part and its packed z-factors.
+template <typename T, int SPLIT, typename PT>
+__device__ __forceinline__ void block_weights(BlockWeights<T, SPLIT>& w, const PT Fp, const PT Zp,
+                                              int kx, int ky, int kz, int s) {
+  const PT z = Zp + kz * 16 + (SPLIT == 4 ? s : 0);
+#pragma unroll
+  for (int p = 0; p < BlockWeights<T, SPLIT>::P; ++p) {
+    w.own0[p] = z[p];
+    w.own1[p] = z[4 + p];
+    w.oth0[p] = z[8 + p];
+    w.oth1[p] = z[12 + p];
+  }
+  const PT F = Fp + (kx + 2 * ky + 4 * kz) * 8;
+#pragma unroll
+  for (int m = 0; m < 8; ++m) w.F[m] = F[m];
+}
+
+// New value of the lane's cell: x_B + A_BB^-1 (b_B - (A x)_B) + noise, which equals A_BB^-1 (b_B -
+// A_B,rest x_rest) + noise: the block's own coupling cancels.  `noise` already holds the lane's
+// entry of sqrt(kT) L_BB^-T n.  Every lane of the wave calls it.
+//
+// ro[r]: element offset of the start of the five-cell x window of row r within a plane.  The two
+// cells y, y + 1 of a block column together need the six rows y - 2 .. y + 3; each lane reduces
+// three of them along x, rows y_lane + s (r - 2) with s = +1 for ky = 0 and -1 for ky = 1, i.e.
+// the outer three of its own window from its far edge inwards.  m_y and a_y are symmetric, so in
+// that order both lanes weight row r by factor r for their own cell, and rows 1, 2 by factors 0,
+// 1 for the partner's, whose share arrives by a DPP move.  The z-partners trade their planes'
+// weighted sums the same way.  45 reads a lane instead of 125.
+//
+// PRELOAD: every read is issued before the first sum, so that a pass waits for LDS once (for
+// kernels with the registers to spare).
+template <typename T, int SPLIT, bool PRELOAD>
+__device__ __forceinline__ T block_update(const T* X, const int (&ro)[3], const T* s1d,
+                                        const BlockWeights<T, SPLIT>& w, int own, T bk, T noise) {
+  constexpr int P = BlockWeights<T, SPLIT>::P;
+  T win[P][3][5];
+#pragma unroll
+  for (int m = 0; m < P; ++m)
+#pragma unroll
+    for (int r = 0; r < 3; ++r)
+#pragma unroll
+      for (int d = 0; d < 5; ++d) win[m][r][d] = X[w.po[m] + ro[r] + d];
+  const T xk = X[own];
+  if (PRELOAD) __builtin_amdgcn_sched_barrier(0);
+  T self = T(0), part = T(0);
+#pragma unroll
+  for (int m = 0; m < P; ++m) {
+    T rm[3], ra[3];
+#pragma unroll
+    for (int r = 0; r < 3; ++r) {
+      const T(&v)[5] = win[m][r];
+      const T e = v[0] + v[4], d = v[1] + v[3], c = v[2];  // the x factors are symmetric
+      rm[r] = fma(s1d[0], e, fma(s1d[1], d, s1d[2] * c));
+      ra[r] = fma(s1d[5], e, fma(s1d[6], d, s1d[7] * c));
+    }
+    const T* my = s1d + 10;
+    const T* ay = s1d + 15;
+    T p0 = my[0] * rm[1], p1 = ay[0] * rm[1];
+    p0 = fma(my[1], rm[2], p0);
+    p1 = fma(ay[1], rm[2], fma(my[0], ra[1], p1));
+    p1 = fma(my[1], ra[2], p1);
+    T q0 = my[0] * rm[0], q1 = ay[0] * rm[0];
+    q0 = fma(my[1], rm[1], fma(my[2], rm[2], q0));
+    q1 = fma(ay[1], rm[1], fma(ay[2], rm[2], q1));
+    T qa = my[0] * ra[0];
+    qa = fma(my[1], ra[1], fma(my[2], ra[2], qa));
+    q0 += dpp_lane<DPP_XOR2>(p0);
+    q1 = (q1 + qa) + dpp_lane<DPP_XOR2>(p1);
+    self = fma(w.own0[m], q0, fma(w.own1[m], q1, self));
+    part = fma(w.oth0[m], q0, fma(w.oth1[m], q1, part));
+  }
+  T ax = self + dpp_lane<DPP_XOR3>(dpp_lane<DPP_XOR7>(part));
+  if (SPLIT == 4) ax = sum_rows(ax);
+  const T res = bk - ax;
+  const T mir = dpp_lane<DPP_XOR7>(res);  // lane ^ 7
+  T v0 = xk, v1 = noise;
+  v0 = fma(w.F[0], res, v0);
+  v1 = fma(w.F[7], mir, v1);
+  v0 = fma(w.F[1], dpp_lane<DPP_XOR1>(res), v0);
+  v1 = fma(w.F[6], dpp_lane<DPP_XOR1>(mir), v1);
+  v0 = fma(w.F[2], dpp_lane<DPP_XOR2>(res), v0);
+  v1 = fma(w.F[5], dpp_lane<DPP_XOR2>(mir), v1);
+  v0 = fma(w.F[3], dpp_lane<DPP_XOR3>(res), v0);
+  v1 = fma(w.F[4], dpp_lane<DPP_XOR3>(mir), v1);
+  return v0 + v1;
+}
+
+// The level's 1D stencils in scalar registers: the table is read-only while kernels run, and only
+// loads from the constant space are taken as such past a kernel's stores.
+template <typename T>
+struct Stencils {
+  T v[20];
+};
+template <typename T>
+__device__ __forceinline__ Stencils<T> load_stencils(const T* s1d) {
+  typedef const __attribute__((address_space(4))) T* cptr;
+  Stencils<T> r;
+#pragma unroll
+  for (int q = 0; q < 20; ++q) r.v[q] = ((cptr)s1d)[q];
+  return r;
+}
+
+// Plane stride of an LDS tile of rows of 2 mod 4 elements: padded so that the lanes served together
+// fall on different banks (32 of four bytes).  FP64 reads are served sixteen lanes at a time (two
+// neighbouring blocks: x steps 0, 1, 4, 5; the y-partners an odd number of rows apart, the
+// z-partners three planes), which need distinct elements mod 16: planes of 8 mod 16.  FP32 reads
+// are served 32 lanes at a time: planes of 16 mod 32.  (With 16 mod 32 for both, the z-partners of
+// FP64 share a bank: a third of the LDS time of the 16^3 .. 4^3 bottom, 109 against 92 us; FP32
+// with 8 mod 16: 82 against 77 us.)
+__host__ __device__ constexpr int block_plane_stride(int plane, size_t elem) {
+  return elem == 8 ? plane + (24 - plane % 16) % 16 : plane + (48 - plane % 32) % 32;
+}
+
+}  // namespace smg

@@ -174,6 +174,70 @@ int rb_pass(Run& r, T* xc, const T* xo, const T* bc, int colour, const NoiseArgs
   return SMG_OK;
 }
 
+// How the sweeps of a level that takes several block colours a launch run: two or four (a half-
+// sweep).
+enum class SweepForm { PAIR, HALF };
+
+bool multi_colour(const Hierarchy& h, const Level& v) {
+  return v.kind == KIND_BLOCK && h.block_pairs && half_level(v.nx, v.ny);
+}
+
+// Lanes of a run's largest half-sweep launch on a level (one pair of block rows a group).
+int64_t half_lanes(const Level& v, int nc) {
+  return (int64_t)v.nx * v.ny * ((v.nz / 2 + 1) / 2) * nc;
+}
+
+// Half-sweeps while the launch does not fill the chip (its latency counts: half as many launches
+// and stagings), two colours above (half-sweeps draw every third block row twice).  A sweep at
+// 64^3 (2^16 lanes a component), half-sweeps / two colours, us: FP64 1 component 18.4 / 25.6, 3
+// 28.7 / 33.0, 4 35.3 / 36.1, 5 40.5 / 39.8, 24 144 / 113; FP32 3 24.0 / 27.7, 6 34.2 / 34.5, 7
+// 37.1 / 36.7, 24 84.5 / 71.2.  Every form gives the same bits.
+template <typename T>
+SweepForm sweep_form(int64_t lanes) {
+  return lanes < (sizeof(T) == 8 ? 9 : 13) * (int64_t)32768 ? SweepForm::HALF : SweepForm::PAIR;
+}
+
+// The passes of layer parity cz in sweep t (0-based on its leg) of a block level.  Two-colour
+// launches work in place on x.  Half-sweeps read one field and write another: even sweeps go from
+// x to the residual field (free between restrictions), odd ones back.
+template <typename T>
+HalfPassItem<T> half_item(const Run& r, int l, int t, bool post, int cz, bool half) {
+  Hierarchy& h = *r.h;
+  Level& v = h.lv[l];
+  T* x = comp_at(Fld<T>::x(v), v.n, r);
+  T* y = comp_at(Fld<T>::r(v), v.n, r);
+  T* from = (t & 1) ? y : x;
+  T* to = (t & 1) ? x : y;
+  if (!half) from = to = x;
+  const bool second = cz == (post ? 0 : 1);  // the other parity's layers are already in `to`
+  const int slot = post ? h.prm.nu1 + t : t;
+  HalfPassItem<T> it;
+  it.xs = from;
+  it.xo = second ? to : from;
+  it.xn = to;
+  it.b = comp_at(Fld<T>::b(v), v.n, r);
+  it.s1d = (const T*)v.s1d_d;
+  it.bfac = (const T*)v.bfac_d;
+  it.zn = r.noise ? (const T*)v.noise_d + ((size_t)slot * h.desc.ncomp + r.c0) * v.n : nullptr;
+  it.nx = v.nx;
+  it.ny = v.ny;
+  it.nz = v.nz;
+  it.ncomp = r.nc;
+  return it;
+}
+
+// After an odd number of half-sweep sweeps the field is in the residual field: back to x.
+template <typename T>
+int settle_halves(const Run& r, int l, int nsweeps) {
+  if (nsweeps % 2 == 0) return SMG_OK;
+  Level& v = r.h->lv[l];
+  // a block level has a multiple of 32 cells
+  SMG_HIP(launch_copy((double*)comp_at(Fld<T>::x(v), v.n, r),
+                      (const double*)comp_at(Fld<T>::r(v), v.n, r),
+                      (int64_t)r.nc * v.n * sizeof(T) / sizeof(double), r.s));
+  return SMG_OK;
+}
+
 template <typename T>
 int sweep(Run& r, int l, int slot, bool post) {
   Hierarchy& h = *r.h;
@@ -194,26 +258,34 @@ int sweep(Run& r, int l, int slot, bool post) {
       SMG_TRY(rb_pass<T>(r, colour ? xb : xr, colour ? xr : xb, bc, colour, na));
     }
     SMG_TRY(ts.close());
+  } else if (multi_colour(h, v)) {
+    const int t = post ? slot - h.prm.nu1 : slot, nsweeps = post ? h.prm.nu2 : h.prm.nu1;
+    const bool half = sweep_form<T>(half_lanes(v, r.nc)) == SweepForm::HALF;
+    TimedScope ts(h, r.s, l == 1 ? SMG_TIMED_LEVEL1_BLOCK_PASS : -1, half ? 2 : 4);
+    SMG_TRY(ts.rc);
+    for (int q = 0; q < 2; ++q) {
+      const int cz = post ? 1 - q : q;
+      const HalfPassItem<T> it = half_item<T>(r, l, t, post, cz, half);
+      if (half) {
+        SMG_HIP(launch_block_half<T>(&it, 1, cz, post, r.noise, r.s));
+      } else {
+        for (int k = 0; k < 2; ++k)
+          SMG_HIP(launch_block_pair<T>(&it, 1, 4 * cz + (post ? 3 - 2 * k : 2 * k), r.noise, r.s));
+      }
+    }
+    SMG_TRY(ts.close());
+    if (half && t + 1 == nsweeps) SMG_TRY(settle_halves<T>(r, l, nsweeps));
   } else {
     const T* noise = (const T*)v.noise_d;
     const T* zn = r.noise ? noise + ((size_t)slot * nc + r.c0) * v.n : nullptr;
     T* x = comp_at(Fld<T>::x(v), v.n, r);
     const T* b = comp_at(Fld<T>::b(v), v.n, r);
-    const bool pairs = h.block_pairs && pair_level(v.nx, v.ny);
-    TimedScope ts(h, r.s, l == 1 ? SMG_TIMED_LEVEL1_BLOCK_PASS : -1, pairs ? 4 : 8);
+    TimedScope ts(h, r.s, l == 1 ? SMG_TIMED_LEVEL1_BLOCK_PASS : -1, 8);
     SMG_TRY(ts.rc);
-    for (int t = 0; t < 8; t += pairs ? 2 : 1) {
-      const int colour = post ? 7 - t : t;  // with pairs: colour, then colour ^ 1
-      if (pairs) {
-        SMG_HIP(launch_block_pair<T>(x, b, (const T*)v.s1d_d, (const T*)v.zt_d,
-                                     (const T*)v.bfac_d, v.nx, v.ny, v.nz, r.nc, colour, zn,
-                                     r.s));
-      } else {
-        SMG_HIP(launch_block_pass<T>(x, b, (const T*)v.s1d_d, (const T*)v.zt_d,
-                                     (const T*)v.bfac_d, v.nx, v.ny, v.nz, r.nc, colour, zn,
-                                     h.block_tile, r.s));
-      }
-    }
+    for (int t = 0; t < 8; ++t)
+      SMG_HIP(launch_block_pass<T>(x, b, (const T*)v.s1d_d, (const T*)v.bfac_d, v.nx,
+                                   v.ny, v.nz, r.nc, post ? 7 - t : t,
+                                   zn, h.block_tile, r.s));
     SMG_TRY(ts.close());
   }
   return SMG_OK;
@@ -499,52 +571,55 @@ int cycle_phases(Run& r, int phases, bool residual_ready = false) {
   return SMG_OK;
 }
 
-// The block-colour pass of colour `colour` in sweep `t` (0-based; pre-sweeps first) of level l
-// for every listed run that has it (level l above its bottom, t < its nu1 + nu2 and on the
-// given leg), in one launch.
-// The block-colour passes of colours `colour` and then colour ^ 1 (pairs), or of `colour`
-// alone, for the listed runs as in block_pass_lockstep: levels that take two-colour launches in
-// one pair launch per group, the others in single-colour launches.
+// The form of the multi-colour launches of level l for the listed runs (one for all of them: their
+// launches are shared, and it must not change within a leg).
 template <typename T>
-int block_pass_lockstep(const std::vector<Run>& legs, int l, int t, bool post, int colour,
-                        bool noise, hipStream_t s, bool pairs) {
-  std::vector<BlockPassItem<T>> items, paired;
+bool half_lockstep(const std::vector<Run>& legs, int l) {
+  int64_t lanes = 0;
+  for (const Run& r : legs)
+    if (l < r.h->bottom && multi_colour(*r.h, r.h->lv[l])) lanes += half_lanes(r.h->lv[l], r.nc);
+  return sweep_form<T>(lanes) == SweepForm::HALF;
+}
+
+// The four block colours of layer parity cz in sweep `t` (0-based) of level l for every listed run
+// that has it (level l above its bottom, t < its sweeps on the given leg, noise as given): in one
+// or two launches for the levels that take several colours a launch, in a launch per colour for
+// the others.
+template <typename T>
+int block_half_lockstep(const std::vector<Run>& legs, int l, int t, bool post, int cz, bool noise,
+                        hipStream_t s) {
+  std::vector<BlockPassItem<T>> items;
+  std::vector<HalfPassItem<T>> multi;
+  const bool half = half_lockstep<T>(legs, l);
   int tile = -1;
   for (const Run& r : legs) {
     Hierarchy& h = *r.h;
     if (r.noise != noise || l >= h.bottom) continue;
     Level& v = h.lv[l];
     if (v.kind != KIND_BLOCK) continue;
-    const int nsw = post ? h.prm.nu2 : h.prm.nu1;
-    if (t >= nsw) continue;
-    const int slot = post ? h.prm.nu1 + t : t;
-    BlockPassItem<T> it;
-    it.x = comp_at(Fld<T>::x(v), v.n, r);
-    it.b = comp_at(Fld<T>::b(v), v.n, r);
-    it.s1d = (const T*)v.s1d_d;
-    it.zt = (const T*)v.zt_d;
-    it.bfac = (const T*)v.bfac_d;
-    it.zn = noise ? (const T*)v.noise_d + ((size_t)slot * h.desc.ncomp + r.c0) * v.n : nullptr;
-    it.nx = v.nx;
-    it.ny = v.ny;
-    it.nz = v.nz;
-    it.ncomp = r.nc;
-    if (pairs && h.block_pairs && pair_level(v.nx, v.ny)) {
-      paired.push_back(it);
+    if (t >= (post ? h.prm.nu2 : h.prm.nu1)) continue;
+    const bool mc = multi_colour(h, v);
+    const HalfPassItem<T> hi = half_item<T>(r, l, t, post, cz, half && mc);
+    if (mc) {
+      multi.push_back(hi);
       continue;
     }
-    items.push_back(it);
+    items.push_back(BlockPassItem<T>{hi.xn, hi.b, hi.s1d, hi.bfac, hi.zn, hi.nx, hi.ny, hi.nz,
+                                     hi.ncomp});
     // one tile shape per launch: the common choice of the items, else by work-group count
     tile = tile == -1 ? h.block_tile : (tile == h.block_tile ? tile : SMG_TILE_AUTO);
   }
-  if (!paired.empty())
-    SMG_HIP(launch_block_pair_multi<T>(paired.data(), (int)paired.size(), colour, noise, s));
-  if (!items.empty()) {
-    SMG_HIP(launch_block_pass_multi<T>(items.data(), (int)items.size(), colour, noise, tile, s));
-    if (pairs)
-      SMG_HIP(launch_block_pass_multi<T>(items.data(), (int)items.size(), colour ^ 1, noise,
-                                         tile, s));
+  const int nm = (int)multi.size(), ni = (int)items.size();
+  if (nm && half) {
+    SMG_HIP(launch_block_half<T>(multi.data(), nm, cz, post, noise, s));
+  } else if (nm) {
+    for (int k = 0; k < 2; ++k)
+      SMG_HIP(launch_block_pair<T>(multi.data(), nm, 4 * cz + (post ? 3 - 2 * k : 2 * k), noise,
+                                   s));
   }
+  for (int q = 0; q < 4 && ni; ++q)
+    SMG_HIP(launch_block_pass_multi<T>(items.data(), ni, 4 * cz + (post ? 3 - q : q), noise, tile,
+                                       s));
   return SMG_OK;
 }
 
@@ -601,10 +676,14 @@ int legs_lockstep(const std::vector<Run>& legs, bool down) {
                                               nz != 0, s));
           }
       }
-      for (int k = 0; k < 8; k += 2) {  // colour pairs (c, c ^ 1) in sweep order
-        const int colour = down ? k : 7 - k;
+      for (int q = 0; q < 2; ++q)
         for (int nz = 0; nz < 2; ++nz)
-          SMG_TRY(block_pass_lockstep<T>(legs, l, t, !down, colour, nz != 0, s, true));
+          SMG_TRY(block_half_lockstep<T>(legs, l, t, !down, down ? q : 1 - q, nz != 0, s));
+      for (const Run& r : legs) {
+        const int nsw = down ? r.h->prm.nu1 : r.h->prm.nu2;
+        if (l < r.h->bottom && t + 1 == nsw && multi_colour(*r.h, r.h->lv[l]) &&
+            half_lockstep<T>(legs, l))
+          SMG_TRY(settle_halves<T>(r, l, nsw));
       }
     }
     return SMG_OK;
@@ -801,12 +880,43 @@ int check_fp64(const Hierarchy& h) {
   return SMG_OK;
 }
 
+// The device form of a block level's factors (block_update.hpp): per block layer A_BB^-1 in lane
+// order, L_BB^-T, and the z-factors of the layer's planes packed for its two cell layers.
+std::vector<double> block_rows(const Level& v) {
+  std::vector<double> out((size_t)(v.nz / 2) * kBlockRow, 0.0);
+  for (int bz = 0; bz < v.nz / 2; ++bz) {
+    const double* src = &v.bfac[(size_t)bz * 192];
+    double* dst = &out[(size_t)bz * kBlockRow];
+    for (int k = 0; k < 8; ++k)
+      for (int m = 0; m < 8; ++m) dst[k * 8 + m] = src[k * 8 + (k ^ m)];
+    for (int q = 0; q < 64; ++q) dst[64 + q] = src[64 + q];
+    for (int kz = 0; kz < 2; ++kz) {
+      const double* zo = &v.zt[(size_t)(2 * bz + kz) * 10];
+      const double* zp = &v.zt[(size_t)(2 * bz + 1 - kz) * 10];
+      double* z = dst + kBlockZ + kz * 16;
+      for (int m = 0; m < 3; ++m) {  // plane 3 kz + m of the layer's six
+        const int own = 2 * kz + m, oth = kz ? 3 + m : m - 1;  // its dz + 2 from either cell
+        if (own < 5) {
+          z[m] = zo[own];
+          z[4 + m] = zo[5 + own];
+        }
+        if (oth >= 0 && oth < 5) {
+          z[8 + m] = zp[oth];
+          z[12 + m] = zp[5 + oth];
+        }
+      }
+    }
+  }
+  return out;
+}
+
 // Block-level tables in the sweep precision T (rounded from the FP64 tables in refined mode).
 template <typename T>
 int upload_tables(Level& v, char* ws, hipStream_t s) {
   std::vector<T> g(v.s1d.begin(), v.s1d.end());
   std::vector<T> z(v.zt.begin(), v.zt.end());
-  std::vector<T> b(v.bfac.begin(), v.bfac.end());
+  const std::vector<double> rows = block_rows(v);
+  std::vector<T> b(rows.begin(), rows.end());
   v.s1d_d = ws + v.off_s1d;
   v.zt_d = ws + v.off_zt;
   v.bfac_d = ws + v.off_bfac;
@@ -1878,7 +1988,7 @@ int smg_debug_smooth(smg_hierarchy* hh, int32_t level, int32_t colour, void* x, 
   } else {
     if (r.noise) SMG_TRY(gen_level_noise<double>(r, level, slot));
     SMG_HIP(launch_block_pass<double>((double*)x, (const double*)b, (const double*)v.s1d_d,
-                                      (const double*)v.zt_d, (const double*)v.bfac_d, v.nx, v.ny,
+                                      (const double*)v.bfac_d, v.nx, v.ny,
                                       v.nz, h.desc.ncomp, colour,
                                       r.noise ? (const double*)v.noise_d : nullptr,
                                       h.block_tile, s));

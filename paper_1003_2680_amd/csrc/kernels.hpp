@@ -8,6 +8,7 @@
 #include <stdint.h>
 
 #include "../../include/smg.h"
+#include "block_update.hpp"
 #include "philox.hpp"
 
 namespace smg {
@@ -26,7 +27,7 @@ struct NoiseLevel {
   int level, nx, ny, nz, nslot, slot0;
   int lg_bx, lg_bxy;      // log2 of nx/2 and of (nx/2)(ny/2) when powers of two, else -1
   void* out;              // T[nslot][ncomp][N]
-  const void* bfac;       // T[nz/2][192]: the level's block factors (L_BB^-T at offset 64)
+  const void* bfac;       // T[nz/2][kBlockRow]: the level's block factors (L_BB^-T at offset 64)
   uint32_t calls_before;  // prefix sum of nslot*nact*N/2 over the previous entries
 };
 struct NoiseGenArgs {
@@ -45,7 +46,7 @@ struct BotLevel {
   const void* noise;   // T: pregenerated noise of this level [slot][ncomp][N] (block levels)
   double s1d[20];      // 1D stencils (m_x, a_x, m_y, a_y), offsets -2..2
   const void* zt;      // T: [nz][10]
-  const void* bfac;    // T: [nz/2][3][64]
+  const void* bfac;    // T: [nz/2][kBlockRow]
   void* xg;            // T [ncomp][n]: the level's x and b in memory, where the two parts of a
   void* bg;            // split bottom leave and find them
 };
@@ -64,20 +65,14 @@ struct BotArgs {
 };
 
 // LDS strides of a bottom level's x: on the block levels rows hold two halo cells per side (the
-// periodic copies) and two more of padding (2 mod 4 elements in all), and planes are padded so
-// that the lanes served together fall on different banks of the 32 four-byte ones.  FP64 reads
-// are served sixteen lanes at a time (two neighbouring blocks: x steps 0, 1, 4, 5; the y-partners
-// an odd number of rows apart, the z-partners three planes), which need distinct elements mod
-// 16: planes of 8 mod 16.  FP32 reads are served 32 lanes at a time: planes of 16 mod 32, which
-// put the z-partners of FP64 on one bank (a third of the LDS time of the 16^3 .. 4^3 bottom, 109
-// against 92 us; FP32 with planes of 8 mod 16 82 against 77 us).  The coarsest stays natural, as
-// do b and the scratch field of every level.
+// periodic copies) and two more of padding (2 mod 4 elements in all), planes as
+// block_plane_stride pads them; the coarsest stays natural, as do b and the scratch field of
+// every level.
 constexpr int kBotHalo = 2;
 inline void bot_strides(int kind, int nx, int ny, size_t elem, int& sy, int& sz) {
   if (kind == KIND_BLOCK) {
     sy = nx + 2 * kBotHalo + 2;
-    const int p = ny * sy;
-    sz = elem == 8 ? p + (24 - p % 16) % 16 : p + (48 - p % 32) % 32;
+    sz = block_plane_stride(ny * sy, elem);
   } else {
     sy = nx;
     sz = nx * ny;
@@ -89,8 +84,9 @@ inline size_t bot_level_elems(int kind, int nx, int ny, int nz, size_t elem) {
   bot_strides(kind, nx, ny, elem, sy, sz);
   return (size_t)nz * sz + 2 * (size_t)nx * ny * nz;
 }
-// elements of a block level's tables (z-factors and A_BB^-1)
-inline size_t bot_table_elems(int nz) { return (size_t)nz * 10 + (size_t)(nz / 2) * 64; }
+// elements of a block level's tables: z-rows, then per block layer A_BB^-1 and packed z-factors
+constexpr int kBotRow = 96;
+inline size_t bot_table_elems(int nz) { return (size_t)nz * 10 + (size_t)(nz / 2) * kBotRow; }
 
 template <typename T>
 hipError_t launch_rb_pass(T* xc, const T* xo, const T* bc, int nx, int ny, int nz, int ncomp,
@@ -122,17 +118,60 @@ hipError_t launch_prolong(T* x, const T* e, int nxf, int nyf, int nzf, int ncomp
 // multiplied by sqrt(kT) L_BB^-T (null without noise); tile: one of the SMG_TILE_* shapes of
 // smg.h (SMG_TILE_AUTO picks by work-group count)
 template <typename T>
-hipError_t launch_block_pass(T* x, const T* b, const T* s1d, const T* zt, const T* bfac, int nx,
+hipError_t launch_block_pass(T* x, const T* b, const T* s1d, const T* bfac, int nx,
                              int ny, int nz, int ncomp, int colour, const T* z, int tile,
                              hipStream_t s);
-// Block colours c_first and then c_first ^ 1 of one sweep in one launch, with the result of
-// the two single-colour passes in that order; levels with nx <= 128 and nx, ny multiples of 4
-// (hipErrorNotSupported otherwise: the caller runs the two passes).
-// true where a Galerkin level's sweeps can run as two-colour launches
-inline bool pair_level(int nx, int ny) { return nx <= 128 && nx % 4 == 0 && ny % 4 == 0; }
+// Several colours a launch.  Items of launch_block_half and launch_block_pair: levels with nx <=
+// 128 and nx, ny multiples of 4 (hipErrorNotSupported otherwise, before any launch).
+//
+// Half a sweep (the four block colours of one layer parity cz, in sweep order) of the levels of one
+// or several hierarchies in one launch (up to kHalfItems per launch), with the result of the four
+// single-colour passes in that order.  xs: the field holding this parity's layers, xo: the one
+// holding the other parity's, xn: receives this parity's layers (xn must not be xs or share xo's
+// layers of this parity).
+inline bool half_level(int nx, int ny) { return nx <= 128 && nx % 4 == 0 && ny % 4 == 0; }
+constexpr int HALF_TPB = 512;   // threads of the largest group: 4 nx
+constexpr int HALF_ROWS = 10;  // cell rows of a half-sweep's tile
 template <typename T>
-hipError_t launch_block_pair(T* x, const T* b, const T* s1d, const T* zt, const T* bfac, int nx,
-                             int ny, int nz, int ncomp, int c_first, const T* z, hipStream_t s);
+struct HalfPassItem {
+  const T* xs;
+  const T* xo;
+  T* xn;
+  const T* b;
+  const T* s1d;
+  const T* bfac;
+  const T* zn;
+  int nx, ny, nz, ncomp;
+};
+constexpr int kHalfItems = 16;
+template <typename T>
+struct HalfItem {
+  const T* xs;
+  const T* xo;
+  T* xn;
+  const T* b;
+  const T* s1d;
+  const T* bfac;
+  const T* zn;
+  int nx, ny, nz;
+  uint32_t N;
+  int P, nbzc, ngx, TP;  // P: block rows (pairs of rows) a work-group owns
+};
+template <typename T>
+struct HalfArgs {
+  int nitems, cz, post;
+  uint32_t begin[kHalfItems + 1];
+  HalfItem<T> it[kHalfItems];
+};
+template <typename T>
+hipError_t launch_block_half(const HalfPassItem<T>* items, int n, int cz, bool post, bool noise,
+                             hipStream_t s);
+
+// Block colours c_first and then c_first ^ 1 of one sweep, in place on xn (xs, xo unused), for the
+// levels launch_block_half takes.
+template <typename T>
+hipError_t launch_block_pair(const HalfPassItem<T>* items, int n, int c_first, bool noise,
+                             hipStream_t s);
 
 // One level-0 colour pass over several hierarchies in one launch (up to 8 per launch): each
 // item as the arguments of launch_rb_pass (its colour arrays, right-hand side, shape, active
@@ -161,7 +200,6 @@ struct BlockPassItem {
   T* x;
   const T* b;
   const T* s1d;
-  const T* zt;
   const T* bfac;
   const T* zn;
   int nx, ny, nz, ncomp;
@@ -172,7 +210,6 @@ struct BlockMultiItem {
   T* x;
   const T* b;
   const T* s1d;
-  const T* zt;
   const T* bfac;
   const T* zn;
   int nx, ny, nz;
@@ -188,30 +225,6 @@ struct BlockMultiArgs {
 template <typename T>
 hipError_t launch_block_pass_multi(const BlockPassItem<T>* items, int n, int colour, bool noise,
                                    int tile, hipStream_t s);
-// Colours c_first, then c_first ^ 1, of several levels in as few launches as possible (items
-// grouped by rows per work-group); every item must satisfy pair_level (hipErrorNotSupported
-// otherwise, before any launch).
-template <typename T>
-struct PairMultiItem {
-  T* x;
-  const T* b;
-  const T* s1d;
-  const T* zt;
-  const T* bfac;
-  const T* zn;
-  int nx, ny, nz;
-  uint32_t N;
-  int nby2, nbzc, ngx, TP;
-};
-template <typename T>
-struct PairMultiArgs {
-  int nitems, c_first;
-  uint32_t begin[kBlockMultiItems + 1];
-  PairMultiItem<T> it[kBlockMultiItems];
-};
-template <typename T>
-hipError_t launch_block_pair_multi(const BlockPassItem<T>* items, int n, int c_first,
-                                   bool noise, hipStream_t s);
 template <typename T>
 hipError_t launch_level_noise(const NoiseGenArgs& a, const NoiseArgs& na, hipStream_t s);
 // `a` points to a BotArgs in device memory; the launch runs components c0 .. c0+ncomp-1 (one

@@ -2,6 +2,7 @@
 // 4096 cells and the coarsest exact draw, one work-group per component, in one launch.
 #include <hip/hip_runtime.h>
 
+#include "block_update.hpp"
 #include "device_common.hpp"
 #include "kernels.hpp"
 
@@ -14,14 +15,13 @@ namespace {
 // work-group barriers instead of kernel launches.  The coarsest draw is FP64 in every mode.
 //
 // What bounds it: the serial chain of 8 (nu1 + nu2) colour passes per level on one compute
-// unit, so a pass is shaped for latency.  Its eight lanes per block are numbered ky + 2 kz +
-// 4 kx, so that both exchanges of partial sums (y- and z-partner) and the eight-value sum of
-// the block solve are DPP moves inside the wave, never LDS permutes; the x rows carry two halo
-// cells per side, so a row's five reads are one address with immediate offsets; the z-factors
-// and the block's A_BB^-1 row stay in registers over the four passes that share them; and the
-// noise of a pair of passes is loaded while the pair before runs.  The 16^3 .. 4^3 bottom takes
-// 92 us (FP64, inside the kernel; FP32 76 us): a 16^3 pass 1.3 us, an 8^3 pass 0.55 us.  With
-// indexed window reads, permutes and a noise load inside each pass it took 203 us.
+// unit, so a pass is shaped for latency.  The exchanges of partial sums between a block's eight
+// lanes and the eight-value sum of its solve are DPP moves, never LDS permutes; the x rows carry
+// two halo cells per side, so a row's five reads are one address with immediate offsets; the
+// z-factors and the block's A_BB^-1 row stay in registers over the four passes that share them;
+// and the noise of a pair of passes is loaded while the pair before runs.  The 16^3 .. 4^3 bottom
+// takes 92 us (FP64, inside the kernel; FP32 76 us): a 16^3 pass 1.3 us, an 8^3 pass 0.55 us.
+// With indexed window reads, permutes and a noise load inside each pass it took 203 us.
 constexpr int BOT_TPB = 512;
 
 // Pointers read from a level descriptor are taken into the global address space: a load through a
@@ -34,53 +34,6 @@ __device__ __forceinline__ gptr<T> global_ptr(const void* p) {
   return (gptr<T>)(const T*)p;
 }
 
-// v of another lane of the same eight: quad_perm moves for lane ^ 1, ^ 2, ^ 3 and the mirror of
-// the eight lanes for lane ^ 7.
-constexpr int DPP_XOR1 = 0xB1, DPP_XOR2 = 0x4E, DPP_XOR3 = 0x1B, DPP_XOR7 = 0x141;
-template <int CTRL>
-__device__ __forceinline__ double dpp_lane(double v) {
-  const long long u = __double_as_longlong(v);
-  const int lo = __builtin_amdgcn_mov_dpp((int)u, CTRL, 0xf, 0xf, false);
-  const int hi = __builtin_amdgcn_mov_dpp((int)(u >> 32), CTRL, 0xf, 0xf, false);
-  return __longlong_as_double(((long long)hi << 32) | (unsigned)lo);
-}
-template <int CTRL>
-__device__ __forceinline__ float dpp_lane(float v) {
-  return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), CTRL, 0xf, 0xf, false));
-}
-
-// Sum over the four lanes l, l ^ 16, l ^ 32, l ^ 48 (the same bits in each of them).
-__device__ __forceinline__ unsigned lane_pairs16(unsigned v, unsigned& other) {
-  const auto r = __builtin_amdgcn_permlane16_swap(v, v, false, false);
-  other = r[1];
-  return r[0];
-}
-__device__ __forceinline__ unsigned lane_pairs32(unsigned v, unsigned& other) {
-  const auto r = __builtin_amdgcn_permlane32_swap(v, v, false, false);
-  other = r[1];
-  return r[0];
-}
-__device__ __forceinline__ double sum_rows(double v) {
-  auto join = [](unsigned lo, unsigned hi) {
-    return __longlong_as_double(((long long)hi << 32) | lo);
-  };
-  long long u = __double_as_longlong(v);
-  unsigned l1, h1;
-  unsigned l0 = lane_pairs16((unsigned)u, l1), h0 = lane_pairs16((unsigned)(u >> 32), h1);
-  v = join(l0, h0) + join(l1, h1);
-  u = __double_as_longlong(v);
-  l0 = lane_pairs32((unsigned)u, l1);
-  h0 = lane_pairs32((unsigned)(u >> 32), h1);
-  return join(l0, h0) + join(l1, h1);
-}
-__device__ __forceinline__ float sum_rows(float v) {
-  unsigned a, b;
-  a = lane_pairs16(__float_as_uint(v), b);
-  v = __uint_as_float(a) + __uint_as_float(b);
-  a = lane_pairs32(__float_as_uint(v), b);
-  return __uint_as_float(a) + __uint_as_float(b);
-}
-
 // The lane's cell within its block, its share s of the cell's planes, and the block's place
 // among the blocks of one colour: bx = 2 i + cx, by = 2 j + cy, bz = 2 l + cz.
 struct BotLane {
@@ -89,9 +42,9 @@ struct BotLane {
 template <int SPLIT>
 __device__ __forceinline__ BotLane bot_lane(const BotLevel& L, int t) {
   BotLane g;
-  g.ky = t & 1;
-  g.kz = (t >> 1) & 1;
-  g.kx = (t >> 2) & 1;
+  g.kx = t & 1;
+  g.ky = (t >> 1) & 1;
+  g.kz = (t >> 2) & 1;
   g.s = SPLIT == 4 ? (t >> 4) & 3 : 0;
   const int nbx2 = L.nx >> 2, nby2 = L.ny >> 2;
   int rest;
@@ -102,109 +55,19 @@ __device__ __forceinline__ BotLane bot_lane(const BotLevel& L, int t) {
   return g;
 }
 
-// What a lane keeps over the passes of one cz.  Of the block's six planes 2 bz - 2 .. 2 bz + 3
-// the lanes of layer kz reduce planes 3 kz + m, m = 0 .. 2: all three (SPLIT 1) or, where the
-// level leaves lanes idle, one each (SPLIT 4: m = s, the fourth lane with zero factors).
-// po: element offset of each plane (clamped at the walls, where the factors are zero); the
-// plane's z-factors for the lane's own cell and for its z-partner's; the lane's row of A_BB^-1
-// in the order of the lanes ^ m.
 template <typename T, int SPLIT>
-struct BotWeights {
-  static constexpr int P = SPLIT == 4 ? 1 : 3;
-  int po[P];
-  T own0[P], own1[P], oth0[P], oth1[P], F[8];
-};
-template <typename T, int SPLIT>
-__device__ __forceinline__ BotWeights<T, SPLIT> bot_weights(int nz, int sz, const T* tab,
-                                                            const BotLane& g, int bz) {
-  BotWeights<T, SPLIT> w;
-  const T* zo = tab + (2 * bz + g.kz) * 10;
-  const T* zp = tab + (2 * bz + 1 - g.kz) * 10;
+__device__ __forceinline__ BlockWeights<T, SPLIT> bot_weights(int nz, int sz, const T* tab,
+                                                              const BotLane& g, int bz) {
+  BlockWeights<T, SPLIT> w;
+  const T* row = tab + nz * 10 + bz * kBotRow;
+  block_weights<T, SPLIT>(w, row, row + 64, g.kx, g.ky, g.kz, g.s);
 #pragma unroll
-  for (int p = 0; p < w.P; ++p) {
-    const int m = SPLIT == 4 ? g.s : p;
-    const int d0 = 2 * g.kz + m;              // the plane's dz + 2 seen from the own cell
-    const int d1 = g.kz ? 3 + m : m - 1;      // and from the partner's
-    const bool in0 = d0 < 5 && m < 3, in1 = d1 >= 0 && d1 < 5 && m < 3;
-    w.own0[p] = in0 ? zo[d0] : T(0);
-    w.own1[p] = in0 ? zo[5 + d0] : T(0);
-    w.oth0[p] = in1 ? zp[d1] : T(0);
-    w.oth1[p] = in1 ? zp[5 + d1] : T(0);
-    int pz = 2 * bz - 2 + 3 * g.kz + m;
+  for (int p = 0; p < BlockWeights<T, SPLIT>::P; ++p) {
+    int pz = 2 * bz - 2 + 3 * g.kz + (SPLIT == 4 ? g.s : p);
     pz = pz < 0 ? 0 : (pz >= nz ? nz - 1 : pz);
     w.po[p] = pz * sz;
   }
-  const T* F = tab + nz * 10 + bz * 64;
-  const int k = g.kx + 2 * g.ky + 4 * g.kz;
-#pragma unroll
-  for (int m = 0; m < 8; ++m) {
-    // lane ^ m in the cell order kx + 2 ky + 4 kz
-    const int km = ((m >> 2) & 1) + 2 * (m & 1) + 4 * ((m >> 1) & 1);
-    w.F[m] = F[k * 8 + (k ^ km)];
-  }
   return w;
-}
-
-// New value of the lane's cell: x_B + A_BB^-1 (b - A x)_B + noise.  ro[r]: element offset of the
-// start of the x window of row r within a plane; rows run from the far edge of the lane's own
-// window inwards (gal_plane_pair explains the sharing of rows between the y-partners; the
-// z-partners trade their planes' weighted sums likewise).
-template <typename T, int SPLIT>
-__device__ __forceinline__ T bot_update(const T* X, const int (&ro)[3], const T* s1d,
-                                        const BotWeights<T, SPLIT>& w, int own, T bk, T noise) {
-  // every read is issued before the first sum (two waves per SIMD leave the registers for it), so
-  // a pass waits for LDS once
-  constexpr int P = BotWeights<T, SPLIT>::P;
-  T win[P][3][5];
-#pragma unroll
-  for (int m = 0; m < P; ++m)
-#pragma unroll
-    for (int r = 0; r < 3; ++r)
-#pragma unroll
-      for (int d = 0; d < 5; ++d) win[m][r][d] = X[w.po[m] + ro[r] + d];
-  const T xk = X[own];
-  __builtin_amdgcn_sched_barrier(0);
-  T self = T(0), part = T(0);
-#pragma unroll
-  for (int m = 0; m < P; ++m) {
-    T rm[3], ra[3];
-#pragma unroll
-    for (int r = 0; r < 3; ++r) {
-      const T(&v)[5] = win[m][r];
-      const T e = v[0] + v[4], d = v[1] + v[3], c = v[2];  // the x factors are symmetric
-      rm[r] = fma(s1d[0], e, fma(s1d[1], d, s1d[2] * c));
-      ra[r] = fma(s1d[5], e, fma(s1d[6], d, s1d[7] * c));
-    }
-    const T* my = s1d + 10;
-    const T* ay = s1d + 15;
-    T p0 = my[0] * rm[1], p1 = ay[0] * rm[1];
-    p0 = fma(my[1], rm[2], p0);
-    p1 = fma(ay[1], rm[2], fma(my[0], ra[1], p1));
-    p1 = fma(my[1], ra[2], p1);
-    T q0 = my[0] * rm[0], q1 = ay[0] * rm[0];
-    q0 = fma(my[1], rm[1], fma(my[2], rm[2], q0));
-    q1 = fma(ay[1], rm[1], fma(ay[2], rm[2], q1));
-    T qa = my[0] * ra[0];
-    qa = fma(my[1], ra[1], fma(my[2], ra[2], qa));
-    q0 += dpp_lane<DPP_XOR1>(p0);
-    q1 = (q1 + qa) + dpp_lane<DPP_XOR1>(p1);
-    self = fma(w.own0[m], q0, fma(w.own1[m], q1, self));
-    part = fma(w.oth0[m], q0, fma(w.oth1[m], q1, part));
-  }
-  T ax = self + dpp_lane<DPP_XOR2>(part);
-  if (SPLIT == 4) ax = sum_rows(ax);
-  const T res = bk - ax;
-  const T mir = dpp_lane<DPP_XOR7>(res);  // lane ^ 7
-  T v0 = xk, v1 = noise;
-  v0 = fma(w.F[0], res, v0);
-  v1 = fma(w.F[7], mir, v1);
-  v0 = fma(w.F[1], dpp_lane<DPP_XOR1>(res), v0);
-  v1 = fma(w.F[6], dpp_lane<DPP_XOR1>(mir), v1);
-  v0 = fma(w.F[2], dpp_lane<DPP_XOR2>(res), v0);
-  v1 = fma(w.F[5], dpp_lane<DPP_XOR2>(mir), v1);
-  v0 = fma(w.F[3], dpp_lane<DPP_XOR3>(res), v0);
-  v1 = fma(w.F[4], dpp_lane<DPP_XOR3>(mir), v1);
-  return v0 + v1;
 }
 
 // x value at LDS element p (row position x) and its copy in the row's halo, if it has one
@@ -244,10 +107,10 @@ __device__ __forceinline__ void bot_sweeps_as(T* X, const T* B, const BotLevel& 
     for (int r = 0; r < 3; ++r)
       ro[r] = wrapm(y + (g.ky ? 2 - r : r - 2), ny) * sy + 4 * g.i + g.kx;
   };
-  auto pass = [&](const BotLane& g, const BotWeights<T, SPLIT>& w, const int (&ro)[3], int own,
+  auto pass = [&](const BotLane& g, const BlockWeights<T, SPLIT>& w, const int (&ro)[3], int own,
                   int cell, int cx, bool active, T noise) {
     const int d = 2 * cx;
-    const T v = bot_update<T, SPLIT>(X + d, ro, s1d, w, own, B[cell + d], noise);
+    const T v = block_update<T, SPLIT, true>(X + d, ro, s1d, w, own, B[cell + d], noise);
     if (active) bot_store(X, own + d, 4 * g.i + g.kx + d, nx, v);
   };
   if constexpr (ONE) {
@@ -284,7 +147,7 @@ __device__ __forceinline__ void bot_sweeps_as(T* X, const T* B, const BotLevel& 
       return;
     }
     if (NOISE) noise_of(0, n0, n1);
-    BotWeights<T, SPLIT> w;
+    BlockWeights<T, SPLIT> w;
     int zown = 0, znat = 0;
 #pragma unroll 1
     for (int st = 0; st < steps; ++st) {
@@ -322,7 +185,7 @@ __device__ __forceinline__ void bot_sweeps_as(T* X, const T* B, const BotLevel& 
           const BotLane g = bot_lane<SPLIT>(L, base + tid);
           const bool active = g.l < layers(cz);
           const int bz = 2 * (active ? g.l : 0) + cz;
-          const BotWeights<T, SPLIT> w = bot_weights<T, SPLIT>(nz, sz, tab, g, bz);
+          const BlockWeights<T, SPLIT> w = bot_weights<T, SPLIT>(nz, sz, tab, g, bz);
           int ro[3];
           rows(g, cy, ro);
           const int y = 4 * g.j + 2 * cy + g.ky, z = 2 * bz + g.kz, x = 4 * g.i + g.kx;
@@ -459,7 +322,7 @@ __device__ __forceinline__ void bottom_body(const BotArgs& a, const uint32_t com
     const gptr<T> bg = global_ptr<T>(a.b_in) + (size_t)comp * n0;
     for (int q = tid; q < n0; q += BOT_TPB) b0[q] = bg[q];
   }
-  // operator tables of the block levels: [zt nz*10][A_BB^-1 nz/2*64] at tab_off[i]; the normals
+  // operator tables of the block levels (bot_table_elems) at tab_off[i]; the normals
   // of the coarsest draw, which depend on nothing above it
   for (int i = 0; i < a.nlev; ++i) {
     const BotLevel& L = a.lv[i];
@@ -468,8 +331,10 @@ __device__ __forceinline__ void bottom_body(const BotArgs& a, const uint32_t com
       T* t = sm + a.tab_off[i];
       const gptr<T> zt = global_ptr<T>(L.zt), bf = global_ptr<T>(L.bfac);
       for (int q = tid; q < nz * 10; q += BOT_TPB) t[q] = zt[q];
-      for (int q = tid; q < (nz / 2) * 64; q += BOT_TPB)
-        t[nz * 10 + q] = bf[(q >> 6) * 192 + (q & 63)];
+      for (int q = tid; q < (nz / 2) * kBotRow; q += BOT_TPB) {
+        const int bz = q / kBotRow, e = q - bz * kBotRow;
+        t[nz * 10 + q] = bf[bz * kBlockRow + (e < 64 ? e : e - 64 + kBlockZ)];
+      }
     } else if (NOISE && part == BOT_WHOLE) {
       const int n = L.nx * L.ny * L.nz;
       T* ri = sm + a.lds_off[i] + 2 * n;

@@ -60,9 +60,9 @@ __global__ __launch_bounds__(TPB) void k_level_noise(NoiseGenArgs a, NoiseArgs n
   for (int m = 0; m < 4; ++m) normal_pair_t<T>(na, sid, comp, 4 * bid + m, n[2 * m], n[2 * m + 1]);
   if ((nbx * nby) % 64 == 0) {
     const uint32_t bzu = __builtin_amdgcn_readfirstlane(bz);
-    colour_block_noise<T, true>((const T*)L.bfac + (size_t)bzu * 192 + 64, n, e);
+    colour_block_noise<T, true>((const T*)L.bfac + (size_t)bzu * kBlockRow + 64, n, e);
   } else {
-    colour_block_noise<T, false>((const T*)L.bfac + (size_t)bz * 192 + 64, n, e);
+    colour_block_noise<T, false>((const T*)L.bfac + (size_t)bz * kBlockRow + 64, n, e);
   }
   const T sq = (T)na.sqkT;
   T* out = (T*)L.out + ((size_t)s * a.ncomp + comp) * N;
@@ -90,17 +90,14 @@ constexpr int TILE_D = 6;
 template <typename T, bool NOISE, int TILE_I, int TILE_J>
 __device__ __forceinline__ void block_tile_body(T* __restrict__ xg, const T* __restrict__ bg,
                                                 const T* __restrict__ s1d,
-                                                const T* __restrict__ zt,
                                                 const T* __restrict__ bfac, int nx, int ny,
                                                 int nz, uint32_t N, int colour, int nbx2,
                                                 int nby2, int ntx, const T* __restrict__ zn,
                                                 const Blk3 wg) {
+  // rows of 2 mod 4 elements (see block_plane_stride)
   constexpr int TILE_W = 4 * TILE_I + 2, TILE_H = 4 * TILE_J + 2;
   constexpr int TILE_TPB = TILE_I * TILE_J * 8;
-  // plane stride: the first count >= the plane that is 16 mod 32 elements.  The two z-layers
-  // of a block read planes three apart, so their lanes then fall on opposite halves of the
-  // 64 LDS banks and a wave's reads of one window offset are free of bank conflicts (FP64).
-  constexpr int TP = TILE_H * TILE_W + ((48 - (TILE_H * TILE_W) % 32) % 32);
+  constexpr int TP = block_plane_stride(TILE_H * TILE_W + 1, sizeof(T));  // + a pad element
   __shared__ T Tl[TILE_D * TP];
   const uint32_t comp = wg.z;
   const int l = wg.y;
@@ -121,7 +118,7 @@ __device__ __forceinline__ void block_tile_body(T* __restrict__ xg, const T* __r
   const int tx = 4 * il + 2 + kx, ty = 4 * jl + 2 + ky, tz = 2 + kz;
   const int gcx = 2 * bx + kx, gcy = 2 * by + ky, gcz = 2 * bz + kz;
   const uint32_t cell = ((uint32_t)gcz * ny + gcy) * nx + gcx;
-  T ax = 0, xk = 0, bk = 0, nrm = 0;
+  T bk = 0, nrm = 0;
   if (active) {
     bk = bg[(size_t)comp * N + cell];
     if (NOISE) nrm = zn[(size_t)comp * N + cell];
@@ -136,7 +133,7 @@ __device__ __forceinline__ void block_tile_body(T* __restrict__ xg, const T* __r
   for (int p = 0; p < PPT; ++p) {
     const int pos = tid + p * TILE_TPB;
     const int sx = pos % TILE_W, sy = pos / TILE_W;
-    // positions past the plane store into its pad element (TP = PLANE + 1): no branch
+    // positions past the plane store into its pad element: no branch
     loff[p] = pos < PLANE ? pos : PLANE;
     goff[p] = pos < PLANE ? wrap_near(y0 + sy, ny) * nx + wrap_near(x0 + sx, nx) : 0;
   }
@@ -154,50 +151,16 @@ __device__ __forceinline__ void block_tile_body(T* __restrict__ xg, const T* __r
 #pragma unroll
     for (int p = 0; p < PPT; ++p) Tl[sz * TP + loff[p]] = stage[sz][p];
   __syncthreads();
-  {
-    // The two z-layers of a block reach the same six staged planes (tile planes 0..5).  Lane
-    // kz computes the in-plane sums of planes 3kz .. 3kz+2 and trades them with its partner
-    // (lane ^ 4, same x and y), so each plane is reduced once per (x, y) pair, not twice.
-    // and each plane's rows are shared with the y-partner (lane ^ 2) the same way
-    const int xs[5] = {tx - 2, tx - 1, tx, tx + 1, tx + 2};
-    const int rows[3] = {ky ? ty + 2 : ty - 2, ty + (ky ? 1 : -1), ty};
-    T q0[3], q1[3];
+  BlockWeights<T, 1> w;
+  const T* row = bfac + (size_t)bz * kBlockRow;
+  block_weights<T, 1>(w, row, row + kBlockZ, kx, ky, kz, 0);
 #pragma unroll
-    for (int j = 0; j < 3; ++j)
-      gal_plane_pair<T>(Tl + (3 * kz + j) * TP, TILE_W, xs, rows, s1d, q0[j], q1[j]);
-    T o0[3], o1[3], w0[5], w1[5];
+  for (int m = 0; m < 3; ++m) w.po[m] = (3 * kz + m) * TP;
+  const Stencils<T> st = load_stencils(s1d);
+  int ro[3];
 #pragma unroll
-    for (int j = 0; j < 3; ++j) {
-      o0[j] = __shfl_xor(q0[j], 4, 8);
-      o1[j] = __shfl_xor(q1[j], 4, 8);
-    }
-    plane_window(kz, q0, o0, w0);
-    plane_window(kz, q1, o1, w1);
-    if (active) {
-      // cell tz = 2 + kz sees planes kz .. kz + 4 as dz = 0 .. 4
-      const T* zr = zt + gcz * 10;
-      T ax0 = 0, ax1 = 0;
-#pragma unroll
-      for (int dz = 0; dz < 5; ++dz) {
-        ax0 = fma(zr[dz], w0[dz], ax0);
-        ax1 = fma(zr[5 + dz], w1[dz], ax1);
-      }
-      ax = ax0 + ax1;
-      xk = Tl[tz * TP + ty * TILE_W + tx];
-    }
-  }
-  // x_B + A_BB^-1 (b_B - (A x)_B) equals A_BB^-1 (b_B - A_B,rest x_rest): the block's own
-  // coupling cancels, so only the residual needs to be shared across the block's lanes
-  const T* F = bfac + (size_t)bz * 192;
-  const T res = bk - ax;
-  // the noise field already holds sqrt(kT) L_BB^-T n for the block
-  T v0 = xk, v1 = NOISE ? nrm : T(0);
-#pragma unroll
-  for (int jj = 0; jj < 8; jj += 2) {
-    v0 = fma(F[k * 8 + jj], __shfl(res, jj, 8), v0);
-    v1 = fma(F[k * 8 + jj + 1], __shfl(res, jj + 1, 8), v1);
-  }
-  const T v = v0 + v1;
+  for (int r = 0; r < 3; ++r) ro[r] = (ty + (ky ? 2 - r : r - 2)) * TILE_W + tx - 2;
+  const T v = block_update<T, 1, false>(Tl, ro, st.v, w, tz * TP + ty * TILE_W + tx, bk, nrm);
   if (active) X[cell] = v;
 }
 
@@ -205,85 +168,74 @@ template <typename T, bool NOISE, int TILE_I, int TILE_J>
 __global__ __launch_bounds__(TILE_I * TILE_J * 8) void k_block_tile(T* __restrict__ xg,
                                                           const T* __restrict__ bg,
                                                           const T* __restrict__ s1d,
-                                                          const T* __restrict__ zt,
                                                           const T* __restrict__ bfac, int nx,
                                                           int ny, int nz, uint32_t N, int colour,
                                                           int nbx2, int nby2, int ntx,
                                                           const T* __restrict__ zn) {
-  block_tile_body<T, NOISE, TILE_I, TILE_J>(xg, bg, s1d, zt, bfac, nx, ny, nz, N, colour, nbx2,
+  block_tile_body<T, NOISE, TILE_I, TILE_J>(xg, bg, s1d, bfac, nx, ny, nz, N, colour, nbx2,
                                             nby2, ntx, zn, xcd_block());
 }
 
-// Two block colours c and c ^ 1 in one launch.  They differ only in the parity of bx, so a
-// block of colour c ^ 1 depends on colour-c blocks only through its x-neighbours in the same
-// block row and layer.  A work-group owns PJ (4, 2 or 1: see pair_rows) block rows
-// by = 2 (j0 + jl) + cy of one block layer bz = 2 l + cz over the whole x-extent (periodic, so
-// no x-halo), stages the cells within two
-// of them (nx x (4 PJ + 2) x 6, wall planes clamped), draws colour c into the tile, then colour
-// c ^ 1 from the updated tile, and writes both.  No other work-group stages a cell that this
-// one writes (rows of parity cy are four cells apart, and rows and layers of the other parity
-// are not written), and every value is computed by the arithmetic of the single-colour pass
-// from the same inputs, so the result is that of the two single-colour passes in order.
-// The work of one work-group wg = (row group, layer, component); threads past the level's
-// (nx / 4) PJ 8 take part in the staging only.
-template <typename T, bool NOISE, int PJ>
-__device__ __forceinline__ void block_pair_body(T* __restrict__ xg, const T* __restrict__ bg,
-                                                const T* __restrict__ s1d,
-                                                const T* __restrict__ zt,
-                                                const T* __restrict__ bfac, int nx, int ny,
-                                                int nz, uint32_t N, int c_first, int nby2,
-                                                int TP, const T* __restrict__ zn,
+// Half a sweep in one launch: the four block colours of one layer parity cz, in sweep order (cy 0
+// then 1, within each cx 0 then 1; reversed in a post-sweep).  A block row depends on the rows of
+// the other cy on both sides, so a work-group that owns a pair of block rows of one layer over
+// the whole (periodic) x-extent also draws the row of the first cy beyond its own (which it does
+// not store), and then all the rows that its second cy needs are in its tile.  Every value is
+// computed from the same inputs by the same arithmetic as in four single-colour passes, so the
+// result is theirs, bit for bit.  The rows a work-group stages are rewritten by its neighbours in
+// the same launch, so the layers are read from one field and written to another: xs holds this
+// parity's layers before the half-sweep, xo the other parity's, xn receives this parity's.
+//
+// The tile is HALF_ROWS cell rows of the layer's six planes with two periodic halo cells per row
+// side; the first row is the cell row 4 j0 - 2 (pre) or 4 j0 - 4 (post), so that the rows of the
+// first cy start at 2 and those of the second at 4 in both.
+//
+// What bounds it: the launch and the latency of the staging loads, on the levels of few
+// components it is used for.  A two-colour launch takes nearly as long (5.9 us at 32^3 x 3, FP64;
+// a half-sweep 8.4 us), and a sweep needs four of those: 23.6 -> 16.8 us.
+template <typename T, bool NOISE>
+__device__ __forceinline__ void block_half_body(const HalfItem<T>& h, int cz, bool post,
                                                 const Blk3 wg) {
   extern __shared__ char smraw[];
   T* Tl = reinterpret_cast<T*>(smraw);
-  const uint32_t comp = wg.z;
-  const int cy = (c_first >> 1) & 1, cz = c_first >> 2;
-  const int bz = 2 * (int)wg.y + cz;
-  const int j0 = (int)wg.x * PJ;
-  const int H = 4 * PJ + 2;  // staged rows
-  const int RS = nx;         // row stride of the tile (padding it measured slower)
-  const int y0 = 4 * j0 + 2 * cy - 2, z0 = 2 * bz - 2;
-  const int nthr = (int)blockDim.x;  // >= (nx / 4) PJ 8
-  T* X = xg + (size_t)comp * N;
-  const int tid = threadIdx.x;
-  const int k = tid & 7;
-  const int nbx2 = nx >> 2;
+  const int nx = h.nx, ny = h.ny, nz = h.nz;
+  const size_t base = (size_t)wg.z * h.N;
+  const int bz = 2 * (int)wg.y + cz, j0 = (int)wg.x;
+  const int RS = nx + 2 * kBotHalo + 2;
+  const int TP = h.TP;
+  const int y0 = 4 * j0 - (post ? 4 : 2), z0 = 2 * bz - 2;
+  const int tid = threadIdx.x, nthr = (int)blockDim.x;
+  const int kx = tid & 1, ky = (tid >> 1) & 1, kz = (tid >> 2) & 1;
   int il, jl;
-  divmod_uniform(tid >> 3, nbx2, jl, il);
-  const bool active = jl < PJ && j0 + jl < nby2;
-  // rows of inactive lanes past the group's PJ rows are taken as row 0 for addressing only,
-  // so that every tile read stays inside the staged rows
-  const int jr = jl < PJ ? jl : 0;
-  const int kx = k & 1, ky = (k >> 1) & 1, kz = k >> 2;
-  const int by = 2 * (j0 + jr) + cy;
-  const int ty = 4 * jr + 2 + ky, tz = 2 + kz;
-  const int gcy = 2 * by + ky, gcz = 2 * bz + kz;
-  // the lane's cell in each phase: bx = 2 il + (colour & 1)
-  const int cx0 = c_first & 1, cx1 = cx0 ^ 1;
-  const int gx0 = 2 * (2 * il + cx0) + kx, gx1 = 2 * (2 * il + cx1) + kx;
-  const uint32_t row = ((uint32_t)gcz * ny + gcy) * nx;
-  T bk0 = 0, bk1 = 0, n0 = 0, n1 = 0;
-  if (active) {
-    bk0 = bg[(size_t)comp * N + row + gx0];
-    bk1 = bg[(size_t)comp * N + row + gx1];
-    if (NOISE) {
-      n0 = zn[(size_t)comp * N + row + gx0];
-      n1 = zn[(size_t)comp * N + row + gx1];
+  divmod_uniform(tid >> 3, nx >> 2, jl, il);
+  const int jr = jl <= 1 ? jl : 0;  // lanes past the tile read inside it and store nothing
+  const int gcz = 2 * bz + kz;
+  // this lane's cells: row jr of the first cy, then of the second, each at cx = 0 and 1
+  uint32_t cell[2];
+  T b[2][2], n[2][2];
+#pragma unroll
+  for (int q = 0; q < 2; ++q) {
+    const int gy = wrap_near(y0 + 2 + 2 * q + 4 * jr + ky, ny);
+    cell[q] = ((uint32_t)gcz * ny + gy) * nx + 4 * il + kx;
+#pragma unroll
+    for (int c = 0; c < 2; ++c) {
+      b[q][c] = h.b[base + cell[q] + 2 * c];
+      n[q][c] = NOISE ? h.zn[base + cell[q] + 2 * c] : T(0);
     }
   }
-  // stage: a plane has nx (4 PJ + 2) positions and the group (nx / 4) PJ 8 threads, so every
-  // thread owns at most three positions (2 + 1/PJ per thread); all their loads in all six
-  // planes are issued before the first store, so the group waits for memory once
+  // stage: at most three positions of a plane per thread (10 nx positions, 4 nx threads); all
+  // their loads in all six planes are issued before the first store
   constexpr int PPT = 3;
-  const int plane = nx * H;
-  int goff[PPT], loff[PPT];
+  const int plane = nx * HALF_ROWS;
+  int goff[PPT], loff[PPT], hoff[PPT];
 #pragma unroll
   for (int p = 0; p < PPT; ++p) {
     const int pos = tid + p * nthr;
     const bool in = pos < plane;
     int py, px;
     divmod_uniform(pos, nx, py, px);
-    loff[p] = in ? py * RS + px : -1;
+    loff[p] = in ? py * RS + px + kBotHalo : -1;
+    hoff[p] = px < 2 ? nx : (px >= nx - 2 ? -nx : 0);
     goff[p] = in ? wrap_near(y0 + py, ny) * nx + px : 0;
   }
   T stage[TILE_D][PPT];
@@ -291,96 +243,196 @@ __device__ __forceinline__ void block_pair_body(T* __restrict__ xg, const T* __r
   for (int sz = 0; sz < TILE_D; ++sz) {
     int gz = z0 + sz;
     gz = gz < 0 ? 0 : (gz >= nz ? nz - 1 : gz);
-    const T* P = X + (size_t)gz * ny * nx;
+    const T* S = ((gz >> 1) & 1) == cz ? h.xs : h.xo;
+    const T* Pl = S + base + (size_t)gz * ny * nx;
 #pragma unroll
-    for (int p = 0; p < PPT; ++p) stage[sz][p] = P[goff[p]];  // goff = 0 (in range) if unused
+    for (int p = 0; p < PPT; ++p) stage[sz][p] = Pl[goff[p]];  // goff = 0 (in range) if unused
   }
 #pragma unroll
   for (int sz = 0; sz < TILE_D; ++sz)
 #pragma unroll
     for (int p = 0; p < PPT; ++p)
-      if (loff[p] >= 0) Tl[sz * TP + loff[p]] = stage[sz][p];
-  __syncthreads();
-  const T* F = bfac + (size_t)bz * 192;
-  const T* zr = zt + gcz * 10;
-  // one phase: the lane's block of colour bit cxp (tile x = global x, periodic)
-  auto lane_update = [&](int gx, T bk, T nrm) -> T {
-    int xs[5];
-#pragma unroll
-    for (int d = 0; d < 5; ++d) xs[d] = wrapm(gx + d - 2, nx);
-    const int rows[3] = {ky ? ty + 2 : ty - 2, ty + (ky ? 1 : -1), ty};
-    T q0[3], q1[3];
-#pragma unroll
-    for (int j = 0; j < 3; ++j)
-      gal_plane_pair<T>(Tl + (3 * kz + j) * TP, RS, xs, rows, s1d, q0[j], q1[j]);
-    T o0[3], o1[3], w0[5], w1[5];
-#pragma unroll
-    for (int j = 0; j < 3; ++j) {
-      o0[j] = __shfl_xor(q0[j], 4, 8);
-      o1[j] = __shfl_xor(q1[j], 4, 8);
-    }
-    plane_window(kz, q0, o0, w0);
-    plane_window(kz, q1, o1, w1);
-    T ax = 0, xk = 0;
-    if (active) {
-      T ax0 = 0, ax1 = 0;
-#pragma unroll
-      for (int dz = 0; dz < 5; ++dz) {
-        ax0 = fma(zr[dz], w0[dz], ax0);
-        ax1 = fma(zr[5 + dz], w1[dz], ax1);
+      if (loff[p] >= 0) {
+        Tl[sz * TP + loff[p]] = stage[sz][p];
+        if (hoff[p]) Tl[sz * TP + loff[p] + hoff[p]] = stage[sz][p];
       }
-      ax = ax0 + ax1;
-      xk = Tl[tz * TP + ty * RS + gx];
-    }
-    const T res = bk - ax;
-    T v0 = xk, v1 = NOISE ? nrm : T(0);
+  __builtin_amdgcn_sched_barrier(0);
+  BlockWeights<T, 1> w;
+  const T* row = h.bfac + (size_t)bz * kBlockRow;
+  block_weights<T, 1>(w, row, row + kBlockZ, kx, ky, kz, 0);
 #pragma unroll
-    for (int jj = 0; jj < 8; jj += 2) {
-      v0 = fma(F[k * 8 + jj], __shfl(res, jj, 8), v0);
-      v1 = fma(F[k * 8 + jj + 1], __shfl(res, jj + 1, 8), v1);
-    }
-    return v0 + v1;
-  };
-  // colour c is written into the tile in place: blocks of one colour never read each other's
-  // cells, and the eight lanes of a block are one wave, whose reads precede its writes
-  const T va = lane_update(gx0, bk0, n0);
-  if (active) {
-    Tl[tz * TP + ty * RS + gx0] = va;
-    X[row + gx0] = va;
-  }
+  for (int m = 0; m < 3; ++m) w.po[m] = (3 * kz + m) * TP;
   __syncthreads();
-  const T vb = lane_update(gx1, bk1, n1);
-  if (active) X[row + gx1] = vb;
+  const Stencils<T> s1d = load_stencils(h.s1d);
+  const int wave_row = __builtin_amdgcn_readfirstlane(jl);  // the wave's first block row
+#pragma unroll
+  for (int q = 0; q < 2; ++q) {
+    const int rows = 2 - q;
+    const int ty = 2 + 2 * q + 4 * jr + ky;
+    int ro[3];
+#pragma unroll
+    for (int r = 0; r < 3; ++r) ro[r] = (ty + (ky ? 2 - r : r - 2)) * RS + 4 * il + kx;
+    const int at = (2 + kz) * TP + ty * RS + 4 * il + kx + kBotHalo;
+    const bool draws = jl < rows;
+    // the row beyond the group's own: the second of a pre-sweep's first cy, the first of a post's
+    const bool stores = draws && (q == 1 || jl == (post ? 1 : 0));
+#pragma unroll
+    for (int c = 0; c < 2; ++c) {
+      if (wave_row < rows) {  // whole waves without a row only keep the barrier
+        const int cx = post ? 1 - c : c, d = 2 * cx;
+        const T v = block_update<T, 1, false>(Tl + d, ro, s1d.v, w, at, cx ? b[q][1] : b[q][0],
+                                              cx ? n[q][1] : n[q][0]);
+        if (draws) {
+          const int x = 4 * il + kx + d;
+          T* t = Tl + at + d;
+          t[0] = v;
+          if (x < 2) t[nx] = v;
+          if (x >= nx - 2) t[-nx] = v;
+          if (stores) h.xn[base + cell[q] + d] = v;
+        }
+      }
+      if (q == 0 || c == 0) __syncthreads();
+    }
+  }
 }
 
-template <typename T, bool NOISE, int PJ>
-__global__ __launch_bounds__(512) void k_block_pair(T* __restrict__ xg, const T* __restrict__ bg,
-                                                    const T* __restrict__ s1d,
-                                                    const T* __restrict__ zt,
-                                                    const T* __restrict__ bfac, int nx, int ny,
-                                                    int nz, uint32_t N, int c_first, int nby2,
-                                                    int TP, const T* __restrict__ zn) {
-  block_pair_body<T, NOISE, PJ>(xg, bg, s1d, zt, bfac, nx, ny, nz, N, c_first, nby2, TP, zn,
-                                xcd_block());
-}
-
-// Two-colour launches of several levels of different hierarchies (the same colour pair and
-// rows per group) in one launch: the flat grid concatenates the items' (row group, layer,
-// component) grids; the block size and the LDS are the largest the items need.
-template <typename T, bool NOISE, int PJ>
-__global__ __launch_bounds__(512) void k_block_pair_multi(PairMultiArgs<T> m) {
+// Half-sweeps of the levels of several hierarchies (or of one) in one launch: the flat grid
+// concatenates the items' (row group, layer, component) grids in XCD-aware order; the block size
+// and the LDS are the largest the items need.
+template <typename T, bool NOISE>
+__global__ __launch_bounds__(HALF_TPB, 3) void k_block_half(HalfArgs<T> m) {
   const uint32_t lin = xcd_block().x;
   int i = 0;
   while (i + 1 < m.nitems && lin >= m.begin[i + 1]) ++i;
-  const PairMultiItem<T>& it = m.it[i];
+  const HalfItem<T>& it = m.it[i];
   const uint32_t local = lin - m.begin[i];
   Blk3 wg;
   wg.x = local % (uint32_t)it.ngx;
   const uint32_t rest = local / (uint32_t)it.ngx;
   wg.y = rest % (uint32_t)it.nbzc;
   wg.z = rest / (uint32_t)it.nbzc;
-  block_pair_body<T, NOISE, PJ>(it.x, it.b, it.s1d, it.zt, it.bfac, it.nx, it.ny, it.nz, it.N,
-                                m.c_first, it.nby2, it.TP, it.zn, wg);
+  block_half_body<T, NOISE>(it, m.cz, m.post != 0, wg);
+}
+
+// Two block colours c and c ^ 1 in one launch.  They differ only in the parity of bx, so a
+// block of colour c ^ 1 depends on colour-c blocks only through its x-neighbours in the same
+// block row and layer.  A work-group owns PJ (4, 2 or 1: see pair_rows) block rows
+// by = 2 (j0 + jl) + cy of one block layer bz = 2 l + cz over the whole x-extent (periodic: two
+// halo cells per row side), stages the cells within two of them ((4 PJ + 2) rows of 6 planes, wall
+// planes clamped), draws colour c into the tile, then colour c ^ 1 from the updated tile, and
+// writes both.  No other work-group stages a cell that this one writes (rows of parity cy are
+// four cells apart, and rows and layers of the other parity are not written), and every value is
+// computed by the arithmetic of the single-colour pass from the same inputs, so the result is that
+// of the two single-colour passes in order.  FP64, 64^3 x 24, two rows a group: 28 us a launch
+// (before the DPP exchanges, the bank-free plane stride and the packed factors 32 us; VALU
+// instructions per wave 753 -> 610, LDS cycles 8.2 M -> 6.1 M a launch).
+template <typename T, bool NOISE>
+__device__ __forceinline__ void block_pair_body(const HalfItem<T>& h, int c_first, const Blk3 wg) {
+  extern __shared__ char smraw[];
+  T* Tl = reinterpret_cast<T*>(smraw);
+  const int nx = h.nx, ny = h.ny, nz = h.nz, PJ = h.P, TP = h.TP;
+  const size_t base = (size_t)wg.z * h.N;
+  const int cy = (c_first >> 1) & 1, cz = c_first >> 2;
+  const int bz = 2 * (int)wg.y + cz, j0 = (int)wg.x * PJ;
+  const int H = 4 * PJ + 2, RS = nx + 2 * kBotHalo + 2;
+  const int y0 = 4 * j0 + 2 * cy - 2, z0 = 2 * bz - 2;
+  const int nthr = (int)blockDim.x;  // >= 2 nx PJ
+  T* X = h.xn + base;
+  const int tid = threadIdx.x;
+  const int kx = tid & 1, ky = (tid >> 1) & 1, kz = (tid >> 2) & 1;
+  const int nbx2 = nx >> 2;
+  int il, jl;
+  divmod_uniform(tid >> 3, nbx2, jl, il);
+  const bool active = jl < PJ && j0 + jl < (ny >> 2);
+  // lanes past the group's rows take row 0 for addressing only
+  const int jr = jl < PJ ? jl : 0;
+  const int ty = 4 * jr + 2 + ky;
+  const int gcy = wrap_near(y0 + ty, ny), gcz = 2 * bz + kz;
+  const uint32_t cell = ((uint32_t)gcz * ny + gcy) * nx + 4 * il + kx;  // at cx = 0
+  const T b0 = h.b[base + cell], b1 = h.b[base + cell + 2];
+  const T n0 = NOISE ? h.zn[base + cell] : T(0), n1 = NOISE ? h.zn[base + cell + 2] : T(0);
+  // stage: a plane has nx (4 PJ + 2) positions and the group 2 nx PJ threads, so every thread
+  // owns at most three positions; all their loads in all six planes are issued before the first
+  // store, so the group waits for memory once
+  constexpr int PPT = 3;
+  const int plane = nx * H;
+  int goff[PPT], loff[PPT], hoff[PPT];
+#pragma unroll
+  for (int p = 0; p < PPT; ++p) {
+    const int pos = tid + p * nthr;
+    const bool in = pos < plane;
+    int py, px;
+    divmod_uniform(pos, nx, py, px);
+    loff[p] = in ? py * RS + px + kBotHalo : -1;
+    hoff[p] = px < 2 ? nx : (px >= nx - 2 ? -nx : 0);
+    goff[p] = in ? wrap_near(y0 + py, ny) * nx + px : 0;
+  }
+  T stage[TILE_D][PPT];
+#pragma unroll
+  for (int sz = 0; sz < TILE_D; ++sz) {
+    int gz = z0 + sz;
+    gz = gz < 0 ? 0 : (gz >= nz ? nz - 1 : gz);
+    const T* Pl = X + (size_t)gz * ny * nx;
+#pragma unroll
+    for (int p = 0; p < PPT; ++p) stage[sz][p] = Pl[goff[p]];  // goff = 0 (in range) if unused
+  }
+#pragma unroll
+  for (int sz = 0; sz < TILE_D; ++sz)
+#pragma unroll
+    for (int p = 0; p < PPT; ++p)
+      if (loff[p] >= 0) {
+        Tl[sz * TP + loff[p]] = stage[sz][p];
+        if (hoff[p]) Tl[sz * TP + loff[p] + hoff[p]] = stage[sz][p];
+      }
+  __builtin_amdgcn_sched_barrier(0);
+  BlockWeights<T, 1> w;
+  const T* row = h.bfac + (size_t)bz * kBlockRow;
+  block_weights<T, 1>(w, row, row + kBlockZ, kx, ky, kz, 0);
+#pragma unroll
+  for (int m = 0; m < 3; ++m) w.po[m] = (3 * kz + m) * TP;
+  __syncthreads();
+  const Stencils<T> s1d = load_stencils(h.s1d);
+  const int cx0 = c_first & 1;
+  int ro[3];
+#pragma unroll
+  for (int r = 0; r < 3; ++r) ro[r] = (ty + (ky ? 2 - r : r - 2)) * RS + 4 * il + kx;
+  const int at = (2 + kz) * TP + ty * RS + 4 * il + kx + kBotHalo;
+  // colour c is written into the tile in place: blocks of one colour never read each other's
+  // cells, and the eight lanes of a block are one wave, whose reads precede its writes
+  {
+    const int d = 2 * cx0, x = 4 * il + kx + d;
+    const T v = block_update<T, 1, false>(Tl + d, ro, s1d.v, w, at, cx0 ? b1 : b0, cx0 ? n1 : n0);
+    if (active) {
+      T* t = Tl + at + d;
+      t[0] = v;
+      if (x < 2) t[nx] = v;
+      if (x >= nx - 2) t[-nx] = v;
+      X[cell + d] = v;
+    }
+  }
+  __syncthreads();
+  {
+    const int d = 2 - 2 * cx0;
+    const T v = block_update<T, 1, false>(Tl + d, ro, s1d.v, w, at, cx0 ? b0 : b1, cx0 ? n0 : n1);
+    if (active) X[cell + d] = v;
+  }
+}
+
+// Two-colour launches of the levels of several hierarchies (or of one) in one launch, as
+// k_block_half.
+template <typename T, bool NOISE>
+__global__ __launch_bounds__(HALF_TPB) void k_block_pair(HalfArgs<T> m) {
+  const uint32_t lin = xcd_block().x;
+  int i = 0;
+  while (i + 1 < m.nitems && lin >= m.begin[i + 1]) ++i;
+  const HalfItem<T>& it = m.it[i];
+  const uint32_t local = lin - m.begin[i];
+  Blk3 wg;
+  wg.x = local % (uint32_t)it.ngx;
+  const uint32_t rest = local / (uint32_t)it.ngx;
+  wg.y = rest % (uint32_t)it.nbzc;
+  wg.z = rest / (uint32_t)it.nbzc;
+  block_pair_body<T, NOISE>(it, m.cz, wg);
 }
 
 // The same pass for several levels of different hierarchies (one colour) in one launch: the
@@ -399,7 +451,7 @@ __global__ __launch_bounds__(TILE_I * TILE_J * 8) void k_block_tile_multi(BlockM
   const uint32_t rest = local / tiles;
   wg.y = rest % (uint32_t)it.nbzc;
   wg.z = rest / (uint32_t)it.nbzc;
-  block_tile_body<T, NOISE, TILE_I, TILE_J>(it.x, it.b, it.s1d, it.zt, it.bfac, it.nx, it.ny,
+  block_tile_body<T, NOISE, TILE_I, TILE_J>(it.x, it.b, it.s1d, it.bfac, it.nx, it.ny,
                                             it.nz, it.N, m.colour, it.nbx2, it.nby2, it.ntx,
                                             it.zn, wg);
 }
@@ -593,7 +645,7 @@ __global__ __launch_bounds__(CO_TPB) void k_coarsest(T* __restrict__ xg,
 }  // namespace
 
 template <typename T, int TI, int TJ>
-void launch_block_tile(T* x, const T* b, const T* s1d, const T* zt, const T* bfac, int nx, int ny,
+void launch_block_tile(T* x, const T* b, const T* s1d, const T* bfac, int nx, int ny,
                        int nz, int ncomp, int colour, const T* zn, int nbx2,
                        int nby2, int nbzc, hipStream_t s) {
   const uint32_t N = (uint32_t)nx * ny * nz;
@@ -601,14 +653,14 @@ void launch_block_tile(T* x, const T* b, const T* s1d, const T* zt, const T* bfa
   dim3 grid(ntx * nty, nbzc, ncomp);
   if (zn)
     k_block_tile<T, true, TI, TJ><<<grid, TI * TJ * 8, 0, s>>>(
-        x, b, s1d, zt, bfac, nx, ny, nz, N, colour, nbx2, nby2, ntx, zn);
+        x, b, s1d, bfac, nx, ny, nz, N, colour, nbx2, nby2, ntx, zn);
   else
     k_block_tile<T, false, TI, TJ><<<grid, TI * TJ * 8, 0, s>>>(
-        x, b, s1d, zt, bfac, nx, ny, nz, N, colour, nbx2, nby2, ntx, zn);
+        x, b, s1d, bfac, nx, ny, nz, N, colour, nbx2, nby2, ntx, zn);
 }
 
 template <typename T>
-hipError_t launch_block_pass(T* x, const T* b, const T* s1d, const T* zt, const T* bfac, int nx,
+hipError_t launch_block_pass(T* x, const T* b, const T* s1d, const T* bfac, int nx,
                              int ny, int nz, int ncomp, int colour, const T* zn,
                              int tile, hipStream_t s) {
   const int nbx2 = nx / 4, nby2 = ny / 4;
@@ -624,12 +676,67 @@ hipError_t launch_block_pass(T* x, const T* b, const T* s1d, const T* zt, const 
     tile = wg84 >= 512 ? SMG_TILE_8X4 : (wg44 >= 512 ? SMG_TILE_4X4 : SMG_TILE_4X2);
   }
   if (tile == SMG_TILE_4X2)
-    launch_block_tile<T, 4, 2>(x, b, s1d, zt, bfac, nx, ny, nz, ncomp, colour, zn, nbx2, nby2, nbzc, s);
+    launch_block_tile<T, 4, 2>(x, b, s1d, bfac, nx, ny, nz, ncomp, colour, zn, nbx2, nby2, nbzc, s);
   else if (tile == SMG_TILE_8X4)
-    launch_block_tile<T, 8, 4>(x, b, s1d, zt, bfac, nx, ny, nz, ncomp, colour, zn, nbx2, nby2, nbzc, s);
+    launch_block_tile<T, 8, 4>(x, b, s1d, bfac, nx, ny, nz, ncomp, colour, zn, nbx2, nby2, nbzc, s);
   else
-    launch_block_tile<T, 4, 4>(x, b, s1d, zt, bfac, nx, ny, nz, ncomp, colour, zn, nbx2, nby2, nbzc, s);
+    launch_block_tile<T, 4, 4>(x, b, s1d, bfac, nx, ny, nz, ncomp, colour, zn, nbx2, nby2, nbzc, s);
   return hipGetLastError();
+}
+
+template <typename T>
+hipError_t launch_block_half(const HalfPassItem<T>* items, int n, int cz, bool post, bool noise,
+                             hipStream_t s) {
+  for (int q = 0; q < n; ++q)
+    if (!half_level(items[q].nx, items[q].ny)) return hipErrorNotSupported;
+  HalfArgs<T> m{};
+  m.cz = cz;
+  m.post = post;
+  uint32_t total = 0;
+  int nthr = 0;
+  size_t lds = 0;
+  auto flush = [&]() -> hipError_t {
+    if (m.nitems == 0) return hipSuccess;
+    m.begin[m.nitems] = total;
+    if (noise) k_block_half<T, true><<<total, nthr, lds, s>>>(m);
+    else k_block_half<T, false><<<total, nthr, lds, s>>>(m);
+    m.nitems = 0;
+    total = 0;
+    nthr = 0;
+    lds = 0;
+    return hipGetLastError();
+  };
+  for (int q = 0; q < n; ++q) {
+    const HalfPassItem<T>& p = items[q];
+    const int nby2 = p.ny / 4, nbzc = (p.nz / 2 + 1 - cz) / 2;
+    if (nby2 * nbzc == 0 || p.ncomp == 0) continue;
+    if (m.nitems == kHalfItems) {
+      hipError_t e = flush();
+      if (e != hipSuccess) return e;
+    }
+    HalfItem<T>& it = m.it[m.nitems];
+    it.xs = p.xs;
+    it.xo = p.xo;
+    it.xn = p.xn;
+    it.b = p.b;
+    it.s1d = p.s1d;
+    it.bfac = p.bfac;
+    it.zn = p.zn;
+    it.nx = p.nx;
+    it.ny = p.ny;
+    it.nz = p.nz;
+    it.N = (uint32_t)p.nx * p.ny * p.nz;
+    it.P = 1;
+    it.nbzc = nbzc;
+    it.ngx = nby2;
+    it.TP = block_plane_stride(HALF_ROWS * (p.nx + 2 * kBotHalo + 2), sizeof(T));
+    m.begin[m.nitems] = total;
+    total += (uint32_t)it.ngx * nbzc * p.ncomp;
+    nthr = std::max(nthr, (4 * p.nx + 63) / 64 * 64);
+    lds = std::max(lds, (size_t)TILE_D * it.TP * sizeof(T));
+    ++m.nitems;
+  }
+  return flush();
 }
 
 // Block rows per work-group of a two-colour launch: the most (4, or 2 above 64 cells in x, for
@@ -643,46 +750,20 @@ inline int pair_rows(int nx, int ny, int nz, int ncomp, int c_first) {
 }
 
 template <typename T>
-hipError_t launch_block_pair(T* x, const T* b, const T* s1d, const T* zt, const T* bfac, int nx,
-                             int ny, int nz, int ncomp, int c_first, const T* zn,
+hipError_t launch_block_pair(const HalfPassItem<T>* items, int n, int c_first, bool noise,
                              hipStream_t s) {
-  if (nx > 128 || nx % 4 || ny % 4) return hipErrorNotSupported;
-  const int nby2 = ny / 4, nbzc = (nz / 2 + 1 - (c_first >> 2)) / 2;
-  if (nby2 * nbzc == 0 || ncomp == 0) return hipSuccess;
-  const int PJ = pair_rows(nx, ny, nz, ncomp, c_first);
-  const int plane = nx * (4 * PJ + 2);
-  const int TP = plane + ((48 - plane % 32) % 32);
-  const size_t lds = (size_t)TILE_D * TP * sizeof(T);
-  const int nthr = (nx / 4) * PJ * 8;
-  dim3 grid((nby2 + PJ - 1) / PJ, nbzc, ncomp);
-  const uint32_t N = (uint32_t)nx * ny * nz;
-#define SMG_PAIR(NZ, P)                                                                   \
-  k_block_pair<T, NZ, P><<<grid, nthr, lds, s>>>(x, b, s1d, zt, bfac, nx, ny, nz, N, c_first, \
-                                                 nby2, TP, zn)
-  if (PJ == 4) {
-    if (zn) SMG_PAIR(true, 4); else SMG_PAIR(false, 4);
-  } else if (PJ == 2) {
-    if (zn) SMG_PAIR(true, 2); else SMG_PAIR(false, 2);
-  } else {
-    if (zn) SMG_PAIR(true, 1); else SMG_PAIR(false, 1);
-  }
-#undef SMG_PAIR
-  return hipGetLastError();
-}
-
-template <typename T, int PJ>
-hipError_t launch_pair_multi_pj(const BlockPassItem<T>* items, int n, int c_first, bool noise,
-                                hipStream_t s) {
-  PairMultiArgs<T> m{};
-  m.c_first = c_first;
+  for (int q = 0; q < n; ++q)
+    if (!half_level(items[q].nx, items[q].ny)) return hipErrorNotSupported;
+  HalfArgs<T> m{};
+  m.cz = c_first;
   uint32_t total = 0;
   int nthr = 0;
   size_t lds = 0;
   auto flush = [&]() -> hipError_t {
     if (m.nitems == 0) return hipSuccess;
     m.begin[m.nitems] = total;
-    if (noise) k_block_pair_multi<T, true, PJ><<<total, nthr, lds, s>>>(m);
-    else k_block_pair_multi<T, false, PJ><<<total, nthr, lds, s>>>(m);
+    if (noise) k_block_pair<T, true><<<total, nthr, lds, s>>>(m);
+    else k_block_pair<T, false><<<total, nthr, lds, s>>>(m);
     m.nitems = 0;
     total = 0;
     nthr = 0;
@@ -690,48 +771,34 @@ hipError_t launch_pair_multi_pj(const BlockPassItem<T>* items, int n, int c_firs
     return hipGetLastError();
   };
   for (int q = 0; q < n; ++q) {
-    const BlockPassItem<T>& p = items[q];
-    if (pair_rows(p.nx, p.ny, p.nz, p.ncomp, c_first) != PJ) continue;
+    const HalfPassItem<T>& p = items[q];
     const int nby2 = p.ny / 4, nbzc = (p.nz / 2 + 1 - (c_first >> 2)) / 2;
     if (nby2 * nbzc == 0 || p.ncomp == 0) continue;
-    if (m.nitems == kBlockMultiItems) {
+    if (m.nitems == kHalfItems) {
       hipError_t e = flush();
       if (e != hipSuccess) return e;
     }
-    PairMultiItem<T>& it = m.it[m.nitems];
-    it.x = p.x;
+    HalfItem<T>& it = m.it[m.nitems];
+    it.xn = p.xn;
     it.b = p.b;
     it.s1d = p.s1d;
-    it.zt = p.zt;
     it.bfac = p.bfac;
     it.zn = p.zn;
     it.nx = p.nx;
     it.ny = p.ny;
     it.nz = p.nz;
     it.N = (uint32_t)p.nx * p.ny * p.nz;
-    it.nby2 = nby2;
+    it.P = pair_rows(p.nx, p.ny, p.nz, p.ncomp, c_first);
     it.nbzc = nbzc;
-    it.ngx = (nby2 + PJ - 1) / PJ;
-    const int plane = p.nx * (4 * PJ + 2);
-    it.TP = plane + ((48 - plane % 32) % 32);
+    it.ngx = (nby2 + it.P - 1) / it.P;
+    it.TP = block_plane_stride((4 * it.P + 2) * (p.nx + 2 * kBotHalo + 2), sizeof(T));
     m.begin[m.nitems] = total;
     total += (uint32_t)it.ngx * nbzc * p.ncomp;
-    nthr = std::max(nthr, (p.nx / 4) * PJ * 8);
+    nthr = std::max(nthr, (2 * it.P * p.nx + 63) / 64 * 64);
     lds = std::max(lds, (size_t)TILE_D * it.TP * sizeof(T));
     ++m.nitems;
   }
   return flush();
-}
-
-template <typename T>
-hipError_t launch_block_pair_multi(const BlockPassItem<T>* items, int n, int c_first,
-                                   bool noise, hipStream_t s) {
-  for (int q = 0; q < n; ++q)
-    if (!pair_level(items[q].nx, items[q].ny)) return hipErrorNotSupported;
-  hipError_t e = launch_pair_multi_pj<T, 4>(items, n, c_first, noise, s);
-  if (e == hipSuccess) e = launch_pair_multi_pj<T, 2>(items, n, c_first, noise, s);
-  if (e == hipSuccess) e = launch_pair_multi_pj<T, 1>(items, n, c_first, noise, s);
-  return e;
 }
 
 template <typename T, int TI, int TJ>
@@ -764,7 +831,6 @@ hipError_t launch_block_multi_tiled(const BlockPassItem<T>* items, int n, int co
     it.x = p.x;
     it.b = p.b;
     it.s1d = p.s1d;
-    it.zt = p.zt;
     it.bfac = p.bfac;
     it.zn = p.zn;
     it.nx = p.nx;
@@ -866,12 +932,11 @@ hipError_t launch_level_noise(const NoiseGenArgs& a, const NoiseArgs& na, hipStr
 }
 
 #define SMG_INST(T)                                                                            \
-  template hipError_t launch_block_pass<T>(T*, const T*, const T*, const T*, const T*, int, int, \
+  template hipError_t launch_block_pass<T>(T*, const T*, const T*, const T*, int, int,           \
                                            int, int, int, const T*, int, hipStream_t);          \
-  template hipError_t launch_block_pair<T>(T*, const T*, const T*, const T*, const T*, int, int,  \
-                                           int, int, int, const T*, hipStream_t);               \
-  template hipError_t launch_block_pair_multi<T>(const BlockPassItem<T>*, int, int, bool,          \
-                                                 hipStream_t);                                   \
+  template hipError_t launch_block_half<T>(const HalfPassItem<T>*, int, int, bool, bool,         \
+                                           hipStream_t);                                         \
+  template hipError_t launch_block_pair<T>(const HalfPassItem<T>*, int, int, bool, hipStream_t);  \
   template hipError_t launch_block_pass_multi<T>(const BlockPassItem<T>*, int, int, bool, int,    \
                                                  hipStream_t);                                   \
   template hipError_t launch_residual_gal<T>(T*, const T*, const T*, const T*, const T*, int,    \

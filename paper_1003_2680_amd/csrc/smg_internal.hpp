@@ -60,7 +60,7 @@ struct Hierarchy {
   bool wide_coarsest = false;    // the coarsest draw is a launch of its own (see plan.cpp)
   bool use_bottom = true;        // false: run those levels with one launch per pass instead
   int block_tile = SMG_TILE_AUTO;  // tile shape of the block-pass launches
-  bool block_pairs = true;         // two block colours per launch where the level allows
+  bool block_pairs = true;         // several block colours per launch where the level allows
   // sampling calls: component groups on streams of their own (1: the caller's stream only)
   int stream_groups = 1;
   std::vector<hipStream_t> side;     // one side stream per group (made on first use)
