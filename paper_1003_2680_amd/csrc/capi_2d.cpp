@@ -10,6 +10,7 @@
 // index, coarsest row.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cmath>
 #include <cstring>
 #include <string>
@@ -32,6 +33,7 @@ struct Level2 {
   std::vector<double> s1d, zt;    // (m_x, a_x); per-row bands [nz][10]
   std::vector<double> bfac;       // [nz/2][32]
   size_t off_x = 0, off_b = 0, off_r = 0, off_s1d = 0, off_zt = 0, off_bfac = 0;
+  size_t off_tab = 0, off_noise = 0;  // levels of the LDS-resident bottom
   double* x = nullptr;
   double* b = nullptr;
   double* r = nullptr;
@@ -56,6 +58,14 @@ struct smg2d {
   double* part_d = nullptr;
   double* norm_d = nullptr;
   char* ws = nullptr;
+  // Level-0 sweeps two to a launch on row strips; the first level of the LDS-resident bottom (-1:
+  // none) and whether its coarsest draw takes a launch of its own.
+  bool strips = false;
+  int bottom = -1;
+  bool wide_coarsest = false;
+  smg::Bot2Args bot{};
+  size_t off_bot = 0;
+  smg::Bot2Args* bot_d = nullptr;
 };
 
 namespace smg {
@@ -75,6 +85,81 @@ namespace {
     int rc_ = (expr);              \
     if (rc_ != SMG_OK) return rc_; \
   } while (0)
+
+// The first Galerkin level from which on every level fits one work-group's LDS (x with halos and
+// b of each, the tables, and scratch rows for half of the largest level's residual).
+void plan_bottom2(smg2d& h) {
+  const int L = (int)h.lv.size();
+  for (int l = 1; l < L; ++l) {
+    if (h.lv[l].kind != KIND_BLOCK || h.lv[l].nx > 1024 || L - l > kMaxBot2Levels) continue;
+    Bot2Args a{};
+    a.nlev = L - l;
+    a.level0 = l;
+    a.nu1 = h.d.nu1;
+    a.nu2 = h.d.nu2;
+    a.ncomp = h.d.ncomp;
+    size_t off = 0, scratch = 0;
+    for (int i = 0; i < a.nlev; ++i) {
+      const Level2& v = h.lv[l + i];
+      Bot2Level& b = a.lv[i];
+      const bool block = v.kind == KIND_BLOCK;
+      b.nx = v.nx;
+      b.nz = v.nz;
+      b.kind = v.kind;
+      b.rs = block ? v.nx + 6 : v.nx;
+      for (int q = 0; q < 10; ++q) b.s1d[q] = v.s1d[q];
+      b.x_off = (int)off;
+      off += (size_t)v.nz * b.rs;
+      b.b_off = (int)off;
+      off += (size_t)v.n * (block ? 1 : 2);  // the coarsest draw's normals beside its b
+      b.tab_off = (int)off;
+      if (block) off += (size_t)v.nz * 10 + (size_t)(v.nz / 2) * 48;
+      if (block && !v.coarsest) {
+        const int half = (v.nz / 2 + 1) / 2;
+        scratch = std::max(scratch, (size_t)(2 * half + 2) * v.nx);
+      }
+    }
+    a.r_off = (int)off;
+    a.lds = (off + scratch) * sizeof(double);
+    if (a.lds > kBot2LdsMax) continue;
+    h.bot = a;
+    h.bottom = l;
+    // as on the three-dimensional grid: large dense draws are spread over the chip (256 unknowns,
+    // 128 x 128 x 8 chains: 135 us a cycle with the draw in the bottom, 106 us with its own launch)
+    h.wide_coarsest = h.nc >= 192;
+    return;
+  }
+}
+
+// Device table of a bottom level: the z-rows, then per block row A_BB^-1 in lane order (entry m
+// of row k for cell k ^ m) and the packed z-factors of its two cell rows (own0, own1, oth0, oth1
+// of rows m = 0 .. 2 and a zero each).
+std::vector<double> bottom_table2(const Level2& v) {
+  std::vector<double> t((size_t)v.nz * 10 + (size_t)(v.nz / 2) * 48, 0.0);
+  std::copy(v.zt.begin(), v.zt.end(), t.begin());
+  for (int bz = 0; bz < v.nz / 2; ++bz) {
+    double* row = &t[(size_t)v.nz * 10 + (size_t)bz * 48];
+    for (int k = 0; k < 4; ++k)
+      for (int m = 0; m < 4; ++m) row[k * 4 + m] = v.bfac[(size_t)bz * 32 + k * 4 + (k ^ m)];
+    for (int kz = 0; kz < 2; ++kz) {
+      const double* zo = &v.zt[(size_t)(2 * bz + kz) * 10];
+      const double* zp = &v.zt[(size_t)(2 * bz + 1 - kz) * 10];
+      double* z = row + 16 + kz * 16;
+      for (int m = 0; m < 3; ++m) {
+        const int own = 2 * kz + m, oth = kz ? 3 + m : m - 1;
+        if (own < 5) {
+          z[m] = zo[own];
+          z[4 + m] = zo[5 + own];
+        }
+        if (oth >= 0 && oth < 5) {
+          z[8 + m] = zp[oth];
+          z[12 + m] = zp[5 + oth];
+        }
+      }
+    }
+  }
+  return t;
+}
 
 int plan2d(smg2d& h, std::string& err) {
   const smg2d_desc& d = h.d;
@@ -210,6 +295,16 @@ int plan2d(smg2d& h, std::string& err) {
     off = align256(off + bytes);
     return o;
   };
+  plan_bottom2(h);
+  h.strips = h.lv[0].kind == KIND_POINT &&
+             level0_rows(d.nx, d.nz, d.ncomp, kMaxPoint2, !h.lv[0].coarsest) > 0;
+  for (int l = 0; l < L && h.bottom >= 0; ++l)
+    if (l >= h.bottom && h.lv[l].kind == KIND_BLOCK) {
+      Level2& v = h.lv[l];
+      v.off_tab = take(((size_t)v.nz * 10 + (size_t)(v.nz / 2) * 48) * sizeof(double));
+      v.off_noise = take((size_t)(d.nu1 + d.nu2) * d.ncomp * v.n * sizeof(double));
+    }
+  if (h.bottom >= 0) h.off_bot = take(sizeof(Bot2Args));
   for (Level2& v : h.lv) {
     const size_t n = (size_t)d.ncomp * v.n * sizeof(double);
     v.off_x = take(n);
@@ -236,6 +331,9 @@ struct Run2 {
   bool noise;
   bool has_b0;
   uint64_t seed, cycle;
+  // level 0 between launches: the strip launches read one field and write the other
+  double* x0;
+  double* y0;
 };
 
 NoiseArgs noise2(const Run2& r, int level, int slot, int colour, uint32_t kind) {
@@ -270,16 +368,37 @@ int sweep2(Run2& r, int l, int slot, bool post) {
   return SMG_OK;
 }
 
+int coarsest2(Run2& r, int l) {
+  smg2d& h = *r.h;
+  Level2& v = h.lv[l];
+  const NoiseArgs na = noise2(r, l, 0, 0, 1);
+  // level 0 drawn exactly: its b is the caller's (zero when sampling)
+  S2_HIP(launch_coarsest<double>(v.x, v.b, h.ainv_d, h.w_d, h.nc, h.d.ncomp, r.noise, na, r.s));
+  return SMG_OK;
+}
+
+// Every level from the bottom one down and back up.
+int bottom2(Run2& r) {
+  smg2d& h = *r.h;
+  const NoiseArgs na = noise2(r, 0, 0, 0, 0);
+  if (r.noise) S2_HIP(launch2_noise(h.bot_d, h.bot, na, r.s));
+  if (!h.wide_coarsest) {
+    S2_HIP(launch2_bottom(h.bot_d, h.bot, BOT_WHOLE, r.noise, na, r.s));
+    return SMG_OK;
+  }
+  S2_HIP(launch2_bottom(h.bot_d, h.bot, BOT_DOWN, r.noise, na, r.s));
+  S2_TRY(coarsest2(r, (int)h.lv.size() - 1));
+  S2_HIP(launch2_bottom(h.bot_d, h.bot, BOT_UP, r.noise, na, r.s));
+  return SMG_OK;
+}
+
+// The cycle on levels l >= 1 (and on a level 0 without strip launches).
 int vcycle2(Run2& r, int l) {
   smg2d& h = *r.h;
   Level2& v = h.lv[l];
   const int nc = h.d.ncomp;
-  if (v.kind == KIND_CHOL) {
-    const NoiseArgs na = noise2(r, l, 0, 0, 1);
-    // level 0 drawn exactly: its b is the caller's (zero when sampling)
-    S2_HIP(launch_coarsest<double>(v.x, v.b, h.ainv_d, h.w_d, h.nc, nc, r.noise, na, r.s));
-    return SMG_OK;
-  }
+  if (l == h.bottom) return bottom2(r);
+  if (v.kind == KIND_CHOL) return coarsest2(r, l);
   for (int s = 0; s < h.d.nu1; ++s) S2_TRY(sweep2(r, l, s, false));
   if (!v.coarsest) {
     Level2& c = h.lv[l + 1];
@@ -290,6 +409,59 @@ int vcycle2(Run2& r, int l) {
   }
   for (int s = 0; s < h.d.nu2; ++s) S2_TRY(sweep2(r, l, h.d.nu1 + s, true));
   return SMG_OK;
+}
+
+// One leg of level 0 in strip launches: `nsweeps` sweeps from slot0, two to a launch, with the
+// prolongation in the first (e) or the restriction in the last (bc); the last also writes `out`.
+int strips2(Run2& r, int slot0, int nsweeps, bool post, const double* e, double* bc, double* xc,
+            double* out) {
+  smg2d& h = *r.h;
+  Level2& v = h.lv[0];
+  constexpr int per = kMaxPoint2 / 2;
+  const NoiseArgs na = noise2(r, 0, 0, 0, 0);
+  if (nsweeps == 0 && !e && !bc && !out) return SMG_OK;
+  int done = 0;
+  do {
+    const int n = std::min(per, nsweeps - done);
+    const bool first = done == 0, last = done + n >= nsweeps;
+    Point2Args a{};
+    a.nx = v.nx;
+    a.nz = v.nz;
+    a.npass = 2 * n;
+    a.slot0 = slot0 + done;
+    a.post = post;
+    a.ih2 = 1.0 / (h.d.h * h.d.h);
+    a.src = r.x0;
+    a.dst = r.y0;
+    a.b = r.has_b0 ? v.b : nullptr;
+    a.e = first ? e : nullptr;
+    a.bc = last ? bc : nullptr;
+    a.xc = last ? xc : nullptr;
+    a.out = last ? out : nullptr;
+    S2_HIP(launch2_level0(a, h.d.ncomp, h.d.kT, r.noise, na, r.s));
+    std::swap(r.x0, r.y0);
+    done += n;
+  } while (done < nsweeps);
+  return SMG_OK;
+}
+
+// One cycle; the field after it goes to `out` too (null: nowhere).
+int cycle2(Run2& r, double* out) {
+  smg2d& h = *r.h;
+  Level2& v = h.lv[0];
+  if (!h.strips) {
+    S2_TRY(vcycle2(r, 0));
+    if (out) S2_HIP(launch_copy(out, v.x, (int64_t)h.d.ncomp * v.n, r.s));
+    return SMG_OK;
+  }
+  if (v.coarsest) {  // smoothing only
+    S2_TRY(strips2(r, 0, h.d.nu1, false, nullptr, nullptr, nullptr, nullptr));
+    return strips2(r, h.d.nu1, h.d.nu2, true, nullptr, nullptr, nullptr, out);
+  }
+  Level2& c = h.lv[1];
+  S2_TRY(strips2(r, 0, h.d.nu1, false, nullptr, c.b, h.bottom == 1 ? nullptr : c.x, nullptr));
+  S2_TRY(vcycle2(r, 1));
+  return strips2(r, h.d.nu1, h.d.nu2, true, c.x, nullptr, nullptr, out);
 }
 
 int check2(const smg2d* h) {
@@ -393,6 +565,26 @@ int smg2d_bind(smg2d* h, void* ws, size_t bytes, void* stream) {
   }
   h->part_d = (double*)(base + h->off_part);
   h->norm_d = (double*)(base + h->off_norm);
+  std::vector<std::vector<double>> tabs;  // until the synchronisation below
+  if (h->bottom >= 0) {
+    for (int i = 0; i < h->bot.nlev; ++i) {
+      const Level2& v = h->lv[h->bottom + i];
+      Bot2Level& b = h->bot.lv[i];
+      b.xg = v.x;
+      b.bg = v.b;
+      b.bfac = v.dev.bfac;
+      if (v.kind != KIND_BLOCK) continue;
+      b.tab = (const double*)(base + v.off_tab);
+      b.noise = (double*)(base + v.off_noise);
+      tabs.push_back(bottom_table2(v));
+      S2_HIP(hipMemcpyAsync(base + v.off_tab, tabs.back().data(),
+                            tabs.back().size() * sizeof(double), hipMemcpyHostToDevice, s));
+    }
+    h->bot.ainv = h->ainv_d;
+    h->bot.w = h->w_d;
+    h->bot_d = (Bot2Args*)(base + h->off_bot);
+    S2_HIP(hipMemcpyAsync(h->bot_d, &h->bot, sizeof(Bot2Args), hipMemcpyHostToDevice, s));
+  }
   S2_HIP(hipStreamSynchronize(s));
   h->ws = base;
   return SMG_OK;
@@ -410,16 +602,14 @@ int smg2d_sample(smg2d* h, int64_t n, uint64_t seed, uint64_t first_cycle, void*
   const int64_t field = (int64_t)h->d.ncomp * v0.n;
   S2_HIP(launch_copy(v0.x, (const double*)state, field, s));
   if (v0.kind == KIND_CHOL) S2_HIP(launch_zero<double>(v0.b, field, s));
-  Run2 r{h, s, h->d.kT > 0.0, false, seed, first_cycle};
+  Run2 r{h, s, h->d.kT > 0.0, false, seed, first_cycle, v0.x, v0.r};
   int64_t k = 0;
-  for (int64_t i = 0; i < n; ++i) {
+  for (int64_t i = 0; i < n; ++i)
     for (int t = 0; t < h->d.stride; ++t, ++k) {
       r.cycle = first_cycle + (uint64_t)k;
-      S2_TRY(vcycle2(r, 0));
+      S2_TRY(cycle2(r, t + 1 == h->d.stride ? (double*)out + i * field : nullptr));
     }
-    S2_HIP(launch_copy((double*)out + i * field, v0.x, field, s));
-  }
-  S2_HIP(launch_copy((double*)state, v0.x, field, s));
+  S2_HIP(launch_copy((double*)state, r.x0, field, s));
   return SMG_OK;
 }
 
@@ -440,17 +630,17 @@ int smg2d_solve(smg2d* h, const void* f, void* u, double rtol, int32_t max_cycle
   S2_HIP(hipStreamSynchronize(s));
   S2_HIP(launch_copy(v0.b, (const double*)f, field, s));
   S2_HIP(launch_zero<double>(v0.x, field, s));
-  Run2 r{h, s, false, true, 0, 0};
+  Run2 r{h, s, false, true, 0, 0, v0.x, v0.r};
   int cycles = 0;
   double relres = 0.0, ratio = 0.0;
   bool zero_f = true;
   for (double v : fn) zero_f = zero_f && v == 0.0;
   if (!zero_f) relres = 1.0;
   while (!zero_f && cycles < max_cycles) {
-    S2_TRY(vcycle2(r, 0));
+    S2_TRY(cycle2(r, nullptr));
     ++cycles;
-    S2_HIP(launch2_residual(v0.r, v0.x, v0.b, v0.dev, nc, s));
-    S2_HIP(launch_sumsq(h->norm_d, h->part_d, v0.r, v0.n, nc, s));
+    S2_HIP(launch2_residual(r.y0, r.x0, v0.b, v0.dev, nc, s));
+    S2_HIP(launch_sumsq(h->norm_d, h->part_d, r.y0, v0.n, nc, s));
     S2_HIP(hipMemcpyAsync(rn.data(), h->norm_d, nc * sizeof(double), hipMemcpyDeviceToHost, s));
     S2_HIP(hipStreamSynchronize(s));
     relres = 0.0;
@@ -467,7 +657,7 @@ int smg2d_solve(smg2d* h, const void* f, void* u, double rtol, int32_t max_cycle
     rprev = rn;
     if (relres <= rtol) break;
   }
-  S2_HIP(launch_copy((double*)u, v0.x, field, s));
+  S2_HIP(launch_copy((double*)u, r.x0, field, s));
   S2_HIP(hipStreamSynchronize(s));
   if (info) {
     info->cycles = cycles;

@@ -4,6 +4,9 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <algorithm>
+
+#include "kernels.hpp"
 #include "philox.hpp"
 
 namespace smg {
@@ -34,5 +37,63 @@ hipError_t launch2_restrict(double* bc, double* xc, const double* r, int nxf, in
 // x += P e
 hipError_t launch2_prolong(double* x, const double* e, int nxf, int nzf, int ncomp,
                            hipStream_t s);
+
+// ---- several level-0 passes per launch (kernels_2d_lds.hip)
+constexpr int kMaxPoint2 = 4;  // point passes per launch
+struct Point2Args {
+  int nx, nz, rows;      // rows: per work-group (set by the launcher)
+  int npass, slot0;      // passes: two per sweep, sweep slots slot0, slot0 + 1, ...
+  int post;              // colour 1 first
+  double ih2;            // 1 / h^2
+  double inv_d[3], sig[3];  // set by the launcher: 1 / diagonal, sqrt(kT / diagonal) by walls
+  const double* src;     // [ncomp][N]
+  double* dst;           // another field
+  const double* b;       // right-hand side or null
+  const double* e;       // coarse correction added (as P e) before the passes, or null
+  double* bc;            // P^T (b - A x) after the passes, or null; xc: cleared with it, or null
+  double* xc;
+  double* out;           // x written there too, or null
+};
+// Rows a work-group owns (even; 0: the window of a row strip does not fit): as many as leave the
+// launch two work-groups per compute unit, at least eight (fewer draw more rows again than they
+// own).
+inline int level0_rows(int nx, int nz, int ncomp, int npass, bool restricts) {
+  const int halo = npass + (restricts ? 2 : 0);
+  int rows = 32;
+  while (rows > 4 && ((size_t)(rows + 2 * halo) * nx * 8 > 64 * 1024 ||
+                      (rows > 8 && (int64_t)((nz + rows - 1) / rows) * ncomp < 512)))
+    rows /= 2;
+  return (size_t)(rows + 2 * halo) * nx * 8 > 64 * 1024 ? 0 : rows;
+}
+hipError_t launch2_level0(const Point2Args& a, int ncomp, double kT, bool noise,
+                          const NoiseArgs& na, hipStream_t s);
+
+// ---- the LDS-resident bottom (kernels_2d_lds.hip)
+constexpr int kMaxBot2Levels = 8;
+constexpr size_t kBot2LdsMax = 160 * 1024;
+struct Bot2Level {
+  int nx, nz, kind;
+  int rs;                   // LDS row stride of x: nx + 6 (two halo cells per side, 2 mod 4), nx coarsest
+  int x_off, b_off, tab_off;  // LDS offsets (doubles)
+  double s1d[10];           // (m_x, a_x)
+  const double* tab;        // device: [zt nz*10][per block row A_BB^-1 in lane order, packed factors]
+  const double* bfac;       // as Lev2
+  double* noise;            // [nu1 + nu2][ncomp][nx nz], pregenerated each cycle
+  double* xg;               // the level's x and b in memory
+  double* bg;
+};
+struct Bot2Args {
+  int nlev, level0, nu1, nu2, ncomp;
+  int r_off;                // scratch rows
+  size_t lds;               // bytes
+  const double* ainv;
+  const double* w;
+  Bot2Level lv[kMaxBot2Levels];
+};
+// `dev` is the device copy of `host`; part: BotPart
+hipError_t launch2_noise(const Bot2Args* dev, const Bot2Args& host, const NoiseArgs& na,
+                         hipStream_t s);
+hipError_t launch2_bottom(const Bot2Args* dev, const Bot2Args& host, int part, bool noise,
+                          const NoiseArgs& na, hipStream_t s);
 
 }  // namespace smg
