@@ -1389,10 +1389,8 @@ struct SolveJob {
       SMG_HIP(launch_refine_residual(v0.bf, v0.x, v0.b, v0.nx, v0.ny, v0.nz, nc, h.desc.ncomp,
                                      h.desc.h, h.part_d, h.norm_d, s));
     } else if (v0.kind == KIND_POINT) {
-      SMG_HIP(launch_residual0<double>(v0.r, v0.x, v0.x + half_field(h), v0.b,
-                                       v0.b + half_field(h), v0.nx, v0.ny, v0.nz, nc, h.desc.h,
-                                       s));
-      SMG_HIP(launch_sumsq(h.norm_d, h.part_d, v0.r, v0.n, nc, s));
+      SMG_HIP(launch_refine_residual(nullptr, v0.x, v0.b, v0.nx, v0.ny, v0.nz, nc, h.desc.ncomp,
+                                     h.desc.h, h.part_d, h.norm_d, s));
     } else {
       // a level 0 drawn exactly (one level) is stored in natural layout; its residual goes to
       // its own buffer, never to u (which holds the exported solutions of finished chains)

@@ -66,6 +66,16 @@ __device__ __forceinline__ int wrap_near(int v, int n) {
   return v < n ? v : n - 1;
 }
 
+// Sum over the work-group of TPB threads in a fixed order (the total is in thread 0): the 64 lanes
+// of a wave by exchanges, the waves through sh.  Called by every thread, once per use of sh.
+__device__ __forceinline__ double block_sum(double v, double (&sh)[TPB / 64]) {
+#pragma unroll
+  for (int m = 32; m > 0; m >>= 1) v += __shfl_xor(v, m, 64);
+  if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = v;
+  __syncthreads();
+  return (sh[0] + sh[1]) + (sh[2] + sh[3]);
+}
+
 // (A x) at cell (cx, cy, cz) of a Galerkin level.  The Galerkin operator of the wall-bounded
 // Laplacian is a Kronecker sum, A = a_z (x) m_y (x) m_x + m_z (x) (a_y (x) m_x + m_y (x) a_x),
 // with 5-point periodic 1D stencils s1d = (m_x, a_x, m_y, a_y) (offsets -2..2, uniform over

@@ -92,9 +92,6 @@ template <typename T>
 hipError_t launch_rb_pass(T* xc, const T* xo, const T* bc, int nx, int ny, int nz, int ncomp,
                           int colour, double h, double kT, bool noise, const NoiseArgs& na,
                           hipStream_t s);
-template <typename T>
-hipError_t launch_residual0(T* r, const T* xr, const T* xb, const T* br, const T* bb, int nx,
-                            int ny, int nz, int ncomp, double h, hipStream_t s);
 // b_c = P^T (b - A x) from split level-0 storage straight to the natural coarse level (r is
 // never written); also x_c = 0 when xc is not null.  br/bb null = 0.
 template <typename T>
@@ -279,7 +276,7 @@ hipError_t launch_sumsq_final_parts(double* out, const double* part, uint32_t np
 
 // FP32-refined bridge on level 0 (split storage, colour 1 starting ncomp_stride*N/2 after
 // colour 0), over the first ncomp components:
-//   r32 = (float)(b64 - A x64)   (b64 null = 0); with `norm` non-null also
+//   r32 = (float)(b64 - A x64)   (b64 null = 0; r32 null = not written); with `norm` non-null also
 //   norm[comp] = ||b64 - A x64||_2^2 (fixed order, via `part`: ncomp * 2*ceil(N/512) doubles)
 hipError_t launch_refine_residual(float* r32, const double* x64, const double* b64, int nx,
                                   int ny, int nz, int ncomp, int ncomp_stride, double h,

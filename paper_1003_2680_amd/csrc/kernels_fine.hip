@@ -290,35 +290,6 @@ __device__ __forceinline__ T split_at(const T* __restrict__ xr, const T* __restr
   return a[cbase + ((size_t)z * ny + y) * nh + (x >> 1)];
 }
 
-// r = b - A x on level 0 (split input, natural output).
-template <typename T, bool HAS_B>
-__global__ __launch_bounds__(TPB) void k_residual0(T* __restrict__ r, const T* __restrict__ xr,
-                                                    const T* __restrict__ xb,
-                                                    const T* __restrict__ br,
-                                                    const T* __restrict__ bb, int nx, int ny,
-                                                    int nz, uint32_t N, T inv_h2) {
-  const uint32_t comp = blockIdx.y;
-  const uint32_t i = blockIdx.x * TPB + threadIdx.x;
-  if (i >= N) return;
-  const int x = i % nx;
-  const uint32_t row = i / nx;
-  const int y = row % ny;
-  const int z = row / ny;
-  const int nh = nx >> 1;
-  const size_t cb = (size_t)comp * (N >> 1);
-  T c = split_at(xr, xb, cb, x, y, z, nh, ny);
-  T s = split_at(xr, xb, cb, wrapm(x - 1, nx), y, z, nh, ny) +
-        split_at(xr, xb, cb, wrapm(x + 1, nx), y, z, nh, ny) +
-        split_at(xr, xb, cb, x, wrapm(y - 1, ny), z, nh, ny) +
-        split_at(xr, xb, cb, x, wrapm(y + 1, ny), z, nh, ny);
-  int nw = 0;
-  if (z + 1 < nz) s += split_at(xr, xb, cb, x, y, z + 1, nh, ny); else ++nw;
-  if (z > 0) s += split_at(xr, xb, cb, x, y, z - 1, nh, ny); else ++nw;
-  T ax = (T(6 + nw) * c - s) * inv_h2;
-  T bv = HAS_B ? split_at(br, bb, cb, x, y, z, nh, ny) : T(0);
-  r[(size_t)comp * N + i] = bv - ax;
-}
-
 // Fused residual and restriction from level 0: b_c = P^T (b - A x) without writing r.
 // A work-group owns an RX x RY column of coarse cells over up to RR_Z coarse layers and
 // marches up through the fine planes of their restriction windows, [2Z0-1, 2Z0+2RZ].  For
@@ -530,8 +501,9 @@ __global__ __launch_bounds__(TPB) void k_restrict_residual0(
   }
 }
 
-// FP32-refined bridge: r32 = (float)(b - A x) from FP64 split storage, written split; the
-// optional fixed-order partial sums of (b - A x)^2 go to part[comp][colour*nblk + block].
+// Residual on level 0 from FP64 split storage, any even nx: r32 = (float)(b - A x), written split
+// unless r32 is null (the FP32-refined bridge); the optional fixed-order partial sums of
+// (b - A x)^2 go to part[comp][colour*nblk + block].
 template <bool HAS_B, bool NORM>
 __global__ __launch_bounds__(TPB) void k_refine_residual(float* __restrict__ r32,
                                                           const double* __restrict__ x64,
@@ -539,7 +511,7 @@ __global__ __launch_bounds__(TPB) void k_refine_residual(float* __restrict__ r32
                                                           int ny, int nz, uint32_t nsite,
                                                           double inv_h2, double* __restrict__ part,
                                                           uint32_t nblk, size_t half) {
-  __shared__ double sh[TPB];
+  __shared__ double sh[TPB / 64];
   const uint32_t comp = blockIdx.y;
   const int colour = blockIdx.z;
   const uint32_t p = blockIdx.x * TPB + threadIdx.x;
@@ -564,34 +536,33 @@ __global__ __launch_bounds__(TPB) void k_refine_residual(float* __restrict__ r32
     if (z > 0) s += split_at(xr, xb, cb, x, y, z - 1, nh, ny); else ++nw;
     const double bv = HAS_B ? b64[colour * half + cb + p] : 0.0;
     rr = bv - ((6 + nw) * c - s) * inv_h2;
-    r32[colour * half + cb + p] = (float)rr;
+    if (r32) r32[colour * half + cb + p] = (float)rr;
   }
   if (NORM) {
-    sh[threadIdx.x] = rr * rr;
-    __syncthreads();
-    for (int st = TPB / 2; st > 0; st >>= 1) {
-      if ((int)threadIdx.x < st) sh[threadIdx.x] += sh[threadIdx.x + st];
-      __syncthreads();
-    }
-    if (threadIdx.x == 0) part[(size_t)comp * 2 * nblk + colour * nblk + blockIdx.x] = sh[0];
+    const double a = block_sum(rr * rr, sh);
+    if (threadIdx.x == 0) part[(size_t)comp * 2 * nblk + colour * nblk + blockIdx.x] = a;
   }
 }
 
-// The same residual (without norms) two sites per thread, as the colour passes move the field:
+// The same residual two sites per thread, as the colour passes move the field:
 // thread (row, jt) of colour c owns sites 2 jt, 2 jt + 1 of its row, reads them and b with one
 // 16-byte load each and its neighbours in the other colour's array with one 16-byte load per
 // neighbour row (plus the entry beyond on the side its x-neighbours lie), and writes both
-// residuals with one 8-byte store.  The neighbour sums run in the order of k_refine_residual,
-// so both kernels give the same bits.
-template <bool HAS_B, bool ZU>
+// residuals with one 8-byte store (WRITE).  The neighbour sums run in the order of
+// k_refine_residual, so both kernels give the same residual bits.  With NORM a work-group takes
+// `per_thread` runs of TPB threads' sites one after the other and leaves one partial sum of
+// squares, part[comp][colour*nb + block].
+template <bool HAS_B, bool ZU, bool WRITE, bool NORM>
 __global__ __launch_bounds__(TPB) void k_refine_residual_vec(float* __restrict__ r32,
                                                               const double* __restrict__ x64,
                                                               const double* __restrict__ b64,
                                                               int nh, int ny, int nz,
                                                               uint32_t nthreads, int lg_nht,
                                                               int lg_ny, double inv_h2,
-                                                              size_t half) {
+                                                              size_t half, int per_thread,
+                                                              double* __restrict__ part) {
   constexpr uint32_t S = 2;
+  __shared__ double sh[TPB / 64];
   // Work-group order: the two colours of a tile run one after the other and, by the XCD-aware
   // numbering, on one XCD, so the rows that one colour reads as neighbours and the other as
   // its own sites come from HBM once and from that XCD's L2 the second time
@@ -601,63 +572,78 @@ __global__ __launch_bounds__(TPB) void k_refine_residual_vec(float* __restrict__
   if (lin < per * kXcds) lin = (lin % kXcds) * per + lin / kXcds;
   const int colour = (int)(lin & 1u);
   const uint32_t comp = (lin >> 1) / nb;
-  const uint32_t t = ((lin >> 1) - comp * nb) * TPB + threadIdx.x;
-  if (t >= nthreads) return;
+  const uint32_t blk = (lin >> 1) - comp * nb;
   const uint32_t nht = (uint32_t)nh / S;
-  uint32_t row, jt, z, y;
-  if (lg_nht >= 0) {
-    row = t >> lg_nht;
-    jt = t & (nht - 1);
-  } else {
-    row = t / nht;
-    jt = t - row * nht;
-  }
-  if (lg_ny >= 0) {
-    z = row >> lg_ny;
-    y = row & ((uint32_t)ny - 1);
-  } else {
-    z = row / (uint32_t)ny;
-    y = row - z * (uint32_t)ny;
-  }
   const uint32_t nsite = (uint32_t)nh * ny * nz;
   const size_t base = (size_t)comp * nsite;
   const double* __restrict__ own = x64 + (size_t)colour * half + base;
   const char* __restrict__ ob = reinterpret_cast<const char*>(x64 + (size_t)(colour ^ 1) * half + base);
   const uint32_t plane = (uint32_t)nh * ny;
-  const uint32_t ic = S * t;
-  const uint32_t rb = ic - S * jt;
-  const uint32_t xs = (y + z + (uint32_t)colour) & 1u;
-  auto ld = [&](uint32_t e) {
-    const double2 v = *reinterpret_cast<const double2*>(ob + e * 8u);
-    return v;
+  double sum = 0.0;
+  auto sites = [&](uint32_t t) {
+    uint32_t row, jt, z, y;
+    if (lg_nht >= 0) {
+      row = t >> lg_nht;
+      jt = t & (nht - 1);
+    } else {
+      row = t / nht;
+      jt = t - row * nht;
+    }
+    if (lg_ny >= 0) {
+      z = row >> lg_ny;
+      y = row & ((uint32_t)ny - 1);
+    } else {
+      z = row / (uint32_t)ny;
+      y = row - z * (uint32_t)ny;
+    }
+    const uint32_t ic = S * t;
+    const uint32_t rb = ic - S * jt;
+    const uint32_t xs = (y + z + (uint32_t)colour) & 1u;
+    auto ld = [&](uint32_t e) {
+      const double2 v = *reinterpret_cast<const double2*>(ob + e * 8u);
+      return v;
+    };
+    const double2 c = ld(ic);
+    const uint32_t ie = xs ? (jt + 1 == nht ? rb : ic + S) : (jt == 0 ? rb + (uint32_t)nh - 1 : ic - 1);
+    const double ex = *reinterpret_cast<const double*>(ob + ie * 8u);
+    const uint32_t in = ic + (y + 1 == (uint32_t)ny ? (uint32_t)nh - plane : (uint32_t)nh);
+    const uint32_t is = ic + (y == 0 ? plane - (uint32_t)nh : 0u - (uint32_t)nh);
+    const double2 n = ld(in), so = ld(is);
+    const uint32_t zw = ZU ? __builtin_amdgcn_readfirstlane(z) : z;
+    const bool top = zw + 1 >= (uint32_t)nz, bottom = zw == 0;
+    const double2 u = ld(ic + (top ? 0u : plane)), d = ld(ic - (bottom ? 0u : plane));
+    const double2 xo = *reinterpret_cast<const double2*>(own + ic);
+    double2 bv = make_double2(0.0, 0.0);
+    if (HAS_B) bv = *reinterpret_cast<const double2*>(b64 + (size_t)colour * half + base + ic);
+    const int nw = (int)top + (int)bottom;
+    // x-neighbour sums (x - 1) + (x + 1): xs == 1 -> (j, j+1), xs == 0 -> (j-1, j); the entry
+    // beyond the owned ones closes the last pair on the side it lies
+    const double sx0 = xs ? c.x + c.y : ex + c.x;
+    const double sx1 = xs ? c.y + ex : c.x + c.y;
+    auto res = [&](double sx, double nv, double sv, double uv, double dv, double xv, double b) {
+      double s = (sx + sv) + nv;
+      if (!top) s += uv;
+      if (!bottom) s += dv;
+      return b - ((6 + nw) * xv - s) * inv_h2;
+    };
+    const double r0 = res(sx0, n.x, so.x, u.x, d.x, xo.x, bv.x);
+    const double r1 = res(sx1, n.y, so.y, u.y, d.y, xo.y, bv.y);
+    if (WRITE)
+      *reinterpret_cast<float2*>(r32 + (size_t)colour * half + base + ic) =
+          make_float2((float)r0, (float)r1);
+    if (NORM) sum = fma(r1, r1, fma(r0, r0, sum));
   };
-  const double2 c = ld(ic);
-  const uint32_t ie = xs ? (jt + 1 == nht ? rb : ic + S) : (jt == 0 ? rb + (uint32_t)nh - 1 : ic - 1);
-  const double ex = *reinterpret_cast<const double*>(ob + ie * 8u);
-  const uint32_t in = ic + (y + 1 == (uint32_t)ny ? (uint32_t)nh - plane : (uint32_t)nh);
-  const uint32_t is = ic + (y == 0 ? plane - (uint32_t)nh : 0u - (uint32_t)nh);
-  const double2 n = ld(in), so = ld(is);
-  const uint32_t zw = ZU ? __builtin_amdgcn_readfirstlane(z) : z;
-  const bool top = zw + 1 >= (uint32_t)nz, bottom = zw == 0;
-  const double2 u = ld(ic + (top ? 0u : plane)), d = ld(ic - (bottom ? 0u : plane));
-  const double2 xo = *reinterpret_cast<const double2*>(own + ic);
-  double2 bv = make_double2(0.0, 0.0);
-  if (HAS_B) bv = *reinterpret_cast<const double2*>(b64 + (size_t)colour * half + base + ic);
-  const int nw = (int)top + (int)bottom;
-  // x-neighbour sums (x - 1) + (x + 1): xs == 1 -> (j, j+1), xs == 0 -> (j-1, j); the entry
-  // beyond the owned ones closes the last pair on the side it lies
-  const double sx0 = xs ? c.x + c.y : ex + c.x;
-  const double sx1 = xs ? c.y + ex : c.x + c.y;
-  auto res = [&](double sx, double nv, double sv, double uv, double dv, double xv, double b) {
-    double s = (sx + sv) + nv;
-    if (!top) s += uv;
-    if (!bottom) s += dv;
-    return b - ((6 + nw) * xv - s) * inv_h2;
-  };
-  float2 out;
-  out.x = (float)res(sx0, n.x, so.x, u.x, d.x, xo.x, bv.x);
-  out.y = (float)res(sx1, n.y, so.y, u.y, d.y, xo.y, bv.y);
-  *reinterpret_cast<float2*>(r32 + (size_t)colour * half + base + ic) = out;
+  if (!NORM) {
+    const uint32_t t = blk * TPB + threadIdx.x;
+    if (t < nthreads) sites(t);
+    return;
+  }
+  for (int q = 0; q < per_thread; ++q) {
+    const uint32_t t = (blk * per_thread + q) * TPB + threadIdx.x;
+    if (t < nthreads) sites(t);
+  }
+  sum = block_sum(sum, sh);
+  if (threadIdx.x == 0) part[((size_t)comp * 2 + colour) * nb + blk] = sum;
 }
 
 __global__ __launch_bounds__(TPB) void k_refine_update(double* __restrict__ x64,
@@ -944,17 +930,6 @@ hipError_t launch_rb_pass_multi(const RbPassItem<T>* items, int n, int colour, b
 }
 
 template <typename T>
-hipError_t launch_residual0(T* r, const T* xr, const T* xb, const T* br, const T* bb, int nx,
-                            int ny, int nz, int ncomp, double h, hipStream_t s) {
-  const uint32_t N = (uint32_t)nx * ny * nz;
-  dim3 grid(blocks_for(N), ncomp);
-  const T ih2 = (T)(1.0 / (h * h));
-  if (br) k_residual0<T, true><<<grid, TPB, 0, s>>>(r, xr, xb, br, bb, nx, ny, nz, N, ih2);
-  else k_residual0<T, false><<<grid, TPB, 0, s>>>(r, xr, xb, br, bb, nx, ny, nz, N, ih2);
-  return hipGetLastError();
-}
-
-template <typename T>
 hipError_t launch_restrict_residual0(T* bc, T* xc, const T* xr, const T* xb, const T* br,
                                      const T* bb, int nx, int ny, int nz, int ncomp, double h,
                                      hipStream_t s) {
@@ -1011,11 +986,6 @@ template hipError_t launch_rb_pass_multi<double>(const RbPassItem<double>*, int,
                                                  hipStream_t);
 template hipError_t launch_rb_pass_multi<float>(const RbPassItem<float>*, int, int, bool, bool,
                                                 hipStream_t);
-template hipError_t launch_residual0<double>(double*, const double*, const double*, const double*,
-                                             const double*, int, int, int, int, double,
-                                             hipStream_t);
-template hipError_t launch_residual0<float>(float*, const float*, const float*, const float*,
-                                            const float*, int, int, int, int, double, hipStream_t);
 template hipError_t launch_prolong0<double>(double*, double*, const double*, int, int, int, int,
                                             int, hipStream_t);
 template hipError_t launch_restrict_residual0<double>(double*, double*, const double*,
@@ -1037,19 +1007,37 @@ hipError_t launch_refine_residual(float* r32, const double* x64, const double* b
   const double ih2 = 1.0 / (h * h);
   const int nh = nx / 2;
   const size_t half = (size_t)ncomp_stride * nsite;
-  if (!norm && nh % 2 == 0 && (uint64_t)nsite * sizeof(double) < (1ull << 32)) {
-    // no norms: two sites per thread
+  if (!r32 && !norm) return hipSuccess;
+  if (nh % 2 == 0 && (uint64_t)nsite * sizeof(double) < (1ull << 32)) {
+    // two sites per thread.  With norms a thread of a large field takes four pairs, so that the
+    // second stage has a quarter of the partials to add (its one work-group a component is a
+    // chain of loads); the rule looks at one component, so that a chain's norms do not depend
+    // on the chains beside it.  (three 128^3 fields: 49 + 17 + 10 us for a residual written in
+    // natural layout and read back by the sum of squares, and 31 + 19 us for one site a thread
+    // with the FP32 residual; now 19 + 6 and 19 + 5)
     const uint32_t nthreads = nsite / 2;
+    const int per = norm && nthreads >= (1u << 17) ? 4 : 1;
     const int lg_nht = ilog2_exact((uint32_t)(nh / 2)), lg_ny = ilog2_exact((uint32_t)ny);
     const bool zu = ((uint64_t)(nh / 2) * ny) % 64 == 0;
-    dim3 gv(blocks_for(nthreads), ncomp, 2);
-#define SMG_RRV(HB, ZU)                                                                     \
-  k_refine_residual_vec<HB, ZU><<<gv, TPB, 0, s>>>(r32, x64, b64, nh, ny, nz, nthreads, lg_nht, \
-                                                   lg_ny, ih2, half)
+    dim3 gv(blocks_for((nthreads + per - 1) / per), ncomp, 2);
+#define SMG_RRV(HB, ZU)                                                                       \
+  do {                                                                                        \
+    if (r32 && norm)                                                                          \
+      k_refine_residual_vec<HB, ZU, true, true><<<gv, TPB, 0, s>>>(                           \
+          r32, x64, b64, nh, ny, nz, nthreads, lg_nht, lg_ny, ih2, half, per, part);          \
+    else if (norm)                                                                            \
+      k_refine_residual_vec<HB, ZU, false, true><<<gv, TPB, 0, s>>>(                          \
+          r32, x64, b64, nh, ny, nz, nthreads, lg_nht, lg_ny, ih2, half, per, part);          \
+    else                                                                                      \
+      k_refine_residual_vec<HB, ZU, true, false><<<gv, TPB, 0, s>>>(                          \
+          r32, x64, b64, nh, ny, nz, nthreads, lg_nht, lg_ny, ih2, half, per, part);          \
+  } while (0)
     if (zu) { if (b64) SMG_RRV(true, true); else SMG_RRV(false, true); }
     else { if (b64) SMG_RRV(true, false); else SMG_RRV(false, false); }
 #undef SMG_RRV
-    return hipGetLastError();
+    hipError_t e = hipGetLastError();
+    if (e != hipSuccess || !norm) return e;
+    return launch_sumsq_final_parts(norm, part, 2 * gv.x, ncomp, s);
   }
 #define SMG_RR(HB, NM) \
   k_refine_residual<HB, NM><<<grid, TPB, 0, s>>>(r32, x64, b64, nx, ny, nz, nsite, ih2, part, nblk, \

@@ -53,41 +53,43 @@ __global__ __launch_bounds__(TPB) void k_cast(T* __restrict__ d, const double* _
   for (; i < n; i += (int64_t)gridDim.x * TPB) d[i] = (T)s[i];
 }
 
-// Fixed-order sums of squares: stage 1 writes one partial per 256-element block.
+// Fixed-order sums of squares: stage 1 writes one partial per kSumsqTile elements, stage 2 one
+// sum per component.  Four elements a thread, all loads in flight at once: 17 -> 10 us for three
+// fields of 128^3 (one element a thread left four times the partials to stage 2, which took 10).
+constexpr int kSumsqPer = 4;
+constexpr int kSumsqTile = kSumsqPer * TPB;
+
 __global__ __launch_bounds__(TPB) void k_sumsq_part(double* __restrict__ part,
                                                      const double* __restrict__ v, int64_t n,
                                                      uint32_t nblk) {
-  __shared__ double sh[TPB];
+  __shared__ double sh[TPB / 64];
   const uint32_t comp = blockIdx.y;
-  const int64_t i = (int64_t)blockIdx.x * TPB + threadIdx.x;
-  double a = 0.0;
-  if (i < n) {
-    double t = v[(size_t)comp * n + i];
-    a = t * t;
-  }
-  sh[threadIdx.x] = a;
-  __syncthreads();
-  for (int s = TPB / 2; s > 0; s >>= 1) {
-    if ((int)threadIdx.x < s) sh[threadIdx.x] += sh[threadIdx.x + s];
-    __syncthreads();
-  }
-  if (threadIdx.x == 0) part[(size_t)comp * nblk + blockIdx.x] = sh[0];
+  const int64_t i = (int64_t)blockIdx.x * kSumsqTile + threadIdx.x;
+  const double* __restrict__ V = v + (size_t)comp * n;
+  double t[kSumsqPer], a = 0.0;
+#pragma unroll
+  for (int k = 0; k < kSumsqPer; ++k) t[k] = i + k * TPB < n ? V[i + k * TPB] : 0.0;
+#pragma unroll
+  for (int k = 0; k < kSumsqPer; ++k) a = fma(t[k], t[k], a);
+  a = block_sum(a, sh);
+  if (threadIdx.x == 0) part[(size_t)comp * nblk + blockIdx.x] = a;
 }
 
 __global__ __launch_bounds__(TPB) void k_sumsq_final(double* __restrict__ out,
                                                       const double* __restrict__ part,
                                                       uint32_t nblk) {
-  __shared__ double sh[TPB];
+  __shared__ double sh[TPB / 64];
   const uint32_t comp = blockIdx.x;
-  double a = 0.0;
-  for (uint32_t i = threadIdx.x; i < nblk; i += TPB) a += part[(size_t)comp * nblk + i];
-  sh[threadIdx.x] = a;
-  __syncthreads();
-  for (int s = TPB / 2; s > 0; s >>= 1) {
-    if ((int)threadIdx.x < s) sh[threadIdx.x] += sh[threadIdx.x + s];
-    __syncthreads();
+  const double* __restrict__ P = part + (size_t)comp * nblk;
+  double a[4] = {};
+  uint32_t i = threadIdx.x;
+  for (; i + 3 * TPB < nblk; i += 4 * TPB) {  // four loads in flight
+#pragma unroll
+    for (int k = 0; k < 4; ++k) a[k] += P[i + k * TPB];
   }
-  if (threadIdx.x == 0) out[comp] = sh[0];
+  for (; i < nblk; i += TPB) a[0] += P[i];
+  const double v = block_sum((a[0] + a[1]) + (a[2] + a[3]), sh);
+  if (threadIdx.x == 0) out[comp] = v;
 }
 
 inline unsigned blocks_for(int64_t n) { return (unsigned)((n + TPB - 1) / TPB); }
@@ -153,7 +155,7 @@ hipError_t launch_cast(void* dst, int out_f32, const double* src, int64_t n, hip
 
 hipError_t launch_sumsq(double* out, double* part, const double* v, int64_t n, int ncomp,
                         hipStream_t s) {
-  const uint32_t nblk = blocks_for(n);
+  const uint32_t nblk = (uint32_t)((n + kSumsqTile - 1) / kSumsqTile);
   k_sumsq_part<<<dim3(nblk, ncomp), TPB, 0, s>>>(part, v, n, nblk);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;

@@ -1,0 +1,40 @@
+"""The residual norm that ends a solve, against the oracle's stencil over the returned field.
+
+The norm kernel takes two sites a thread where nx/2 is even and one where it is odd, and four
+pairs a thread from 2^17 pairs of a colour on.  A solve is stopped early (rtol 1e-2), so the
+reported relative residual is far above rounding, and compared with ||f - A u|| / ||f|| of the
+returned u per component (the largest counts).  Both evaluate f - A u with an absolute rounding
+error of a few eps ||A|| ||u||, ||A|| <= 12 and ||u|| <= (nz / pi)^2 (1 + a bit) ||f||, so they
+agree to 40 eps * 12 (nz / pi)^2 / relres.
+"""
+import numpy as np
+import pytest
+
+from oracle.operator import apply_A
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("precision", ["fp64", "fp32_refined"])
+@pytest.mark.parametrize("dims", [
+    (22, 12, 8),     # nx/2 odd: one site a thread
+    (8, 8, 4),       # a single work-group, mostly idle
+    (40, 24, 12),    # two sites a thread, a ragged last work-group
+    (72, 80, 92),    # four pairs a thread, rows that do not align with waves
+])
+def test_reported_residual(dims, precision):
+    from paper_1003_2680_amd.api import Hierarchy
+    from paper_1003_2680_amd.inputs import gaussian_field
+    print("[gpu-case] residual norm %s %s" % (dims, precision), flush=True)
+    H = Hierarchy(*dims, ncomp=2, levels=0, coarsest_max=512, precision=precision)
+    f = gaussian_field(H.shape, 5)
+    f[1] *= 3.0
+    u, cycles, relres = H.solve(torch.from_numpy(f).cuda(), rtol=1e-2)
+    torch.cuda.synchronize()
+    u = u.cpu().numpy()
+    want = max(np.linalg.norm(f[c].ravel() - apply_A(u[c], *dims)) / np.linalg.norm(f[c])
+               for c in range(2))
+    tol = 40 * 2.3e-16 * 12 * (dims[2] / np.pi) ** 2 / want
+    print("  reported %.6e recomputed %.6e tol %.1e" % (relres, want, tol), flush=True)
+    assert 0 < relres <= 1e-2 and abs(relres - want) <= tol * want
