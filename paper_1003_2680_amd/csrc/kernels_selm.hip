@@ -9,6 +9,8 @@
 // 4-point function (cells beyond a no-slip wall are antisymmetric ghosts of their mirrors).
 #include <hip/hip_runtime.h>
 
+#include <type_traits>
+
 #include "device_common.hpp"
 #include "selm.hpp"
 
@@ -17,55 +19,99 @@ namespace {
 
 inline unsigned blocks_for(int64_t n) { return (unsigned)((n + TPB - 1) / TPB); }
 
-// div = D u (one thread per cell; a wave lies in one (y, z) row when nx is a multiple of 64, so
-// the row of S it reads is the same for every lane)
+// The wall transform S v down the z columns: acc[j] = sum_k S[z0 + j][k] v[k][col], the terms in
+// the order of k.  A lane carries ZT layers of its column, so an entry of v is loaded once per
+// ZT products, and the rows of S (uniform over a wave) come through the scalar cache, KU entries
+// of each row at a time.  The four waves of a work-group take the same 64 columns, ZT layers
+// each, and share the columns' lines in the CU's cache.  128^3 (537 MFLOP): 45-48 us a call, bound
+// by the latency of the scalar loads (with the next entries of v prefetched 57-61 us); one output
+// a thread loaded each entry of v for one product and took 249-264 us.
+constexpr int kSelmKU = 4;
+template <int ZT>
+__device__ __forceinline__ void wall_transform(double (&acc)[ZT], const double* __restrict__ v,
+                                               const double* S, int z0, int nz, size_t plane) {
+  typedef const __attribute__((address_space(4))) double* cptr;
+  const cptr R = (cptr)(S + (size_t)z0 * nz);
+#pragma unroll
+  for (int j = 0; j < ZT; ++j) acc[j] = 0.0;
+  int k = 0;
+  for (; k + kSelmKU <= nz; k += kSelmKU) {
+    double c[kSelmKU];
+#pragma unroll
+    for (int q = 0; q < kSelmKU; ++q) c[q] = v[(size_t)(k + q) * plane];
+#pragma unroll
+    for (int q = 0; q < kSelmKU; ++q)
+#pragma unroll
+      for (int j = 0; j < ZT; ++j) acc[j] = fma(R[j * nz + k + q], c[q], acc[j]);
+  }
+  for (; k < nz; ++k) {
+    const double c = v[(size_t)k * plane];
+#pragma unroll
+    for (int j = 0; j < ZT; ++j) acc[j] = fma(R[j * nz + k], c, acc[j]);
+  }
+}
+
+// This thread's (x, y) column and first layer; false beyond the columns or layers.
+template <int ZT>
+__device__ __forceinline__ bool wall_tile(int nx, int ny, int nz, uint32_t& col, int& z0) {
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  col = blockIdx.x * 64 + (threadIdx.x & 63);
+  z0 = ((int)blockIdx.y * (TPB / 64) + wave) * ZT;
+  return z0 < nz && col < (uint32_t)nx * ny;
+}
+
+// div = D u
+template <int ZT>
 __global__ __launch_bounds__(TPB) void k_selm_div(double* __restrict__ div,
                                                    const double* __restrict__ u,
                                                    const double* __restrict__ S, int nx, int ny,
                                                    int nz, double inv_h) {
-  const int64_t N = (int64_t)nx * ny * nz;
-  const int64_t i = (int64_t)blockIdx.x * TPB + threadIdx.x;
-  if (i >= N) return;
-  const int x = (int)(i % nx);
-  const int64_t row = i / nx;
-  const int y = (int)(row % ny);
-  const int z = (int)(row / ny);
-  const double* ux = u;
-  const double* uy = u + N;
-  const double* uz = u + 2 * N;
-  const int xp = x + 1 == nx ? 0 : x + 1;
-  const int yp = y + 1 == ny ? 0 : y + 1;
-  const int64_t col = (int64_t)y * nx + x;  // (x, y) column of the z sum
-  double d = (ux[row * nx + xp] - ux[i]) * inv_h;
-  d += (uy[((int64_t)z * ny + yp) * nx + x] - uy[i]) * inv_h;
-  const double* Sz = S + (int64_t)z * nz;
-  double acc = 0.0;
-  for (int k = 0; k < nz; ++k) acc = fma(Sz[k], uz[(int64_t)k * nx * ny + col], acc);
-  div[i] = d + acc;
+  uint32_t col;
+  int z0;
+  if (!wall_tile<ZT>(nx, ny, nz, col, z0)) return;
+  const size_t plane = (size_t)nx * ny, N = plane * nz;
+  double acc[ZT];
+  wall_transform<ZT>(acc, u + 2 * N + col, S, z0, nz, plane);
+  const int y = (int)(col / nx), x = (int)(col - (uint32_t)y * nx);
+  const uint32_t xp = col - x + (x + 1 == nx ? 0 : x + 1);
+  const uint32_t yp = (uint32_t)(y + 1 == ny ? 0 : y + 1) * nx + x;
+#pragma unroll
+  for (int j = 0; j < ZT; ++j) {
+    const size_t o = (size_t)(z0 + j) * plane;
+    const double *ux = u + o, *uy = u + N + o;
+    double d = (ux[xp] - ux[col]) * inv_h;
+    d += (uy[yp] - uy[col]) * inv_h;
+    div[o + col] = d + acc[j];
+  }
 }
 
 // out = u - D^T p: delta_x^T p = (p[x-1] - p[x]) / h, the same in y, and S p in z (S symmetric)
-// (out may be u: each thread reads and writes the same three entries)
+// (out may be u: each thread reads and writes the same entries)
+template <int ZT>
 __global__ __launch_bounds__(TPB) void k_selm_grad_sub(double* out, const double* u,
                                                         const double* __restrict__ p,
                                                         const double* __restrict__ S, int nx,
                                                         int ny, int nz, double inv_h) {
-  const int64_t N = (int64_t)nx * ny * nz;
-  const int64_t i = (int64_t)blockIdx.x * TPB + threadIdx.x;
-  if (i >= N) return;
-  const int x = (int)(i % nx);
-  const int64_t row = i / nx;
-  const int y = (int)(row % ny);
-  const int z = (int)(row / ny);
-  const int xm = x == 0 ? nx - 1 : x - 1;
-  const int ym = y == 0 ? ny - 1 : y - 1;
-  const int64_t col = (int64_t)y * nx + x;
-  out[i] = u[i] - (p[row * nx + xm] - p[i]) * inv_h;
-  out[N + i] = u[N + i] - (p[((int64_t)z * ny + ym) * nx + x] - p[i]) * inv_h;
-  const double* Sz = S + (int64_t)z * nz;
-  double acc = 0.0;
-  for (int k = 0; k < nz; ++k) acc = fma(Sz[k], p[(int64_t)k * nx * ny + col], acc);
-  out[2 * N + i] = u[2 * N + i] - acc;
+  uint32_t col;
+  int z0;
+  if (!wall_tile<ZT>(nx, ny, nz, col, z0)) return;
+  const size_t plane = (size_t)nx * ny, N = plane * nz;
+  double acc[ZT];
+  wall_transform<ZT>(acc, p + col, S, z0, nz, plane);
+  const int y = (int)(col / nx), x = (int)(col - (uint32_t)y * nx);
+  const uint32_t xm = col - x + (x == 0 ? nx - 1 : x - 1);
+  const uint32_t ym = (uint32_t)(y == 0 ? ny - 1 : y - 1) * nx + x;
+#pragma unroll
+  for (int j = 0; j < ZT; ++j) {
+    const size_t o = (size_t)(z0 + j) * plane;
+    const double* P = p + o;
+    const double pc = P[col];
+    const size_t i = o + col;
+    const double u0 = u[i], u1 = u[N + i], u2 = u[2 * N + i];
+    out[i] = u0 - (P[xm] - pc) * inv_h;
+    out[N + i] = u1 - (P[ym] - pc) * inv_h;
+    out[2 * N + i] = u2 - acc[j];
+  }
 }
 
 // Peskin's 4-point immersed-boundary function phi(r)
@@ -151,18 +197,35 @@ __global__ __launch_bounds__(TPB) void k_selm_em(double* __restrict__ X,
 
 }  // namespace
 
+// Runs go with the layers per lane and the grid of a wall transform: the most of 8, 4, 2 and 1
+// that divides nz, so that no tile overhangs (16 layers need more scalar registers for S than a
+// wave has).
+template <typename F>
+static hipError_t with_wall_tile(int nx, int ny, int nz, F go) {
+  auto run = [&](auto zt) {
+    constexpr int ZT = decltype(zt)::value;
+    constexpr int per = ZT * (TPB / 64);
+    go(zt, dim3((unsigned)(((int64_t)nx * ny + 63) / 64), (unsigned)((nz + per - 1) / per)));
+  };
+  if (nz % 8 == 0) run(std::integral_constant<int, 8>());
+  else if (nz % 4 == 0) run(std::integral_constant<int, 4>());
+  else if (nz % 2 == 0) run(std::integral_constant<int, 2>());
+  else run(std::integral_constant<int, 1>());
+  return hipGetLastError();
+}
+
 hipError_t launch_selm_div(double* div, const double* u, const double* S, int nx, int ny, int nz,
                            double h, hipStream_t s) {
-  const int64_t N = (int64_t)nx * ny * nz;
-  k_selm_div<<<blocks_for(N), TPB, 0, s>>>(div, u, S, nx, ny, nz, 1.0 / h);
-  return hipGetLastError();
+  return with_wall_tile(nx, ny, nz, [&](auto zt, dim3 grid) {
+    k_selm_div<decltype(zt)::value><<<grid, TPB, 0, s>>>(div, u, S, nx, ny, nz, 1.0 / h);
+  });
 }
 
 hipError_t launch_selm_grad_sub(double* out, const double* u, const double* p, const double* S,
                                 int nx, int ny, int nz, double h, hipStream_t s) {
-  const int64_t N = (int64_t)nx * ny * nz;
-  k_selm_grad_sub<<<blocks_for(N), TPB, 0, s>>>(out, u, p, S, nx, ny, nz, 1.0 / h);
-  return hipGetLastError();
+  return with_wall_tile(nx, ny, nz, [&](auto zt, dim3 grid) {
+    k_selm_grad_sub<decltype(zt)::value><<<grid, TPB, 0, s>>>(out, u, p, S, nx, ny, nz, 1.0 / h);
+  });
 }
 
 hipError_t launch_selm_spread(double* f, const double* X, const double* F, int m, int nx, int ny,

@@ -19,9 +19,9 @@ pytestmark = pytest.mark.gpu
 @pytest.mark.parametrize("precision", ["fp64", "fp32_refined"])
 @pytest.mark.parametrize("dims", [
     (22, 12, 8),     # nx/2 odd: one site a thread
-    (8, 8, 4),       # a single work-group, mostly idle
+    (16, 12, 8),     # two work-groups a colour, the second mostly idle
     (40, 24, 12),    # two sites a thread, a ragged last work-group
-    (72, 80, 92),    # four pairs a thread, rows that do not align with waves
+    (80, 112, 72),   # four pairs a thread, half of them in the last work-group
 ])
 def test_reported_residual(dims, precision):
     from paper_1003_2680_amd.api import Hierarchy
