@@ -362,7 +362,9 @@ int gen_level_noise(Run& r, int only_level = -1, int only_slot = 0) {
   uint32_t calls = 0;
   for (int l = 0; l < (int)h.lv.size(); ++l) {
     const Level& v = h.lv[l];
-    if (v.kind != KIND_BLOCK || (only_level >= 0 && l != only_level)) continue;
+    // a point level's passes draw their own noise, except in the bottom launch
+    const bool point = v.kind == KIND_POINT && l == h.bottom && h.use_bottom && only_level < 0;
+    if ((v.kind != KIND_BLOCK && !point) || (only_level >= 0 && l != only_level)) continue;
     if (a.nlev == kMaxNoiseLevels) {
       set_error("too many block levels");
       return SMG_EINVAL;
@@ -375,7 +377,7 @@ int gen_level_noise(Run& r, int only_level = -1, int only_slot = 0) {
     e.nslot = only_level >= 0 ? 1 : h.prm.nu1 + h.prm.nu2;
     e.slot0 = only_level >= 0 ? only_slot : 0;
     e.out = comp_at((T*)v.noise_d, v.n, r);
-    e.bfac = v.bfac_d;
+    e.bfac = point ? nullptr : v.bfac_d;
     e.lg_bx = log2_exact(v.nx / 2);
     e.lg_bxy = log2_exact((v.nx / 2) * (v.ny / 2));
     e.calls_before = calls;
@@ -412,6 +414,15 @@ BotArgs make_botargs(Hierarchy& h) {
     bl.sz = sz;
     bl.noise = v.noise_d;
     for (int q = 0; q < 20; ++q) bl.s1d[q] = v.s1d.empty() ? 0.0 : v.s1d[q];
+    if (v.kind == KIND_POINT) {
+      const double hh = h.desc.h * h.desc.h;
+      for (int w = 0; w < 3; ++w) {
+        bl.s1d[w] = hh / (6.0 + w);
+        bl.s1d[3 + w] = std::sqrt(h.desc.kT * hh / (6.0 + w));
+        bl.s1d[6 + w] = 1.0 / (6.0 + w);
+      }
+      bl.s1d[9] = 1.0 / hh;
+    }
     bl.zt = v.zt_d;
     bl.bfac = v.bfac_d;
     bl.xg = f32 ? (void*)v.xf : (void*)v.x;
@@ -434,7 +445,15 @@ BotArgs make_botargs(Hierarchy& h) {
 
 // The bottom's block levels are in front of a coarsest draw that takes a launch of its own.
 bool splits_bottom(const Hierarchy& h) {
-  return h.wide_coarsest && h.lv[h.bottom].kind == KIND_BLOCK;
+  return h.wide_coarsest && h.lv[h.bottom].kind != KIND_CHOL;
+}
+
+// The whole cycle, its point level included, runs in the bottom launch.
+bool point_bottom(const Hierarchy& h) {
+  return h.bottom >= 0 && h.lv[h.bottom].kind == KIND_POINT;
+}
+int bottom_part(const Run& r, BotPart part) {
+  return (int)part | (point_bottom(*r.h) && r.has_b0 ? kBotHasB : 0);
 }
 
 // Every level from h.bottom down: in one launch (LDS-resident, one work-group per component), or
@@ -448,14 +467,19 @@ int bottom_cycle(Run& r) {
   const int last = (int)h.lv.size() - 1;
   TimedScope ts(h, r.s, SMG_TIMED_BOTTOM, 1);
   SMG_TRY(ts.rc);
+  auto launch = [&](BotPart part) -> int {
+    SMG_HIP(launch_bottom<T>(h.botargs_d, r.nc, r.c0, h.bottom_lds, r.noise, point_bottom(h),
+                             bottom_part(r, part), na, r.s));
+    return SMG_OK;
+  };
   if (h.lv[h.bottom].kind == KIND_CHOL) {
     SMG_TRY(coarsest_step<T>(r, last));
   } else if (splits_bottom(h)) {
-    SMG_HIP(launch_bottom<T>(h.botargs_d, r.nc, r.c0, h.bottom_lds, r.noise, BOT_DOWN, na, r.s));
+    SMG_TRY(launch(BOT_DOWN));
     SMG_TRY(coarsest_step<T>(r, last));
-    SMG_HIP(launch_bottom<T>(h.botargs_d, r.nc, r.c0, h.bottom_lds, r.noise, BOT_UP, na, r.s));
+    SMG_TRY(launch(BOT_UP));
   } else {
-    SMG_HIP(launch_bottom<T>(h.botargs_d, r.nc, r.c0, h.bottom_lds, r.noise, BOT_WHOLE, na, r.s));
+    SMG_TRY(launch(BOT_WHOLE));
   }
   return ts.close();
 }
@@ -483,7 +507,8 @@ int vcycle(Run& r, int l) {
 // The cycle split around the LDS-resident bottom: the down-leg (levels above the bottom: pre-
 // sweeps and restrictions) and the up-leg (prolongations and post-sweeps), in the order of
 // vcycle, so that down-leg + bottom + up-leg is vcycle(0) exactly.
-bool split_bottom(const Hierarchy& h) { return h.use_bottom && h.bottom > 0; }
+// Where the bottom is the whole cycle both legs are empty.
+bool split_bottom(const Hierarchy& h) { return h.use_bottom && h.bottom >= 0; }
 
 template <typename T>
 int vdown(Run& r) {
@@ -723,11 +748,12 @@ int batch_bottoms(const std::vector<Run*>& runs) {
       m.bm = box_muller_coef();
       int nwg = 0;
       size_t lds = 0;
+      bool point = false;
       hipStream_t s = nullptr;
       auto flush = [&]() -> int {
         if (m.nitems == 0) return SMG_OK;
-        hipError_t e = f32 ? launch_bottom_multi<float>(m, nwg, lds, nz != 0, s)
-                           : launch_bottom_multi<double>(m, nwg, lds, nz != 0, s);
+        hipError_t e = f32 ? launch_bottom_multi<float>(m, nwg, lds, nz != 0, point, s)
+                           : launch_bottom_multi<double>(m, nwg, lds, nz != 0, point, s);
         if (e != hipSuccess) {
           set_error(std::string("launch_bottom_multi: ") + hipGetErrorString(e));
           return SMG_EHIP;
@@ -735,9 +761,10 @@ int batch_bottoms(const std::vector<Run*>& runs) {
         m.nitems = 0;
         nwg = 0;
         lds = 0;
+        point = false;
         return SMG_OK;
       };
-      auto add = [&](Run* r, int part) -> int {
+      auto add = [&](Run* r, BotPart part) -> int {
         Hierarchy& h = *r->h;
         if (m.nitems == kBotMultiItems || nwg + r->nc > kBotMultiWG) SMG_TRY(flush());
         const NoiseArgs na = make_noise(*r, 0, 0, 0, KIND_SMOOTH_NOISE);
@@ -750,7 +777,8 @@ int batch_bottoms(const std::vector<Run*>& runs) {
         it.chains = na.chains;
         it.cpc = na.comps_per_chain;
         it.cpc_magic = na.cpc_magic;
-        it.part = part;
+        it.part = bottom_part(leg_run(*r), part);
+        point = point || point_bottom(h);
         it.sqkT = na.sqkT;
         // the bottom numbers components absolutely (its noise keys take the chain table as is)
         for (int c = r->c0; c < r->c0 + r->nc; ++c)
@@ -1524,6 +1552,7 @@ int bind_impl(Hierarchy& h, char* ws, bool upload, hipStream_t s) {
       v.bf = (float*)(ws + v.off_bf);
       v.rf = v.kind == KIND_CHOL ? nullptr : (float*)(ws + v.off_rf);
     }
+    if (v.kind == KIND_POINT && h.bottom == 0) v.noise_d = ws + v.off_noise;
     if (v.kind == KIND_BLOCK) {
       v.s1d_d = ws + v.off_s1d;
       v.zt_d = ws + v.off_zt;

@@ -27,7 +27,9 @@ struct NoiseLevel {
   int level, nx, ny, nz, nslot, slot0;
   int lg_bx, lg_bxy;      // log2 of nx/2 and of (nx/2)(ny/2) when powers of two, else -1
   void* out;              // T[nslot][ncomp][N]
-  const void* bfac;       // T[nz/2][kBlockRow]: the level's block factors (L_BB^-T at offset 64)
+  const void* bfac;       // T[nz/2][kBlockRow]: the level's block factors (L_BB^-T at offset 64);
+                          // null: a point level (split colours: colour c of a component begins
+                          // at c N/2, call q is sites 2q, 2q + 1)
   uint32_t calls_before;  // prefix sum of nslot*nact*N/2 over the previous entries
 };
 struct NoiseGenArgs {
@@ -44,15 +46,17 @@ struct BotLevel {
   int nx, ny, nz, kind;
   int sy, sz;          // LDS strides of x: padded for block levels, natural for the coarsest
   const void* noise;   // T: pregenerated noise of this level [slot][ncomp][N] (block levels)
-  double s1d[20];      // 1D stencils (m_x, a_x, m_y, a_y), offsets -2..2
+  double s1d[20];      // 1D stencils (m_x, a_x, m_y, a_y), offsets -2..2; a point level (level 0):
+                       // h^2/d, sqrt(kT h^2/d) and 1/d for d = 6, 7, 8, then 1/h^2
   const void* zt;      // T: [nz][10]
   const void* bfac;    // T: [nz/2][kBlockRow]
   void* xg;            // T [ncomp][n]: the level's x and b in memory, where the two parts of a
-  void* bg;            // split bottom leave and find them
+  void* bg;            // split bottom leave and find them; a point level: its split state and b
 };
 // What a bottom launch runs: everything, or the two halves around a coarsest draw that the whole
 // chip makes (launch_coarsest): down to its right-hand side, and up from its result.
 enum BotPart { BOT_WHOLE = 0, BOT_DOWN = 1, BOT_UP = 2 };
+constexpr int kBotHasB = 4;  // added to the part: level 0 is in the bottom and has a right-hand side
 struct BotArgs {
   int nlev, level0, nu1, nu2, ncomp;
   BotLevel lv[kMaxBotLevels];
@@ -225,13 +229,15 @@ hipError_t launch_block_pass_multi(const BlockPassItem<T>* items, int n, int col
 template <typename T>
 hipError_t launch_level_noise(const NoiseGenArgs& a, const NoiseArgs& na, hipStream_t s);
 // `a` points to a BotArgs in device memory; the launch runs components c0 .. c0+ncomp-1 (one
-// work-group each; the noise is keyed by those absolute component numbers)
+// work-group each; the noise is keyed by those absolute component numbers).  point: the bottom
+// begins at a point level; part: a BotPart, plus kBotHasB
 template <typename T>
-hipError_t launch_bottom(const BotArgs* a, int ncomp, int c0, size_t lds, bool noise, int part,
-                         const NoiseArgs& na, hipStream_t s);
+hipError_t launch_bottom(const BotArgs* a, int ncomp, int c0, size_t lds, bool noise, bool point,
+                         int part, const NoiseArgs& na, hipStream_t s);
 // The bottoms of several hierarchies in one launch (kernel arguments only): item i brings its
 // device BotArgs and its noise keys; work-group w runs component wg[w] >> 16 of item
-// wg[w] & 0xffff.  lds: the largest bottom LDS size of the items.
+// wg[w] & 0xffff.  lds: the largest bottom LDS size of the items; point: one of them begins at a
+// point level.
 constexpr int kBotMultiItems = 16;
 constexpr int kBotMultiWG = 256;
 struct BotMultiItem {
@@ -239,7 +245,7 @@ struct BotMultiItem {
   uint32_t k0, k1, c2, c3;   // as NoiseArgs
   const ChainKey* chains;
   uint32_t cpc, cpc_magic;
-  int part;                  // BotPart
+  int part;                  // BotPart, plus kBotHasB
   double sqkT;
 };
 struct BotMultiArgs {
@@ -249,7 +255,7 @@ struct BotMultiArgs {
   uint32_t wg[kBotMultiWG];
 };
 template <typename T>
-hipError_t launch_bottom_multi(const BotMultiArgs& m, int nwg, size_t lds, bool noise,
+hipError_t launch_bottom_multi(const BotMultiArgs& m, int nwg, size_t lds, bool noise, bool point,
                                hipStream_t s);
 // x = A_c^-1 b (+ sqrt(kT) L_c^-T n), FP64 arithmetic, T storage
 template <typename T>

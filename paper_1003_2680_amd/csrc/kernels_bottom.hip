@@ -2,6 +2,8 @@
 // 4096 cells and the coarsest exact draw, one work-group per component, in one launch.
 #include <hip/hip_runtime.h>
 
+#include <type_traits>
+
 #include "block_update.hpp"
 #include "device_common.hpp"
 #include "kernels.hpp"
@@ -282,14 +284,158 @@ __device__ __forceinline__ void bot_residual(T* R, const T* X, const T* B, const
   }
 }
 
+// Level 0 in the bottom: the red-black point heat bath of a hierarchy of at most 4096 cells, its
+// state in LDS in the split layout (natural, no halo: consecutive lanes touch consecutive words).
+// A thread owns the sites p = tid + k BOT_TPB of either colour, so a site's row, plane and wall
+// are found once, and the normals of a pass are loaded while the pass before runs.  A launch per
+// colour pass and transfer of such a grid is all latency: a 16^3 cycle took 75 us in 12 launches
+// and takes 55 in two (noise and this one), of which the point level 17: a pass 0.55 us, the
+// residual 1.8, its restriction 3.0, the prolongation 1.8.
+constexpr int PT_PER = 4096 / 2 / BOT_TPB;
+template <typename T>
+struct PointSites {
+  int p[PT_PER], n[PT_PER], s[PT_PER], u[PT_PER], d[PT_PER];  // the site, its y and z neighbours
+  int o[PT_PER][2];      // per colour: the x-neighbour beside entry p of the other colour
+  int nat[PT_PER][2];    // per colour: the site's natural index
+  int wall[PT_PER];      // bit 0: at the top, bit 1: at the bottom
+  int nsite;
+  __device__ __forceinline__ void init(const BotLevel& L) {
+    int tid = (int)threadIdx.x;
+    asm volatile("" : "+v"(tid));  // formed anew by each leg: not kept over the levels between
+    const int nh = L.nx >> 1, ny = L.ny, nz = L.nz, plane = nh * ny;
+    nsite = plane * nz;
+#pragma unroll
+    for (int k = 0; k < PT_PER; ++k) {
+      p[k] = tid + k * BOT_TPB;
+      const int q = p[k] < nsite ? p[k] : 0;  // lanes past the sites stay in range
+      int row, j, z, y;
+      divmod_uniform(q, nh, row, j);
+      divmod_uniform(row, ny, z, y);
+      n[k] = q + (y + 1 == ny ? nh - plane : nh);
+      s[k] = q + (y == 0 ? plane - nh : -nh);
+      u[k] = z + 1 < nz ? q + plane : q;
+      d[k] = z > 0 ? q - plane : q;
+      wall[k] = (z + 1 >= nz ? 1 : 0) | (z == 0 ? 2 : 0);
+#pragma unroll
+      for (int c = 0; c < 2; ++c) {
+        const int xs = (y + z + c) & 1;  // x = 2j + xs: neighbours j and j + 1 or j - 1
+        o[k][c] = xs ? (j + 1 == nh ? q - j : q + 1) : (j == 0 ? q + nh - 1 : q - 1);
+        nat[k][c] = row * L.nx + 2 * j + xs;
+      }
+    }
+  }
+};
+
+// The normals of colour pass q of the sweeps slot0 .. of a leg.
+template <typename T>
+__device__ __forceinline__ void point_noise(T (&z)[PT_PER], const PointSites<T>& S, gptr<T> Z,
+                                            size_t slot_stride, int slot0, int q, bool post) {
+  const int colour = post ? 1 - (q & 1) : q & 1;
+  const gptr<T> P = Z + (size_t)(slot0 + (q >> 1)) * slot_stride + (size_t)colour * S.nsite;
+#pragma unroll
+  for (int k = 0; k < PT_PER; ++k) z[k] = P[S.p[k] < S.nsite ? S.p[k] : 0];
+}
+
+// Sweeps slot0 .. slot0 + nslot - 1; z holds the normals of the first pass (point_noise).
 template <typename T, bool NOISE>
+__device__ __forceinline__ void point_sweeps(T* X, const T* B, bool has_b, const BotLevel& L,
+                                             const PointSites<T>& S, T (&z)[PT_PER], gptr<T> Z,
+                                             size_t slot_stride, int slot0, int nslot, bool post) {
+  const int nsite = S.nsite;
+  T dg[10];
+#pragma unroll
+  for (int e = 0; e < 10; ++e) dg[e] = (T)L.s1d[e];  // uniform: scalar registers
+#pragma unroll 1
+  for (int q = 0; q < 2 * nslot; ++q) {
+    const int c = post ? 1 - (q & 1) : q & 1;
+    T zn[PT_PER];
+#pragma unroll
+    for (int k = 0; k < PT_PER; ++k) zn[k] = z[k];
+    if (NOISE && q + 1 < 2 * nslot) point_noise<T>(z, S, Z, slot_stride, slot0, q + 1, post);
+    T* xc = X + c * nsite;
+    const T* xo = X + (1 - c) * nsite;
+    const T* bc = B + c * nsite;
+#pragma unroll
+    for (int k = 0; k < PT_PER; ++k) {
+      if (k * BOT_TPB >= nsite) break;
+      const bool top = S.wall[k] & 1, low = S.wall[k] & 2;
+      const int own = S.p[k] < nsite ? S.p[k] : 0, ox = c ? S.o[k][1] : S.o[k][0];
+      const T sx = xo[own] + xo[ox];
+      const T sum = (sx + (xo[S.n[k]] + xo[S.s[k]])) +
+                    fma(xo[S.u[k]], top ? T(0) : T(1), xo[S.d[k]] * (low ? T(0) : T(1)));
+      const int nw = (int)top + (int)low;
+      auto by_walls = [&](T d6, T d7, T d8) { return nw == 0 ? d6 : (nw == 1 ? d7 : d8); };
+      T v = has_b ? fma(sum, dg[9], bc[own]) * by_walls(dg[0], dg[1], dg[2])
+                  : sum * by_walls(dg[6], dg[7], dg[8]);
+      if (NOISE) v = fma(by_walls(dg[3], dg[4], dg[5]), zn[k], v);
+      if (S.p[k] < nsite) xc[own] = v;
+    }
+    __syncthreads();
+  }
+}
+
+// R = b - A x in natural layout.
+template <typename T>
+__device__ __forceinline__ void point_residual(T* R, const T* X, const T* B, bool has_b,
+                                               const BotLevel& L, const PointSites<T>& S) {
+  const int nsite = S.nsite;
+  const T ih2 = (T)L.s1d[9];
+#pragma unroll
+  for (int k = 0; k < PT_PER; ++k) {
+    if (S.p[k] >= nsite) break;
+    const bool top = S.wall[k] & 1, low = S.wall[k] & 2;
+#pragma unroll
+    for (int c = 0; c < 2; ++c) {
+      const T* xo = X + (1 - c) * nsite;
+      T sn = (xo[S.p[k]] + xo[S.o[k][c]]) + (xo[S.s[k]] + xo[S.n[k]]);
+      if (!top) sn += xo[S.u[k]];
+      if (!low) sn += xo[S.d[k]];
+      T r = -(T(6 + (int)top + (int)low) * X[c * nsite + S.p[k]] - sn) * ih2;
+      if (has_b) r += B[c * nsite + S.p[k]];
+      R[S.nat[k][c]] = r;
+    }
+  }
+}
+
+// POINT: the first level may be a point level (level 0).
+template <typename T, bool NOISE, bool POINT>
 __device__ __forceinline__ void bottom_body(const BotArgs& a, const uint32_t comp,
-                                            const NoiseArgs& na, int part) {
+                                            const NoiseArgs& na, int part_b) {
+  const int part = part_b & 3;
+  const bool has_b = part_b & kBotHasB;
   extern __shared__ char smraw[];
   T* sm = reinterpret_cast<T*>(smraw);
   const int tid = threadIdx.x;
   const BotLevel& L0 = a.lv[0];
   const int n0 = L0.nx * L0.ny * L0.nz;
+  const bool point = POINT && L0.kind == KIND_POINT;
+  const int first = point ? 1 : 0;
+  const gptr<T> pn = global_ptr<T>(L0.noise) + (size_t)comp * n0;
+  const size_t pstride = (size_t)a.ncomp * n0;
+  auto point_load = [&](const PointSites<T>& ps) {
+    T* X = sm + a.lds_off[0];
+#pragma unroll
+    for (int c = 0; c < 2; ++c) {
+      const size_t at = ((size_t)c * a.ncomp + comp) * ps.nsite;
+      const gptr<T> xg = global_ptr<T>(L0.xg) + at, bg = global_ptr<T>(L0.bg) + at;
+#pragma unroll
+      for (int k = 0; k < PT_PER; ++k) {
+        if (ps.p[k] >= ps.nsite) break;
+        X[c * ps.nsite + ps.p[k]] = xg[ps.p[k]];
+        if (has_b) X[n0 + c * ps.nsite + ps.p[k]] = bg[ps.p[k]];
+      }
+    }
+  };
+  auto point_store = [&](const PointSites<T>& ps) {
+    const T* X = sm + a.lds_off[0];
+#pragma unroll
+    for (int c = 0; c < 2; ++c) {
+      T* xg = (T*)L0.xg + ((size_t)c * a.ncomp + comp) * ps.nsite;
+#pragma unroll
+      for (int k = 0; k < PT_PER; ++k)
+        if (ps.p[k] < ps.nsite) xg[ps.p[k]] = X[c * ps.nsite + ps.p[k]];
+    }
+  };
   // element of the LDS field x for the natural index q of level L, halo copies beside it
   auto place = [](const BotLevel& L, int q, int& x) {
     int y, z, r;
@@ -298,7 +444,7 @@ __device__ __forceinline__ void bottom_body(const BotArgs& a, const uint32_t com
     return z * L.sz + y * L.sy + x + (L.kind == KIND_BLOCK ? kBotHalo : 0);
   };
   if (part == BOT_UP) {  // x and b of every block level, and the coarsest x, as BOT_DOWN left them
-    for (int i = 0; i < a.nlev; ++i) {
+    for (int i = first; i < a.nlev; ++i) {
       const BotLevel& L = a.lv[i];
       const int n = L.nx * L.ny * L.nz;
       T* xi = sm + a.lds_off[i];
@@ -315,7 +461,7 @@ __device__ __forceinline__ void bottom_body(const BotArgs& a, const uint32_t com
         }
       }
     }
-  } else {
+  } else if (!point) {
     T* x0 = sm + a.lds_off[0];
     for (int q = tid; q < L0.nz * L0.sz; q += BOT_TPB) x0[q] = T(0);
     T* b0 = x0 + L0.nz * L0.sz;
@@ -324,7 +470,7 @@ __device__ __forceinline__ void bottom_body(const BotArgs& a, const uint32_t com
   }
   // operator tables of the block levels (bot_table_elems) at tab_off[i]; the normals
   // of the coarsest draw, which depend on nothing above it
-  for (int i = 0; i < a.nlev; ++i) {
+  for (int i = first; i < a.nlev; ++i) {
     const BotLevel& L = a.lv[i];
     if (L.kind == KIND_BLOCK) {
       const int nz = L.nz;
@@ -349,7 +495,45 @@ __device__ __forceinline__ void bottom_body(const BotArgs& a, const uint32_t com
   }
   __syncthreads();
   int last = a.nlev - 1;
-  for (int i = 0; i < a.nlev && part != BOT_UP; ++i) {
+  // b_{i+1} = P^T r_i, x_{i+1} = 0
+  auto restrict_to_next = [&](int i) {
+    const BotLevel& L = a.lv[i];
+    const T* ri = sm + a.lds_off[i] + L.nz * L.sz + L.nx * L.ny * L.nz;
+    const BotLevel& C = a.lv[i + 1];
+    T* xc = sm + a.lds_off[i + 1];
+    T* bc = xc + C.nz * C.sz;
+    for (int q = tid; q < C.nz * C.sz; q += BOT_TPB) xc[q] = T(0);
+    for (int q = tid; q < C.nx * C.ny * C.nz; q += BOT_TPB) {
+      int X, Y, Z2, r;
+      divmod_uniform(q, C.nx, r, X);
+      divmod_uniform(r, C.ny, Z2, Y);
+      bc[q] = restrict_at<T>(ri, L.nx, L.nx * L.ny, L.nx, L.ny, L.nz, X, Y, Z2);
+    }
+    __syncthreads();
+  };
+  T pz[PT_PER] = {};  // the point level's normals of its next pass
+  if (point && part != BOT_UP) {
+    PointSites<T> ps;
+    ps.init(L0);
+    T* X = sm + a.lds_off[0];
+    if (NOISE && a.nu1 > 0) point_noise<T>(pz, ps, pn, pstride, 0, 0, false);
+    point_load(ps);
+    __syncthreads();
+    point_sweeps<T, NOISE>(X, X + n0, has_b, L0, ps, pz, pn, pstride, 0, a.nu1, false);
+    if (NOISE && part != BOT_DOWN && a.nu2 > 0)
+      point_noise<T>(pz, ps, pn, pstride, a.nu1, 0, true);
+    if (a.nlev == 1) {
+      // smoothing-only: the post-sweeps follow at once
+      point_sweeps<T, NOISE>(X, X + n0, has_b, L0, ps, pz, pn, pstride, a.nu1, a.nu2, true);
+      point_store(ps);
+      return;
+    }
+    if (part == BOT_DOWN) point_store(ps);
+    point_residual<T>(X + 2 * n0, X, X + n0, has_b, L0, ps);
+    __syncthreads();
+    restrict_to_next(0);
+  }
+  for (int i = first; i < a.nlev && part != BOT_UP; ++i) {
     const BotLevel& L = a.lv[i];
     const int n = L.nx * L.ny * L.nz;
     T* xi = sm + a.lds_off[i];
@@ -403,22 +587,11 @@ __device__ __forceinline__ void bottom_body(const BotArgs& a, const uint32_t com
         xg[q] = xi[place(L, q, x)];
       }
     }
-    // b_{i+1} = P^T (b_i - A_i x_i), x_{i+1} = 0
     bot_residual<T>(ri, xi, bi, L, tab);
     __syncthreads();
-    const BotLevel& C = a.lv[i + 1];
-    T* xc = sm + a.lds_off[i + 1];
-    T* bc = xc + C.nz * C.sz;
-    for (int q = tid; q < C.nz * C.sz; q += BOT_TPB) xc[q] = T(0);
-    for (int q = tid; q < C.nx * C.ny * C.nz; q += BOT_TPB) {
-      int X, Y, Z2, r;
-      divmod_uniform(q, C.nx, r, X);
-      divmod_uniform(r, C.ny, Z2, Y);
-      bc[q] = restrict_at<T>(ri, L.nx, L.nx * L.ny, L.nx, L.ny, L.nz, X, Y, Z2);
-    }
-    __syncthreads();
+    restrict_to_next(i);
   }
-  for (int i = last - 1; i >= 0; --i) {
+  for (int i = last - 1; i >= first; --i) {
     const BotLevel& L = a.lv[i];
     const BotLevel& C = a.lv[i + 1];
     const int n = L.nx * L.ny * L.nz;
@@ -436,6 +609,33 @@ __device__ __forceinline__ void bottom_body(const BotArgs& a, const uint32_t com
     bot_sweeps<T, NOISE>(xi, xi + L.nz * L.sz, L, sm + a.tab_off[i], a.nu1, a.nu2, true,
                          global_ptr<T>(L.noise) + (size_t)comp * n, (size_t)a.ncomp * n);
   }
+  if (point) {
+    T* X = sm + a.lds_off[0];
+    PointSites<T> ps;
+    ps.init(L0);
+    if (part == BOT_UP) {
+      if (NOISE && a.nu2 > 0) point_noise<T>(pz, ps, pn, pstride, a.nu1, 0, true);
+      point_load(ps);
+      __syncthreads();
+    }
+    // x += P e; with post-sweeps colour 1, drawn afresh by their first pass, needs none
+    const BotLevel& C = a.lv[1];
+    const T* xc = sm + a.lds_off[1] + (C.kind == KIND_BLOCK ? kBotHalo : 0);
+    for (int c = 0; c < (a.nu2 > 0 ? 1 : 2); ++c)
+#pragma unroll
+      for (int k = 0; k < PT_PER; ++k) {
+        if (ps.p[k] >= ps.nsite) break;
+        int x, y, z, r;
+        divmod_uniform(c ? ps.nat[k][1] : ps.nat[k][0], L0.nx, r, x);
+        divmod_uniform(r, L0.ny, z, y);
+        X[c * ps.nsite + ps.p[k]] +=
+            prolong_at<T>(xc, C.sy, C.sz, x, y, z, C.nx, C.ny, C.nz);
+      }
+    __syncthreads();
+    point_sweeps<T, NOISE>(X, X + n0, has_b, L0, ps, pz, pn, pstride, a.nu1, a.nu2, true);
+    point_store(ps);
+    return;
+  }
   for (int q = tid; q < n0; q += BOT_TPB) {
     int x;
     ((T*)a.x_out)[(size_t)comp * n0 + q] = sm[a.lds_off[0] + place(L0, q, x)];
@@ -443,17 +643,17 @@ __device__ __forceinline__ void bottom_body(const BotArgs& a, const uint32_t com
 }
 
 // One hierarchy, one work-group per component.
-template <typename T, bool NOISE>
+template <typename T, bool NOISE, bool POINT>
 __global__ __launch_bounds__(BOT_TPB)
 __attribute__((amdgpu_waves_per_eu(2, 2))) void k_bottom(const BotArgs* __restrict__ ap, int c0,
                                                     int part, NoiseArgs na) {
-  bottom_body<T, NOISE>(*ap, c0 + (int)blockIdx.x, na, part);
+  bottom_body<T, NOISE, POINT>(*ap, c0 + (int)blockIdx.x, na, part);
 }
 
 // Several hierarchies (of any sizes) in one launch: work-group w runs component wg >> 16 of
 // item wg & 0xffff, with that item's level descriptors and noise keys, so the latency-bound
 // bottoms of uneven instances overlap instead of running one launch after another.
-template <typename T, bool NOISE>
+template <typename T, bool NOISE, bool POINT>
 __global__ __launch_bounds__(BOT_TPB)
 __attribute__((amdgpu_waves_per_eu(2, 2))) void k_bottom_multi(BotMultiArgs m) {
   const uint32_t w = m.wg[blockIdx.x];
@@ -469,54 +669,62 @@ __attribute__((amdgpu_waves_per_eu(2, 2))) void k_bottom_multi(BotMultiArgs m) {
   na.comps_per_chain = it.cpc;
   na.cpc_magic = it.cpc_magic;
   na.bm = m.bm;
-  bottom_body<T, NOISE>(*it.args, w >> 16, na, it.part);
+  bottom_body<T, NOISE, POINT>(*it.args, w >> 16, na, it.part);
 }
 
 }  // namespace
 
-template <typename T>
-hipError_t launch_bottom(const BotArgs* a, int ncomp, int c0, size_t lds, bool noise, int part,
-                         const NoiseArgs& na, hipStream_t s) {
-  static bool attr_set = false;
-  if (!attr_set) {
-    hipError_t e = hipFuncSetAttribute((const void*)k_bottom<T, true>,
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
-    if (e == hipSuccess)
-      e = hipFuncSetAttribute((const void*)k_bottom<T, false>,
-                              hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
-    if (e != hipSuccess) return e;
-    attr_set = true;
-  }
-  if (noise) k_bottom<T, true><<<ncomp, BOT_TPB, lds, s>>>(a, c0, part, na);
-  else k_bottom<T, false><<<ncomp, BOT_TPB, lds, s>>>(a, c0, part, na);
-  return hipGetLastError();
+// The kernels with dynamic LDS of up to 160 KB (the attribute is set once a process each).
+template <typename K>
+static hipError_t big_lds(K k, bool& set) {
+  if (set) return hipSuccess;
+  const hipError_t e = hipFuncSetAttribute((const void*)k,
+                                           hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
+  set = e == hipSuccess;
+  return e;
 }
 
 template <typename T>
-hipError_t launch_bottom_multi(const BotMultiArgs& m, int nwg, size_t lds, bool noise,
-                               hipStream_t s) {
-  static bool attr_set = false;
-  if (!attr_set) {
-    hipError_t e = hipFuncSetAttribute((const void*)k_bottom_multi<T, true>,
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
-    if (e == hipSuccess)
-      e = hipFuncSetAttribute((const void*)k_bottom_multi<T, false>,
-                              hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
+hipError_t launch_bottom(const BotArgs* a, int ncomp, int c0, size_t lds, bool noise, bool point,
+                         int part, const NoiseArgs& na, hipStream_t s) {
+  auto go = [&](auto nz, auto pt) -> hipError_t {
+    static bool set = false;
+    auto k = k_bottom<T, decltype(nz)::value, decltype(pt)::value>;
+    const hipError_t e = big_lds(k, set);
     if (e != hipSuccess) return e;
-    attr_set = true;
-  }
+    k<<<ncomp, BOT_TPB, lds, s>>>(a, c0, part, na);
+    return hipGetLastError();
+  };
+  if (noise) return point ? go(std::true_type(), std::true_type())
+                          : go(std::true_type(), std::false_type());
+  return point ? go(std::false_type(), std::true_type())
+               : go(std::false_type(), std::false_type());
+}
+
+template <typename T>
+hipError_t launch_bottom_multi(const BotMultiArgs& m, int nwg, size_t lds, bool noise, bool point,
+                               hipStream_t s) {
   if (nwg <= 0) return hipSuccess;
   if (nwg > kBotMultiWG || m.nitems > kBotMultiItems) return hipErrorInvalidValue;
-  if (noise) k_bottom_multi<T, true><<<nwg, BOT_TPB, lds, s>>>(m);
-  else k_bottom_multi<T, false><<<nwg, BOT_TPB, lds, s>>>(m);
-  return hipGetLastError();
+  auto go = [&](auto nz, auto pt) -> hipError_t {
+    static bool set = false;
+    auto k = k_bottom_multi<T, decltype(nz)::value, decltype(pt)::value>;
+    const hipError_t e = big_lds(k, set);
+    if (e != hipSuccess) return e;
+    k<<<nwg, BOT_TPB, lds, s>>>(m);
+    return hipGetLastError();
+  };
+  if (noise) return point ? go(std::true_type(), std::true_type())
+                          : go(std::true_type(), std::false_type());
+  return point ? go(std::false_type(), std::true_type())
+               : go(std::false_type(), std::false_type());
 }
 
 #define SMG_INST(T)                                                                  \
-  template hipError_t launch_bottom<T>(const BotArgs*, int, int, size_t, bool, int,  \
-                                       const NoiseArgs&, hipStream_t);               \
+  template hipError_t launch_bottom<T>(const BotArgs*, int, int, size_t, bool, bool, \
+                                       int, const NoiseArgs&, hipStream_t);          \
   template hipError_t launch_bottom_multi<T>(const BotMultiArgs&, int, size_t, bool, \
-                                             hipStream_t);
+                                             bool, hipStream_t);
 SMG_INST(double)
 SMG_INST(float)
 #undef SMG_INST

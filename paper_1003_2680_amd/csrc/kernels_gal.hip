@@ -47,6 +47,26 @@ __global__ __launch_bounds__(TPB) void k_level_noise(NoiseGenArgs a, NoiseArgs n
   const uint32_t bid = blockIdx.x * TPB + threadIdx.x;  // block within (slot, comp)
   const uint32_t s = blockIdx.z / (uint32_t)a.nact;
   const uint32_t comp = blockIdx.z - s * (uint32_t)a.nact;
+  if (!L.bfac) {
+    // a point level: N/4 calls a colour, four of the N/2 a thread, neighbours side by side
+    const uint32_t per = (N / 2 + 3) / 4;
+    if (bid >= per || (int)s >= L.nslot) return;
+    T* out = (T*)L.out + ((size_t)s * a.ncomp + comp) * N;
+#pragma unroll
+    for (int m = 0; m < 4; ++m) {
+      const uint32_t q = bid + m * per, c = q >= N / 4 ? 1u : 0u;
+      if (q >= N / 2) return;
+      const uint32_t sid = (uint32_t)L.level | ((uint32_t)(L.slot0 + s) << 4) | (c << 12);
+      T z0, z1;
+      if constexpr (sizeof(T) == 8) normal_pair_notable(na, sid, comp, q - c * (N / 4), z0, z1);
+      else normal_pair_t<T>(na, sid, comp, q - c * (N / 4), z0, z1);
+      V2 v;
+      v.x = z0;
+      v.y = z1;
+      *reinterpret_cast<V2*>(out + 2 * q) = v;
+    }
+    return;
+  }
   if (bid >= (N >> 3) || (int)s >= L.nslot) return;
   const uint32_t nbx = (uint32_t)L.nx >> 1, nby = (uint32_t)L.ny >> 1;
   const uint32_t bz = udiv(bid, nbx * nby, L.lg_bxy);
@@ -922,7 +942,7 @@ hipError_t launch_level_noise(const NoiseGenArgs& a, const NoiseArgs& na, hipStr
   uint32_t maxblk = 0;
   int maxslot = 0;
   for (int e = 0; e < a.nlev; ++e) {
-    const uint32_t nb = (uint32_t)a.lv[e].nx * a.lv[e].ny * a.lv[e].nz / 8;
+    const uint32_t nb = ((uint32_t)a.lv[e].nx * a.lv[e].ny * a.lv[e].nz + 7) / 8;
     maxblk = nb > maxblk ? nb : maxblk;
     maxslot = a.lv[e].nslot > maxslot ? a.lv[e].nslot : maxslot;
   }

@@ -420,10 +420,11 @@ int build_plan(const smg_grid_desc& d, const smg_cycle_params& p, Hierarchy& h, 
       v.off_noise = take((size_t)(p.nu1 + p.nu2) * n * ts);
     }
   }
-  // Bottom of the V-cycle: the first Galerkin level with at most kBottomCells cells and every
-  // level below it live in one work-group's LDS per component (x, b and one scratch field per
-  // level; the coarsest draw stages b and the noise).
-  for (int l = 1; l < L; ++l) {
+  // Bottom of the V-cycle: the first level with at most kBottomCells cells and every level below
+  // it live in one work-group's LDS per component (x, b and one scratch field per level; the
+  // coarsest draw stages b and the noise).  A whole hierarchy of that size, its point level
+  // included, is one launch a cycle; where its LDS does not hold that, the bottom begins below.
+  for (int l = h.lv[0].kind == KIND_POINT ? 0 : 1; l < L; ++l) {
     if (h.lv[l].n > kBottomCells) continue;
     size_t lds = 0;
     for (int m = l; m < L; ++m) {
@@ -434,9 +435,12 @@ int build_plan(const smg_grid_desc& d, const smg_cycle_params& p, Hierarchy& h, 
     if (lds <= kBottomLdsMax && L - l <= kBottomLevelsMax) {
       h.bottom = l;
       h.bottom_lds = lds;
+    } else if (l == 0) {
+      continue;
     }
     break;
   }
+  if (h.bottom == 0) h.lv[0].off_noise = take((size_t)(p.nu1 + p.nu2) * nc * h.lv[0].n * ts);
   h.wide_coarsest = h.bottom >= 0 && h.nc >= kWideCoarsest;
   if (h.nc > 0) {
     h.off_ainv = take((size_t)h.nc * h.nc * sizeof(double));
