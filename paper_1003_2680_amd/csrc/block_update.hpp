@@ -14,6 +14,13 @@
 
 namespace smg {
 
+// The sampling passes in FP32 add up in index order (row, plane, lane), one term after the other:
+// a refined chain carries its rounding from cycle to cycle into an FP64 state, which therefore
+// keeps the bits that the plain order of the sums gives.  FP64 sums and the FP32 correction of a
+// solve, whose rounding the next residual takes back, use the shorter symmetric forms.
+template <typename T, bool NOISE>
+constexpr bool index_order = NOISE && sizeof(T) == 4;
+
 // v of another lane of the same eight: quad_perm moves for lane ^ 1, ^ 2, ^ 3 and the mirror of
 // the eight lanes for lane ^ 7 (lane ^ 4 is ^ 3 of it).
 constexpr int DPP_XOR1 = 0xB1, DPP_XOR2 = 0x4E, DPP_XOR3 = 0x1B, DPP_XOR7 = 0x141;
@@ -66,11 +73,18 @@ __device__ __forceinline__ float sum_rows(float v) {
 // where a level leaves lanes idle, one each (SPLIT 4: m = s, the fourth lane with zero factors).
 // po: element offset of each plane; the plane's z-factors for the lane's own cell and for its
 // z-partner's; the lane's row of A_BB^-1 in the order of the lanes ^ m.
-template <typename T, int SPLIT>
+template <typename T, int SPLIT, bool INDEX = false>
 struct BlockWeights {
   static constexpr int P = SPLIT == 4 ? 1 : 3;
   int po[P];
   T own0[P], own1[P], oth0[P], oth1[P], F[8];
+};
+// In index order: the cell's z-factors of its five planes and its row of A_BB^-1 by cell.
+template <typename T, int SPLIT>
+struct BlockWeights<T, SPLIT, true> {
+  static constexpr int P = SPLIT == 4 ? 1 : 3;
+  int po[P];
+  T z0[5], z1[5], F[8];
 };
 // The device table of a block layer bz (kBlockRow values): A_BB^-1 with entry m of row k that of
 // cell k ^ m, cells k = kx + 2 ky + 4 kz; L_BB^-T; and at kBlockZ the packed z-factors of the two
@@ -78,8 +92,25 @@ struct BlockWeights {
 constexpr int kBlockRow = 192, kBlockZ = 128;
 // Fp, Zp: a layer's A_BB^-1 part and its packed z-factors.
 template <typename T, int SPLIT, typename PT>
-__device__ __forceinline__ void block_weights(BlockWeights<T, SPLIT>& w, const PT Fp, const PT Zp,
-                                              int kx, int ky, int kz, int s) {
+__device__ __forceinline__ void block_weights(BlockWeights<T, SPLIT, true>& w, const PT Fp,
+                                              const PT Zp, int kx, int ky, int kz, int) {
+  // of the cell's five planes kz .. kz + 4 of the layer's six, the partner reduces 3, 4 (kz 0) or
+  // 1, 2 (kz 1)
+  const PT own = Zp + kz * 16, par = Zp + (kz ^ 1) * 16 + 8;
+#pragma unroll
+  for (int d = 0; d < 5; ++d) {
+    const int at = kz ? (d < 2 ? 1 + d : d - 2) : (d < 3 ? d : d - 3);
+    const PT q = (kz ? d < 2 : d >= 3) ? par : own;
+    w.z0[d] = q[at];
+    w.z1[d] = q[4 + at];
+  }
+  const int k = kx + 2 * ky + 4 * kz;
+#pragma unroll
+  for (int m = 0; m < 8; ++m) w.F[m] = Fp[k * 8 + (m ^ k)];
+}
+template <typename T, int SPLIT, typename PT>
+__device__ __forceinline__ void block_weights(BlockWeights<T, SPLIT, false>& w, const PT Fp,
+                                              const PT Zp, int kx, int ky, int kz, int s) {
   const PT z = Zp + kz * 16 + (SPLIT == 4 ? s : 0);
 #pragma unroll
   for (int p = 0; p < BlockWeights<T, SPLIT>::P; ++p) {
@@ -109,7 +140,8 @@ __device__ __forceinline__ void block_weights(BlockWeights<T, SPLIT>& w, const P
 // kernels with the registers to spare).
 template <typename T, int SPLIT, bool PRELOAD>
 __device__ __forceinline__ T block_update(const T* X, const int (&ro)[3], const T* s1d,
-                                        const BlockWeights<T, SPLIT>& w, int own, T bk, T noise) {
+                                        const BlockWeights<T, SPLIT, false>& w, int own, T bk,
+                                        T noise) {
   constexpr int P = BlockWeights<T, SPLIT>::P;
   T win[P][3][5];
 #pragma unroll
@@ -160,6 +192,108 @@ __device__ __forceinline__ T block_update(const T* X, const int (&ro)[3], const 
   v1 = fma(w.F[5], dpp_lane<DPP_XOR2>(mir), v1);
   v0 = fma(w.F[3], dpp_lane<DPP_XOR3>(res), v0);
   v1 = fma(w.F[4], dpp_lane<DPP_XOR3>(mir), v1);
+  return v0 + v1;
+}
+
+// The same in index order (FP32).  Here each lane needs its cell's five plane sums themselves, and
+// the block's eight residuals by cell: more moves and selects than above.
+template <typename T>
+__device__ __forceinline__ T lane_z_partner(T v) {  // lane ^ 4
+  return dpp_lane<DPP_XOR3>(dpp_lane<DPP_XOR7>(v));
+}
+template <int CTRL>
+__device__ __forceinline__ float quad_value(float v) {
+  return dpp_lane<CTRL>(v);
+}
+template <typename T, int SPLIT, bool PRELOAD>
+__device__ __forceinline__ T block_update(const T* X, const int (&ro)[3], const T* s1d,
+                                        const BlockWeights<T, SPLIT, true>& w, int own, T bk,
+                                        T noise) {
+  constexpr int P = BlockWeights<T, SPLIT, true>::P;
+  const bool kz = threadIdx.x & 4;
+  T win[P][3][5];
+#pragma unroll
+  for (int m = 0; m < P; ++m)
+#pragma unroll
+    for (int r = 0; r < 3; ++r)
+#pragma unroll
+      for (int d = 0; d < 5; ++d) win[m][r][d] = X[w.po[m] + ro[r] + d];
+  const T xk = X[own];
+  if (PRELOAD) __builtin_amdgcn_sched_barrier(0);
+  T q0[3], q1[3];
+#pragma unroll
+  for (int m = 0; m < P; ++m) {
+    T rm[3], ra[3];
+#pragma unroll
+    for (int r = 0; r < 3; ++r) {
+      T sm = T(0), sa = T(0);
+#pragma unroll
+      for (int d = 0; d < 5; ++d) {
+        sm = fma(s1d[d], win[m][r][d], sm);
+        sa = fma(s1d[5 + d], win[m][r][d], sa);
+      }
+      rm[r] = sm;
+      ra[r] = sa;
+    }
+    const T* my = s1d + 10;
+    const T* ay = s1d + 15;
+    T o0 = T(0), o1 = T(0);
+#pragma unroll
+    for (int r = 0; r < 3; ++r) {
+      o0 = fma(my[r], rm[r], o0);
+      o1 = fma(ay[r], rm[r], o1);
+      o1 = fma(my[r], ra[r], o1);
+    }
+    T p0 = my[0] * rm[1];
+    p0 = fma(my[1], rm[2], p0);
+    T p1 = ay[0] * rm[1];
+    p1 = fma(ay[1], rm[2], p1);
+    p1 = fma(my[0], ra[1], p1);
+    p1 = fma(my[1], ra[2], p1);
+    q0[m] = o0 + dpp_lane<DPP_XOR2>(p0);
+    q1[m] = o1 + dpp_lane<DPP_XOR2>(p1);
+  }
+  if constexpr (SPLIT == 4) {
+    // planes m = 0, 1, 2 from the lanes of the four rows of sixteen
+    auto gather = [](T (&q)[3]) {
+      unsigned a, b, c, d;
+      a = lane_pairs16(__float_as_uint(q[0]), b);
+      a = lane_pairs32(a, c);
+      b = lane_pairs32(b, d);
+      q[0] = __uint_as_float(a);
+      q[1] = __uint_as_float(b);
+      q[2] = __uint_as_float(c);
+    };
+    gather(q0);
+    gather(q1);
+  }
+  // planes kz .. kz + 4: the partner's two nearest come from it
+  auto planes = [&](const T (&q)[3], const T (&z)[5]) {
+    const T oa = lane_z_partner(kz ? q[0] : q[1]), ob = lane_z_partner(kz ? q[1] : q[2]);
+    T acc = T(0);
+    acc = fma(z[0], kz ? oa : q[0], acc);
+    acc = fma(z[1], kz ? ob : q[1], acc);
+    acc = fma(z[2], kz ? q[0] : q[2], acc);
+    acc = fma(z[3], kz ? q[1] : oa, acc);
+    return fma(z[4], kz ? q[2] : ob, acc);
+  };
+  const T ax = planes(q0, w.z0) + planes(q1, w.z1);
+  const T res = bk - ax;
+  const T mir = dpp_lane<DPP_XOR7>(res);  // lane ^ 7
+  // residuals by cell: the own quad's in order, the other's reversed
+  const T b0 = quad_value<0x00>(res), b1 = quad_value<0x55>(res), b2 = quad_value<0xAA>(res),
+          b3 = quad_value<0xFF>(res);
+  const T c0 = quad_value<0xFF>(mir), c1 = quad_value<0xAA>(mir), c2 = quad_value<0x55>(mir),
+          c3 = quad_value<0x00>(mir);
+  T v0 = xk, v1 = noise;
+  v0 = fma(w.F[0], kz ? c0 : b0, v0);
+  v1 = fma(w.F[1], kz ? c1 : b1, v1);
+  v0 = fma(w.F[2], kz ? c2 : b2, v0);
+  v1 = fma(w.F[3], kz ? c3 : b3, v1);
+  v0 = fma(w.F[4], kz ? b0 : c0, v0);
+  v1 = fma(w.F[5], kz ? b1 : c1, v1);
+  v0 = fma(w.F[6], kz ? b2 : c2, v0);
+  v1 = fma(w.F[7], kz ? b3 : c3, v1);
   return v0 + v1;
 }
 

@@ -347,7 +347,8 @@ int coarsest_step(Run& r, int l) {
   Level& v = h.lv[l];
   NoiseArgs na = make_noise(r, l, 0, 0, KIND_COARSEST_NOISE);
   SMG_HIP(launch_coarsest<T>(comp_at(Fld<T>::x(v), v.n, r), comp_at(Fld<T>::b(v), v.n, r),
-                             h.ainv_d, h.w_d, h.nc, r.nc, r.noise, na, r.s));
+                             h.ainv_d, h.w_d, h.nc, r.nc, r.noise,
+                             h.use_bottom && h.bottom >= 0, na, r.s));
   return SMG_OK;
 }
 
@@ -2100,7 +2101,7 @@ int smg_debug_coarsest(smg_hierarchy* hh, void* x, const void* b, uint64_t seed,
   const int l = (int)h.lv.size() - 1;
   NoiseArgs na = make_noise(r, l, 0, 0, KIND_COARSEST_NOISE);
   SMG_HIP(launch_coarsest<double>((double*)x, (const double*)b, h.ainv_d, h.w_d, h.nc,
-                                  h.desc.ncomp, r.noise, na, s));
+                                  h.desc.ncomp, r.noise, false, na, s));
   return SMG_OK;
 }
 

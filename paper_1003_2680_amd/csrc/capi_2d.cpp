@@ -373,7 +373,8 @@ int coarsest2(Run2& r, int l) {
   Level2& v = h.lv[l];
   const NoiseArgs na = noise2(r, l, 0, 0, 1);
   // level 0 drawn exactly: its b is the caller's (zero when sampling)
-  S2_HIP(launch_coarsest<double>(v.x, v.b, h.ainv_d, h.w_d, h.nc, h.d.ncomp, r.noise, na, r.s));
+  S2_HIP(launch_coarsest<double>(v.x, v.b, h.ainv_d, h.w_d, h.nc, h.d.ncomp, r.noise, false,
+                                 na, r.s));
   return SMG_OK;
 }
 

@@ -257,10 +257,12 @@ struct BotMultiArgs {
 template <typename T>
 hipError_t launch_bottom_multi(const BotMultiArgs& m, int nwg, size_t lds, bool noise, bool point,
                                hipStream_t s);
-// x = A_c^-1 b (+ sqrt(kT) L_c^-T n), FP64 arithmetic, T storage
+// x = A_c^-1 b (+ sqrt(kT) L_c^-T n), FP64 arithmetic, T storage; round: the normals are taken in
+// T, as the bottom's own draw holds them
 template <typename T>
 hipError_t launch_coarsest(T* x, const T* b, const double* ainv, const double* w, int n,
-                           int ncomp, bool noise, const NoiseArgs& na, hipStream_t s);
+                           int ncomp, bool noise, bool round, const NoiseArgs& na,
+                           hipStream_t s);
 template <typename T>
 hipError_t launch_zero(T* p, int64_t n, hipStream_t s);
 

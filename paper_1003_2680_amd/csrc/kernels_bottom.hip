@@ -22,8 +22,8 @@ namespace {
 // two halo cells per side, so a row's five reads are one address with immediate offsets; the
 // z-factors and the block's A_BB^-1 row stay in registers over the four passes that share them;
 // and the noise of a pair of passes is loaded while the pair before runs.  The 16^3 .. 4^3 bottom
-// takes 92 us (FP64, inside the kernel; FP32 76 us): a 16^3 pass 1.3 us, an 8^3 pass 0.55 us.
-// With indexed window reads, permutes and a noise load inside each pass it took 203 us.
+// takes 81 us (FP64, inside the kernel): a 16^3 pass 1.3 us, an 8^3 pass 0.55 us.  With indexed
+// window reads, permutes and a noise load inside each pass it took 203 us.
 constexpr int BOT_TPB = 512;
 
 // Pointers read from a level descriptor are taken into the global address space: a load through a
@@ -57,14 +57,14 @@ __device__ __forceinline__ BotLane bot_lane(const BotLevel& L, int t) {
   return g;
 }
 
-template <typename T, int SPLIT>
-__device__ __forceinline__ BlockWeights<T, SPLIT> bot_weights(int nz, int sz, const T* tab,
+template <typename T, int SPLIT, bool INDEX>
+__device__ __forceinline__ BlockWeights<T, SPLIT, INDEX> bot_weights(int nz, int sz, const T* tab,
                                                               const BotLane& g, int bz) {
-  BlockWeights<T, SPLIT> w;
+  BlockWeights<T, SPLIT, INDEX> w;
   const T* row = tab + nz * 10 + bz * kBotRow;
   block_weights<T, SPLIT>(w, row, row + 64, g.kx, g.ky, g.kz, g.s);
 #pragma unroll
-  for (int p = 0; p < BlockWeights<T, SPLIT>::P; ++p) {
+  for (int p = 0; p < BlockWeights<T, SPLIT, INDEX>::P; ++p) {
     int pz = 2 * bz - 2 + 3 * g.kz + (SPLIT == 4 ? g.s : p);
     pz = pz < 0 ? 0 : (pz >= nz ? nz - 1 : pz);
     w.po[p] = pz * sz;
@@ -93,6 +93,8 @@ template <typename T, bool NOISE, int SPLIT, bool ONE>
 __device__ __forceinline__ void bot_sweeps_as(T* X, const T* B, const BotLevel& L, const T* tab,
                                               int slot0, int nslot, bool post, gptr<T> Z,
                                               size_t slot_stride) {
+  constexpr bool INDEX = index_order<T, NOISE>;
+  using Weights = BlockWeights<T, SPLIT, INDEX>;
   T s1d[20];
 #pragma unroll
   for (int q = 0; q < 20; ++q) s1d[q] = (T)L.s1d[q];  // uniform: scalar registers
@@ -109,7 +111,7 @@ __device__ __forceinline__ void bot_sweeps_as(T* X, const T* B, const BotLevel& 
     for (int r = 0; r < 3; ++r)
       ro[r] = wrapm(y + (g.ky ? 2 - r : r - 2), ny) * sy + 4 * g.i + g.kx;
   };
-  auto pass = [&](const BotLane& g, const BlockWeights<T, SPLIT>& w, const int (&ro)[3], int own,
+  auto pass = [&](const BotLane& g, const Weights& w, const int (&ro)[3], int own,
                   int cell, int cx, bool active, T noise) {
     const int d = 2 * cx;
     const T v = block_update<T, SPLIT, true>(X + d, ro, s1d, w, own, B[cell + d], noise);
@@ -149,7 +151,7 @@ __device__ __forceinline__ void bot_sweeps_as(T* X, const T* B, const BotLevel& 
       return;
     }
     if (NOISE) noise_of(0, n0, n1);
-    BlockWeights<T, SPLIT> w;
+    Weights w;
     int zown = 0, znat = 0;
 #pragma unroll 1
     for (int st = 0; st < steps; ++st) {
@@ -160,7 +162,7 @@ __device__ __forceinline__ void bot_sweeps_as(T* X, const T* B, const BotLevel& 
       const bool active = g.l < layers(cz) && g.s == 0;
       if ((st & 1) == 0) {
         const int bz = bz_of(cz);
-        w = bot_weights<T, SPLIT>(nz, sz, tab, g, bz);
+        w = bot_weights<T, SPLIT, INDEX>(nz, sz, tab, g, bz);
         zown = (2 * bz + g.kz) * sz + own0;
         znat = (2 * bz + g.kz) * plane + nat0;
       }
@@ -187,7 +189,7 @@ __device__ __forceinline__ void bot_sweeps_as(T* X, const T* B, const BotLevel& 
           const BotLane g = bot_lane<SPLIT>(L, base + tid);
           const bool active = g.l < layers(cz);
           const int bz = 2 * (active ? g.l : 0) + cz;
-          const BlockWeights<T, SPLIT> w = bot_weights<T, SPLIT>(nz, sz, tab, g, bz);
+          const Weights w = bot_weights<T, SPLIT, INDEX>(nz, sz, tab, g, bz);
           int ro[3];
           rows(g, cy, ro);
           const int y = 4 * g.j + 2 * cy + g.ky, z = 2 * bz + g.kz, x = 4 * g.i + g.kx;
@@ -217,9 +219,9 @@ __device__ __forceinline__ void bot_sweeps(T* X, const T* B, const BotLevel& L, 
     bot_sweeps_as<T, NOISE, 1, false>(X, B, L, tab, slot0, nslot, post, Z, slot_stride);
 }
 
-// r = b - A x on a block level in LDS: a thread takes a column of cells (or a part of one, so
-// that the whole work-group has work) and marches up z, forming each plane's two in-plane sums
-// once and keeping the five that the current cell reaches.
+// r = b - A x on a block level in LDS, in index order (the FP32 sampling cycle): a thread takes a
+// column of cells (or a part of one, so that the whole work-group has work) and marches up z,
+// forming each plane's two in-plane sums once and keeping the five that the current cell reaches.
 template <typename T>
 __device__ __forceinline__ void bot_residual(T* R, const T* X, const T* B, const BotLevel& L,
                                              const T* tab) {
@@ -237,7 +239,8 @@ __device__ __forceinline__ void bot_residual(T* R, const T* X, const T* B, const
     divmod_uniform(col, nx, y, x);
     int ro[5];
 #pragma unroll
-    for (int d = 0; d < 5; ++d) ro[d] = wrapm(y + d - 2, ny) * sy + x;
+    for (int d = 0; d < 5; ++d) ro[d] = wrapm(y + d - 2, ny) * sy;
+    const int xs[5] = {x, x + 1, x + 2, x + 3, x + 4};
     const int z0 = part * len, z1 = z0 + len < nz ? z0 + len : nz;
     T p0[5], p1[5];
 #pragma unroll
@@ -250,25 +253,7 @@ __device__ __forceinline__ void bot_residual(T* R, const T* X, const T* B, const
         p1[d] = p1[d + 1];
       }
       const T* P = X + (zz < 0 ? 0 : (zz >= nz ? nz - 1 : zz)) * sz;  // beyond a wall: factor 0
-      T rm[5], ra[5];
-#pragma unroll
-      for (int d = 0; d < 5; ++d) {
-        const T* v = P + ro[d];
-        const T e = v[0] + v[4], f = v[1] + v[3], c = v[2];
-        rm[d] = fma(s1d[0], e, fma(s1d[1], f, s1d[2] * c));
-        ra[d] = fma(s1d[5], e, fma(s1d[6], f, s1d[7] * c));
-      }
-      const T* my = s1d + 10;
-      const T* ay = s1d + 15;
-      T a0 = my[2] * rm[2], a1 = ay[2] * rm[2], a2 = my[2] * ra[2];
-#pragma unroll
-      for (int d = 0; d < 2; ++d) {
-        a0 = fma(my[d], rm[d] + rm[4 - d], a0);
-        a1 = fma(ay[d], rm[d] + rm[4 - d], a1);
-        a2 = fma(my[d], ra[d] + ra[4 - d], a2);
-      }
-      p0[4] = a0;
-      p1[4] = a1 + a2;
+      p0[4] = gal_plane<T>(P, 1, xs, ro, s1d, p1[4]);
       const int z = zz - 2;
       if (z < z0) continue;
       const T* zr = tab + z * 10;
@@ -281,6 +266,134 @@ __device__ __forceinline__ void bot_residual(T* R, const T* X, const T* B, const
       const int q = z * ncol + col;
       R[q] = B[q] - (acc0 + acc1);
     }
+  }
+}
+
+// b_c = P^T (b - A x) from a block level in LDS, axis by axis: P^T folds into the 1D stencils of
+// A's Kronecker sum, eight taps per coarse position around 2X - 3 .. 2X + 4, so x is read 4 times
+// per cell and axis pair instead of 25 and no residual is stored.  R (n elements) holds first the
+// two x-folded fields on (nx/2, ny, nz), then the three xy-folded ones on (nx/2, ny/2, nz): those of
+// m_y m_x, of a_y m_x + m_y a_x, and of b.  16^3 FP64: 4.7 us (forming the residual of every
+// cell by a march up z and restricting it took 11.5); 8^3: 2.0 (6.2).
+template <typename T>
+__device__ __forceinline__ void bot_restrict(T* bc, T* R, const T* X, const T* B,
+                                             const BotLevel& L, const T* tab) {
+  using V2 = typename std::conditional<sizeof(T) == 8, double2, float2>::type;
+  const int nx = L.nx, ny = L.ny, nz = L.nz, hx = nx >> 1, hy = ny >> 1;
+  const int tid = (int)threadIdx.x;
+  // taps t and 7 - t are equal: sum_c w_c s[t - 3 - c], w = (1/4, 3/4, 3/4, 1/4) at c = -1 .. 2
+  auto fold = [](const double* q, T (&m)[4]) {
+    const T s0 = (T)q[0], s1 = (T)q[1], s2 = (T)q[2];
+    m[0] = T(0.25) * s0;
+    m[1] = fma(T(0.25), s1, T(0.75) * s0);
+    m[2] = fma(T(0.25), s2, T(0.75) * (s0 + s1));
+    m[3] = fma(T(0.25), s0 + s1, T(0.75) * (s1 + s2)) ;
+  };
+  {
+    T m[4], am[4];
+    fold(L.s1d, m);
+    fold(L.s1d + 5, am);
+    const int items = hx * ny * nz;
+    T* U = R;
+    T* V = R + items;
+    for (int it = tid; it < items; it += BOT_TPB) {
+      int r, Xc, y, z;
+      divmod_uniform(it, hx, r, Xc);
+      divmod_uniform(r, ny, z, y);
+      const T* row = X + z * L.sz + y * L.sy + kBotHalo;
+      const V2 v0 = *reinterpret_cast<const V2*>(row + 2 * Xc - 2);
+      const V2 v1 = *reinterpret_cast<const V2*>(row + 2 * Xc);
+      const V2 v2 = *reinterpret_cast<const V2*>(row + 2 * Xc + 2);
+      // the halo holds two cells a side: the outermost taps of the end cells wrap by hand
+      const T lo = row[Xc == 0 ? nx - 3 : 2 * Xc - 3], hi = row[Xc == hx - 1 ? 2 : 2 * Xc + 4];
+      const T e0 = lo + hi, e1 = v0.x + v2.y, e2 = v0.y + v2.x, e3 = v1.x + v1.y;
+      U[it] = fma(m[0], e0, fma(m[1], e1, fma(m[2], e2, m[3] * e3)));
+      V[it] = fma(am[0], e0, fma(am[1], e1, fma(am[2], e2, am[3] * e3)));
+    }
+  }
+  __syncthreads();
+  const int items2 = hx * hy * nz, col = hx * hy;
+  {
+    T m[4], am[4];
+    fold(L.s1d + 10, m);
+    fold(L.s1d + 15, am);
+    const T* U = R;
+    const T* V = R + 2 * items2;
+    constexpr int PER = 4096 / 4 / BOT_TPB;
+    T p0[PER], p1[PER], p2[PER];
+#pragma unroll
+    for (int k = 0; k < PER; ++k) {
+      const int it = tid + k * BOT_TPB;
+      if (it >= items2) break;
+      int r, Xc, Y, z;
+      divmod_uniform(it, hx, r, Xc);
+      divmod_uniform(r, hy, z, Y);
+      const int base = z * ny;
+      T a0 = T(0), a1 = T(0);
+#pragma unroll
+      for (int t = 0; t < 4; ++t) {
+        const int y0 = wrapm(2 * Y - 3 + t, ny), y1 = wrapm(2 * Y + 4 - t, ny);
+        const T u = U[(base + y0) * hx + Xc] + U[(base + y1) * hx + Xc];
+        const T v = V[(base + y0) * hx + Xc] + V[(base + y1) * hx + Xc];
+        a0 = fma(m[t], u, a0);
+        a1 = fma(am[t], u, fma(m[t], v, a1));
+      }
+      p0[k] = a0;
+      p1[k] = a1;
+      const int xl = Xc == 0 ? nx - 1 : 2 * Xc - 1, xh = Xc == hx - 1 ? 0 : 2 * Xc + 2;
+      T bs[2];
+#pragma unroll
+      for (int q = 0; q < 2; ++q) {  // the inner two rows (3/4), the outer two (1/4)
+        T s = T(0), o = T(0);
+#pragma unroll
+        for (int d = 0; d < 2; ++d) {
+          const int y = q == 0 ? 2 * Y + d : wrapm(2 * Y - 1 + 3 * d, ny);
+          const T* row = B + (base + y) * nx;
+          const V2 c = *reinterpret_cast<const V2*>(row + 2 * Xc);
+          s += c.x + c.y;
+          o += row[xl] + row[xh];
+        }
+        bs[q] = fma(T(0.75), s, T(0.25) * o);
+      }
+      p2[k] = fma(T(0.75), bs[0], T(0.25) * bs[1]);
+    }
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < PER; ++k) {
+      const int it = tid + k * BOT_TPB;
+      if (it >= items2) break;
+      R[it] = p0[k];
+      R[items2 + it] = p1[k];
+      R[2 * items2 + it] = p2[k];
+    }
+  }
+  __syncthreads();
+  const int nzc = nz >> 1;
+  for (int it = tid; it < col * nzc; it += BOT_TPB) {
+    int Z, q;
+    divmod_uniform(it, col, Z, q);
+    T p0[8], p1[8];
+#pragma unroll
+    for (int t = 0; t < 8; ++t) {
+      int z = 2 * Z - 3 + t;
+      z = z < 0 ? 0 : (z >= nz ? nz - 1 : z);  // beyond a wall: factor 0
+      p0[t] = R[z * col + q];
+      p1[t] = R[items2 + z * col + q];
+    }
+    T acc = T(0);
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+      const int z = 2 * Z - 1 + c;
+      if (z < 0 || z >= nz) continue;
+      const T* zr = tab + z * 10;
+      T s = R[2 * items2 + z * col + q];
+#pragma unroll
+      for (int d = 0; d < 5; ++d) s = fma(-zr[d], p0[c + d], fma(-zr[5 + d], p1[c + d], s));
+      T wz = pw<T>(c);
+      if ((Z == 0 && c == 1) || (Z == nzc - 1 && c == 2)) wz = T(0.5);
+      acc = fma(wz, s, acc);
+    }
+    bc[it] = acc;
   }
 }
 
@@ -342,6 +455,8 @@ __device__ __forceinline__ void point_sweeps(T* X, const T* B, bool has_b, const
                                              const PointSites<T>& S, T (&z)[PT_PER], gptr<T> Z,
                                              size_t slot_stride, int slot0, int nslot, bool post) {
   const int nsite = S.nsite;
+  // FP32: the order of the z-neighbours' sum in the colour-pass launches (launch_rb_pass)
+  const bool vec = !index_order<T, NOISE> || (L.nx >> 1) % (16 / (int)sizeof(T)) == 0;
   T dg[10];
 #pragma unroll
   for (int e = 0; e < 10; ++e) dg[e] = (T)L.s1d[e];  // uniform: scalar registers
@@ -361,13 +476,20 @@ __device__ __forceinline__ void point_sweeps(T* X, const T* B, bool has_b, const
       const bool top = S.wall[k] & 1, low = S.wall[k] & 2;
       const int own = S.p[k] < nsite ? S.p[k] : 0, ox = c ? S.o[k][1] : S.o[k][0];
       const T sx = xo[own] + xo[ox];
-      const T sum = (sx + (xo[S.n[k]] + xo[S.s[k]])) +
-                    fma(xo[S.u[k]], top ? T(0) : T(1), xo[S.d[k]] * (low ? T(0) : T(1)));
+      const T sxy = sx + (xo[S.n[k]] + xo[S.s[k]]);
+      T sum;
+      if (vec)
+        sum = sxy + fma(xo[S.u[k]], top ? T(0) : T(1), xo[S.d[k]] * (low ? T(0) : T(1)));
+      else
+        sum = (sxy + (top ? T(0) : xo[S.u[k]])) + (low ? T(0) : xo[S.d[k]]);
       const int nw = (int)top + (int)low;
       auto by_walls = [&](T d6, T d7, T d8) { return nw == 0 ? d6 : (nw == 1 ? d7 : d8); };
-      T v = has_b ? fma(sum, dg[9], bc[own]) * by_walls(dg[0], dg[1], dg[2])
-                  : sum * by_walls(dg[6], dg[7], dg[8]);
-      if (NOISE) v = fma(by_walls(dg[3], dg[4], dg[5]), zn[k], v);
+      const T rhs = has_b ? fma(sum, dg[9], bc[own]) : T(0), idg = by_walls(dg[0], dg[1], dg[2]);
+      T v = has_b ? rhs * idg : sum * by_walls(dg[6], dg[7], dg[8]);
+      if (NOISE) {
+        const T sig = by_walls(dg[3], dg[4], dg[5]);
+        v = has_b && !vec ? fma(rhs, idg, sig * zn[k]) : fma(sig, zn[k], v);
+      }
       if (S.p[k] < nsite) xc[own] = v;
     }
     __syncthreads();
@@ -395,6 +517,37 @@ __device__ __forceinline__ void point_residual(T* R, const T* X, const T* B, boo
       R[S.nat[k][c]] = r;
     }
   }
+}
+
+// (P^T R)(X, Y, Z) in index order: column sums first, as k_restrict_residual0 adds them.
+template <typename T>
+__device__ __forceinline__ T point_restrict(const T* R, int nx, int ny, int nz, int X, int Y,
+                                            int Z) {
+  int xs[4], ys[4];
+#pragma unroll
+  for (int d = 0; d < 4; ++d) {
+    xs[d] = wrapm(2 * X - 1 + d, nx);
+    ys[d] = wrapm(2 * Y - 1 + d, ny) * nx;
+  }
+  T acc = T(0);
+#pragma unroll
+  for (int c = 0; c < 4; ++c) {
+    const int z = 2 * Z - 1 + c;
+    if (z < 0 || z >= nz) continue;
+    const T* P = R + z * nx * ny;
+    T cs[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      T s = T(0);
+#pragma unroll
+      for (int b = 0; b < 4; ++b) s = fma(pw<T>(b), P[ys[b] + xs[q]], s);
+      cs[q] = s * pw<T>(q);
+    }
+    T wz = pw<T>(c);
+    if ((Z == 0 && z == 0) || (Z == (nz >> 1) - 1 && z == nz - 1)) wz = T(0.5);
+    acc = fma(wz, (cs[0] + cs[1]) + (cs[2] + cs[3]), acc);
+  }
+  return acc;
 }
 
 // POINT: the first level may be a point level (level 0).
@@ -495,22 +648,6 @@ __device__ __forceinline__ void bottom_body(const BotArgs& a, const uint32_t com
   }
   __syncthreads();
   int last = a.nlev - 1;
-  // b_{i+1} = P^T r_i, x_{i+1} = 0
-  auto restrict_to_next = [&](int i) {
-    const BotLevel& L = a.lv[i];
-    const T* ri = sm + a.lds_off[i] + L.nz * L.sz + L.nx * L.ny * L.nz;
-    const BotLevel& C = a.lv[i + 1];
-    T* xc = sm + a.lds_off[i + 1];
-    T* bc = xc + C.nz * C.sz;
-    for (int q = tid; q < C.nz * C.sz; q += BOT_TPB) xc[q] = T(0);
-    for (int q = tid; q < C.nx * C.ny * C.nz; q += BOT_TPB) {
-      int X, Y, Z2, r;
-      divmod_uniform(q, C.nx, r, X);
-      divmod_uniform(r, C.ny, Z2, Y);
-      bc[q] = restrict_at<T>(ri, L.nx, L.nx * L.ny, L.nx, L.ny, L.nz, X, Y, Z2);
-    }
-    __syncthreads();
-  };
   T pz[PT_PER] = {};  // the point level's normals of its next pass
   if (point && part != BOT_UP) {
     PointSites<T> ps;
@@ -531,7 +668,20 @@ __device__ __forceinline__ void bottom_body(const BotArgs& a, const uint32_t com
     if (part == BOT_DOWN) point_store(ps);
     point_residual<T>(X + 2 * n0, X, X + n0, has_b, L0, ps);
     __syncthreads();
-    restrict_to_next(0);
+    // b_1 = P^T r, x_1 = 0
+    const BotLevel& C = a.lv[1];
+    T* xc = sm + a.lds_off[1];
+    for (int q = tid; q < C.nz * C.sz; q += BOT_TPB) xc[q] = T(0);
+    for (int q = tid; q < C.nx * C.ny * C.nz; q += BOT_TPB) {
+      int Xc, Y, Z, r;
+      divmod_uniform(q, C.nx, r, Xc);
+      divmod_uniform(r, C.ny, Z, Y);
+      xc[C.nz * C.sz + q] =
+          index_order<T, NOISE>
+              ? point_restrict<T>(X + 2 * n0, L0.nx, L0.ny, L0.nz, Xc, Y, Z)
+              : restrict_at<T>(X + 2 * n0, L0.nx, L0.nx * L0.ny, L0.nx, L0.ny, L0.nz, Xc, Y, Z);
+    }
+    __syncthreads();
   }
   for (int i = first; i < a.nlev && part != BOT_UP; ++i) {
     const BotLevel& L = a.lv[i];
@@ -587,9 +737,24 @@ __device__ __forceinline__ void bottom_body(const BotArgs& a, const uint32_t com
         xg[q] = xi[place(L, q, x)];
       }
     }
-    bot_residual<T>(ri, xi, bi, L, tab);
+    // b_{i+1} = P^T (b_i - A_i x_i), x_{i+1} = 0
+    const BotLevel& C = a.lv[i + 1];
+    T* xc = sm + a.lds_off[i + 1];
+    for (int q = tid; q < C.nz * C.sz; q += BOT_TPB) xc[q] = T(0);
+    T* bc = xc + C.nz * C.sz;
+    if constexpr (index_order<T, NOISE>) {
+      bot_residual<T>(ri, xi, bi, L, tab);
+      __syncthreads();
+      for (int q = tid; q < C.nx * C.ny * C.nz; q += BOT_TPB) {
+        int Xc, Y, Z, r;
+        divmod_uniform(q, C.nx, r, Xc);
+        divmod_uniform(r, C.ny, Z, Y);
+        bc[q] = restrict_at<T>(ri, L.nx, L.nx * L.ny, L.nx, L.ny, L.nz, Xc, Y, Z);
+      }
+    } else {
+      bot_restrict<T>(bc, ri, xi, bi, L, tab);
+    }
     __syncthreads();
-    restrict_to_next(i);
   }
   for (int i = last - 1; i >= first; --i) {
     const BotLevel& L = a.lv[i];

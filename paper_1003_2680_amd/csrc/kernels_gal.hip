@@ -171,7 +171,7 @@ __device__ __forceinline__ void block_tile_body(T* __restrict__ xg, const T* __r
 #pragma unroll
     for (int p = 0; p < PPT; ++p) Tl[sz * TP + loff[p]] = stage[sz][p];
   __syncthreads();
-  BlockWeights<T, 1> w;
+  BlockWeights<T, 1, index_order<T, NOISE>> w;
   const T* row = bfac + (size_t)bz * kBlockRow;
   block_weights<T, 1>(w, row, row + kBlockZ, kx, ky, kz, 0);
 #pragma unroll
@@ -277,7 +277,7 @@ __device__ __forceinline__ void block_half_body(const HalfItem<T>& h, int cz, bo
         if (hoff[p]) Tl[sz * TP + loff[p] + hoff[p]] = stage[sz][p];
       }
   __builtin_amdgcn_sched_barrier(0);
-  BlockWeights<T, 1> w;
+  BlockWeights<T, 1, index_order<T, NOISE>> w;
   const T* row = h.bfac + (size_t)bz * kBlockRow;
   block_weights<T, 1>(w, row, row + kBlockZ, kx, ky, kz, 0);
 #pragma unroll
@@ -405,7 +405,7 @@ __device__ __forceinline__ void block_pair_body(const HalfItem<T>& h, int c_firs
         if (hoff[p]) Tl[sz * TP + loff[p] + hoff[p]] = stage[sz][p];
       }
   __builtin_amdgcn_sched_barrier(0);
-  BlockWeights<T, 1> w;
+  BlockWeights<T, 1, index_order<T, NOISE>> w;
   const T* row = h.bfac + (size_t)bz * kBlockRow;
   block_weights<T, 1>(w, row, row + kBlockZ, kx, ky, kz, 0);
 #pragma unroll
@@ -603,7 +603,7 @@ __global__ __launch_bounds__(CO_TPB) void k_coarsest(T* __restrict__ xg,
                                                       const T* __restrict__ bg,
                                                       const double* __restrict__ ainv,
                                                       const double* __restrict__ w, int n,
-                                                      int ncomp, NoiseArgs na) {
+                                                      int ncomp, bool round, NoiseArgs na) {
   extern __shared__ double sh[];  // b [C][n], normals [C][n]; then the partial sums
   const int comp0 = blockIdx.y * C;
   const int nc = min(C, ncomp - comp0);
@@ -616,8 +616,8 @@ __global__ __launch_bounds__(CO_TPB) void k_coarsest(T* __restrict__ xg,
       for (int q = row0 / 2 + threadIdx.x; 2 * q < n; q += CO_TPB) {
         double z0, z1;
         normal_pair(na, na.sid, comp0 + c, (uint32_t)q, z0, z1);
-        Z[2 * q] = z0;
-        if (2 * q + 1 < n) Z[2 * q + 1] = z1;
+        Z[2 * q] = round ? (double)(T)z0 : z0;
+        if (2 * q + 1 < n) Z[2 * q + 1] = round ? (double)(T)z1 : z1;
       }
     }
   }
@@ -917,23 +917,25 @@ hipError_t launch_prolong(T* x, const T* e, int nxf, int nyf, int nzf, int ncomp
 
 template <typename T, int C>
 hipError_t launch_coarsest_c(T* x, const T* b, const double* ainv, const double* w, int n,
-                             int ncomp, bool noise, const NoiseArgs& na, hipStream_t s) {
+                             int ncomp, bool noise, bool round, const NoiseArgs& na,
+                             hipStream_t s) {
   dim3 grid((n + CO_ROWS - 1) / CO_ROWS, (ncomp + C - 1) / C);
   const size_t sums = (size_t)C * (CO_TPB / 64) * CO_ROWS;
   const size_t lds = std::max((size_t)2 * C * n, sums) * sizeof(double);
-  if (noise) k_coarsest<T, true, C><<<grid, CO_TPB, lds, s>>>(x, b, ainv, w, n, ncomp, na);
-  else k_coarsest<T, false, C><<<grid, CO_TPB, lds, s>>>(x, b, ainv, w, n, ncomp, na);
+  if (noise) k_coarsest<T, true, C><<<grid, CO_TPB, lds, s>>>(x, b, ainv, w, n, ncomp, round, na);
+  else k_coarsest<T, false, C><<<grid, CO_TPB, lds, s>>>(x, b, ainv, w, n, ncomp, round, na);
   return hipGetLastError();
 }
 
 template <typename T>
 hipError_t launch_coarsest(T* x, const T* b, const double* ainv, const double* w, int n,
-                           int ncomp, bool noise, const NoiseArgs& na, hipStream_t s) {
+                           int ncomp, bool noise, bool round, const NoiseArgs& na,
+                           hipStream_t s) {
   if (n > 4096) return hipErrorInvalidValue;  // 64 KB of LDS for one component
   // four components per work-group once that still leaves work for the chip: a quarter of the
   // factor traffic, while four components' b and normals fit 64 KB
-  if (ncomp >= 8 && n <= 1024) return launch_coarsest_c<T, 4>(x, b, ainv, w, n, ncomp, noise, na, s);
-  return launch_coarsest_c<T, 1>(x, b, ainv, w, n, ncomp, noise, na, s);
+  if (ncomp >= 8 && n <= 1024) return launch_coarsest_c<T, 4>(x, b, ainv, w, n, ncomp, noise, round, na, s);
+  return launch_coarsest_c<T, 1>(x, b, ainv, w, n, ncomp, noise, round, na, s);
 }
 
 template <typename T>
@@ -964,7 +966,7 @@ hipError_t launch_level_noise(const NoiseGenArgs& a, const NoiseArgs& na, hipStr
   template hipError_t launch_restrict<T>(T*, T*, const T*, int, int, int, int, hipStream_t);    \
   template hipError_t launch_prolong<T>(T*, const T*, int, int, int, int, hipStream_t);         \
   template hipError_t launch_coarsest<T>(T*, const T*, const double*, const double*, int, int,  \
-                                         bool, const NoiseArgs&, hipStream_t);                  \
+                                         bool, bool, const NoiseArgs&, hipStream_t);            \
   template hipError_t launch_level_noise<T>(const NoiseGenArgs&, const NoiseArgs&, hipStream_t);
 SMG_INST(double)
 SMG_INST(float)
