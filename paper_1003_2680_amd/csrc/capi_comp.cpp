@@ -931,15 +931,29 @@ template <typename T>
 int comp_class_pass(const CRun& r, int cls, int slot, T* xc, T* xf, const T* bc, const T* bf) {
   Composite& C = *r.c;
   const NoiseArgs na = comp_noise(C, r.seed, r.cycle, 0, slot, cls, KIND_COMP);
-  if (cls < 2) {
-    CMP_HIP(launch_comp_coarse_pass<T>(xc, bc, xf, C.g, cls, r.noise, na, r.s));
-  } else if (cls < 4) {
-    CMP_HIP(launch_comp_fine_pass<T>(xf, bf, C.g, cls - 2, r.noise, na, r.s));
+  if (cls < 4) {
+    CMP_HIP(launch_comp_colour_pass<T>(xc, xf, bc, bf, C.g, cls & 1, cls < 2 ? 1 : 2, r.noise, na,
+                                       na.sid, r.s));
   } else {
     const int p = cls - 4;
     CMP_HIP(launch_comp_layer_pass<T>(xf, bf, xc, C.g, C.layer_d + C.layer_off[p],
                                       C.layer_off[p + 1] - C.layer_off[p], r.noise, na, r.s));
   }
+  return SMG_OK;
+}
+
+// One composite sweep: classes 0 .. 11, the coarse and the fine class of a colour in one launch.
+template <typename T>
+int comp_sweep(const CRun& r, int slot, T* xc, T* xf, const T* bc, const T* bf) {
+  Composite& C = *r.c;
+  for (int colour = 0; colour < 2; ++colour) {
+    const NoiseArgs na = comp_noise(C, r.seed, r.cycle, 0, slot, colour, KIND_COMP);
+    const uint32_t sid_fine = comp_noise(C, r.seed, r.cycle, 0, slot, 2 + colour, KIND_COMP).sid;
+    CMP_HIP(launch_comp_colour_pass<T>(xc, xf, bc, bf, C.g, colour, 3, r.noise, na, sid_fine,
+                                       r.s));
+  }
+  for (int cls = 4; cls < 12; ++cls)
+    if (int rc = comp_class_pass<T>(r, cls, slot, xc, xf, bc, bf)) return rc;
   return SMG_OK;
 }
 
@@ -990,8 +1004,7 @@ int fac_cycle(const CRun& r, T* xc, T* xf, const T* bc, const T* bf, T* rf) {
     CMP_HIP(launch_comp_prolong<T>(xc, xf, LvF<T>::x(L0), C.g, r.s));
   }
   for (int s = 0; s < C.nu; ++s)
-    for (int cls = 0; cls < 12; ++cls)
-      if (int rc = comp_class_pass<T>(r, cls, s, xc, xf, bc, bf)) return rc;
+    if (int rc = comp_sweep<T>(r, s, xc, xf, bc, bf)) return rc;
   return SMG_OK;
 }
 
@@ -1003,11 +1016,7 @@ int run_cycle(const CRun& r, double* xc, double* xf, const double* bc, const dou
   if (C.prec == SMG_FP64) return fac_cycle<double>(r, xc, xf, bc, bf, C.rf);
   const int64_t nbase = (int64_t)C.g.nx * C.g.ny * C.g.nz;
   const int64_t nf = (int64_t)C.g.fx * C.g.fy * C.g.fz;
-  CMP_HIP(launch_comp_residual<double>(C.rc, C.rf, xc, xf, bc, bf, C.g, r.s));
-  CMP_HIP(launch_cast(C.r32c, 1, C.rc, nbase, r.s));
-  CMP_HIP(launch_cast(C.r32f, 1, C.rf, nf, r.s));
-  CMP_HIP(launch_zero<float>(C.e32c, nbase, r.s));
-  CMP_HIP(launch_zero<float>(C.e32f, nf, r.s));
+  CMP_HIP(launch_comp_bridge(C.r32c, C.r32f, C.e32c, C.e32f, xc, xf, bc, bf, C.g, r.s));
   if (int rc = fac_cycle<float>(r, C.e32c, C.e32f, C.r32c, C.r32f, C.rf32)) return rc;
   CMP_HIP(launch_refine_update(xc, C.e32c, nbase, r.s));
   CMP_HIP(launch_refine_update(xf, C.e32f, nf, r.s));
@@ -1037,14 +1046,11 @@ int comp_solve(Composite& C, const double* fc, const double* ff, double* uc, dou
   CMP_HIP(launch_zero<double>(uc, nbase, s));
   CMP_HIP(launch_zero<double>(uf, nf, s));
   auto resnorm = [&](double& out) -> int {
-    CMP_HIP(launch_comp_residual(C.rc, C.rf, (const double*)uc, (const double*)uf, fc, ff,
-                                 C.g, s));
-    CMP_HIP(launch_sumsq(C.norm, C.part, C.rc, nbase, 1, s));
-    CMP_HIP(launch_sumsq(C.norm + 1, C.part, C.rf, nf, 1, s));
-    double hn[2];
-    CMP_HIP(hipMemcpyAsync(hn, C.norm, 16, hipMemcpyDeviceToHost, s));
+    CMP_HIP(launch_comp_residual_norm(C.norm, C.part, uc, uf, fc, ff, C.g, s));
+    double hn;
+    CMP_HIP(hipMemcpyAsync(&hn, C.norm, sizeof(hn), hipMemcpyDeviceToHost, s));
     CMP_HIP(hipStreamSynchronize(s));
-    out = std::sqrt(hn[0] + hn[1]);
+    out = std::sqrt(hn);
     return SMG_OK;
   };
   double f0, rn, prev;

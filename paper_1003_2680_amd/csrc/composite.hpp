@@ -69,20 +69,28 @@ struct GStencilT {
 // Point heat bath of one class of the composite sweep (x_i = (b_i - sum_j A_ij x_j)/A_ii +
 // sqrt(kT/A_ii) n_i), b null = 0.  Classes: coarse cells of parity `colour`; fine cells off the
 // interface layer of parity `colour`; the listed layer cells (one parity class per list).
+// launch_comp_colour_pass: which & 1 the coarse class, which & 2 the fine one, together in one launch
+// (na: the coarse class's streams; sid_fine: the fine class's stream).
 template <typename T>
-hipError_t launch_comp_coarse_pass(T* xc, const T* bc, const T* xf, const CompGeom& g, int colour,
-                                   bool noise, const NoiseArgs& na, hipStream_t s);
-template <typename T>
-hipError_t launch_comp_fine_pass(T* xf, const T* bf, const CompGeom& g, int colour, bool noise,
-                                 const NoiseArgs& na, hipStream_t s);
+hipError_t launch_comp_colour_pass(T* xc, T* xf, const T* bc, const T* bf, const CompGeom& g,
+                                   int colour, int which, bool noise, const NoiseArgs& na,
+                                   uint32_t sid_fine, hipStream_t s);
 template <typename T>
 hipError_t launch_comp_layer_pass(T* xf, const T* bf, const T* xc, const CompGeom& g,
                                   const int32_t* cells, int count, bool noise, const NoiseArgs& na,
                                   hipStream_t s);
 // rc = bc - (A x)_coarse on every base cell (covered cells: 0), rf = bf - (A x)_fine
-template <typename T>
-hipError_t launch_comp_residual(T* rc, T* rf, const T* xc, const T* xf, const T* bc, const T* bf,
-                                const CompGeom& g, hipStream_t s);
+hipError_t launch_comp_residual(double* rc, double* rf, const double* xc, const double* xf,
+                                const double* bc, const double* bf, const CompGeom& g,
+                                hipStream_t s);
+// the same rounded to float, and (ec, ef) = 0
+hipError_t launch_comp_bridge(float* rc, float* rf, float* ec, float* ef, const double* xc,
+                              const double* xf, const double* bc, const double* bf,
+                              const CompGeom& g, hipStream_t s);
+// out[0] = ||(bc, bf) - A (xc, xf)||^2 (fixed order); part: a double per 1024 base or fine cells
+hipError_t launch_comp_residual_norm(double* out, double* part, const double* xc, const double* xf,
+                                     const double* bc, const double* bf, const CompGeom& g,
+                                     hipStream_t s);
 // b0 = P^T (rc, rf) over the base grid and x0 = 0 (P: identity on coarse cells, trilinear
 // onto fine cells)
 template <typename T>

@@ -7,6 +7,7 @@
 // coarsest draw stay FP64).
 #include "composite.hpp"
 #include "device_common.hpp"
+#include "kernels.hpp"
 
 namespace smg {
 namespace {
@@ -228,12 +229,10 @@ __device__ __forceinline__ void fine_row(const T* __restrict__ xf, const T* __re
 // index halved, h = jx + (nx/2) row with x = 2 jx + ((y+z+colour) & 1); thread t takes the
 // sites 2t and 2t + 1, the two normals of Philox call t.
 template <typename T, bool NOISE>
-__global__ __launch_bounds__(TPB) void k_comp_coarse_pass(T* __restrict__ xc,
-                                                          const T* __restrict__ bc,
-                                                          const T* __restrict__ xf, CompGeom g,
-                                                          int colour, NoiseArgs na) {
+__device__ __forceinline__ void coarse_class(T* __restrict__ xc, const T* __restrict__ bc,
+                                             const T* __restrict__ xf, const CompGeom& g,
+                                             int colour, const NoiseArgs& na, uint32_t t) {
   const int hx = g.nx >> 1;
-  const uint32_t t = blockIdx.x * TPB + threadIdx.x;
   if (2 * t >= (uint32_t)hx * g.ny * g.nz) return;  // hx ny nz is even (ny is)
   T z[2] = {T(0), T(0)};
   if (NOISE) normal_pair_t<T>(na, na.sid, 0u, t, z[0], z[1]);
@@ -299,11 +298,10 @@ __device__ __forceinline__ void fine_update(T* __restrict__ xf, const T* __restr
 // Fine class 2 + colour off the interface layer: noise sites as for the coarse classes (the
 // box index halved), thread t the sites 2t and 2t + 1 of Philox call t.
 template <typename T, bool NOISE>
-__global__ __launch_bounds__(TPB) void k_comp_fine_pass(T* __restrict__ xf,
-                                                        const T* __restrict__ bf, CompGeom g,
-                                                        int colour, NoiseArgs na) {
+__device__ __forceinline__ void fine_class(T* __restrict__ xf, const T* __restrict__ bf,
+                                           const CompGeom& g, int colour, const NoiseArgs& na,
+                                           uint32_t t) {
   const int hx = g.fx >> 1;
-  const uint32_t t = blockIdx.x * TPB + threadIdx.x;
   if (2 * t >= (uint32_t)hx * g.fy * g.fz) return;  // hx fy fz is even (fy is)
   T z[2] = {T(0), T(0)};
   if (NOISE) normal_pair_t<T>(na, na.sid, 0u, t, z[0], z[1]);
@@ -317,6 +315,24 @@ __global__ __launch_bounds__(TPB) void k_comp_fine_pass(T* __restrict__ xf,
     if (on_layer(g, i, j, k)) continue;
     // off the layer every neighbour is a fine cell or a wall: the coarse field is never read
     fine_update<T, NOISE>(xf, bf, nullptr, g, i, j, k, na, z[q]);
+  }
+}
+
+// Coarse class `colour` (the first `coarse_wg` work-groups) and fine class 2 + colour (the rest).
+// The two touch different fields and neither reads what the other writes: a coarse row reaches
+// only fine cells on the interface layer, a fine row off the layer no coarse cell.  So classes 0
+// and 2 share a launch, as do 1 and 3 (on small grids a pass is all launch latency, about 4 us).
+template <typename T, bool NOISE>
+__global__ __launch_bounds__(TPB) void k_comp_colour_pass(T* __restrict__ xc, T* __restrict__ xf,
+                                                          const T* __restrict__ bc,
+                                                          const T* __restrict__ bf, CompGeom g,
+                                                          int colour, uint32_t coarse_wg,
+                                                          NoiseArgs nac, uint32_t sid_fine) {
+  if (blockIdx.x < coarse_wg) {
+    coarse_class<T, NOISE>(xc, bc, xf, g, colour, nac, blockIdx.x * TPB + threadIdx.x);
+  } else {
+    nac.sid = sid_fine;
+    fine_class<T, NOISE>(xf, bf, g, colour, nac, (blockIdx.x - coarse_wg) * TPB + threadIdx.x);
   }
 }
 
@@ -335,13 +351,10 @@ __global__ __launch_bounds__(TPB) void k_comp_layer_pass(T* __restrict__ xf,
                         NOISE ? normal_at<T>(na, (uint32_t)site) : T(0));
 }
 
+// b - A x at base cell t (covered cells: 0) and at fine cell t.
 template <typename T>
-__global__ __launch_bounds__(TPB) void k_comp_res_coarse(T* __restrict__ rc,
-                                                         const T* __restrict__ xc,
-                                                         const T* __restrict__ xf,
-                                                         const T* __restrict__ bc, CompGeom g) {
-  const uint32_t t = blockIdx.x * TPB + threadIdx.x;
-  if (t >= (uint32_t)g.nx * g.ny * g.nz) return;
+__device__ __forceinline__ T res_coarse(const T* __restrict__ xc, const T* __restrict__ xf,
+                                        const T* __restrict__ bc, const CompGeom& g, uint32_t t) {
   int x, row, y, z;
   divmod_uniform((int)t, g.nx, row, x);
   divmod_uniform(row, g.ny, z, y);
@@ -350,12 +363,20 @@ __global__ __launch_bounds__(TPB) void k_comp_res_coarse(T* __restrict__ rc,
     far_coarse_row<T>(xc, g, x, row, y + 1 == g.ny ? row + 1 - g.ny : row + 1,
                       y == 0 ? row - 1 + g.ny : row - 1, z == 0, z == g.nz - 1, diag, off);
   } else if (covered(g, x, y, z)) {
-    rc[t] = T(0);
-    return;
+    return T(0);
   } else {
     coarse_row<T>(xc, xf, g, x, y, z, diag, off);
   }
-  rc[t] = (bc ? bc[t] : T(0)) - (diag * xc[t] - off) * (T)g.ih2;
+  return (bc ? bc[t] : T(0)) - (diag * xc[t] - off) * (T)g.ih2;
+}
+template <typename T>
+__device__ __forceinline__ T res_fine(const T* __restrict__ xf, const T* __restrict__ xc,
+                                      const T* __restrict__ bf, const CompGeom& g, uint32_t t) {
+  const int i = t % g.fx;
+  const int row = t / g.fx;
+  T diag, off;
+  fine_row<T>(xf, xc, g, i, row % g.fy, row / g.fy, diag, off);
+  return (bf ? bf[t] : T(0)) - (diag * xf[t] - off) * (T)g.ih2;
 }
 
 template <typename T>
@@ -365,11 +386,62 @@ __global__ __launch_bounds__(TPB) void k_comp_res_fine(T* __restrict__ rf,
                                                        const T* __restrict__ bf, CompGeom g) {
   const uint32_t t = blockIdx.x * TPB + threadIdx.x;
   if (t >= (uint32_t)g.fx * g.fy * g.fz) return;
-  const int i = t % g.fx;
-  const int row = t / g.fx;
-  T diag, off;
-  fine_row<T>(xf, xc, g, i, row % g.fy, row / g.fy, diag, off);
-  rf[t] = (bf ? bf[t] : T(0)) - (diag * xf[t] - off) * (T)g.ih2;
+  rf[t] = res_fine<T>(xf, xc, bf, g, t);
+}
+
+// The composite residual: the first `coarse_wg` work-groups take the base grid, the rest the fine
+// cells.  TO float (the FP32-refined bridge): rounded, and the correction (ec, ef) set to zero.
+template <typename TO>
+__global__ __launch_bounds__(TPB) void k_comp_residual(TO* __restrict__ rc, TO* __restrict__ rf,
+                                                       TO* __restrict__ ec, TO* __restrict__ ef,
+                                                       const double* __restrict__ xc,
+                                                       const double* __restrict__ xf,
+                                                       const double* __restrict__ bc,
+                                                       const double* __restrict__ bf, CompGeom g,
+                                                       uint32_t coarse_wg) {
+  if (blockIdx.x < coarse_wg) {
+    const uint32_t t = blockIdx.x * TPB + threadIdx.x;
+    if (t >= (uint32_t)g.nx * g.ny * g.nz) return;
+    rc[t] = (TO)res_coarse<double>(xc, xf, bc, g, t);
+    if (ec) ec[t] = TO(0);
+  } else {
+    const uint32_t t = (blockIdx.x - coarse_wg) * TPB + threadIdx.x;
+    if (t >= (uint32_t)g.fx * g.fy * g.fz) return;
+    rf[t] = (TO)res_fine<double>(xf, xc, bf, g, t);
+    if (ef) ef[t] = TO(0);
+  }
+}
+
+// Its squares instead, one partial sum per work-group of kNormPer runs of TPB cells: the solve needs
+// no residual after a cycle, only its norm (written and summed field by field that was six
+// launches of about 3 us at 64x64x32).
+constexpr int kNormPer = 4;
+__global__ __launch_bounds__(TPB) void k_comp_residual_sq(double* __restrict__ part,
+                                                          const double* __restrict__ xc,
+                                                          const double* __restrict__ xf,
+                                                          const double* __restrict__ bc,
+                                                          const double* __restrict__ bf,
+                                                          CompGeom g, uint32_t coarse_wg) {
+  __shared__ double sh[TPB / 64];
+  double sum = 0.0;
+  if (blockIdx.x < coarse_wg) {
+    const uint32_t n = (uint32_t)g.nx * g.ny * g.nz, t0 = blockIdx.x * (kNormPer * TPB);
+    for (int q = 0; q < kNormPer; ++q) {
+      const uint32_t t = t0 + q * TPB + threadIdx.x;
+      const double r = t < n ? res_coarse<double>(xc, xf, bc, g, t) : 0.0;
+      sum = fma(r, r, sum);
+    }
+  } else {
+    const uint32_t n = (uint32_t)g.fx * g.fy * g.fz,
+                   t0 = (blockIdx.x - coarse_wg) * (kNormPer * TPB);
+    for (int q = 0; q < kNormPer; ++q) {
+      const uint32_t t = t0 + q * TPB + threadIdx.x;
+      const double r = t < n ? res_fine<double>(xf, xc, bf, g, t) : 0.0;
+      sum = fma(r, r, sum);
+    }
+  }
+  sum = block_sum(sum, sh);
+  if (threadIdx.x == 0) part[blockIdx.x] = sum;
 }
 
 // 1D weights P(p, J) of the fine cells p = 2J-1 .. 2J+2 (absolute fine coordinates) around base
@@ -468,21 +540,20 @@ __device__ __forceinline__ void prolong_1d(int p, int nbase, bool periodic, int*
   }
 }
 
+// (xc, xf) += P y: the first `coarse_wg` work-groups take the base grid, the rest the fine cells.
 template <typename T>
-__global__ __launch_bounds__(TPB) void k_comp_prolong_coarse(T* __restrict__ xc,
-                                                             const T* __restrict__ y,
-                                                             CompGeom g) {
-  const uint32_t t = blockIdx.x * TPB + threadIdx.x;
-  if (t >= (uint32_t)g.nx * g.ny * g.nz) return;
-  const int x = t % g.nx;
-  const int row = t / g.nx;
-  if (!covered(g, x, row % g.ny, row / g.ny)) xc[t] += y[t];
-}
-
-template <typename T>
-__global__ __launch_bounds__(TPB) void k_comp_prolong_fine(T* __restrict__ xf,
-                                                           const T* __restrict__ y, CompGeom g) {
-  const uint32_t t = blockIdx.x * TPB + threadIdx.x;
+__global__ __launch_bounds__(TPB) void k_comp_prolong(T* __restrict__ xc, T* __restrict__ xf,
+                                                      const T* __restrict__ y, CompGeom g,
+                                                      uint32_t coarse_wg) {
+  if (blockIdx.x < coarse_wg) {
+    const uint32_t t = blockIdx.x * TPB + threadIdx.x;
+    if (t >= (uint32_t)g.nx * g.ny * g.nz) return;
+    const int x = t % g.nx;
+    const int row = t / g.nx;
+    if (!covered(g, x, row % g.ny, row / g.ny)) xc[t] += y[t];
+    return;
+  }
+  const uint32_t t = (blockIdx.x - coarse_wg) * TPB + threadIdx.x;
   if (t >= (uint32_t)g.fx * g.fy * g.fz) return;
   const int i = t % g.fx;
   const int row = t / g.fx;
@@ -875,20 +946,18 @@ hipError_t launch_dense_draw(T* x, const T* b, const double* ainv, const double*
 }
 
 template <typename T>
-hipError_t launch_comp_coarse_pass(T* xc, const T* bc, const T* xf, const CompGeom& g, int colour,
-                                   bool noise, const NoiseArgs& na, hipStream_t s) {
-  const uint32_t grid = grid_for((int64_t)(g.nx / 2) * g.ny * g.nz / 2);  // two cells a thread
-  if (noise) k_comp_coarse_pass<T, true><<<grid, TPB, 0, s>>>(xc, bc, xf, g, colour, na);
-  else k_comp_coarse_pass<T, false><<<grid, TPB, 0, s>>>(xc, bc, xf, g, colour, na);
-  return hipGetLastError();
-}
-
-template <typename T>
-hipError_t launch_comp_fine_pass(T* xf, const T* bf, const CompGeom& g, int colour, bool noise,
-                                 const NoiseArgs& na, hipStream_t s) {
-  const uint32_t grid = grid_for((int64_t)(g.fx / 2) * g.fy * g.fz / 2);  // two cells a thread
-  if (noise) k_comp_fine_pass<T, true><<<grid, TPB, 0, s>>>(xf, bf, g, colour, na);
-  else k_comp_fine_pass<T, false><<<grid, TPB, 0, s>>>(xf, bf, g, colour, na);
+hipError_t launch_comp_colour_pass(T* xc, T* xf, const T* bc, const T* bf, const CompGeom& g,
+                                   int colour, int which, bool noise, const NoiseArgs& na,
+                                   uint32_t sid_fine, hipStream_t s) {
+  // two cells a thread
+  const uint32_t cw = which & 1 ? grid_for((int64_t)(g.nx / 2) * g.ny * g.nz / 2) : 0;
+  const uint32_t fw = which & 2 ? grid_for((int64_t)(g.fx / 2) * g.fy * g.fz / 2) : 0;
+  if (cw + fw == 0) return hipSuccess;
+  if (noise)
+    k_comp_colour_pass<T, true><<<cw + fw, TPB, 0, s>>>(xc, xf, bc, bf, g, colour, cw, na, sid_fine);
+  else
+    k_comp_colour_pass<T, false><<<cw + fw, TPB, 0, s>>>(xc, xf, bc, bf, g, colour, cw, na,
+                                                         sid_fine);
   return hipGetLastError();
 }
 
@@ -903,14 +972,34 @@ hipError_t launch_comp_layer_pass(T* xf, const T* bf, const T* xc, const CompGeo
   return hipGetLastError();
 }
 
-template <typename T>
-hipError_t launch_comp_residual(T* rc, T* rf, const T* xc, const T* xf, const T* bc, const T* bf,
-                                const CompGeom& g, hipStream_t s) {
-  k_comp_res_coarse<T><<<grid_for((int64_t)g.nx * g.ny * g.nz), TPB, 0, s>>>(rc, xc, xf, bc, g);
+hipError_t launch_comp_residual(double* rc, double* rf, const double* xc, const double* xf,
+                                const double* bc, const double* bf, const CompGeom& g,
+                                hipStream_t s) {
+  const uint32_t cw = grid_for((int64_t)g.nx * g.ny * g.nz);
+  k_comp_residual<double><<<cw + grid_for((int64_t)g.fx * g.fy * g.fz), TPB, 0, s>>>(
+      rc, rf, nullptr, nullptr, xc, xf, bc, bf, g, cw);
+  return hipGetLastError();
+}
+
+hipError_t launch_comp_bridge(float* rc, float* rf, float* ec, float* ef, const double* xc,
+                              const double* xf, const double* bc, const double* bf,
+                              const CompGeom& g, hipStream_t s) {
+  const uint32_t cw = grid_for((int64_t)g.nx * g.ny * g.nz);
+  k_comp_residual<float><<<cw + grid_for((int64_t)g.fx * g.fy * g.fz), TPB, 0, s>>>(
+      rc, rf, ec, ef, xc, xf, bc, bf, g, cw);
+  return hipGetLastError();
+}
+
+hipError_t launch_comp_residual_norm(double* out, double* part, const double* xc, const double* xf,
+                                     const double* bc, const double* bf, const CompGeom& g,
+                                     hipStream_t s) {
+  auto groups = [](int64_t n) { return (uint32_t)((n + kNormPer * TPB - 1) / (kNormPer * TPB)); };
+  const uint32_t cw = groups((int64_t)g.nx * g.ny * g.nz);
+  const uint32_t all = cw + groups((int64_t)g.fx * g.fy * g.fz);
+  k_comp_residual_sq<<<all, TPB, 0, s>>>(part, xc, xf, bc, bf, g, cw);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  k_comp_res_fine<T><<<grid_for((int64_t)g.fx * g.fy * g.fz), TPB, 0, s>>>(rf, xf, xc, bf, g);
-  return hipGetLastError();
+  return launch_sumsq_final_parts(out, part, all, 1, s);
 }
 
 template <typename T>
@@ -935,10 +1024,8 @@ hipError_t launch_comp_residual_restrict(T* b0, T* x0, T* rf, const T* xc, const
 
 template <typename T>
 hipError_t launch_comp_prolong(T* xc, T* xf, const T* y, const CompGeom& g, hipStream_t s) {
-  k_comp_prolong_coarse<T><<<grid_for((int64_t)g.nx * g.ny * g.nz), TPB, 0, s>>>(xc, y, g);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  k_comp_prolong_fine<T><<<grid_for((int64_t)g.fx * g.fy * g.fz), TPB, 0, s>>>(xf, y, g);
+  const uint32_t cw = grid_for((int64_t)g.nx * g.ny * g.nz);
+  k_comp_prolong<T><<<cw + grid_for((int64_t)g.fx * g.fy * g.fz), TPB, 0, s>>>(xc, xf, y, g, cw);
   return hipGetLastError();
 }
 
@@ -1042,15 +1129,12 @@ hipError_t launch_comp_forcing(double* bc, double* bf, const double* qc, const d
 #define SMG_COMP_INSTANTIATE(T)                                                                 \
   template hipError_t launch_dense_draw<T>(T*, const T*, const double*, const double*, double*,   \
                                            int, bool, const NoiseArgs&, hipStream_t);           \
-  template hipError_t launch_comp_coarse_pass<T>(T*, const T*, const T*, const CompGeom&, int,  \
-                                                 bool, const NoiseArgs&, hipStream_t);          \
-  template hipError_t launch_comp_fine_pass<T>(T*, const T*, const CompGeom&, int, bool,        \
-                                               const NoiseArgs&, hipStream_t);                  \
+  template hipError_t launch_comp_colour_pass<T>(T*, T*, const T*, const T*, const CompGeom&,    \
+                                                 int, int, bool, const NoiseArgs&, uint32_t,    \
+                                                 hipStream_t);                                  \
   template hipError_t launch_comp_layer_pass<T>(T*, const T*, const T*, const CompGeom&,        \
                                                 const int32_t*, int, bool, const NoiseArgs&,    \
                                                 hipStream_t);                                   \
-  template hipError_t launch_comp_residual<T>(T*, T*, const T*, const T*, const T*, const T*,   \
-                                              const CompGeom&, hipStream_t);                    \
   template hipError_t launch_comp_restrict<T>(T*, T*, const T*, const T*, const CompGeom&,      \
                                               hipStream_t);                                     \
   template hipError_t launch_comp_residual_restrict<T>(T*, T*, T*, const T*, const T*,          \
