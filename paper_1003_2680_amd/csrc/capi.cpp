@@ -311,7 +311,7 @@ int restrict_residual(Run& r, int l) {
         bc, xc, comp_at(xr, hn, r), comp_at(xr + half_field(h), hn, r),
         r.has_b0 ? comp_at(br, hn, r) : nullptr,
         r.has_b0 ? comp_at(br + half_field(h), hn, r) : nullptr, v.nx, v.ny, v.nz, nc, h.desc.h,
-        r.s));
+        r.noise, r.s));
     return SMG_OK;
   }
   SMG_HIP(launch_residual_gal<T>(rr, comp_at(Fld<T>::x(v), v.n, r), comp_at(Fld<T>::b(v), v.n, r),
@@ -2049,7 +2049,7 @@ int smg_debug_restrict_residual(smg_hierarchy* hh, int32_t level, const void* x,
     SMG_HIP(launch_restrict_residual0<double>((double*)b_coarse, nullptr, v.x,
                                               v.x + half_field(h), b ? v.b : nullptr,
                                               b ? v.b + half_field(h) : nullptr, v.nx, v.ny,
-                                              v.nz, nc, h.desc.h, s));
+                                              v.nz, nc, h.desc.h, false, s));
     return SMG_OK;
   } else {
     SMG_HIP(launch_residual_gal<double>(v.r, (const double*)x, (const double*)b,

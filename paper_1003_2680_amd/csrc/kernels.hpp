@@ -97,11 +97,11 @@ hipError_t launch_rb_pass(T* xc, const T* xo, const T* bc, int nx, int ny, int n
                           int colour, double h, double kT, bool noise, const NoiseArgs& na,
                           hipStream_t s);
 // b_c = P^T (b - A x) from split level-0 storage straight to the natural coarse level (r is
-// never written); also x_c = 0 when xc is not null.  br/bb null = 0.
+// never written); also x_c = 0 when xc is not null.  br/bb null = 0.  noise: part of a sampling cycle.
 template <typename T>
 hipError_t launch_restrict_residual0(T* bc, T* xc, const T* xr, const T* xb, const T* br,
                                      const T* bb, int nx, int ny, int nz, int ncomp, double h,
-                                     hipStream_t s);
+                                     bool noise, hipStream_t s);
 // colours: bit c set = add P e to the sites of colour c
 template <typename T>
 hipError_t launch_prolong0(T* xr, T* xb, const T* e, int nxf, int nyf, int nzf, int ncomp,

@@ -501,6 +501,194 @@ __global__ __launch_bounds__(TPB) void k_restrict_residual0(
   }
 }
 
+// b_c = P^T (b - A x) from level 0 axis by axis: P^T folds into the three second differences, so a
+// fine row (y, z) leaves two values per coarse column,
+//   u = Px^T x,  s = Px^T (b - a_x x),
+// these two per coarse row (p = Py^T u, q = Py^T s - Py^T a_y u), and coarse layer Z takes
+// Pz^T q - Pz^T a_z p of the six planes 2Z - 2 .. 2Z + 3.  The folded second difference is
+// (-1, -1, 2, 2, -1, -1) / 4h^2; at a wall the outer taps fall away and the middle ones gain 1/4.
+//
+// A work-group owns RX x RY coarse columns and marches up z.  A lane forms u and s of two
+// neighbouring columns of a row: its two entries of either split colour array come with one
+// 16-byte load each (FP64), the entries beside them from the neighbouring lanes by DPP moves, and
+// for the end lanes of a row by a load of their own.  The next plane's loads are in flight
+// meanwhile.  The rows meet in LDS (two planes in turn: one barrier a plane): 10 reads per coarse
+// column and plane, where the residual of every fine cell and its window sums took 13 per fine
+// cell.  us, residual and window sums / here (FP64): 128^3, 24 components 205 / 131 (500 MB, 100 us at
+// the rate of a copy), 3 components 30.5 / 16.7, with b 34.3 / 26.3, 512x512x256 265 / 170,
+// 72x40x48 x 2 19.5 / 7.2; with six 8-byte loads per column and no moves 195, 26, 39, 249 and 9.2.
+template <int RX>
+struct Fold0 {
+  static constexpr int RY = TPB / RX;
+  static constexpr int YS = 2 * RY + 4;  // rows 2Y0 - 2 .. 2Y0 + 2RY + 1
+  static constexpr int ITEMS = RX * YS;
+  // A wave's rows are of one parity, so that its colour arrays are uniform: group a of RW rows
+  // takes 2 RW (a / 2) + a % 2 + 2 (0 .. RW - 1)
+  static constexpr int LANES = RX / 2, RW = 64 / LANES;
+  static constexpr int GROUPS = 2 * ((YS + 2 * RW - 1) / (2 * RW));
+  static constexpr int IPT = (GROUPS + TPB / 64 - 1) / (TPB / 64);
+};
+
+// v of the lane before and after within sixteen
+__device__ __forceinline__ float lane_before(float v) {
+  return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), 0x111, 0xf, 0xf, true));
+}
+__device__ __forceinline__ float lane_after(float v) {
+  return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), 0x101, 0xf, 0xf, true));
+}
+__device__ __forceinline__ double lane_before(double v) {
+  const long long u = __double_as_longlong(v);
+  const int lo = __builtin_amdgcn_mov_dpp((int)u, 0x111, 0xf, 0xf, true);
+  const int hi = __builtin_amdgcn_mov_dpp((int)(u >> 32), 0x111, 0xf, 0xf, true);
+  return __longlong_as_double(((long long)hi << 32) | (unsigned)lo);
+}
+__device__ __forceinline__ double lane_after(double v) {
+  const long long u = __double_as_longlong(v);
+  const int lo = __builtin_amdgcn_mov_dpp((int)u, 0x101, 0xf, 0xf, true);
+  const int hi = __builtin_amdgcn_mov_dpp((int)(u >> 32), 0x101, 0xf, 0xf, true);
+  return __longlong_as_double(((long long)hi << 32) | (unsigned)lo);
+}
+
+template <typename T, bool HAS_B, int RX>
+__global__ __launch_bounds__(TPB) void k_fold_residual0(
+    T* __restrict__ bc, T* __restrict__ xc, const T* __restrict__ xr, const T* __restrict__ xb,
+    const T* __restrict__ br, const T* __restrict__ bb, int ny, int nz, int nxc, int ntx, int zper,
+    T inv_h2) {
+  using F = Fold0<RX>;
+  using V2 = typename Vec2<T>::type;
+  __shared__ __attribute__((aligned(16))) T Us[2][F::ITEMS], Ss[2][F::ITEMS];
+  const Blk3 wg = xcd_block();
+  const uint32_t comp = wg.z;
+  const int nyc = ny >> 1, nzc = nz >> 1;
+  const int X0 = (int)(wg.x % (uint32_t)ntx) * RX, Y0 = (int)(wg.x / (uint32_t)ntx) * F::RY;
+  const int Z0 = (int)wg.y * zper, Z1 = min(Z0 + zper, nzc);
+  const uint32_t plane = (uint32_t)nxc * ny;  // of one colour
+  const size_t cb = (size_t)comp * plane * nz;
+  const T *X[2] = {xr + cb, xb + cb};
+  const T *B[2] = {HAS_B ? br + cb : nullptr, HAS_B ? bb + cb : nullptr};
+  const int tid = threadIdx.x;
+  // the items: byte offsets of the lane's columns (periodic, nxc is even; lanes beyond the grid
+  // hold its continuation) and of the column beside them for the first and last lane of a row
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int lr = tid & (F::LANES - 1);
+  const bool first = lr == 0, last = lr == F::LANES - 1;
+  uint32_t em[F::IPT], eh[F::IPT];
+  int at[F::IPT], par[F::IPT];
+#pragma unroll
+  for (int k = 0; k < F::IPT; ++k) {
+    const int a = wave + k * (TPB / 64);
+    const int row = 2 * F::RW * (a >> 1) + (a & 1) + 2 * ((tid & 63) / F::LANES);
+    const bool in = a < F::GROUPS && row < F::YS;
+    at[k] = in ? row * RX + 2 * lr : -1;
+    const int y = wrap_near(2 * Y0 - 2 + (in ? row : a & 1), ny);
+    int x = X0 + 2 * lr;
+    x = x < nxc ? x : (x < 2 * nxc ? x - nxc : 0);
+    const int xh = first ? (x == 0 ? nxc - 1 : x - 1) : (x + 2 == nxc ? 0 : x + 2);
+    par[k] = __builtin_amdgcn_readfirstlane(a & 1);  // the window begins at an even row, ny is even
+    em[k] = ((uint32_t)y * nxc + x) * (uint32_t)sizeof(T);
+    eh[k] = ((uint32_t)y * nxc + xh) * (uint32_t)sizeof(T);
+  }
+  // The even cells of a row are the entries of colour (y + z) & 1, the odd ones of the other.
+  V2 ve[F::IPT], vo[F::IPT], be[F::IPT], bo[F::IPT];
+  T he[F::IPT], ho[F::IPT], hb[F::IPT];
+  auto at_byte = [](const T* p, uint32_t off) { return reinterpret_cast<const char*>(p) + off; };
+  auto ld2 = [&](const T* p, uint32_t off) { return *reinterpret_cast<const V2*>(at_byte(p, off)); };
+  auto ld1 = [&](const T* p, uint32_t off) { return *reinterpret_cast<const T*>(at_byte(p, off)); };
+  auto load = [&](int f) {
+    const size_t z = (size_t)f * plane;
+#pragma unroll
+    for (int k = 0; k < F::IPT; ++k) {
+      const bool odd = (par[k] ^ f) & 1;
+      const T *E = (odd ? X[1] : X[0]) + z, *O = (odd ? X[0] : X[1]) + z;
+      ve[k] = ld2(E, em[k]);
+      vo[k] = ld2(O, em[k]);
+      const T *Eb = nullptr, *Ob = nullptr;
+      if (HAS_B) {
+        Eb = (odd ? B[1] : B[0]) + z;
+        Ob = (odd ? B[0] : B[1]) + z;
+        be[k] = ld2(Eb, em[k]);
+        bo[k] = ld2(Ob, em[k]);
+      }
+      if (first || last) {
+        he[k] = ld1(E, eh[k]);
+        ho[k] = ld1(O, eh[k]);
+        if (HAS_B) hb[k] = ld1(first ? Ob : Eb, eh[k]);
+      }
+    }
+  };
+  const T q1 = T(0.25), q3 = T(0.75), d1 = T(0.25) * inv_h2, d2 = T(0.5) * inv_h2;
+  const int lx = tid % RX, ly = tid / RX;
+  const bool owner = X0 + lx < nxc && Y0 + ly < nyc;
+  const size_t out = (size_t)comp * nxc * nyc * nzc + (size_t)(Y0 + ly) * nxc + X0 + lx;
+  const size_t cplane = (size_t)nxc * nyc;
+  auto emit = [&](int Z, T a) {
+    if (Z < Z0 || Z >= Z1 || !owner) return;
+    bc[out + Z * cplane] = a;
+    if (xc) xc[out + Z * cplane] = T(0);
+  };
+  // running sums of layers m - 1, m, m + 1 while planes 2m, 2m + 1 go by
+  T a0 = T(0), a1 = T(0), a2 = T(0);
+  const int f0 = max(0, 2 * Z0 - 2), f1 = min(nz - 1, 2 * Z1 + 1);
+  load(f0);
+#pragma unroll 1
+  for (int f = f0; f <= f1; ++f) {
+    const int buf = f & 1;
+#pragma unroll
+    for (int k = 0; k < F::IPT; ++k) {
+      // every lane takes part in the moves
+      T e0 = lane_before(ve[k].y), o0 = lane_before(vo[k].y);
+      T e3 = lane_after(ve[k].x), o3 = lane_after(vo[k].x);
+      e0 = first ? he[k] : e0;
+      o0 = first ? ho[k] : o0;
+      e3 = last ? he[k] : e3;
+      o3 = last ? ho[k] : o3;
+      const T m0 = ve[k].x + vo[k].x, m1 = ve[k].y + vo[k].y;
+      const T n0 = o0 + ve[k].y, n1 = vo[k].x + e3;
+      V2 u, s;
+      u.x = fma(q3, m0, q1 * n0);
+      u.y = fma(q3, m1, q1 * n1);
+      s.x = fma(d1, n0 + (e0 + vo[k].y), -d2 * m0);
+      s.y = fma(d1, n1 + (ve[k].x + o3), -d2 * m1);
+      if (HAS_B) {
+        T bl = lane_before(bo[k].y), bh = lane_after(be[k].x);
+        bl = first ? hb[k] : bl;
+        bh = last ? hb[k] : bh;
+        s.x += fma(q3, be[k].x + bo[k].x, q1 * (bl + be[k].y));
+        s.y += fma(q3, be[k].y + bo[k].y, q1 * (bo[k].x + bh));
+      }
+      if (at[k] >= 0) {
+        *reinterpret_cast<V2*>(&Us[buf][at[k]]) = u;
+        *reinterpret_cast<V2*>(&Ss[buf][at[k]]) = s;
+      }
+    }
+    if (f < f1) load(f + 1);
+    __syncthreads();
+    const T* U = &Us[buf][2 * ly * RX + lx];
+    const T* S = &Ss[buf][2 * ly * RX + lx];
+    const T umid = U[2 * RX] + U[3 * RX], unear = U[RX] + U[4 * RX], ufar = U[0] + U[5 * RX];
+    const T p = fma(q3, umid, q1 * unear);
+    const T q = fma(q3, S[2 * RX] + S[3 * RX], q1 * (S[RX] + S[4 * RX])) +
+                fma(d1, unear + ufar, -d2 * umid);
+    const int m = f >> 1;
+    const T mid = d2 + (m == 0 ? d1 : T(0)) + (m == nzc - 1 ? d1 : T(0));
+    a0 = fma(d1, p, a0);
+    a1 = fma(-mid, p, a1);
+    a2 = fma(d1, p, a2);
+    if (buf == 0) {
+      a0 = fma(q1, q, a0);
+      a1 = fma(m == 0 ? T(0.5) : q3, q, a1);
+    } else {
+      a1 = fma(m == nzc - 1 ? T(0.5) : q3, q, a1);
+      a2 = fma(q1, q, a2);
+      emit(m - 1, a0);
+      a0 = a1;
+      a1 = a2;
+      a2 = T(0);
+    }
+  }
+  if (f1 == nz - 1) emit(nzc - 1, a0);  // the layer at the upper wall has no planes above
+}
+
 // Residual on level 0 from FP64 split storage, any even nx: r32 = (float)(b - A x), written split
 // unless r32 is null (the FP32-refined bridge); the optional fixed-order partial sums of
 // (b - A x)^2 go to part[comp][colour*nblk + block].
@@ -929,31 +1117,61 @@ hipError_t launch_rb_pass_multi(const RbPassItem<T>* items, int n, int colour, b
   return flush();
 }
 
+template <typename T, bool HAS_B>
+static void launch_fold_residual0(T* bc, T* xc, const T* xr, const T* xb, const T* br, const T* bb,
+                                  int nx, int ny, int nz, int ncomp, T ih2, hipStream_t s) {
+  const int nxc = nx >> 1, nyc = ny >> 1, nzc = nz >> 1;
+  auto go = [&](auto rx) {
+    constexpr int RX = decltype(rx)::value, RY = Fold0<RX>::RY;
+    const int ntx = (nxc + RX - 1) / RX, nty = (nyc + RY - 1) / RY;
+    // Coarse layers a work-group: each takes two planes, and four more are its halo.  Two work-groups
+    // a CU are enough (128^3 x 3: 16.7 us with 4 layers, 19.8 with 8); more layers than 16 gain
+    // nothing.
+    int zper = 16;
+    while (zper > 2 && (int64_t)ntx * nty * ((nzc + zper - 1) / zper) * ncomp < 512) zper /= 2;
+    dim3 grid(ntx * nty, (nzc + zper - 1) / zper, ncomp);
+    k_fold_residual0<T, HAS_B, RX><<<grid, TPB, 0, s>>>(bc, xc, xr, xb, br, bb, ny, nz, nxc, ntx,
+                                                        zper, ih2);
+  };
+  // 32 x 8 or 16 x 16 coarse columns a work-group, whichever covers the level with fewer
+  auto cover = [&](int rx, int ry) { return (int64_t)((nxc + rx - 1) / rx) * ((nyc + ry - 1) / ry); };
+  if (cover(32, 8) <= cover(16, 16)) go(std::integral_constant<int, 32>());
+  else go(std::integral_constant<int, 16>());
+}
+
 template <typename T>
 hipError_t launch_restrict_residual0(T* bc, T* xc, const T* xr, const T* xb, const T* br,
                                      const T* bb, int nx, int ny, int nz, int ncomp, double h,
-                                     hipStream_t s) {
+                                     bool noise, hipStream_t s) {
   const int nxc = nx >> 1, nyc = ny >> 1, nzc = nz >> 1;
   if (nxc * nyc * nzc == 0) return hipSuccess;
   const T ih2 = (T)(1.0 / (h * h));
-  auto go = [&](auto rx, auto ry) {
-    constexpr int RX = decltype(rx)::value, RY = decltype(ry)::value;
-    const int ntx = (nxc + RX - 1) / RX, nty = (nyc + RY - 1) / RY;
-    dim3 grid(ntx * nty, (nzc + RR_Z - 1) / RR_Z, ncomp);
-    if (br)
-      k_restrict_residual0<T, true, RX, RY>
-          <<<grid, TPB, 0, s>>>(bc, xc, xr, xb, br, bb, nx, ny, nz, ntx, ih2);
-    else
-      k_restrict_residual0<T, false, RX, RY>
-          <<<grid, TPB, 0, s>>>(bc, xc, xr, xb, br, bb, nx, ny, nz, ntx, ih2);
-  };
-  // 16 x 8 coarse cells per work-group where the grid is that wide (less halo and scalar work
-  // per cell: 190 us against 229 us for 8 x 8 at 128^3 x 24; 16 x 16 took 219 us at half the
-  // occupancy), else 8 x 8
-  if (nxc >= 16)
-    go(std::integral_constant<int, 16>(), std::integral_constant<int, 8>());
-  else
-    go(std::integral_constant<int, 8>(), std::integral_constant<int, 8>());
+  {
+    // the sampling cycle in FP32 keeps its order of additions (block_update.hpp: index_order), and
+    // an odd number of coarse columns does not pair up
+    if ((sizeof(T) == 4 && noise) || nxc % 2) {
+      auto go = [&](auto rx, auto ry) {
+        constexpr int RX = decltype(rx)::value, RY = decltype(ry)::value;
+        const int ntx = (nxc + RX - 1) / RX, nty = (nyc + RY - 1) / RY;
+        dim3 grid(ntx * nty, (nzc + RR_Z - 1) / RR_Z, ncomp);
+        if (br)
+          k_restrict_residual0<T, true, RX, RY>
+              <<<grid, TPB, 0, s>>>(bc, xc, xr, xb, br, bb, nx, ny, nz, ntx, ih2);
+        else
+          k_restrict_residual0<T, false, RX, RY>
+              <<<grid, TPB, 0, s>>>(bc, xc, xr, xb, br, bb, nx, ny, nz, ntx, ih2);
+      };
+      // 16 x 8 coarse cells per work-group where the grid is that wide (less halo and scalar work
+      // per cell), else 8 x 8
+      if (nxc >= 16)
+        go(std::integral_constant<int, 16>(), std::integral_constant<int, 8>());
+      else
+        go(std::integral_constant<int, 8>(), std::integral_constant<int, 8>());
+      return hipGetLastError();
+    }
+  }
+  if (br) launch_fold_residual0<T, true>(bc, xc, xr, xb, br, bb, nx, ny, nz, ncomp, ih2, s);
+  else launch_fold_residual0<T, false>(bc, xc, xr, xb, br, bb, nx, ny, nz, ncomp, ih2, s);
   return hipGetLastError();
 }
 
@@ -991,10 +1209,10 @@ template hipError_t launch_prolong0<double>(double*, double*, const double*, int
 template hipError_t launch_restrict_residual0<double>(double*, double*, const double*,
                                                       const double*, const double*,
                                                       const double*, int, int, int, int, double,
-                                                      hipStream_t);
+                                                      bool, hipStream_t);
 template hipError_t launch_restrict_residual0<float>(float*, float*, const float*, const float*,
                                                      const float*, const float*, int, int, int,
-                                                     int, double, hipStream_t);
+                                                     int, double, bool, hipStream_t);
 template hipError_t launch_prolong0<float>(float*, float*, const float*, int, int, int, int,
                                             int, hipStream_t);
 
