@@ -24,6 +24,8 @@ constexpr bool index_order = NOISE && sizeof(T) == 4;
 // v of another lane of the same eight: quad_perm moves for lane ^ 1, ^ 2, ^ 3 and the mirror of
 // the eight lanes for lane ^ 7 (lane ^ 4 is ^ 3 of it).
 constexpr int DPP_XOR1 = 0xB1, DPP_XOR2 = 0x4E, DPP_XOR3 = 0x1B, DPP_XOR7 = 0x141;
+// the lane before and after within sixteen (nothing for the first, the last)
+constexpr int DPP_BEFORE = 0x111, DPP_AFTER = 0x101;
 template <int CTRL>
 __device__ __forceinline__ double dpp_lane(double v) {
   const long long u = __double_as_longlong(v);

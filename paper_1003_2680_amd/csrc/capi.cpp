@@ -291,6 +291,20 @@ int sweep(Run& r, int l, int slot, bool post) {
   return SMG_OK;
 }
 
+template <typename T>
+FoldTaps<T> level_taps(const Level& v) {
+  FoldTaps<T> m;
+  double f[4][4];
+  for (int q = 0; q < 4; ++q) fold_taps(&v.s1d[5 * q], f[q]);
+  for (int t = 0; t < 4; ++t) {
+    m.mx[t] = (T)f[0][t];
+    m.ax[t] = (T)f[1][t];
+    m.my[t] = (T)f[2][t];
+    m.ay[t] = (T)f[3][t];
+  }
+  return m;
+}
+
 // b^(l+1) = P^T (b^(l) - A^(l) x^(l)); the coarse iterate starts from zero
 template <typename T>
 int restrict_residual(Run& r, int l) {
@@ -314,6 +328,13 @@ int restrict_residual(Run& r, int l) {
         r.noise, r.s));
     return SMG_OK;
   }
+  if (sizeof(T) == 8 || !r.noise) {
+    SMG_HIP(launch_fold_residual<T>(bc, xc, comp_at(Fld<T>::x(v), v.n, r),
+                                    comp_at(Fld<T>::b(v), v.n, r), (const T*)v.zt_d,
+                                    level_taps<T>(v), v.nx, v.ny, v.nz, nc, r.s));
+    return SMG_OK;
+  }
+  // the FP32 sampling cycle keeps its order of additions
   SMG_HIP(launch_residual_gal<T>(rr, comp_at(Fld<T>::x(v), v.n, r), comp_at(Fld<T>::b(v), v.n, r),
                                  (const T*)v.s1d_d, (const T*)v.zt_d, v.nx, v.ny, v.nz, nc, r.s));
   SMG_HIP(launch_restrict<T>(bc, xc, rr, v.nx, v.ny, v.nz, nc, r.s));
@@ -2051,12 +2072,10 @@ int smg_debug_restrict_residual(smg_hierarchy* hh, int32_t level, const void* x,
                                               b ? v.b + half_field(h) : nullptr, v.nx, v.ny,
                                               v.nz, nc, h.desc.h, false, s));
     return SMG_OK;
-  } else {
-    SMG_HIP(launch_residual_gal<double>(v.r, (const double*)x, (const double*)b,
-                                        (const double*)v.s1d_d, (const double*)v.zt_d, v.nx,
-                                        v.ny, v.nz, nc, s));
   }
-  SMG_HIP(launch_restrict<double>((double*)b_coarse, nullptr, v.r, v.nx, v.ny, v.nz, nc, s));
+  SMG_HIP(launch_fold_residual<double>((double*)b_coarse, nullptr, (const double*)x,
+                                       (const double*)b, (const double*)v.zt_d,
+                                       level_taps<double>(v), v.nx, v.ny, v.nz, nc, s));
   return SMG_OK;
 }
 

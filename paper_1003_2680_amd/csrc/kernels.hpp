@@ -109,6 +109,24 @@ hipError_t launch_prolong0(T* xr, T* xb, const T* e, int nxf, int nyf, int nzf, 
 template <typename T>
 hipError_t launch_residual_gal(T* r, const T* x, const T* b, const T* s1d, const T* zt, int nx,
                                int ny, int nz, int ncomp, hipStream_t s);
+// The 1D stencils m, a of a Galerkin level's periodic axes with P^T folded in: taps t and 7 - t (fine
+// cells 2J - 3 + t of coarse position J) are sum_c w_c s[t - 3 - c], w = (1/4, 3/4, 3/4, 1/4) at
+// c = -1 .. 2.
+template <typename T>
+struct FoldTaps {
+  T mx[4], ax[4], my[4], ay[4];
+};
+inline void fold_taps(const double* s, double (&m)[4]) {  // s: offsets -2 .. 2, symmetric
+  m[0] = 0.25 * s[0];
+  m[1] = 0.25 * s[1] + 0.75 * s[0];
+  m[2] = 0.25 * s[2] + 0.75 * (s[0] + s[1]);
+  m[3] = 0.25 * (s[0] + s[1]) + 0.75 * (s[1] + s[2]);
+}
+// b_c = P^T (b - A x) on a block level (zt: its wall-axis rows); also x_c = 0 when xc is not null
+template <typename T>
+hipError_t launch_fold_residual(T* bc, T* xc, const T* x, const T* b, const T* zt,
+                                const FoldTaps<T>& m, int nx, int ny, int nz, int ncomp,
+                                hipStream_t s);
 // b_c = P^T r; also x_c = 0 when xc is not null
 template <typename T>
 hipError_t launch_restrict(T* bc, T* xc, const T* r, int nxf, int nyf, int nzf, int ncomp,

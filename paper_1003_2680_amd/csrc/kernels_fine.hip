@@ -10,6 +10,7 @@
 
 #include <type_traits>
 
+#include "block_update.hpp"
 #include "device_common.hpp"
 #include "kernels.hpp"
 
@@ -514,9 +515,12 @@ __global__ __launch_bounds__(TPB) void k_restrict_residual0(
 // for the end lanes of a row by a load of their own.  The next plane's loads are in flight
 // meanwhile.  The rows meet in LDS (two planes in turn: one barrier a plane): 10 reads per coarse
 // column and plane, where the residual of every fine cell and its window sums took 13 per fine
-// cell.  us, residual and window sums / here (FP64): 128^3, 24 components 205 / 131 (500 MB, 100 us at
-// the rate of a copy), 3 components 30.5 / 16.7, with b 34.3 / 26.3, 512x512x256 265 / 170,
-// 72x40x48 x 2 19.5 / 7.2; with six 8-byte loads per column and no moves 195, 26, 39, 249 and 9.2.
+// cell.  us, residual and window sums / here (FP64): 128^3, 24 components 205 / 132 (500 MB, 100 us at
+// the rate of a copy), 3 components 30.5 / 16.5, with b 34.3 / 25.5, 512x512x256 265 / 170,
+// 72x40x48 x 2 19.5 / 6.5; with six 8-byte loads per column and no moves 195, 26, 39, 249 and 9.2.
+// Twice as many lanes as columns: every item of a plane has one (with 256 lanes 72x40x48 x 2 took
+// 7.2 instead of 6.5 us).
+constexpr int FOLD_TPB = 2 * TPB;
 template <int RX>
 struct Fold0 {
   static constexpr int RY = TPB / RX;
@@ -526,31 +530,11 @@ struct Fold0 {
   // takes 2 RW (a / 2) + a % 2 + 2 (0 .. RW - 1)
   static constexpr int LANES = RX / 2, RW = 64 / LANES;
   static constexpr int GROUPS = 2 * ((YS + 2 * RW - 1) / (2 * RW));
-  static constexpr int IPT = (GROUPS + TPB / 64 - 1) / (TPB / 64);
+  static constexpr int IPT = (GROUPS + FOLD_TPB / 64 - 1) / (FOLD_TPB / 64);
 };
 
-// v of the lane before and after within sixteen
-__device__ __forceinline__ float lane_before(float v) {
-  return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), 0x111, 0xf, 0xf, true));
-}
-__device__ __forceinline__ float lane_after(float v) {
-  return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), 0x101, 0xf, 0xf, true));
-}
-__device__ __forceinline__ double lane_before(double v) {
-  const long long u = __double_as_longlong(v);
-  const int lo = __builtin_amdgcn_mov_dpp((int)u, 0x111, 0xf, 0xf, true);
-  const int hi = __builtin_amdgcn_mov_dpp((int)(u >> 32), 0x111, 0xf, 0xf, true);
-  return __longlong_as_double(((long long)hi << 32) | (unsigned)lo);
-}
-__device__ __forceinline__ double lane_after(double v) {
-  const long long u = __double_as_longlong(v);
-  const int lo = __builtin_amdgcn_mov_dpp((int)u, 0x101, 0xf, 0xf, true);
-  const int hi = __builtin_amdgcn_mov_dpp((int)(u >> 32), 0x101, 0xf, 0xf, true);
-  return __longlong_as_double(((long long)hi << 32) | (unsigned)lo);
-}
-
 template <typename T, bool HAS_B, int RX>
-__global__ __launch_bounds__(TPB) void k_fold_residual0(
+__global__ __launch_bounds__(FOLD_TPB) void k_fold_residual0(
     T* __restrict__ bc, T* __restrict__ xc, const T* __restrict__ xr, const T* __restrict__ xb,
     const T* __restrict__ br, const T* __restrict__ bb, int ny, int nz, int nxc, int ntx, int zper,
     T inv_h2) {
@@ -576,7 +560,7 @@ __global__ __launch_bounds__(TPB) void k_fold_residual0(
   int at[F::IPT], par[F::IPT];
 #pragma unroll
   for (int k = 0; k < F::IPT; ++k) {
-    const int a = wave + k * (TPB / 64);
+    const int a = wave + k * (FOLD_TPB / 64);
     const int row = 2 * F::RW * (a >> 1) + (a & 1) + 2 * ((tid & 63) / F::LANES);
     const bool in = a < F::GROUPS && row < F::YS;
     at[k] = in ? row * RX + 2 * lr : -1;
@@ -618,7 +602,7 @@ __global__ __launch_bounds__(TPB) void k_fold_residual0(
   };
   const T q1 = T(0.25), q3 = T(0.75), d1 = T(0.25) * inv_h2, d2 = T(0.5) * inv_h2;
   const int lx = tid % RX, ly = tid / RX;
-  const bool owner = X0 + lx < nxc && Y0 + ly < nyc;
+  const bool owner = tid < TPB && X0 + lx < nxc && Y0 + ly < nyc;
   const size_t out = (size_t)comp * nxc * nyc * nzc + (size_t)(Y0 + ly) * nxc + X0 + lx;
   const size_t cplane = (size_t)nxc * nyc;
   auto emit = [&](int Z, T a) {
@@ -636,8 +620,8 @@ __global__ __launch_bounds__(TPB) void k_fold_residual0(
 #pragma unroll
     for (int k = 0; k < F::IPT; ++k) {
       // every lane takes part in the moves
-      T e0 = lane_before(ve[k].y), o0 = lane_before(vo[k].y);
-      T e3 = lane_after(ve[k].x), o3 = lane_after(vo[k].x);
+      T e0 = dpp_lane<DPP_BEFORE>(ve[k].y), o0 = dpp_lane<DPP_BEFORE>(vo[k].y);
+      T e3 = dpp_lane<DPP_AFTER>(ve[k].x), o3 = dpp_lane<DPP_AFTER>(vo[k].x);
       e0 = first ? he[k] : e0;
       o0 = first ? ho[k] : o0;
       e3 = last ? he[k] : e3;
@@ -650,7 +634,7 @@ __global__ __launch_bounds__(TPB) void k_fold_residual0(
       s.x = fma(d1, n0 + (e0 + vo[k].y), -d2 * m0);
       s.y = fma(d1, n1 + (ve[k].x + o3), -d2 * m1);
       if (HAS_B) {
-        T bl = lane_before(bo[k].y), bh = lane_after(be[k].x);
+        T bl = dpp_lane<DPP_BEFORE>(bo[k].y), bh = dpp_lane<DPP_AFTER>(be[k].x);
         bl = first ? hb[k] : bl;
         bh = last ? hb[k] : bh;
         s.x += fma(q3, be[k].x + bo[k].x, q1 * (bl + be[k].y));
@@ -663,6 +647,7 @@ __global__ __launch_bounds__(TPB) void k_fold_residual0(
     }
     if (f < f1) load(f + 1);
     __syncthreads();
+    if (tid >= TPB) continue;  // more lanes than columns: whole waves
     const T* U = &Us[buf][2 * ly * RX + lx];
     const T* S = &Ss[buf][2 * ly * RX + lx];
     const T umid = U[2 * RX] + U[3 * RX], unear = U[RX] + U[4 * RX], ufar = U[0] + U[5 * RX];
@@ -1122,7 +1107,7 @@ static void launch_fold_residual0(T* bc, T* xc, const T* xr, const T* xb, const 
                                   int nx, int ny, int nz, int ncomp, T ih2, hipStream_t s) {
   const int nxc = nx >> 1, nyc = ny >> 1, nzc = nz >> 1;
   auto go = [&](auto rx) {
-    constexpr int RX = decltype(rx)::value, RY = Fold0<RX>::RY;
+    constexpr int RX = decltype(rx)::value, RY = TPB / RX;
     const int ntx = (nxc + RX - 1) / RX, nty = (nyc + RY - 1) / RY;
     // Coarse layers a work-group: each takes two planes, and four more are its halo.  Two work-groups
     // a CU are enough (128^3 x 3: 16.7 us with 4 layers, 19.8 with 8); more layers than 16 gain
@@ -1130,8 +1115,8 @@ static void launch_fold_residual0(T* bc, T* xc, const T* xr, const T* xb, const 
     int zper = 16;
     while (zper > 2 && (int64_t)ntx * nty * ((nzc + zper - 1) / zper) * ncomp < 512) zper /= 2;
     dim3 grid(ntx * nty, (nzc + zper - 1) / zper, ncomp);
-    k_fold_residual0<T, HAS_B, RX><<<grid, TPB, 0, s>>>(bc, xc, xr, xb, br, bb, ny, nz, nxc, ntx,
-                                                        zper, ih2);
+    k_fold_residual0<T, HAS_B, RX><<<grid, FOLD_TPB, 0, s>>>(bc, xc, xr, xb, br, bb, ny, nz, nxc,
+                                                             ntx, zper, ih2);
   };
   // 32 x 8 or 16 x 16 coarse columns a work-group, whichever covers the level with fewer
   auto cover = [&](int rx, int ry) { return (int64_t)((nxc + rx - 1) / rx) * ((nyc + ry - 1) / ry); };

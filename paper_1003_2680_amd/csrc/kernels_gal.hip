@@ -553,6 +553,171 @@ __global__ __launch_bounds__(TPB) void k_residual_gal_tile(T* __restrict__ r,
   }
 }
 
+// b_c = P^T (b - A x) on a Galerkin level axis by axis, and x_c = 0: as k_fold_residual0, with the
+// eight-tap folds of m and a along x and y (symmetric: four coefficients each) and the rows of a_z
+// and m_z along z.  A fine row leaves u = Px^T m_x x, v = Px^T a_x x and w = Px^T b per coarse
+// column, these p0 = Py^T m_y u, p1 = Py^T (a_y u + m_y v) and q = Py^T w per coarse row; a plane's
+// p0, p1 go into the five z-rows that they reach, and a finished row into its two coarse layers.
+// A lane forms two coarse columns of a row from its four cells (16-byte loads) and three beside
+// them on either side, from the neighbouring lanes by DPP moves and, for the end lanes of a row, by
+// loads of their own.  us, residual kernel + restriction / here (FP64): 64^3 x 24 57 + 27 / 33, x 3
+// 11.9 + 5.8 / 11.1, 256x256x128 73 + 35 / 36.
+constexpr int FOLD_Z = 16;  // coarse layers a work-group at most
+template <int RX, int NT>
+struct FoldG {
+  static constexpr int RY = TPB / RX;
+  static constexpr int YS = 2 * RY + 6;  // rows 2Y0 - 3 .. 2Y0 + 2RY + 2
+  static constexpr int ITEMS = RX * YS;
+  static constexpr int LANES = RX / 2, ROWS = NT / LANES;
+  static constexpr int IPT = (YS + ROWS - 1) / ROWS;
+};
+
+template <typename T, int RX, int NT>
+__global__ __launch_bounds__(NT) void k_fold_residual(T* __restrict__ bc, T* __restrict__ xc,
+                                                        const T* __restrict__ xg,
+                                                        const T* __restrict__ bg,
+                                                        const T* __restrict__ zt, int nx, int ny,
+                                                        int nz, int ntx, int zper,
+                                                        FoldTaps<T> m) {
+  using F = FoldG<RX, NT>;
+  using V2 = typename std::conditional<sizeof(T) == 8, double2, float2>::type;
+  __shared__ __attribute__((aligned(16))) T Us[2][F::ITEMS], Vs[2][F::ITEMS], Ws[2][F::ITEMS];
+  __shared__ T Zt[(2 * FOLD_Z + 10) * 10];  // the z-rows that the run's planes reach
+  const Blk3 wg = xcd_block();
+  const uint32_t comp = wg.z;
+  const int nxc = nx >> 1, nyc = ny >> 1, nzc = nz >> 1;
+  const int X0 = (int)(wg.x % (uint32_t)ntx) * RX, Y0 = (int)(wg.x / (uint32_t)ntx) * F::RY;
+  const int Z0 = (int)wg.y * zper, Z1 = min(Z0 + zper, nzc);
+  const size_t plane = (size_t)nx * ny, N = plane * nz;
+  const T *X = xg + comp * N, *B = bg + comp * N;
+  const int tid = threadIdx.x;
+  const int lr = tid & (F::LANES - 1);
+  const bool first = lr == 0, last = lr == F::LANES - 1;
+  // cell offsets within a plane: the lane's four, and the four beside them of an end lane
+  uint32_t em[F::IPT], eh[F::IPT];
+  int at[F::IPT];
+#pragma unroll
+  for (int k = 0; k < F::IPT; ++k) {
+    const int row = tid / F::LANES + k * F::ROWS;
+    at[k] = row < F::YS ? row * RX + 2 * lr : -1;
+    const uint32_t y = (uint32_t)wrap_near(2 * Y0 - 3 + (row < F::YS ? row : 0), ny) * nx;
+    int x = X0 + 2 * lr;  // lanes beyond the grid hold its periodic continuation
+    x = 2 * (x < nxc ? x : (x < 2 * nxc ? x - nxc : 0));
+    em[k] = y + x;
+    eh[k] = y + (first ? (x == 0 ? nx - 4 : x - 4) : (x + 4 == nx ? 0 : x + 4));
+  }
+  V2 x0[F::IPT], x1[F::IPT], b0[F::IPT], b1[F::IPT], h0[F::IPT], h1[F::IPT], hb[F::IPT];
+  auto ld = [](const T* p) { return *reinterpret_cast<const V2*>(p); };
+  auto load = [&](int f) {
+    const T *P = X + f * plane, *Q = B + f * plane;
+#pragma unroll
+    for (int k = 0; k < F::IPT; ++k) {
+      x0[k] = ld(P + em[k]);
+      x1[k] = ld(P + em[k] + 2);
+      b0[k] = ld(Q + em[k]);
+      b1[k] = ld(Q + em[k] + 2);
+      if (first || last) {
+        h0[k] = ld(P + eh[k]);
+        h1[k] = ld(P + eh[k] + 2);
+        hb[k] = ld(Q + eh[k] + (first ? 2 : 0));
+      }
+    }
+  };
+  const T q1 = T(0.25), q3 = T(0.75);
+  const int lx = tid % RX, ly = tid / RX;
+  const bool owner = tid < TPB && X0 + lx < nxc && Y0 + ly < nyc;
+  const size_t out = (size_t)comp * nxc * nyc * nzc + (size_t)(Y0 + ly) * nxc + X0 + lx;
+  const size_t cplane = (size_t)nxc * nyc;
+  auto emit = [&](int Z, T a) {
+    if (Z < Z0 || Z >= Z1 || !owner) return;
+    bc[out + Z * cplane] = a;
+    if (xc) xc[out + Z * cplane] = T(0);
+  };
+  // r[j]: the residual of z-row f - 2 + j so far; lo, hi: the coarse layers that it goes into
+  T r[5] = {}, lo = T(0), hi = T(0);
+  const int f0 = max(0, 2 * Z0 - 3), f1 = 2 * Z1 + 2;
+  load(f0);
+  for (int q = tid; q < (f1 - f0 + 5) * 10; q += NT) {
+    const int z = min(max(f0 - 2 + q / 10, 0), nz - 1);  // a row beyond a wall is never used
+    Zt[q] = zt[z * 10 + q % 10];
+  }
+#pragma unroll 1
+  for (int f = f0; f <= f1; ++f) {
+    const int buf = f & 1;
+    if (f < nz) {
+#pragma unroll
+      for (int k = 0; k < F::IPT; ++k) {
+        const T c0 = x0[k].x, c1 = x0[k].y, c2 = x1[k].x, c3 = x1[k].y;
+        T l1 = dpp_lane<DPP_BEFORE>(c1), l2 = dpp_lane<DPP_BEFORE>(c2),
+          l3 = dpp_lane<DPP_BEFORE>(c3);
+        T r4 = dpp_lane<DPP_AFTER>(c0), r5 = dpp_lane<DPP_AFTER>(c1), r6 = dpp_lane<DPP_AFTER>(c2);
+        T bl = dpp_lane<DPP_BEFORE>(b1[k].y), bh = dpp_lane<DPP_AFTER>(b0[k].x);
+        l1 = first ? h0[k].y : l1;
+        l2 = first ? h1[k].x : l2;
+        l3 = first ? h1[k].y : l3;
+        bl = first ? hb[k].y : bl;
+        r4 = last ? h0[k].x : r4;
+        r5 = last ? h0[k].y : r5;
+        r6 = last ? h1[k].x : r6;
+        bh = last ? hb[k].x : bh;
+        const T ea[4] = {l1 + r4, l2 + c3, l3 + c2, c0 + c1};
+        const T eb[4] = {l3 + r6, c0 + r5, c1 + r4, c2 + c3};
+        V2 u, v, w;
+        u.x = u.y = v.x = v.y = T(0);
+#pragma unroll
+        for (int t = 0; t < 4; ++t) {
+          u.x = fma(m.mx[t], ea[t], u.x);
+          u.y = fma(m.mx[t], eb[t], u.y);
+          v.x = fma(m.ax[t], ea[t], v.x);
+          v.y = fma(m.ax[t], eb[t], v.y);
+        }
+        w.x = fma(q3, b0[k].x + b0[k].y, q1 * (bl + b1[k].x));
+        w.y = fma(q3, b1[k].x + b1[k].y, q1 * (b0[k].y + bh));
+        if (at[k] >= 0) {
+          *reinterpret_cast<V2*>(&Us[buf][at[k]]) = u;
+          *reinterpret_cast<V2*>(&Vs[buf][at[k]]) = v;
+          *reinterpret_cast<V2*>(&Ws[buf][at[k]]) = w;
+        }
+      }
+      if (f + 1 < nz && f < f1) load(f + 1);
+      __syncthreads();
+      if (tid >= TPB) continue;  // more lanes than columns: whole waves
+      const int o = 2 * ly * RX + lx;
+      T p0 = T(0), p1 = T(0);
+#pragma unroll
+      for (int t = 0; t < 4; ++t) {
+        const T u = Us[buf][o + t * RX] + Us[buf][o + (7 - t) * RX];
+        const T v = Vs[buf][o + t * RX] + Vs[buf][o + (7 - t) * RX];
+        p0 = fma(m.my[t], u, p0);
+        p1 = fma(m.ay[t], u, fma(m.my[t], v, p1));
+      }
+      const T* W = &Ws[buf][o];
+      r[2] += fma(q3, W[3 * RX] + W[4 * RX], q1 * (W[2 * RX] + W[5 * RX]));
+      const T* zr = &Zt[(f - f0) * 10];  // row f - 2 + j holds plane f at its offset 2 - j
+#pragma unroll
+      for (int j = 0; j < 5; ++j) r[j] = fma(-zr[j * 10 + 4 - j], p0, fma(-zr[j * 10 + 9 - j], p1, r[j]));
+    }
+    // row z = f - 2 has all its planes
+    const int z = f - 2, Z = z >> 1;
+    if (z >= 0 && z < nz) {
+      if (z & 1) {
+        lo = fma(Z == nzc - 1 ? T(0.5) : q3, r[0], lo);
+        hi = fma(q1, r[0], hi);
+      } else {
+        lo = fma(q1, r[0], lo);
+        hi = fma(Z == 0 ? T(0.5) : q3, r[0], hi);
+        emit(Z - 1, lo);
+        lo = hi;
+        hi = T(0);
+      }
+    }
+#pragma unroll
+    for (int j = 0; j < 4; ++j) r[j] = r[j + 1];
+    r[4] = T(0);
+  }
+  if (Z1 == nzc) emit(nzc - 1, lo);  // no plane above the layer at the upper wall
+}
+
 // b_c = P^T r, and x_c = 0 (the coarse iterate of Alg. 3 starts from zero)
 template <typename T>
 __global__ __launch_bounds__(TPB) void k_restrict(T* __restrict__ bc, T* __restrict__ xc,
@@ -898,6 +1063,37 @@ hipError_t launch_residual_gal(T* r, const T* x, const T* b, const T* s1d, const
 }
 
 template <typename T>
+hipError_t launch_fold_residual(T* bc, T* xc, const T* x, const T* b, const T* zt,
+                                const FoldTaps<T>& m, int nx, int ny, int nz, int ncomp,
+                                hipStream_t s) {
+  const int nxc = nx >> 1, nyc = ny >> 1, nzc = nz >> 1;
+  if (nx % 4 || ny % 2 || nz % 2) return hipErrorInvalidValue;
+  if (nxc * nyc * nzc == 0) return hipSuccess;
+  auto go = [&](auto rx) {
+    constexpr int RX = decltype(rx)::value, RY = TPB / RX;
+    const int ntx = (nxc + RX - 1) / RX, nty = (nyc + RY - 1) / RY;
+    int zper = FOLD_Z;  // see launch_fold_residual0; six planes are a run's halo
+    auto groups = [&]() { return (int64_t)ntx * nty * ((nzc + zper - 1) / zper) * ncomp; };
+    while (zper > 2 && groups() < 512) zper /= 2;
+    // the time is that of a run's planes one after the other: a single layer where few groups
+    // share the chip (32^3 x 3: 9.0 against 10.4 us, but 64^3 x 3 14.0 against 13.3)
+    if (groups() < 128) zper = 1;
+    dim3 grid(ntx * nty, (nzc + zper - 1) / zper, ncomp);
+    // 512 lanes (one item of a plane each) where the work-groups are few, else two items a lane
+    // (64^3 x 3 11.1 / 13.3 us, 64^3 x 24 38.9 / 33.0)
+    if ((int64_t)grid.x * grid.y * grid.z < 640)
+      k_fold_residual<T, RX, 2 * TPB><<<grid, 2 * TPB, 0, s>>>(bc, xc, x, b, zt, nx, ny, nz, ntx,
+                                                               zper, m);
+    else
+      k_fold_residual<T, RX, TPB><<<grid, TPB, 0, s>>>(bc, xc, x, b, zt, nx, ny, nz, ntx, zper, m);
+  };
+  auto cover = [&](int rx, int ry) { return (int64_t)((nxc + rx - 1) / rx) * ((nyc + ry - 1) / ry); };
+  if (cover(32, 8) <= cover(16, 16)) go(std::integral_constant<int, 32>());
+  else go(std::integral_constant<int, 16>());
+  return hipGetLastError();
+}
+
+template <typename T>
 hipError_t launch_restrict(T* bc, T* xc, const T* r, int nxf, int nyf, int nzf, int ncomp,
                            hipStream_t s) {
   const uint32_t Nf = (uint32_t)nxf * nyf * nzf;
@@ -963,6 +1159,9 @@ hipError_t launch_level_noise(const NoiseGenArgs& a, const NoiseArgs& na, hipStr
                                                  hipStream_t);                                   \
   template hipError_t launch_residual_gal<T>(T*, const T*, const T*, const T*, const T*, int,    \
                                              int, int, int, hipStream_t);                        \
+  template hipError_t launch_fold_residual<T>(T*, T*, const T*, const T*, const T*,             \
+                                              const FoldTaps<T>&, int, int, int, int,          \
+                                              hipStream_t);                                     \
   template hipError_t launch_restrict<T>(T*, T*, const T*, int, int, int, int, hipStream_t);    \
   template hipError_t launch_prolong<T>(T*, const T*, int, int, int, int, hipStream_t);         \
   template hipError_t launch_coarsest<T>(T*, const T*, const double*, const double*, int, int,  \

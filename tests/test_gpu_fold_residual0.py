@@ -20,7 +20,7 @@ pytestmark = pytest.mark.gpu
     ((22, 8, 10), 2),     # eleven columns: window sums
     ((36, 32, 8), 1),     # 16 x 16 columns, the second column tile ragged
     ((64, 16, 20), 2),    # 32 x 8 columns exactly
-    ((68, 20, 12), 1),    # 32 x 8 with two columns beyond, ragged rows
+    ((68, 20, 4), 1),     # 32 x 8 with two columns beyond, ragged rows
     ((64, 64, 36), 5),    # 18 layers, 4 a work-group
     ((64, 64, 44), 33),   # 22 layers, 16 a work-group
 ])
@@ -45,3 +45,32 @@ def test_fold(dims, ncomp):
         for c in (0, ncomp - 1):
             ref = P.T @ ((b[c] if use_b else 0.0) - A @ x[c])
             assert np.max(np.abs(got[c] - ref)) <= 1e-12 * np.max(np.abs(ref))
+
+
+@pytest.mark.parametrize("dims,ncomp", [
+    ((8, 8, 4), 1),       # level 1 of 4 x 4 x 2: one lane is a whole row, both walls in a layer
+    ((72, 40, 24), 2),    # 36 x 20 x 12: 16 x 16 columns, ragged in x and y
+    ((128, 32, 40), 1),   # 64 x 16 x 20: 32 x 8 columns exactly, a layer a work-group
+    ((136, 16, 8), 3),    # 68 x 8 x 4: two columns beyond the second tile
+    ((64, 64, 40), 60),   # 32 x 32 x 20 x 60: several layers a work-group, the last run short
+    ((64, 64, 64), 170),  # 32 x 32 x 32 x 170: two items a lane
+])
+def test_fold_block_level(dims, ncomp):
+    """The same on level 1 (a block level), whose tiles also come with 512 or 256 lanes."""
+    from paper_1003_2680_amd.api import Hierarchy
+    print("[gpu-case] folded block-level restriction %s x %d" % (dims, ncomp), flush=True)
+    # level 2 is smoothed where it can be, else drawn
+    smooth = dims[0] % 16 == 0 and dims[1] % 16 == 0 and dims[2] % 8 == 0
+    kw = dict(levels=3, coarsest="smooth") if smooth else dict(levels=3, coarsest_max=4096)
+    H = Hierarchy(*dims, ncomp=ncomp, **kw)
+    mg = StochasticMG(*dims, **kw)
+    L, C = mg.levels[1], mg.levels[2]
+    x, b = np.random.default_rng(4).standard_normal((2, ncomp, L.n))
+    shape = (ncomp,) + tuple(reversed(L.dims))
+    out = torch.empty((ncomp, C.n), dtype=torch.float64, device="cuda")
+    H.debug_restrict_residual(1, torch.from_numpy(x.reshape(shape)).cuda(),
+                              torch.from_numpy(b.reshape(shape)).cuda(), out)
+    got = out.cpu().numpy()
+    for c in (0, ncomp - 1):
+        ref = L.P.T @ (b[c] - L.A @ x[c])
+        assert np.max(np.abs(got[c] - ref)) <= 1e-12 * np.max(np.abs(ref))
