@@ -879,7 +879,7 @@ int plan(Composite& C, const smg_composite_desc& d, const smg_fac_params& p, std
   }
   C.off_ainv = take((size_t)C.ncd * C.ncd * 8);
   C.off_w = take((size_t)C.ncd * C.ncd * 8);
-  C.off_part = take((size_t)((std::max(nbase, nf) + 255) / 256 + 1) * 8);
+  C.off_part = take((size_t)((nbase + 255) / 256 + (nf + 255) / 256) * 8);
   C.off_norm = take(64);
   C.off_znoise = take((size_t)C.ncd * 8);
   C.ws_bytes = off;

@@ -87,7 +87,7 @@ hipError_t launch_comp_residual(double* rc, double* rf, const double* xc, const 
 hipError_t launch_comp_bridge(float* rc, float* rf, float* ec, float* ef, const double* xc,
                               const double* xf, const double* bc, const double* bf,
                               const CompGeom& g, hipStream_t s);
-// out[0] = ||(bc, bf) - A (xc, xf)||^2 (fixed order); part: a double per 1024 base or fine cells
+// out[0] = ||(bc, bf) - A (xc, xf)||^2 (fixed order); part: a double per 256 base or fine cells
 hipError_t launch_comp_residual_norm(double* out, double* part, const double* xc, const double* xf,
                                      const double* bc, const double* bf, const CompGeom& g,
                                      hipStream_t s);

@@ -5,6 +5,8 @@
 // described in composite.hpp.  T is the storage and arithmetic type of a sweep: double in the
 // FP64 form, float for the inner cycle of the FP32-refined form (whose residual, refinement and
 // coarsest draw stay FP64).
+#include <type_traits>
+
 #include "composite.hpp"
 #include "device_common.hpp"
 #include "kernels.hpp"
@@ -412,10 +414,10 @@ __global__ __launch_bounds__(TPB) void k_comp_residual(TO* __restrict__ rc, TO* 
   }
 }
 
-// Its squares instead, one partial sum per work-group of kNormPer runs of TPB cells: the solve needs
-// no residual after a cycle, only its norm (written and summed field by field that was six
-// launches of about 3 us at 64x64x32).
-constexpr int kNormPer = 4;
+// Its squares instead, one partial sum per work-group of PER runs of TPB cells: the solve needs no
+// residual after a cycle, only its norm (written and summed field by field that was six launches of
+// about 3 us at 64x64x32).
+template <int PER>
 __global__ __launch_bounds__(TPB) void k_comp_residual_sq(double* __restrict__ part,
                                                           const double* __restrict__ xc,
                                                           const double* __restrict__ xf,
@@ -425,16 +427,16 @@ __global__ __launch_bounds__(TPB) void k_comp_residual_sq(double* __restrict__ p
   __shared__ double sh[TPB / 64];
   double sum = 0.0;
   if (blockIdx.x < coarse_wg) {
-    const uint32_t n = (uint32_t)g.nx * g.ny * g.nz, t0 = blockIdx.x * (kNormPer * TPB);
-    for (int q = 0; q < kNormPer; ++q) {
+    const uint32_t n = (uint32_t)g.nx * g.ny * g.nz, t0 = blockIdx.x * (PER * TPB);
+    for (int q = 0; q < PER; ++q) {
       const uint32_t t = t0 + q * TPB + threadIdx.x;
       const double r = t < n ? res_coarse<double>(xc, xf, bc, g, t) : 0.0;
       sum = fma(r, r, sum);
     }
   } else {
     const uint32_t n = (uint32_t)g.fx * g.fy * g.fz,
-                   t0 = (blockIdx.x - coarse_wg) * (kNormPer * TPB);
-    for (int q = 0; q < kNormPer; ++q) {
+                   t0 = (blockIdx.x - coarse_wg) * (PER * TPB);
+    for (int q = 0; q < PER; ++q) {
       const uint32_t t = t0 + q * TPB + threadIdx.x;
       const double r = t < n ? res_fine<double>(xf, xc, bf, g, t) : 0.0;
       sum = fma(r, r, sum);
@@ -993,10 +995,19 @@ hipError_t launch_comp_bridge(float* rc, float* rf, float* ec, float* ef, const 
 hipError_t launch_comp_residual_norm(double* out, double* part, const double* xc, const double* xf,
                                      const double* bc, const double* bf, const CompGeom& g,
                                      hipStream_t s) {
-  auto groups = [](int64_t n) { return (uint32_t)((n + kNormPer * TPB - 1) / (kNormPer * TPB)); };
-  const uint32_t cw = groups((int64_t)g.nx * g.ny * g.nz);
-  const uint32_t all = cw + groups((int64_t)g.fx * g.fy * g.fz);
-  k_comp_residual_sq<<<all, TPB, 0, s>>>(part, xc, xf, bc, bf, g, cw);
+  const int64_t nb = (int64_t)g.nx * g.ny * g.nz, nf = (int64_t)g.fx * g.fy * g.fz;
+  uint32_t all = 0;
+  auto go = [&](auto per) {
+    constexpr int PER = decltype(per)::value;
+    auto groups = [](int64_t n) { return (uint32_t)((n + PER * TPB - 1) / (PER * TPB)); };
+    const uint32_t cw = groups(nb);
+    all = cw + groups(nf);
+    k_comp_residual_sq<PER><<<all, TPB, 0, s>>>(part, xc, xf, bc, bf, g, cw);
+  };
+  // four cells a thread leave a quarter of the partials to the one work-group that adds them; on
+  // small meshes the cells one after the other cost more (64x64x32: 10.9 against 4.8 us)
+  if (nb + nf >= (1 << 21)) go(std::integral_constant<int, 4>());
+  else go(std::integral_constant<int, 1>());
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   return launch_sumsq_final_parts(out, part, all, 1, s);
