@@ -420,33 +420,10 @@ int build_plan(const smg_grid_desc& d, const smg_cycle_params& p, Hierarchy& h, 
       v.off_noise = take((size_t)(p.nu1 + p.nu2) * n * ts);
     }
   }
-  // Bottom of the V-cycle: the first level with at most kBottomCells cells and every level below
-  // it live in one work-group's LDS per component (x, b and one scratch field per level; the
-  // coarsest draw stages b and the noise).  A whole hierarchy of that size, its point level
-  // included, is one launch a cycle; where its LDS does not hold that, the bottom begins below.
-  for (int l = h.lv[0].kind == KIND_POINT ? 0 : 1; l < L; ++l) {
-    if (h.lv[l].n > kBottomCells) continue;
-    size_t lds = 0;
-    for (int m = l; m < L; ++m) {
-      const Level& v = h.lv[m];
-      lds += bot_level_elems(v.kind, v.nx, v.ny, v.nz, ts) * ts;
-      if (v.kind == KIND_BLOCK) lds += bot_table_elems(v.nz) * ts;
-    }
-    if (lds <= kBottomLdsMax && L - l <= kBottomLevelsMax) {
-      h.bottom = l;
-      h.bottom_lds = lds;
-    } else if (l == 0) {
-      continue;
-    }
-    break;
-  }
-  if (h.bottom == 0) h.lv[0].off_noise = take((size_t)(p.nu1 + p.nu2) * nc * h.lv[0].n * ts);
-  h.wide_coarsest = h.bottom >= 0 && h.nc >= kWideCoarsest;
   if (h.nc > 0) {
     h.off_ainv = take((size_t)h.nc * h.nc * sizeof(double));
     h.off_w = take((size_t)h.nc * h.nc * sizeof(double));
   }
-  if (h.bottom >= 0) h.off_botargs = take(sizeof(BotArgs));
   // partial sums for the residual norms: one per 256-cell block of level 0
   h.part_len = (size_t)((h.lv[0].n + 255) / 256) + 2;
   h.off_part = take((size_t)nc * h.part_len * sizeof(double));
@@ -458,6 +435,45 @@ int build_plan(const smg_grid_desc& d, const smg_cycle_params& p, Hierarchy& h, 
     h.off_spart = take((size_t)nc * h.stats_nblk * (kMaxModes + 1) * sizeof(double));
   }
   h.off_chains = take((size_t)kMaxChains * sizeof(ChainKey));
+  // Bottom of the V-cycle: the first level with at most kBottomCells cells and every level below
+  // it live in one work-group's LDS per component (x, b and one scratch field per level; the
+  // coarsest draw stages b and the noise).  A whole hierarchy of that size, its point level
+  // included, is one launch a cycle; where its LDS does not hold that, the bottom begins below.
+  auto plan_bottom = [&](int from) {
+    for (int l = from; l < L; ++l) {
+      if (h.lv[l].n > kBottomCells) continue;
+      size_t lds = 0;
+      for (int m = l; m < L; ++m) {
+        const Level& v = h.lv[m];
+        lds += bot_level_elems(v.kind, v.nx, v.ny, v.nz, ts) * ts;
+        if (v.kind == KIND_BLOCK) lds += bot_table_elems(v.nz) * ts;
+      }
+      if (lds <= kBottomLdsMax && L - l <= kBottomLevelsMax) {
+        h.bottom = l;
+        h.bottom_lds = lds;
+      } else if (l == 0) {
+        continue;
+      }
+      return;
+    }
+  };
+  plan_bottom(h.lv[0].kind == KIND_POINT ? 0 : 1);
+  if (h.bottom == 0) {
+    // The point level in the bottom needs its normals in memory, (nu1 + nu2) fields: it stays out
+    // where they alone would make the hierarchy too large for the allocation-free entry point
+    // (16^3, V(8, 8), 128 components: 17 MiB without them, 81 MiB with).
+    const size_t noise = align_up((size_t)(p.nu1 + p.nu2) * nc * h.lv[0].n * ts);
+    const size_t args = align_up(sizeof(BotArgs));
+    if (off + args <= SMG_STATIC_SCRATCH_BYTES && off + args + noise > SMG_STATIC_SCRATCH_BYTES) {
+      h.bottom = -1;
+      h.bottom_lds = 0;
+      plan_bottom(1);
+    } else {
+      h.lv[0].off_noise = take(noise);
+    }
+  }
+  h.wide_coarsest = h.bottom >= 0 && h.nc >= kWideCoarsest;
+  if (h.bottom >= 0) h.off_botargs = take(sizeof(BotArgs));
   h.ws_bytes = off;
   return SMG_OK;
 }
