@@ -12,14 +12,28 @@
 
 #include <hip/hip_runtime.h>
 
+#include <type_traits>
+
 namespace smg {
 
-// The sampling passes in FP32 add up in index order (row, plane, lane), one term after the other:
+// What a cycle belongs to: a solve, a chain without noise (kT = 0) or a chain with it.
+enum CycleKind { CYCLE_SOLVE = 0, CYCLE_STILL = 1, CYCLE_NOISE = 2 };
+
+// The passes of a chain in FP32 add up in index order (row, plane, lane), one term after the other:
 // a refined chain carries its rounding from cycle to cycle into an FP64 state, which therefore
 // keeps the bits that the plain order of the sums gives.  FP64 sums and the FP32 correction of a
 // solve, whose rounding the next residual takes back, use the shorter symmetric forms.
-template <typename T, bool NOISE>
-constexpr bool index_order = NOISE && sizeof(T) == 4;
+template <typename T, int KIND>
+constexpr bool index_order = KIND != CYCLE_SOLVE && sizeof(T) == 4;
+
+// Runs go with the kind as a constant; an FP64 chain without noise makes a solve's passes.
+template <typename T, typename F>
+void by_kind(int kind, F go) {
+  if (kind == CYCLE_NOISE) go(std::integral_constant<int, CYCLE_NOISE>());
+  else if (sizeof(T) == 4 && kind == CYCLE_STILL)
+    go(std::integral_constant<int, sizeof(T) == 4 ? CYCLE_STILL : CYCLE_SOLVE>());
+  else go(std::integral_constant<int, CYCLE_SOLVE>());
+}
 
 // v of another lane of the same eight: quad_perm moves for lane ^ 1, ^ 2, ^ 3 and the mirror of
 // the eight lanes for lane ^ 7 (lane ^ 4 is ^ 3 of it).

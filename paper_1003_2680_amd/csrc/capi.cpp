@@ -62,11 +62,15 @@ struct Run {
   // FP32-refined form: the correction e is known to be zero (the previous cycle of this run
   // folded it into x and cleared it), so the next cycle need not clear it
   bool e_zero;
+  bool chain;  // part of a chain, with or without noise (not of a solve)
 };
 
 Run make_run(Hierarchy& h, hipStream_t s, bool noise, bool has_b0, uint64_t seed,
-             uint64_t cycle) {
-  return Run{&h, s, noise, has_b0, seed, cycle, h.desc.ncomp, nullptr, 1, 0, false};
+             uint64_t cycle, bool chain = false) {
+  return Run{&h, s, noise, has_b0, seed, cycle, h.desc.ncomp, nullptr, 1, 0, false, chain};
+}
+int kind_of(const Run& r) {
+  return r.noise ? CYCLE_NOISE : (r.chain ? CYCLE_STILL : CYCLE_SOLVE);
 }
 
 // The run's share of a component-major buffer with `per` elements per component (null stays
@@ -267,10 +271,11 @@ int sweep(Run& r, int l, int slot, bool post) {
       const int cz = post ? 1 - q : q;
       const HalfPassItem<T> it = half_item<T>(r, l, t, post, cz, half);
       if (half) {
-        SMG_HIP(launch_block_half<T>(&it, 1, cz, post, r.noise, r.s));
+        SMG_HIP(launch_block_half<T>(&it, 1, cz, post, kind_of(r), r.s));
       } else {
         for (int k = 0; k < 2; ++k)
-          SMG_HIP(launch_block_pair<T>(&it, 1, 4 * cz + (post ? 3 - 2 * k : 2 * k), r.noise, r.s));
+          SMG_HIP(launch_block_pair<T>(&it, 1, 4 * cz + (post ? 3 - 2 * k : 2 * k), kind_of(r),
+                                       r.s));
       }
     }
     SMG_TRY(ts.close());
@@ -284,7 +289,7 @@ int sweep(Run& r, int l, int slot, bool post) {
     SMG_TRY(ts.rc);
     for (int t = 0; t < 8; ++t)
       SMG_HIP(launch_block_pass<T>(x, b, (const T*)v.s1d_d, (const T*)v.bfac_d, v.nx,
-                                   v.ny, v.nz, r.nc, post ? 7 - t : t,
+                                   v.ny, v.nz, r.nc, post ? 7 - t : t, kind_of(r),
                                    zn, h.block_tile, r.s));
     SMG_TRY(ts.close());
   }
@@ -325,16 +330,16 @@ int restrict_residual(Run& r, int l) {
         bc, xc, comp_at(xr, hn, r), comp_at(xr + half_field(h), hn, r),
         r.has_b0 ? comp_at(br, hn, r) : nullptr,
         r.has_b0 ? comp_at(br + half_field(h), hn, r) : nullptr, v.nx, v.ny, v.nz, nc, h.desc.h,
-        r.noise, r.s));
+        r.chain, r.s));
     return SMG_OK;
   }
-  if (sizeof(T) == 8 || !r.noise) {
+  if (sizeof(T) == 8 || !r.chain) {
     SMG_HIP(launch_fold_residual<T>(bc, xc, comp_at(Fld<T>::x(v), v.n, r),
                                     comp_at(Fld<T>::b(v), v.n, r), (const T*)v.zt_d,
                                     level_taps<T>(v), v.nx, v.ny, v.nz, nc, r.s));
     return SMG_OK;
   }
-  // the FP32 sampling cycle keeps its order of additions
+  // an FP32 chain keeps its order of additions
   SMG_HIP(launch_residual_gal<T>(rr, comp_at(Fld<T>::x(v), v.n, r), comp_at(Fld<T>::b(v), v.n, r),
                                  (const T*)v.s1d_d, (const T*)v.zt_d, v.nx, v.ny, v.nz, nc, r.s));
   SMG_HIP(launch_restrict<T>(bc, xc, rr, v.nx, v.ny, v.nz, nc, r.s));
@@ -490,7 +495,7 @@ int bottom_cycle(Run& r) {
   TimedScope ts(h, r.s, SMG_TIMED_BOTTOM, 1);
   SMG_TRY(ts.rc);
   auto launch = [&](BotPart part) -> int {
-    SMG_HIP(launch_bottom<T>(h.botargs_d, r.nc, r.c0, h.bottom_lds, r.noise, point_bottom(h),
+    SMG_HIP(launch_bottom<T>(h.botargs_d, r.nc, r.c0, h.bottom_lds, kind_of(r), point_bottom(h),
                              bottom_part(r, part), na, r.s));
     return SMG_OK;
   };
@@ -629,11 +634,11 @@ bool half_lockstep(const std::vector<Run>& legs, int l) {
 }
 
 // The four block colours of layer parity cz in sweep `t` (0-based) of level l for every listed run
-// that has it (level l above its bottom, t < its sweeps on the given leg, noise as given): in one
+// that has it (level l above its bottom, t < its sweeps on the given leg, kind as given): in one
 // or two launches for the levels that take several colours a launch, in a launch per colour for
 // the others.
 template <typename T>
-int block_half_lockstep(const std::vector<Run>& legs, int l, int t, bool post, int cz, bool noise,
+int block_half_lockstep(const std::vector<Run>& legs, int l, int t, bool post, int cz, int kind,
                         hipStream_t s) {
   std::vector<BlockPassItem<T>> items;
   std::vector<HalfPassItem<T>> multi;
@@ -641,7 +646,7 @@ int block_half_lockstep(const std::vector<Run>& legs, int l, int t, bool post, i
   int tile = -1;
   for (const Run& r : legs) {
     Hierarchy& h = *r.h;
-    if (r.noise != noise || l >= h.bottom) continue;
+    if (kind_of(r) != kind || l >= h.bottom) continue;
     Level& v = h.lv[l];
     if (v.kind != KIND_BLOCK) continue;
     if (t >= (post ? h.prm.nu2 : h.prm.nu1)) continue;
@@ -658,14 +663,14 @@ int block_half_lockstep(const std::vector<Run>& legs, int l, int t, bool post, i
   }
   const int nm = (int)multi.size(), ni = (int)items.size();
   if (nm && half) {
-    SMG_HIP(launch_block_half<T>(multi.data(), nm, cz, post, noise, s));
+    SMG_HIP(launch_block_half<T>(multi.data(), nm, cz, post, kind, s));
   } else if (nm) {
     for (int k = 0; k < 2; ++k)
-      SMG_HIP(launch_block_pair<T>(multi.data(), nm, 4 * cz + (post ? 3 - 2 * k : 2 * k), noise,
+      SMG_HIP(launch_block_pair<T>(multi.data(), nm, 4 * cz + (post ? 3 - 2 * k : 2 * k), kind,
                                    s));
   }
   for (int q = 0; q < 4 && ni; ++q)
-    SMG_HIP(launch_block_pass_multi<T>(items.data(), ni, 4 * cz + (post ? 3 - q : q), noise, tile,
+    SMG_HIP(launch_block_pass_multi<T>(items.data(), ni, 4 * cz + (post ? 3 - q : q), kind, tile,
                                        s));
   return SMG_OK;
 }
@@ -724,8 +729,8 @@ int legs_lockstep(const std::vector<Run>& legs, bool down) {
           }
       }
       for (int q = 0; q < 2; ++q)
-        for (int nz = 0; nz < 2; ++nz)
-          SMG_TRY(block_half_lockstep<T>(legs, l, t, !down, down ? q : 1 - q, nz != 0, s));
+        for (int kind = 0; kind < 3; ++kind)
+          SMG_TRY(block_half_lockstep<T>(legs, l, t, !down, down ? q : 1 - q, kind, s));
       for (const Run& r : legs) {
         const int nsw = down ? r.h->prm.nu1 : r.h->prm.nu2;
         if (l < r.h->bottom && t + 1 == nsw && multi_colour(*r.h, r.h->lv[l]) &&
@@ -760,12 +765,12 @@ int full_cycle(Run& r, bool residual_ready = false) {
 }
 
 // The LDS-resident bottoms of every run that has one, in as few launches as possible (one per
-// sweep precision and noise setting, up to kBotMultiItems hierarchies and kBotMultiWG
+// sweep precision and kind of cycle, up to kBotMultiItems hierarchies and kBotMultiWG
 // components each; a run with more components takes launches of its own).  Runs with a wide
 // coarsest draw go down with the others, make their draws in a launch each, and go up together.
 int batch_bottoms(const std::vector<Run*>& runs) {
   for (int f32 = 0; f32 < 2; ++f32)
-    for (int nz = 0; nz < 2; ++nz) {
+    for (int kind = 0; kind < 3; ++kind) {
       BotMultiArgs m{};
       m.bm = box_muller_coef();
       int nwg = 0;
@@ -774,8 +779,8 @@ int batch_bottoms(const std::vector<Run*>& runs) {
       hipStream_t s = nullptr;
       auto flush = [&]() -> int {
         if (m.nitems == 0) return SMG_OK;
-        hipError_t e = f32 ? launch_bottom_multi<float>(m, nwg, lds, nz != 0, point, s)
-                           : launch_bottom_multi<double>(m, nwg, lds, nz != 0, point, s);
+        hipError_t e = f32 ? launch_bottom_multi<float>(m, nwg, lds, kind, point, s)
+                           : launch_bottom_multi<double>(m, nwg, lds, kind, point, s);
         if (e != hipSuccess) {
           set_error(std::string("launch_bottom_multi: ") + hipGetErrorString(e));
           return SMG_EHIP;
@@ -813,7 +818,7 @@ int batch_bottoms(const std::vector<Run*>& runs) {
       std::vector<Run*> wide;
       for (Run* r : runs) {
         Hierarchy& h = *r->h;
-        if (!split_bottom(h) || (int)refined(h) != f32 || (int)r->noise != nz) continue;
+        if (!split_bottom(h) || (int)refined(h) != f32 || kind_of(*r) != kind) continue;
         if (r->nc > kBotMultiWG || h.lv[h.bottom].kind == KIND_CHOL) {  // launches of its own
           Run ri = *r;
           ri.has_b0 = ri.has_b0 || refined(h);
@@ -837,7 +842,7 @@ int batch_bottoms(const std::vector<Run*>& runs) {
 
 // One cycle of several runs on one stream (distinct hierarchies): every run's down-leg, then
 // the LDS-resident bottoms of all runs that have one in as few launches as possible (one per
-// sweep precision and noise setting, up to kBotMultiItems hierarchies and kBotMultiWG
+// sweep precision and kind of cycle, up to kBotMultiItems hierarchies and kBotMultiWG
 // components each), then every run's up-leg.  Each run's own kernels keep their order and the
 // runs touch disjoint memory, so every run computes exactly what full_cycle computes.
 // `phases`: PH_PRE (noise, bridge in, down-legs), PH_BOTTOM, PH_POST (up-legs, bridge out), or
@@ -1185,7 +1190,7 @@ struct SampleJob {
     field = (int64_t)nc * v0.n;
     SMG_TRY(import_level0(h, v0.x, (const double*)state, s, nc));
     if (v0.kind == KIND_CHOL) SMG_HIP(launch_zero<double>(v0.b, field, s));
-    r = make_run(h, s, h.desc.kT > 0.0, false, seed, first_cycle);
+    r = make_run(h, s, h.desc.kT > 0.0, false, seed, first_cycle, true);
     r.nc = nc;
     if (bt.nchains > 0) {
       r.chains = h.chains_d;
@@ -2038,7 +2043,7 @@ int smg_debug_smooth(smg_hierarchy* hh, int32_t level, int32_t colour, void* x, 
     if (r.noise) SMG_TRY(gen_level_noise<double>(r, level, slot));
     SMG_HIP(launch_block_pass<double>((double*)x, (const double*)b, (const double*)v.s1d_d,
                                       (const double*)v.bfac_d, v.nx, v.ny,
-                                      v.nz, h.desc.ncomp, colour,
+                                      v.nz, h.desc.ncomp, colour, kind_of(r),
                                       r.noise ? (const double*)v.noise_d : nullptr,
                                       h.block_tile, s));
   }

@@ -97,11 +97,11 @@ hipError_t launch_rb_pass(T* xc, const T* xo, const T* bc, int nx, int ny, int n
                           int colour, double h, double kT, bool noise, const NoiseArgs& na,
                           hipStream_t s);
 // b_c = P^T (b - A x) from split level-0 storage straight to the natural coarse level (r is
-// never written); also x_c = 0 when xc is not null.  br/bb null = 0.  noise: part of a sampling cycle.
+// never written); also x_c = 0 when xc is not null.  br/bb null = 0.  chain: part of a chain's cycle.
 template <typename T>
 hipError_t launch_restrict_residual0(T* bc, T* xc, const T* xr, const T* xb, const T* br,
                                      const T* bb, int nx, int ny, int nz, int ncomp, double h,
-                                     bool noise, hipStream_t s);
+                                     bool chain, hipStream_t s);
 // colours: bit c set = add P e to the sites of colour c
 template <typename T>
 hipError_t launch_prolong0(T* xr, T* xb, const T* e, int nxf, int nyf, int nzf, int ncomp,
@@ -134,11 +134,11 @@ hipError_t launch_restrict(T* bc, T* xc, const T* r, int nxf, int nyf, int nzf, 
 template <typename T>
 hipError_t launch_prolong(T* x, const T* e, int nxf, int nyf, int nzf, int ncomp, hipStream_t s);
 // z: pregenerated noise of this pass's sweep, [ncomp][N], each block's normals already
-// multiplied by sqrt(kT) L_BB^-T (null without noise); tile: one of the SMG_TILE_* shapes of
-// smg.h (SMG_TILE_AUTO picks by work-group count)
+// multiplied by sqrt(kT) L_BB^-T (null without noise); kind: a CycleKind, here and below; tile: one
+// of the SMG_TILE_* shapes of smg.h (SMG_TILE_AUTO picks by work-group count)
 template <typename T>
 hipError_t launch_block_pass(T* x, const T* b, const T* s1d, const T* bfac, int nx,
-                             int ny, int nz, int ncomp, int colour, const T* z, int tile,
+                             int ny, int nz, int ncomp, int colour, int kind, const T* z, int tile,
                              hipStream_t s);
 // Several colours a launch.  Items of launch_block_half and launch_block_pair: levels with nx <=
 // 128 and nx, ny multiples of 4 (hipErrorNotSupported otherwise, before any launch).
@@ -183,13 +183,13 @@ struct HalfArgs {
   HalfItem<T> it[kHalfItems];
 };
 template <typename T>
-hipError_t launch_block_half(const HalfPassItem<T>* items, int n, int cz, bool post, bool noise,
+hipError_t launch_block_half(const HalfPassItem<T>* items, int n, int cz, bool post, int kind,
                              hipStream_t s);
 
 // Block colours c_first and then c_first ^ 1 of one sweep, in place on xn (xs, xo unused), for the
 // levels launch_block_half takes.
 template <typename T>
-hipError_t launch_block_pair(const HalfPassItem<T>* items, int n, int c_first, bool noise,
+hipError_t launch_block_pair(const HalfPassItem<T>* items, int n, int c_first, int kind,
                              hipStream_t s);
 
 // One level-0 colour pass over several hierarchies in one launch (up to 8 per launch): each
@@ -242,7 +242,7 @@ struct BlockMultiArgs {
   BlockMultiItem<T> it[kBlockMultiItems];
 };
 template <typename T>
-hipError_t launch_block_pass_multi(const BlockPassItem<T>* items, int n, int colour, bool noise,
+hipError_t launch_block_pass_multi(const BlockPassItem<T>* items, int n, int colour, int kind,
                                    int tile, hipStream_t s);
 template <typename T>
 hipError_t launch_level_noise(const NoiseGenArgs& a, const NoiseArgs& na, hipStream_t s);
@@ -250,7 +250,7 @@ hipError_t launch_level_noise(const NoiseGenArgs& a, const NoiseArgs& na, hipStr
 // work-group each; the noise is keyed by those absolute component numbers).  point: the bottom
 // begins at a point level; part: a BotPart, plus kBotHasB
 template <typename T>
-hipError_t launch_bottom(const BotArgs* a, int ncomp, int c0, size_t lds, bool noise, bool point,
+hipError_t launch_bottom(const BotArgs* a, int ncomp, int c0, size_t lds, int kind, bool point,
                          int part, const NoiseArgs& na, hipStream_t s);
 // The bottoms of several hierarchies in one launch (kernel arguments only): item i brings its
 // device BotArgs and its noise keys; work-group w runs component wg[w] >> 16 of item
@@ -273,7 +273,7 @@ struct BotMultiArgs {
   uint32_t wg[kBotMultiWG];
 };
 template <typename T>
-hipError_t launch_bottom_multi(const BotMultiArgs& m, int nwg, size_t lds, bool noise, bool point,
+hipError_t launch_bottom_multi(const BotMultiArgs& m, int nwg, size_t lds, int kind, bool point,
                                hipStream_t s);
 // x = A_c^-1 b (+ sqrt(kT) L_c^-T n), FP64 arithmetic, T storage; round: the normals are taken in
 // T, as the bottom's own draw holds them

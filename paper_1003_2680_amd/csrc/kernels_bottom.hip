@@ -89,11 +89,11 @@ __device__ __forceinline__ void bot_store(T* X, int p, int x, int nx, T v) {
 // us per pass, and 0.55 with the bank-free strides).  Without ONE
 // (the flat levels whose nz is not a multiple of four, where one layer parity holds more than
 // half of the blocks) the work-group goes over the colour in rounds.
-template <typename T, bool NOISE, int SPLIT, bool ONE>
+template <typename T, int KIND, int SPLIT, bool ONE>
 __device__ __forceinline__ void bot_sweeps_as(T* X, const T* B, const BotLevel& L, const T* tab,
                                               int slot0, int nslot, bool post, gptr<T> Z,
                                               size_t slot_stride) {
-  constexpr bool INDEX = index_order<T, NOISE>;
+  constexpr bool NOISE = KIND == CYCLE_NOISE, INDEX = index_order<T, KIND>;
   using Weights = BlockWeights<T, SPLIT, INDEX>;
   T s1d[20];
 #pragma unroll
@@ -204,7 +204,7 @@ __device__ __forceinline__ void bot_sweeps_as(T* X, const T* B, const BotLevel& 
   }
 }
 
-template <typename T, bool NOISE>
+template <typename T, int KIND>
 __device__ __forceinline__ void bot_sweeps(T* X, const T* B, const BotLevel& L, const T* tab,
                                            int slot0, int nslot, bool post, gptr<T> Z,
                                            size_t slot_stride) {
@@ -212,14 +212,14 @@ __device__ __forceinline__ void bot_sweeps(T* X, const T* B, const BotLevel& L, 
   // lanes of the larger layer parity's colours
   const int lanes = (L.nx >> 2) * (L.ny >> 2) * (((L.nz >> 1) + 1) >> 1) * 8;
   if (4 * lanes <= BOT_TPB)
-    bot_sweeps_as<T, NOISE, 4, true>(X, B, L, tab, slot0, nslot, post, Z, slot_stride);
+    bot_sweeps_as<T, KIND, 4, true>(X, B, L, tab, slot0, nslot, post, Z, slot_stride);
   else if (lanes <= BOT_TPB)
-    bot_sweeps_as<T, NOISE, 1, true>(X, B, L, tab, slot0, nslot, post, Z, slot_stride);
+    bot_sweeps_as<T, KIND, 1, true>(X, B, L, tab, slot0, nslot, post, Z, slot_stride);
   else
-    bot_sweeps_as<T, NOISE, 1, false>(X, B, L, tab, slot0, nslot, post, Z, slot_stride);
+    bot_sweeps_as<T, KIND, 1, false>(X, B, L, tab, slot0, nslot, post, Z, slot_stride);
 }
 
-// r = b - A x on a block level in LDS, in index order (the FP32 sampling cycle): a thread takes a
+// r = b - A x on a block level in LDS, in index order (the FP32 chain): a thread takes a
 // column of cells (or a part of one, so that the whole work-group has work) and marches up z,
 // forming each plane's two in-plane sums once and keeping the five that the current cell reaches.
 template <typename T>
@@ -450,13 +450,14 @@ __device__ __forceinline__ void point_noise(T (&z)[PT_PER], const PointSites<T>&
 }
 
 // Sweeps slot0 .. slot0 + nslot - 1; z holds the normals of the first pass (point_noise).
-template <typename T, bool NOISE>
+template <typename T, int KIND>
 __device__ __forceinline__ void point_sweeps(T* X, const T* B, bool has_b, const BotLevel& L,
                                              const PointSites<T>& S, T (&z)[PT_PER], gptr<T> Z,
                                              size_t slot_stride, int slot0, int nslot, bool post) {
+  constexpr bool NOISE = KIND == CYCLE_NOISE;
   const int nsite = S.nsite;
   // FP32: the order of the z-neighbours' sum in the colour-pass launches (launch_rb_pass)
-  const bool vec = !index_order<T, NOISE> || (L.nx >> 1) % (16 / (int)sizeof(T)) == 0;
+  const bool vec = !index_order<T, KIND> || (L.nx >> 1) % (16 / (int)sizeof(T)) == 0;
   T dg[10];
 #pragma unroll
   for (int e = 0; e < 10; ++e) dg[e] = (T)L.s1d[e];  // uniform: scalar registers
@@ -551,9 +552,10 @@ __device__ __forceinline__ T point_restrict(const T* R, int nx, int ny, int nz, 
 }
 
 // POINT: the first level may be a point level (level 0).
-template <typename T, bool NOISE, bool POINT>
+template <typename T, int KIND, bool POINT>
 __device__ __forceinline__ void bottom_body(const BotArgs& a, const uint32_t comp,
                                             const NoiseArgs& na, int part_b) {
+  constexpr bool NOISE = KIND == CYCLE_NOISE;
   const int part = part_b & 3;
   const bool has_b = part_b & kBotHasB;
   extern __shared__ char smraw[];
@@ -656,12 +658,12 @@ __device__ __forceinline__ void bottom_body(const BotArgs& a, const uint32_t com
     if (NOISE && a.nu1 > 0) point_noise<T>(pz, ps, pn, pstride, 0, 0, false);
     point_load(ps);
     __syncthreads();
-    point_sweeps<T, NOISE>(X, X + n0, has_b, L0, ps, pz, pn, pstride, 0, a.nu1, false);
+    point_sweeps<T, KIND>(X, X + n0, has_b, L0, ps, pz, pn, pstride, 0, a.nu1, false);
     if (NOISE && part != BOT_DOWN && a.nu2 > 0)
       point_noise<T>(pz, ps, pn, pstride, a.nu1, 0, true);
     if (a.nlev == 1) {
       // smoothing-only: the post-sweeps follow at once
-      point_sweeps<T, NOISE>(X, X + n0, has_b, L0, ps, pz, pn, pstride, a.nu1, a.nu2, true);
+      point_sweeps<T, KIND>(X, X + n0, has_b, L0, ps, pz, pn, pstride, a.nu1, a.nu2, true);
       point_store(ps);
       return;
     }
@@ -677,7 +679,7 @@ __device__ __forceinline__ void bottom_body(const BotArgs& a, const uint32_t com
       divmod_uniform(q, C.nx, r, Xc);
       divmod_uniform(r, C.ny, Z, Y);
       xc[C.nz * C.sz + q] =
-          index_order<T, NOISE>
+          index_order<T, KIND>
               ? point_restrict<T>(X + 2 * n0, L0.nx, L0.ny, L0.nz, Xc, Y, Z)
               : restrict_at<T>(X + 2 * n0, L0.nx, L0.nx * L0.ny, L0.nx, L0.ny, L0.nz, Xc, Y, Z);
     }
@@ -723,10 +725,10 @@ __device__ __forceinline__ void bottom_body(const BotArgs& a, const uint32_t com
     const T* tab = sm + a.tab_off[i];
     const gptr<T> Z = global_ptr<T>(L.noise) + (size_t)comp * n;
     const size_t zs = (size_t)a.ncomp * n;
-    bot_sweeps<T, NOISE>(xi, bi, L, tab, 0, a.nu1, false, Z, zs);
+    bot_sweeps<T, KIND>(xi, bi, L, tab, 0, a.nu1, false, Z, zs);
     if (i == a.nlev - 1) {
       // smoothing-only coarsest level: the post-sweeps follow at once
-      bot_sweeps<T, NOISE>(xi, bi, L, tab, a.nu1, a.nu2, true, Z, zs);
+      bot_sweeps<T, KIND>(xi, bi, L, tab, a.nu1, a.nu2, true, Z, zs);
       last = i;
       break;
     }
@@ -742,7 +744,7 @@ __device__ __forceinline__ void bottom_body(const BotArgs& a, const uint32_t com
     T* xc = sm + a.lds_off[i + 1];
     for (int q = tid; q < C.nz * C.sz; q += BOT_TPB) xc[q] = T(0);
     T* bc = xc + C.nz * C.sz;
-    if constexpr (index_order<T, NOISE>) {
+    if constexpr (index_order<T, KIND>) {
       bot_residual<T>(ri, xi, bi, L, tab);
       __syncthreads();
       for (int q = tid; q < C.nx * C.ny * C.nz; q += BOT_TPB) {
@@ -771,7 +773,7 @@ __device__ __forceinline__ void bottom_body(const BotArgs& a, const uint32_t com
                 xi[p] + prolong_at<T>(xc, C.sy, C.sz, x, y, z, C.nx, C.ny, C.nz));
     }
     __syncthreads();
-    bot_sweeps<T, NOISE>(xi, xi + L.nz * L.sz, L, sm + a.tab_off[i], a.nu1, a.nu2, true,
+    bot_sweeps<T, KIND>(xi, xi + L.nz * L.sz, L, sm + a.tab_off[i], a.nu1, a.nu2, true,
                          global_ptr<T>(L.noise) + (size_t)comp * n, (size_t)a.ncomp * n);
   }
   if (point) {
@@ -797,7 +799,7 @@ __device__ __forceinline__ void bottom_body(const BotArgs& a, const uint32_t com
             prolong_at<T>(xc, C.sy, C.sz, x, y, z, C.nx, C.ny, C.nz);
       }
     __syncthreads();
-    point_sweeps<T, NOISE>(X, X + n0, has_b, L0, ps, pz, pn, pstride, a.nu1, a.nu2, true);
+    point_sweeps<T, KIND>(X, X + n0, has_b, L0, ps, pz, pn, pstride, a.nu1, a.nu2, true);
     point_store(ps);
     return;
   }
@@ -808,17 +810,17 @@ __device__ __forceinline__ void bottom_body(const BotArgs& a, const uint32_t com
 }
 
 // One hierarchy, one work-group per component.
-template <typename T, bool NOISE, bool POINT>
+template <typename T, int KIND, bool POINT>
 __global__ __launch_bounds__(BOT_TPB)
 __attribute__((amdgpu_waves_per_eu(2, 2))) void k_bottom(const BotArgs* __restrict__ ap, int c0,
                                                     int part, NoiseArgs na) {
-  bottom_body<T, NOISE, POINT>(*ap, c0 + (int)blockIdx.x, na, part);
+  bottom_body<T, KIND, POINT>(*ap, c0 + (int)blockIdx.x, na, part);
 }
 
 // Several hierarchies (of any sizes) in one launch: work-group w runs component wg >> 16 of
 // item wg & 0xffff, with that item's level descriptors and noise keys, so the latency-bound
 // bottoms of uneven instances overlap instead of running one launch after another.
-template <typename T, bool NOISE, bool POINT>
+template <typename T, int KIND, bool POINT>
 __global__ __launch_bounds__(BOT_TPB)
 __attribute__((amdgpu_waves_per_eu(2, 2))) void k_bottom_multi(BotMultiArgs m) {
   const uint32_t w = m.wg[blockIdx.x];
@@ -834,7 +836,7 @@ __attribute__((amdgpu_waves_per_eu(2, 2))) void k_bottom_multi(BotMultiArgs m) {
   na.comps_per_chain = it.cpc;
   na.cpc_magic = it.cpc_magic;
   na.bm = m.bm;
-  bottom_body<T, NOISE, POINT>(*it.args, w >> 16, na, it.part);
+  bottom_body<T, KIND, POINT>(*it.args, w >> 16, na, it.part);
 }
 
 }  // namespace
@@ -850,45 +852,47 @@ static hipError_t big_lds(K k, bool& set) {
 }
 
 template <typename T>
-hipError_t launch_bottom(const BotArgs* a, int ncomp, int c0, size_t lds, bool noise, bool point,
+hipError_t launch_bottom(const BotArgs* a, int ncomp, int c0, size_t lds, int kind, bool point,
                          int part, const NoiseArgs& na, hipStream_t s) {
-  auto go = [&](auto nz, auto pt) -> hipError_t {
+  hipError_t rc = hipSuccess;
+  auto go = [&](auto kd, auto pt) -> hipError_t {
     static bool set = false;
-    auto k = k_bottom<T, decltype(nz)::value, decltype(pt)::value>;
+    auto k = k_bottom<T, decltype(kd)::value, decltype(pt)::value>;
     const hipError_t e = big_lds(k, set);
     if (e != hipSuccess) return e;
     k<<<ncomp, BOT_TPB, lds, s>>>(a, c0, part, na);
     return hipGetLastError();
   };
-  if (noise) return point ? go(std::true_type(), std::true_type())
-                          : go(std::true_type(), std::false_type());
-  return point ? go(std::false_type(), std::true_type())
-               : go(std::false_type(), std::false_type());
+  by_kind<T>(kind, [&](auto kd) {
+    rc = point ? go(kd, std::true_type()) : go(kd, std::false_type());
+  });
+  return rc;
 }
 
 template <typename T>
-hipError_t launch_bottom_multi(const BotMultiArgs& m, int nwg, size_t lds, bool noise, bool point,
+hipError_t launch_bottom_multi(const BotMultiArgs& m, int nwg, size_t lds, int kind, bool point,
                                hipStream_t s) {
   if (nwg <= 0) return hipSuccess;
   if (nwg > kBotMultiWG || m.nitems > kBotMultiItems) return hipErrorInvalidValue;
-  auto go = [&](auto nz, auto pt) -> hipError_t {
+  hipError_t rc = hipSuccess;
+  auto go = [&](auto kd, auto pt) -> hipError_t {
     static bool set = false;
-    auto k = k_bottom_multi<T, decltype(nz)::value, decltype(pt)::value>;
+    auto k = k_bottom_multi<T, decltype(kd)::value, decltype(pt)::value>;
     const hipError_t e = big_lds(k, set);
     if (e != hipSuccess) return e;
     k<<<nwg, BOT_TPB, lds, s>>>(m);
     return hipGetLastError();
   };
-  if (noise) return point ? go(std::true_type(), std::true_type())
-                          : go(std::true_type(), std::false_type());
-  return point ? go(std::false_type(), std::true_type())
-               : go(std::false_type(), std::false_type());
+  by_kind<T>(kind, [&](auto kd) {
+    rc = point ? go(kd, std::true_type()) : go(kd, std::false_type());
+  });
+  return rc;
 }
 
 #define SMG_INST(T)                                                                  \
-  template hipError_t launch_bottom<T>(const BotArgs*, int, int, size_t, bool, bool, \
+  template hipError_t launch_bottom<T>(const BotArgs*, int, int, size_t, int, bool,  \
                                        int, const NoiseArgs&, hipStream_t);          \
-  template hipError_t launch_bottom_multi<T>(const BotMultiArgs&, int, size_t, bool, \
+  template hipError_t launch_bottom_multi<T>(const BotMultiArgs&, int, size_t, int,  \
                                              bool, hipStream_t);
 SMG_INST(double)
 SMG_INST(float)

@@ -1127,14 +1127,14 @@ static void launch_fold_residual0(T* bc, T* xc, const T* xr, const T* xb, const 
 template <typename T>
 hipError_t launch_restrict_residual0(T* bc, T* xc, const T* xr, const T* xb, const T* br,
                                      const T* bb, int nx, int ny, int nz, int ncomp, double h,
-                                     bool noise, hipStream_t s) {
+                                     bool chain, hipStream_t s) {
   const int nxc = nx >> 1, nyc = ny >> 1, nzc = nz >> 1;
   if (nxc * nyc * nzc == 0) return hipSuccess;
   const T ih2 = (T)(1.0 / (h * h));
   {
-    // the sampling cycle in FP32 keeps its order of additions (block_update.hpp: index_order), and
+    // a chain in FP32 keeps its order of additions (block_update.hpp: index_order), and
     // an odd number of coarse columns does not pair up
-    if ((sizeof(T) == 4 && noise) || nxc % 2) {
+    if ((sizeof(T) == 4 && chain) || nxc % 2) {
       auto go = [&](auto rx, auto ry) {
         constexpr int RX = decltype(rx)::value, RY = decltype(ry)::value;
         const int ntx = (nxc + RX - 1) / RX, nty = (nyc + RY - 1) / RY;

@@ -107,13 +107,14 @@ __global__ __launch_bounds__(TPB) void k_level_noise(NoiseGenArgs a, NoiseArgs n
 constexpr int TILE_D = 6;
 
 // The pass of one work-group: wg = (tile, block layer l, component).
-template <typename T, bool NOISE, int TILE_I, int TILE_J>
+template <typename T, int KIND, int TILE_I, int TILE_J>
 __device__ __forceinline__ void block_tile_body(T* __restrict__ xg, const T* __restrict__ bg,
                                                 const T* __restrict__ s1d,
                                                 const T* __restrict__ bfac, int nx, int ny,
                                                 int nz, uint32_t N, int colour, int nbx2,
                                                 int nby2, int ntx, const T* __restrict__ zn,
                                                 const Blk3 wg) {
+  constexpr bool NOISE = KIND == CYCLE_NOISE;
   // rows of 2 mod 4 elements (see block_plane_stride)
   constexpr int TILE_W = 4 * TILE_I + 2, TILE_H = 4 * TILE_J + 2;
   constexpr int TILE_TPB = TILE_I * TILE_J * 8;
@@ -171,7 +172,7 @@ __device__ __forceinline__ void block_tile_body(T* __restrict__ xg, const T* __r
 #pragma unroll
     for (int p = 0; p < PPT; ++p) Tl[sz * TP + loff[p]] = stage[sz][p];
   __syncthreads();
-  BlockWeights<T, 1, index_order<T, NOISE>> w;
+  BlockWeights<T, 1, index_order<T, KIND>> w;
   const T* row = bfac + (size_t)bz * kBlockRow;
   block_weights<T, 1>(w, row, row + kBlockZ, kx, ky, kz, 0);
 #pragma unroll
@@ -184,7 +185,7 @@ __device__ __forceinline__ void block_tile_body(T* __restrict__ xg, const T* __r
   if (active) X[cell] = v;
 }
 
-template <typename T, bool NOISE, int TILE_I, int TILE_J>
+template <typename T, int KIND, int TILE_I, int TILE_J>
 __global__ __launch_bounds__(TILE_I * TILE_J * 8) void k_block_tile(T* __restrict__ xg,
                                                           const T* __restrict__ bg,
                                                           const T* __restrict__ s1d,
@@ -192,7 +193,7 @@ __global__ __launch_bounds__(TILE_I * TILE_J * 8) void k_block_tile(T* __restric
                                                           int ny, int nz, uint32_t N, int colour,
                                                           int nbx2, int nby2, int ntx,
                                                           const T* __restrict__ zn) {
-  block_tile_body<T, NOISE, TILE_I, TILE_J>(xg, bg, s1d, bfac, nx, ny, nz, N, colour, nbx2,
+  block_tile_body<T, KIND, TILE_I, TILE_J>(xg, bg, s1d, bfac, nx, ny, nz, N, colour, nbx2,
                                             nby2, ntx, zn, xcd_block());
 }
 
@@ -213,9 +214,10 @@ __global__ __launch_bounds__(TILE_I * TILE_J * 8) void k_block_tile(T* __restric
 // What bounds it: the launch and the latency of the staging loads, on the levels of few
 // components it is used for.  A two-colour launch takes nearly as long (5.9 us at 32^3 x 3, FP64;
 // a half-sweep 8.4 us), and a sweep needs four of those: 23.6 -> 16.8 us.
-template <typename T, bool NOISE>
+template <typename T, int KIND>
 __device__ __forceinline__ void block_half_body(const HalfItem<T>& h, int cz, bool post,
                                                 const Blk3 wg) {
+  constexpr bool NOISE = KIND == CYCLE_NOISE;
   extern __shared__ char smraw[];
   T* Tl = reinterpret_cast<T*>(smraw);
   const int nx = h.nx, ny = h.ny, nz = h.nz;
@@ -277,7 +279,7 @@ __device__ __forceinline__ void block_half_body(const HalfItem<T>& h, int cz, bo
         if (hoff[p]) Tl[sz * TP + loff[p] + hoff[p]] = stage[sz][p];
       }
   __builtin_amdgcn_sched_barrier(0);
-  BlockWeights<T, 1, index_order<T, NOISE>> w;
+  BlockWeights<T, 1, index_order<T, KIND>> w;
   const T* row = h.bfac + (size_t)bz * kBlockRow;
   block_weights<T, 1>(w, row, row + kBlockZ, kx, ky, kz, 0);
 #pragma unroll
@@ -319,7 +321,7 @@ __device__ __forceinline__ void block_half_body(const HalfItem<T>& h, int cz, bo
 // Half-sweeps of the levels of several hierarchies (or of one) in one launch: the flat grid
 // concatenates the items' (row group, layer, component) grids in XCD-aware order; the block size
 // and the LDS are the largest the items need.
-template <typename T, bool NOISE>
+template <typename T, int KIND>
 __global__ __launch_bounds__(HALF_TPB, 3) void k_block_half(HalfArgs<T> m) {
   const uint32_t lin = xcd_block().x;
   int i = 0;
@@ -331,7 +333,7 @@ __global__ __launch_bounds__(HALF_TPB, 3) void k_block_half(HalfArgs<T> m) {
   const uint32_t rest = local / (uint32_t)it.ngx;
   wg.y = rest % (uint32_t)it.nbzc;
   wg.z = rest / (uint32_t)it.nbzc;
-  block_half_body<T, NOISE>(it, m.cz, m.post != 0, wg);
+  block_half_body<T, KIND>(it, m.cz, m.post != 0, wg);
 }
 
 // Two block colours c and c ^ 1 in one launch.  They differ only in the parity of bx, so a
@@ -346,8 +348,9 @@ __global__ __launch_bounds__(HALF_TPB, 3) void k_block_half(HalfArgs<T> m) {
 // of the two single-colour passes in order.  FP64, 64^3 x 24, two rows a group: 28 us a launch
 // (before the DPP exchanges, the bank-free plane stride and the packed factors 32 us; VALU
 // instructions per wave 753 -> 610, LDS cycles 8.2 M -> 6.1 M a launch).
-template <typename T, bool NOISE>
+template <typename T, int KIND>
 __device__ __forceinline__ void block_pair_body(const HalfItem<T>& h, int c_first, const Blk3 wg) {
+  constexpr bool NOISE = KIND == CYCLE_NOISE;
   extern __shared__ char smraw[];
   T* Tl = reinterpret_cast<T*>(smraw);
   const int nx = h.nx, ny = h.ny, nz = h.nz, PJ = h.P, TP = h.TP;
@@ -405,7 +408,7 @@ __device__ __forceinline__ void block_pair_body(const HalfItem<T>& h, int c_firs
         if (hoff[p]) Tl[sz * TP + loff[p] + hoff[p]] = stage[sz][p];
       }
   __builtin_amdgcn_sched_barrier(0);
-  BlockWeights<T, 1, index_order<T, NOISE>> w;
+  BlockWeights<T, 1, index_order<T, KIND>> w;
   const T* row = h.bfac + (size_t)bz * kBlockRow;
   block_weights<T, 1>(w, row, row + kBlockZ, kx, ky, kz, 0);
 #pragma unroll
@@ -440,7 +443,7 @@ __device__ __forceinline__ void block_pair_body(const HalfItem<T>& h, int c_firs
 
 // Two-colour launches of the levels of several hierarchies (or of one) in one launch, as
 // k_block_half.
-template <typename T, bool NOISE>
+template <typename T, int KIND>
 __global__ __launch_bounds__(HALF_TPB) void k_block_pair(HalfArgs<T> m) {
   const uint32_t lin = xcd_block().x;
   int i = 0;
@@ -452,13 +455,13 @@ __global__ __launch_bounds__(HALF_TPB) void k_block_pair(HalfArgs<T> m) {
   const uint32_t rest = local / (uint32_t)it.ngx;
   wg.y = rest % (uint32_t)it.nbzc;
   wg.z = rest / (uint32_t)it.nbzc;
-  block_pair_body<T, NOISE>(it, m.cz, wg);
+  block_pair_body<T, KIND>(it, m.cz, wg);
 }
 
 // The same pass for several levels of different hierarchies (one colour) in one launch: the
 // one-dimensional grid is the concatenation of every item's (tile, layer, component) grid, in
 // XCD-aware order; a work-group finds its item from the offsets and runs the item's pass.
-template <typename T, bool NOISE, int TILE_I, int TILE_J>
+template <typename T, int KIND, int TILE_I, int TILE_J>
 __global__ __launch_bounds__(TILE_I * TILE_J * 8) void k_block_tile_multi(BlockMultiArgs<T> m) {
   const uint32_t lin = xcd_block().x;
   int i = 0;
@@ -471,7 +474,7 @@ __global__ __launch_bounds__(TILE_I * TILE_J * 8) void k_block_tile_multi(BlockM
   const uint32_t rest = local / tiles;
   wg.y = rest % (uint32_t)it.nbzc;
   wg.z = rest / (uint32_t)it.nbzc;
-  block_tile_body<T, NOISE, TILE_I, TILE_J>(it.x, it.b, it.s1d, it.bfac, it.nx, it.ny,
+  block_tile_body<T, KIND, TILE_I, TILE_J>(it.x, it.b, it.s1d, it.bfac, it.nx, it.ny,
                                             it.nz, it.N, m.colour, it.nbx2, it.nby2, it.ntx,
                                             it.zn, wg);
 }
@@ -831,22 +834,20 @@ __global__ __launch_bounds__(CO_TPB) void k_coarsest(T* __restrict__ xg,
 
 template <typename T, int TI, int TJ>
 void launch_block_tile(T* x, const T* b, const T* s1d, const T* bfac, int nx, int ny,
-                       int nz, int ncomp, int colour, const T* zn, int nbx2,
+                       int nz, int ncomp, int colour, int kind, const T* zn, int nbx2,
                        int nby2, int nbzc, hipStream_t s) {
   const uint32_t N = (uint32_t)nx * ny * nz;
   const int ntx = (nbx2 + TI - 1) / TI, nty = (nby2 + TJ - 1) / TJ;
   dim3 grid(ntx * nty, nbzc, ncomp);
-  if (zn)
-    k_block_tile<T, true, TI, TJ><<<grid, TI * TJ * 8, 0, s>>>(
+  by_kind<T>(kind, [&](auto k) {
+    k_block_tile<T, decltype(k)::value, TI, TJ><<<grid, TI * TJ * 8, 0, s>>>(
         x, b, s1d, bfac, nx, ny, nz, N, colour, nbx2, nby2, ntx, zn);
-  else
-    k_block_tile<T, false, TI, TJ><<<grid, TI * TJ * 8, 0, s>>>(
-        x, b, s1d, bfac, nx, ny, nz, N, colour, nbx2, nby2, ntx, zn);
+  });
 }
 
 template <typename T>
 hipError_t launch_block_pass(T* x, const T* b, const T* s1d, const T* bfac, int nx,
-                             int ny, int nz, int ncomp, int colour, const T* zn,
+                             int ny, int nz, int ncomp, int colour, int kind, const T* zn,
                              int tile, hipStream_t s) {
   const int nbx2 = nx / 4, nby2 = ny / 4;
   const int nbz = nz / 2;
@@ -861,16 +862,19 @@ hipError_t launch_block_pass(T* x, const T* b, const T* s1d, const T* bfac, int 
     tile = wg84 >= 512 ? SMG_TILE_8X4 : (wg44 >= 512 ? SMG_TILE_4X4 : SMG_TILE_4X2);
   }
   if (tile == SMG_TILE_4X2)
-    launch_block_tile<T, 4, 2>(x, b, s1d, bfac, nx, ny, nz, ncomp, colour, zn, nbx2, nby2, nbzc, s);
+    launch_block_tile<T, 4, 2>(x, b, s1d, bfac, nx, ny, nz, ncomp, colour, kind, zn, nbx2,
+                                nby2, nbzc, s);
   else if (tile == SMG_TILE_8X4)
-    launch_block_tile<T, 8, 4>(x, b, s1d, bfac, nx, ny, nz, ncomp, colour, zn, nbx2, nby2, nbzc, s);
+    launch_block_tile<T, 8, 4>(x, b, s1d, bfac, nx, ny, nz, ncomp, colour, kind, zn, nbx2,
+                                nby2, nbzc, s);
   else
-    launch_block_tile<T, 4, 4>(x, b, s1d, bfac, nx, ny, nz, ncomp, colour, zn, nbx2, nby2, nbzc, s);
+    launch_block_tile<T, 4, 4>(x, b, s1d, bfac, nx, ny, nz, ncomp, colour, kind, zn, nbx2,
+                                nby2, nbzc, s);
   return hipGetLastError();
 }
 
 template <typename T>
-hipError_t launch_block_half(const HalfPassItem<T>* items, int n, int cz, bool post, bool noise,
+hipError_t launch_block_half(const HalfPassItem<T>* items, int n, int cz, bool post, int kind,
                              hipStream_t s) {
   for (int q = 0; q < n; ++q)
     if (!half_level(items[q].nx, items[q].ny)) return hipErrorNotSupported;
@@ -883,8 +887,9 @@ hipError_t launch_block_half(const HalfPassItem<T>* items, int n, int cz, bool p
   auto flush = [&]() -> hipError_t {
     if (m.nitems == 0) return hipSuccess;
     m.begin[m.nitems] = total;
-    if (noise) k_block_half<T, true><<<total, nthr, lds, s>>>(m);
-    else k_block_half<T, false><<<total, nthr, lds, s>>>(m);
+    by_kind<T>(kind, [&](auto k) {
+      k_block_half<T, decltype(k)::value><<<total, nthr, lds, s>>>(m);
+    });
     m.nitems = 0;
     total = 0;
     nthr = 0;
@@ -935,7 +940,7 @@ inline int pair_rows(int nx, int ny, int nz, int ncomp, int c_first) {
 }
 
 template <typename T>
-hipError_t launch_block_pair(const HalfPassItem<T>* items, int n, int c_first, bool noise,
+hipError_t launch_block_pair(const HalfPassItem<T>* items, int n, int c_first, int kind,
                              hipStream_t s) {
   for (int q = 0; q < n; ++q)
     if (!half_level(items[q].nx, items[q].ny)) return hipErrorNotSupported;
@@ -947,8 +952,9 @@ hipError_t launch_block_pair(const HalfPassItem<T>* items, int n, int c_first, b
   auto flush = [&]() -> hipError_t {
     if (m.nitems == 0) return hipSuccess;
     m.begin[m.nitems] = total;
-    if (noise) k_block_pair<T, true><<<total, nthr, lds, s>>>(m);
-    else k_block_pair<T, false><<<total, nthr, lds, s>>>(m);
+    by_kind<T>(kind, [&](auto k) {
+      k_block_pair<T, decltype(k)::value><<<total, nthr, lds, s>>>(m);
+    });
     m.nitems = 0;
     total = 0;
     nthr = 0;
@@ -987,7 +993,7 @@ hipError_t launch_block_pair(const HalfPassItem<T>* items, int n, int c_first, b
 }
 
 template <typename T, int TI, int TJ>
-hipError_t launch_block_multi_tiled(const BlockPassItem<T>* items, int n, int colour, bool noise,
+hipError_t launch_block_multi_tiled(const BlockPassItem<T>* items, int n, int colour, int kind,
                                     hipStream_t s) {
   BlockMultiArgs<T> m{};
   m.colour = colour;
@@ -995,8 +1001,9 @@ hipError_t launch_block_multi_tiled(const BlockPassItem<T>* items, int n, int co
   auto flush = [&]() -> hipError_t {
     if (m.nitems == 0) return hipSuccess;
     m.begin[m.nitems] = total;
-    if (noise) k_block_tile_multi<T, true, TI, TJ><<<total, TI * TJ * 8, 0, s>>>(m);
-    else k_block_tile_multi<T, false, TI, TJ><<<total, TI * TJ * 8, 0, s>>>(m);
+    by_kind<T>(kind, [&](auto k) {
+      k_block_tile_multi<T, decltype(k)::value, TI, TJ><<<total, TI * TJ * 8, 0, s>>>(m);
+    });
     m.nitems = 0;
     total = 0;
     return hipGetLastError();
@@ -1035,7 +1042,7 @@ hipError_t launch_block_multi_tiled(const BlockPassItem<T>* items, int n, int co
 }
 
 template <typename T>
-hipError_t launch_block_pass_multi(const BlockPassItem<T>* items, int n, int colour, bool noise,
+hipError_t launch_block_pass_multi(const BlockPassItem<T>* items, int n, int colour, int kind,
                                    int tile, hipStream_t s) {
   if (tile == SMG_TILE_AUTO) {
     // the rule of launch_block_pass over the work-groups of all items together
@@ -1048,9 +1055,9 @@ hipError_t launch_block_pass_multi(const BlockPassItem<T>* items, int n, int col
     }
     tile = wg84 >= 512 ? SMG_TILE_8X4 : (wg44 >= 512 ? SMG_TILE_4X4 : SMG_TILE_4X2);
   }
-  if (tile == SMG_TILE_4X2) return launch_block_multi_tiled<T, 4, 2>(items, n, colour, noise, s);
-  if (tile == SMG_TILE_8X4) return launch_block_multi_tiled<T, 8, 4>(items, n, colour, noise, s);
-  return launch_block_multi_tiled<T, 4, 4>(items, n, colour, noise, s);
+  if (tile == SMG_TILE_4X2) return launch_block_multi_tiled<T, 4, 2>(items, n, colour, kind, s);
+  if (tile == SMG_TILE_8X4) return launch_block_multi_tiled<T, 8, 4>(items, n, colour, kind, s);
+  return launch_block_multi_tiled<T, 4, 4>(items, n, colour, kind, s);
 }
 
 template <typename T>
@@ -1151,11 +1158,11 @@ hipError_t launch_level_noise(const NoiseGenArgs& a, const NoiseArgs& na, hipStr
 
 #define SMG_INST(T)                                                                            \
   template hipError_t launch_block_pass<T>(T*, const T*, const T*, const T*, int, int,           \
-                                           int, int, int, const T*, int, hipStream_t);          \
-  template hipError_t launch_block_half<T>(const HalfPassItem<T>*, int, int, bool, bool,         \
+                                           int, int, int, int, const T*, int, hipStream_t);     \
+  template hipError_t launch_block_half<T>(const HalfPassItem<T>*, int, int, bool, int,          \
                                            hipStream_t);                                         \
-  template hipError_t launch_block_pair<T>(const HalfPassItem<T>*, int, int, bool, hipStream_t);  \
-  template hipError_t launch_block_pass_multi<T>(const BlockPassItem<T>*, int, int, bool, int,    \
+  template hipError_t launch_block_pair<T>(const HalfPassItem<T>*, int, int, int, hipStream_t);   \
+  template hipError_t launch_block_pass_multi<T>(const BlockPassItem<T>*, int, int, int, int,     \
                                                  hipStream_t);                                   \
   template hipError_t launch_residual_gal<T>(T*, const T*, const T*, const T*, const T*, int,    \
                                              int, int, int, hipStream_t);                        \
