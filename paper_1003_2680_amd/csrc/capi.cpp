@@ -109,6 +109,15 @@ int log2_exact(int v) {
   return l;
 }
 
+// The first level of the bottom launches (-1: none).  A timed level-0 colour pass is a launch of its
+// own, so a hierarchy whose level 0 is in the bottom begins it one level lower meanwhile.
+int first_bottom(const Hierarchy& h) {
+  if (!h.use_bottom || h.bottom < 0) return -1;
+  if (h.bottom == 0 && h.timing && h.timed_kernel == SMG_TIMED_FINE_PASS)
+    return h.lv.size() > 1 ? 1 : -1;
+  return h.bottom;
+}
+
 size_t half_field(const Hierarchy& h) { return (size_t)h.desc.ncomp * (h.lv[0].n / 2); }
 
 // The fields a sweep of precision T works on: FP64 mode x, b, r; refined mode xf, bf, rf.
@@ -318,7 +327,7 @@ int restrict_residual(Run& r, int l) {
   const int nc = r.nc;
   T* rr = comp_at(Fld<T>::r(v), v.n, r);
   Level& c = h.lv[l + 1];
-  const bool bottom_next = (l + 1 == h.bottom) && h.use_bottom;
+  const bool bottom_next = l + 1 == first_bottom(h);
   T* bc = comp_at(Fld<T>::b(c), c.n, r);
   T* xc = bottom_next ? nullptr : comp_at(Fld<T>::x(c), c.n, r);
   if (v.kind == KIND_POINT) {
@@ -374,7 +383,7 @@ int coarsest_step(Run& r, int l) {
   NoiseArgs na = make_noise(r, l, 0, 0, KIND_COARSEST_NOISE);
   SMG_HIP(launch_coarsest<T>(comp_at(Fld<T>::x(v), v.n, r), comp_at(Fld<T>::b(v), v.n, r),
                              h.ainv_d, h.w_d, h.nc, r.nc, r.noise,
-                             h.use_bottom && h.bottom >= 0, na, r.s));
+                             first_bottom(h) >= 0, na, r.s));
   return SMG_OK;
 }
 
@@ -390,7 +399,7 @@ int gen_level_noise(Run& r, int only_level = -1, int only_slot = 0) {
   for (int l = 0; l < (int)h.lv.size(); ++l) {
     const Level& v = h.lv[l];
     // a point level's passes draw their own noise, except in the bottom launch
-    const bool point = v.kind == KIND_POINT && l == h.bottom && h.use_bottom && only_level < 0;
+    const bool point = v.kind == KIND_POINT && l == first_bottom(h) && only_level < 0;
     if ((v.kind != KIND_BLOCK && !point) || (only_level >= 0 && l != only_level)) continue;
     if (a.nlev == kMaxNoiseLevels) {
       set_error("too many block levels");
@@ -462,9 +471,6 @@ BotArgs make_botargs(Hierarchy& h) {
     a.tab_off[i] = off;
     if (v.kind == KIND_BLOCK) off += (int)bot_table_elems(v.nz);
   }
-  Level& b0 = h.lv[h.bottom];
-  a.b_in = f32 ? (const void*)b0.bf : (const void*)b0.b;
-  a.x_out = f32 ? (void*)b0.xf : (void*)b0.x;
   a.ainv = h.ainv_d;
   a.w = h.w_d;
   return a;
@@ -472,15 +478,17 @@ BotArgs make_botargs(Hierarchy& h) {
 
 // The bottom's block levels are in front of a coarsest draw that takes a launch of its own.
 bool splits_bottom(const Hierarchy& h) {
-  return h.wide_coarsest && h.lv[h.bottom].kind != KIND_CHOL;
+  return h.wide_coarsest && h.lv[first_bottom(h)].kind != KIND_CHOL;
 }
 
 // The whole cycle, its point level included, runs in the bottom launch.
 bool point_bottom(const Hierarchy& h) {
-  return h.bottom >= 0 && h.lv[h.bottom].kind == KIND_POINT;
+  const int l = first_bottom(h);
+  return l >= 0 && h.lv[l].kind == KIND_POINT;
 }
 int bottom_part(const Run& r, BotPart part) {
-  return (int)part | (point_bottom(*r.h) && r.has_b0 ? kBotHasB : 0);
+  return (int)part | (point_bottom(*r.h) && r.has_b0 ? kBotHasB : 0) |
+         (first_bottom(*r.h) > r.h->bottom ? kBotBelow : 0);
 }
 
 // Every level from h.bottom down: in one launch (LDS-resident, one work-group per component), or
@@ -499,7 +507,7 @@ int bottom_cycle(Run& r) {
                              bottom_part(r, part), na, r.s));
     return SMG_OK;
   };
-  if (h.lv[h.bottom].kind == KIND_CHOL) {
+  if (h.lv[first_bottom(h)].kind == KIND_CHOL) {
     SMG_TRY(coarsest_step<T>(r, last));
   } else if (splits_bottom(h)) {
     SMG_TRY(launch(BOT_DOWN));
@@ -516,7 +524,7 @@ int vcycle(Run& r, int l) {
   Hierarchy& h = *r.h;
   Level& v = h.lv[l];
   const int nu1 = h.prm.nu1, nu2 = h.prm.nu2;
-  if (l == h.bottom && h.use_bottom) return bottom_cycle<T>(r);
+  if (l == first_bottom(h)) return bottom_cycle<T>(r);
   if (v.kind == KIND_CHOL) return coarsest_step<T>(r, l);
   for (int s = 0; s < nu1; ++s) SMG_TRY(sweep<T>(r, l, s, false));
   if (!v.coarsest) {
@@ -535,12 +543,12 @@ int vcycle(Run& r, int l) {
 // sweeps and restrictions) and the up-leg (prolongations and post-sweeps), in the order of
 // vcycle, so that down-leg + bottom + up-leg is vcycle(0) exactly.
 // Where the bottom is the whole cycle both legs are empty.
-bool split_bottom(const Hierarchy& h) { return h.use_bottom && h.bottom >= 0; }
+bool split_bottom(const Hierarchy& h) { return first_bottom(h) >= 0; }
 
 template <typename T>
 int vdown(Run& r) {
   Hierarchy& h = *r.h;
-  for (int l = 0; l < h.bottom; ++l) {
+  for (int l = 0; l < first_bottom(h); ++l) {
     for (int s = 0; s < h.prm.nu1; ++s) SMG_TRY(sweep<T>(r, l, s, false));
     SMG_TRY(restrict_residual<T>(r, l));
   }
@@ -550,7 +558,7 @@ int vdown(Run& r) {
 template <typename T>
 int vup(Run& r) {
   Hierarchy& h = *r.h;
-  for (int l = h.bottom - 1; l >= 0; --l) {
+  for (int l = first_bottom(h) - 1; l >= 0; --l) {
     SMG_TRY(prolong_add<T>(r, l));
     for (int s = 0; s < h.prm.nu2; ++s) SMG_TRY(sweep<T>(r, l, h.prm.nu1 + s, true));
   }
@@ -629,7 +637,7 @@ template <typename T>
 bool half_lockstep(const std::vector<Run>& legs, int l) {
   int64_t lanes = 0;
   for (const Run& r : legs)
-    if (l < r.h->bottom && multi_colour(*r.h, r.h->lv[l])) lanes += half_lanes(r.h->lv[l], r.nc);
+    if (l < first_bottom(*r.h) && multi_colour(*r.h, r.h->lv[l])) lanes += half_lanes(r.h->lv[l], r.nc);
   return sweep_form<T>(lanes) == SweepForm::HALF;
 }
 
@@ -646,7 +654,7 @@ int block_half_lockstep(const std::vector<Run>& legs, int l, int t, bool post, i
   int tile = -1;
   for (const Run& r : legs) {
     Hierarchy& h = *r.h;
-    if (kind_of(r) != kind || l >= h.bottom) continue;
+    if (kind_of(r) != kind || l >= first_bottom(h)) continue;
     Level& v = h.lv[l];
     if (v.kind != KIND_BLOCK) continue;
     if (t >= (post ? h.prm.nu2 : h.prm.nu1)) continue;
@@ -687,7 +695,7 @@ int legs_lockstep(const std::vector<Run>& legs, bool down) {
   hipStream_t s = legs[0].s;
   int maxb = 0, maxnu = 0;
   for (const Run& r : legs) {
-    maxb = std::max(maxb, r.h->bottom);
+    maxb = std::max(maxb, first_bottom(*r.h));
     maxnu = std::max(maxnu, down ? r.h->prm.nu1 : r.h->prm.nu2);
   }
   auto sweeps = [&](int l) -> int {
@@ -701,7 +709,7 @@ int legs_lockstep(const std::vector<Run>& legs, bool down) {
             std::vector<RbPassItem<T>> items;
             for (const Run& r : legs) {
               Hierarchy& h = *r.h;
-              if (l >= h.bottom || h.lv[l].kind != KIND_POINT) continue;
+              if (l >= first_bottom(h) || h.lv[l].kind != KIND_POINT) continue;
               if (t >= (down ? h.prm.nu1 : h.prm.nu2)) continue;
               if ((int)r.has_b0 != hb || (int)r.noise != nz) continue;
               Level& v = h.lv[l];
@@ -733,7 +741,7 @@ int legs_lockstep(const std::vector<Run>& legs, bool down) {
           SMG_TRY(block_half_lockstep<T>(legs, l, t, !down, down ? q : 1 - q, kind, s));
       for (const Run& r : legs) {
         const int nsw = down ? r.h->prm.nu1 : r.h->prm.nu2;
-        if (l < r.h->bottom && t + 1 == nsw && multi_colour(*r.h, r.h->lv[l]) &&
+        if (l < first_bottom(*r.h) && t + 1 == nsw && multi_colour(*r.h, r.h->lv[l]) &&
             half_lockstep<T>(legs, l))
           SMG_TRY(settle_halves<T>(r, l, nsw));
       }
@@ -745,14 +753,14 @@ int legs_lockstep(const std::vector<Run>& legs, bool down) {
       SMG_TRY(sweeps(l));
       for (const Run& r0 : legs) {
         Run r = r0;
-        if (l < r.h->bottom) SMG_TRY(restrict_residual<T>(r, l));
+        if (l < first_bottom(*r.h)) SMG_TRY(restrict_residual<T>(r, l));
       }
     }
   } else {
     for (int l = maxb - 1; l >= 0; --l) {
       for (const Run& r0 : legs) {
         Run r = r0;
-        if (l < r.h->bottom) SMG_TRY(prolong_add<T>(r, l));
+        if (l < first_bottom(*r.h)) SMG_TRY(prolong_add<T>(r, l));
       }
       SMG_TRY(sweeps(l));
     }
@@ -819,7 +827,7 @@ int batch_bottoms(const std::vector<Run*>& runs) {
       for (Run* r : runs) {
         Hierarchy& h = *r->h;
         if (!split_bottom(h) || (int)refined(h) != f32 || kind_of(*r) != kind) continue;
-        if (r->nc > kBotMultiWG || h.lv[h.bottom].kind == KIND_CHOL) {  // launches of its own
+        if (r->nc > kBotMultiWG || h.lv[first_bottom(h)].kind == KIND_CHOL) {  // launches of its own
           Run ri = *r;
           ri.has_b0 = ri.has_b0 || refined(h);
           SMG_TRY(f32 ? bottom_cycle<float>(ri) : bottom_cycle<double>(ri));

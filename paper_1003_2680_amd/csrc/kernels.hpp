@@ -57,13 +57,12 @@ struct BotLevel {
 // chip makes (launch_coarsest): down to its right-hand side, and up from its result.
 enum BotPart { BOT_WHOLE = 0, BOT_DOWN = 1, BOT_UP = 2 };
 constexpr int kBotHasB = 4;  // added to the part: level 0 is in the bottom and has a right-hand side
+constexpr int kBotBelow = 8;  // added to the part: the launch begins below the bottom's first level
 struct BotArgs {
   int nlev, level0, nu1, nu2, ncomp;
   BotLevel lv[kMaxBotLevels];
   int lds_off[kMaxBotLevels];  // LDS offset (elements of T) of level i's x; b, scratch follow
   int tab_off[kMaxBotLevels];  // LDS offset (elements of T) of level i's tables
-  const void* b_in;    // T [ncomp][n of the first bottom level]
-  void* x_out;         // T [ncomp][n of the first bottom level]
   const double* ainv;  // coarsest A_c^-1 (FP64 in every mode)
   const double* w;     // coarsest L_c^-1
 };

@@ -563,8 +563,9 @@ __device__ __forceinline__ void bottom_body(const BotArgs& a, const uint32_t com
   const int tid = threadIdx.x;
   const BotLevel& L0 = a.lv[0];
   const int n0 = L0.nx * L0.ny * L0.nz;
-  const bool point = POINT && L0.kind == KIND_POINT;
-  const int first = point ? 1 : 0;
+  const bool below = part_b & kBotBelow;
+  const bool point = POINT && L0.kind == KIND_POINT && !below;
+  const int first = point || below ? 1 : 0;  // the first level in the natural layout
   const gptr<T> pn = global_ptr<T>(L0.noise) + (size_t)comp * n0;
   const size_t pstride = (size_t)a.ncomp * n0;
   auto point_load = [&](const PointSites<T>& ps) {
@@ -617,11 +618,13 @@ __device__ __forceinline__ void bottom_body(const BotArgs& a, const uint32_t com
       }
     }
   } else if (!point) {
-    T* x0 = sm + a.lds_off[0];
-    for (int q = tid; q < L0.nz * L0.sz; q += BOT_TPB) x0[q] = T(0);
-    T* b0 = x0 + L0.nz * L0.sz;
-    const gptr<T> bg = global_ptr<T>(a.b_in) + (size_t)comp * n0;
-    for (int q = tid; q < n0; q += BOT_TPB) b0[q] = bg[q];
+    const BotLevel& L = a.lv[first];
+    const int n = L.nx * L.ny * L.nz;
+    T* x0 = sm + a.lds_off[first];
+    for (int q = tid; q < L.nz * L.sz; q += BOT_TPB) x0[q] = T(0);
+    T* b0 = x0 + L.nz * L.sz;
+    const gptr<T> bg = global_ptr<T>(L.bg) + (size_t)comp * n;
+    for (int q = tid; q < n; q += BOT_TPB) b0[q] = bg[q];
   }
   // operator tables of the block levels (bot_table_elems) at tab_off[i]; the normals
   // of the coarsest draw, which depend on nothing above it
@@ -803,9 +806,12 @@ __device__ __forceinline__ void bottom_body(const BotArgs& a, const uint32_t com
     point_store(ps);
     return;
   }
-  for (int q = tid; q < n0; q += BOT_TPB) {
+  const BotLevel& L = a.lv[first];
+  const int n = L.nx * L.ny * L.nz;
+  T* xg = (T*)L.xg + (size_t)comp * n;
+  for (int q = tid; q < n; q += BOT_TPB) {
     int x;
-    ((T*)a.x_out)[(size_t)comp * n0 + q] = sm[a.lds_off[0] + place(L0, q, x)];
+    xg[q] = sm[a.lds_off[first] + place(L, q, x)];
   }
 }
 
