@@ -1581,11 +1581,12 @@ int bind_impl(Hierarchy& h, char* ws, bool upload, hipStream_t s) {
       v.b = (double*)(ws + v.off_b);
     }
     if (!f32) {
-      v.r = (v.kind == KIND_CHOL && l > 0) ? nullptr : (double*)(ws + v.off_r);
+      const bool r = v.kind == KIND_BLOCK || (v.kind == KIND_CHOL && l == 0);
+      v.r = r ? (double*)(ws + v.off_r) : nullptr;
     } else {
       v.xf = (float*)(ws + v.off_xf);
       v.bf = (float*)(ws + v.off_bf);
-      v.rf = v.kind == KIND_CHOL ? nullptr : (float*)(ws + v.off_rf);
+      v.rf = v.kind == KIND_BLOCK ? (float*)(ws + v.off_rf) : nullptr;
     }
     if (v.kind == KIND_POINT && h.bottom == 0) v.noise_d = ws + v.off_noise;
     if (v.kind == KIND_BLOCK) {

@@ -131,12 +131,11 @@ struct Composite {
   std::vector<double> ainv, w;  // A_c^-1 and L_c^-T (row-major)
   std::vector<int32_t> layer;  // layer cells grouped by parity class
   int layer_off[9] = {0};
-  size_t ws_bytes = 0, off_rc = 0, off_rf = 0, off_layer = 0, off_ainv = 0, off_w = 0,
+  size_t ws_bytes = 0, off_rf = 0, off_layer = 0, off_ainv = 0, off_w = 0,
          off_part = 0, off_norm = 0, off_znoise = 0, off_e32c = 0, off_e32f = 0, off_r32c = 0,
-         off_r32f = 0, off_rf32 = 0, off_fc = 0, off_ff = 0;
+         off_r32f = 0, off_fc = 0, off_ff = 0;
   char* ws = nullptr;
   int device = -1;
-  double* rc = nullptr;
   double* rf = nullptr;
   double* ainv_d = nullptr;
   double* w_d = nullptr;
@@ -829,8 +828,7 @@ int plan(Composite& C, const smg_composite_desc& d, const smg_fac_params& p, std
   const int64_t nf = (int64_t)g.fx * g.fy * g.fz;
   const bool f32 = C.prec == SMG_FP32_REFINED;
   const size_t es = f32 ? 4 : 8;  // bytes of a value of the sweep precision
-  C.off_rc = take(nbase * 8);
-  C.off_rf = take(nf * 8);
+  C.off_rf = take(nf * es);  // fine residual of a cycle
   C.off_fc = take(nbase * 8);  // right-hand side of the forced field
   C.off_ff = take(nf * 8);
   C.off_layer = take(std::max<size_t>(1, C.layer.size()) * 4);
@@ -839,7 +837,6 @@ int plan(Composite& C, const smg_composite_desc& d, const smg_fac_params& p, std
     C.off_e32f = take(nf * 4);
     C.off_r32c = take(nbase * 4);
     C.off_r32f = take(nf * 4);
-    C.off_rf32 = take(nf * 4);
   }
   for (auto& L : C.lv) {
     L.off_x = take(L.n * es);
@@ -1264,8 +1261,7 @@ int smg_composite_bind(smg_composite* h, void* dev_ptr, size_t bytes, void* stre
   CMP_HIP(hipStreamSynchronize(s));
   CMP_HIP(hipGetDevice(&C.device));
   C.ws = ws;
-  C.rc = (double*)(ws + C.off_rc);
-  C.rf = (double*)(ws + C.off_rf);
+  if (!f32) C.rf = (double*)(ws + C.off_rf);
   C.layer_d = (int32_t*)(ws + C.off_layer);
   C.ainv_d = (double*)(ws + C.off_ainv);
   C.w_d = (double*)(ws + C.off_w);
@@ -1277,7 +1273,7 @@ int smg_composite_bind(smg_composite* h, void* dev_ptr, size_t bytes, void* stre
     C.e32f = (float*)(ws + C.off_e32f);
     C.r32c = (float*)(ws + C.off_r32c);
     C.r32f = (float*)(ws + C.off_r32f);
-    C.rf32 = (float*)(ws + C.off_rf32);
+    C.rf32 = (float*)(ws + C.off_rf);
   }
   return SMG_OK;
 }

@@ -401,9 +401,9 @@ int build_plan(const smg_grid_desc& d, const smg_cycle_params& p, Hierarchy& h, 
     if (!f32) {
       v.off_x = take(n * sizeof(double));
       v.off_b = take(n * sizeof(double));
-      // level 0 always has a residual buffer (the solve's norms); a drawn-exact level 0 (one
-      // level) needs it for nothing else
-      if (v.kind != KIND_CHOL || l == 0) v.off_r = take(n * sizeof(double));
+      // block levels keep a residual; a drawn-exact level 0 (one level) for the solve's norms
+      if (v.kind == KIND_BLOCK || (v.kind == KIND_CHOL && l == 0))
+        v.off_r = take(n * sizeof(double));
     } else {
       if (l == 0) {
         v.off_x = take(n * sizeof(double));
@@ -411,7 +411,7 @@ int build_plan(const smg_grid_desc& d, const smg_cycle_params& p, Hierarchy& h, 
       }
       v.off_xf = take(n * sizeof(float));
       v.off_bf = take(n * sizeof(float));
-      if (v.kind != KIND_CHOL) v.off_rf = take(n * sizeof(float));
+      if (v.kind == KIND_BLOCK) v.off_rf = take(n * sizeof(float));
     }
     if (v.kind == KIND_BLOCK) {
       v.off_s1d = take(v.s1d.size() * ts);

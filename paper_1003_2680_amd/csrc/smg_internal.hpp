@@ -32,9 +32,10 @@ struct Level {
   std::vector<double> zt;    // KIND_BLOCK: [nz][10]
   std::vector<double> bfac;  // KIND_BLOCK: [nz/2][3][64]: A_BB^-1, L_BB^-T, A_BB (row-major)
   // workspace offsets (bytes); level 0 of KIND_POINT stores x and b split by colour
-  // Workspace offsets (bytes).  FP64 mode: x, b, r and the tables and noise in double.
+  // Workspace offsets (bytes).  FP64 mode: x, b, the tables and noise in double, and r on block
+  // levels (and on a level 0 drawn exactly).
   // FP32-refined mode: level 0 keeps x (the FP64 state) and b (the FP64 right-hand side), and
-  // every level has FP32 fields xf, bf, rf (level 0: xf = correction e, bf = FP32 residual,
+  // every level has FP32 fields xf, bf, and rf on block levels (level 0: xf = correction e, bf = FP32 residual,
   // both split by colour), FP32 tables and FP32 noise.
   size_t off_x = 0, off_b = 0, off_r = 0, off_xf = 0, off_bf = 0, off_rf = 0;
   size_t off_s1d = 0, off_zt = 0, off_bfac = 0, off_noise = 0;
