@@ -325,7 +325,6 @@ int restrict_residual(Run& r, int l) {
   Hierarchy& h = *r.h;
   Level& v = h.lv[l];
   const int nc = r.nc;
-  T* rr = comp_at(Fld<T>::r(v), v.n, r);
   Level& c = h.lv[l + 1];
   const bool bottom_next = l + 1 == first_bottom(h);
   T* bc = comp_at(Fld<T>::b(c), c.n, r);
@@ -342,16 +341,19 @@ int restrict_residual(Run& r, int l) {
         r.chain, r.s));
     return SMG_OK;
   }
-  if (sizeof(T) == 8 || !r.chain) {
-    SMG_HIP(launch_fold_residual<T>(bc, xc, comp_at(Fld<T>::x(v), v.n, r),
-                                    comp_at(Fld<T>::b(v), v.n, r), (const T*)v.zt_d,
-                                    level_taps<T>(v), v.nx, v.ny, v.nz, nc, r.s));
-    return SMG_OK;
+  const T* x = comp_at(Fld<T>::x(v), v.n, r);
+  const T* b = comp_at(Fld<T>::b(v), v.n, r);
+  if constexpr (sizeof(T) == 4) {
+    if (r.chain) {  // an FP32 chain keeps its order of additions
+      T* rr = comp_at(Fld<T>::r(v), v.n, r);
+      SMG_HIP(launch_residual_gal(rr, x, b, (const T*)v.s1d_d, (const T*)v.zt_d, v.nx, v.ny, v.nz,
+                                  nc, r.s));
+      SMG_HIP(launch_restrict<T>(bc, xc, rr, v.nx, v.ny, v.nz, nc, r.s));
+      return SMG_OK;
+    }
   }
-  // an FP32 chain keeps its order of additions
-  SMG_HIP(launch_residual_gal<T>(rr, comp_at(Fld<T>::x(v), v.n, r), comp_at(Fld<T>::b(v), v.n, r),
-                                 (const T*)v.s1d_d, (const T*)v.zt_d, v.nx, v.ny, v.nz, nc, r.s));
-  SMG_HIP(launch_restrict<T>(bc, xc, rr, v.nx, v.ny, v.nz, nc, r.s));
+  SMG_HIP(launch_fold_residual<T>(bc, xc, x, b, (const T*)v.zt_d, level_taps<T>(v), v.nx, v.ny,
+                                  v.nz, nc, r.s));
   return SMG_OK;
 }
 
@@ -395,7 +397,6 @@ int gen_level_noise(Run& r, int only_level = -1, int only_slot = 0) {
   NoiseGenArgs a{};
   a.ncomp = h.desc.ncomp;
   a.nact = r.nc;
-  uint32_t calls = 0;
   for (int l = 0; l < (int)h.lv.size(); ++l) {
     const Level& v = h.lv[l];
     // a point level's passes draw their own noise, except in the bottom launch
@@ -416,11 +417,7 @@ int gen_level_noise(Run& r, int only_level = -1, int only_slot = 0) {
     e.bfac = point ? nullptr : v.bfac_d;
     e.lg_bx = log2_exact(v.nx / 2);
     e.lg_bxy = log2_exact((v.nx / 2) * (v.ny / 2));
-    e.calls_before = calls;
-    calls += (uint32_t)(e.nslot * a.nact * (v.n / 2));
   }
-  if (a.nlev == 0) return SMG_OK;
-  a.total = calls;
   NoiseArgs na = make_noise(r, 0, 0, 0, KIND_SMOOTH_NOISE);
   SMG_HIP(launch_level_noise<T>(a, na, r.s));
   return SMG_OK;

@@ -76,16 +76,12 @@ __device__ __forceinline__ double block_sum(double v, double (&sh)[TPB / 64]) {
   return (sh[0] + sh[1]) + (sh[2] + sh[3]);
 }
 
-// (A x) at cell (cx, cy, cz) of a Galerkin level.  The Galerkin operator of the wall-bounded
-// Laplacian is a Kronecker sum, A = a_z (x) m_y (x) m_x + m_z (x) (a_y (x) m_x + m_y (x) a_x),
-// with 5-point periodic 1D stencils s1d = (m_x, a_x, m_y, a_y) (offsets -2..2, uniform over
-// the level) and the wall-axis rows zt[cz] = (a_z[cz][cz+dz], m_z[cz][cz+dz]).  Each row of a
-// plane is reduced with m_x and a_x, then the plane with m_y and a_y: 65 FMAs per plane.
-// Rows beyond a wall have zero z-factors; their loads are clamped into the grid so the
-// accumulation is branch-free.
-// Fields are addressed as X[z*sz + y*sy + x]; global fields use sy = nx, sz = nx*ny, LDS copies
-// use padded strides (sy = 2 mod 4, sz = 1 mod 4 doubles) so that the 64 lanes of a wave --
-// 8 blocks x 8 cells -- spread evenly over the LDS banks.
+// The two in-plane sums of a cell's row of A on a Galerkin level, p0 = (m_y (x) m_x) x and p1 =
+// (a_y (x) m_x + m_y (x) a_x) x over the 5 x 5 window of plane P, in index order.  The Galerkin
+// operator of the wall-bounded Laplacian is a Kronecker sum, A = a_z (x) m_y (x) m_x + m_z (x)
+// (a_y (x) m_x + m_y (x) a_x), with 5-point periodic 1D stencils s1d = (m_x, a_x, m_y, a_y)
+// (offsets -2..2, uniform over the level): each row of the plane is reduced with m_x and a_x, then
+// the plane with m_y and a_y, 65 FMAs.  P is a tile in LDS, element ys[dy] * sy + xs[dx].
 template <typename T>
 __device__ __forceinline__ T gal_plane(const T* __restrict__ P, int sy, const int* xs,
                                        const int* ys, const T* s1d, T& p1) {

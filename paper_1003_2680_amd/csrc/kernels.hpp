@@ -30,13 +30,11 @@ struct NoiseLevel {
   const void* bfac;       // T[nz/2][kBlockRow]: the level's block factors (L_BB^-T at offset 64);
                           // null: a point level (split colours: colour c of a component begins
                           // at c N/2, call q is sites 2q, 2q + 1)
-  uint32_t calls_before;  // prefix sum of nslot*nact*N/2 over the previous entries
 };
 struct NoiseGenArgs {
   int nlev;
   int ncomp;   // component stride of the noise buffers
   int nact;    // components drawn (the first nact)
-  uint32_t total;
   NoiseLevel lv[kMaxNoiseLevels];
 };
 
@@ -105,9 +103,9 @@ hipError_t launch_restrict_residual0(T* bc, T* xc, const T* xr, const T* xb, con
 template <typename T>
 hipError_t launch_prolong0(T* xr, T* xb, const T* e, int nxf, int nyf, int nzf, int ncomp,
                            int colours, hipStream_t s);
-template <typename T>
-hipError_t launch_residual_gal(T* r, const T* x, const T* b, const T* s1d, const T* zt, int nx,
-                               int ny, int nz, int ncomp, hipStream_t s);
+// r = b - A x on a block level, in index order (the FP32 chain)
+hipError_t launch_residual_gal(float* r, const float* x, const float* b, const float* s1d,
+                               const float* zt, int nx, int ny, int nz, int ncomp, hipStream_t s);
 // The 1D stencils m, a of a Galerkin level's periodic axes with P^T folded in: taps t and 7 - t (fine
 // cells 2J - 3 + t of coarse position J) are sum_c w_c s[t - 3 - c], w = (1/4, 3/4, 3/4, 1/4) at
 // c = -1 .. 2.

@@ -1131,29 +1131,27 @@ hipError_t launch_restrict_residual0(T* bc, T* xc, const T* xr, const T* xb, con
   const int nxc = nx >> 1, nyc = ny >> 1, nzc = nz >> 1;
   if (nxc * nyc * nzc == 0) return hipSuccess;
   const T ih2 = (T)(1.0 / (h * h));
-  {
-    // a chain in FP32 keeps its order of additions (block_update.hpp: index_order), and
-    // an odd number of coarse columns does not pair up
-    if ((sizeof(T) == 4 && chain) || nxc % 2) {
-      auto go = [&](auto rx, auto ry) {
-        constexpr int RX = decltype(rx)::value, RY = decltype(ry)::value;
-        const int ntx = (nxc + RX - 1) / RX, nty = (nyc + RY - 1) / RY;
-        dim3 grid(ntx * nty, (nzc + RR_Z - 1) / RR_Z, ncomp);
-        if (br)
-          k_restrict_residual0<T, true, RX, RY>
-              <<<grid, TPB, 0, s>>>(bc, xc, xr, xb, br, bb, nx, ny, nz, ntx, ih2);
-        else
-          k_restrict_residual0<T, false, RX, RY>
-              <<<grid, TPB, 0, s>>>(bc, xc, xr, xb, br, bb, nx, ny, nz, ntx, ih2);
-      };
-      // 16 x 8 coarse cells per work-group where the grid is that wide (less halo and scalar work
-      // per cell), else 8 x 8
-      if (nxc >= 16)
-        go(std::integral_constant<int, 16>(), std::integral_constant<int, 8>());
+  // a chain in FP32 keeps its order of additions (block_update.hpp: index_order), and an odd
+  // number of coarse columns does not pair up
+  if ((sizeof(T) == 4 && chain) || nxc % 2) {
+    auto go = [&](auto rx, auto ry) {
+      constexpr int RX = decltype(rx)::value, RY = decltype(ry)::value;
+      const int ntx = (nxc + RX - 1) / RX, nty = (nyc + RY - 1) / RY;
+      dim3 grid(ntx * nty, (nzc + RR_Z - 1) / RR_Z, ncomp);
+      if (br)
+        k_restrict_residual0<T, true, RX, RY>
+            <<<grid, TPB, 0, s>>>(bc, xc, xr, xb, br, bb, nx, ny, nz, ntx, ih2);
       else
-        go(std::integral_constant<int, 8>(), std::integral_constant<int, 8>());
-      return hipGetLastError();
-    }
+        k_restrict_residual0<T, false, RX, RY>
+            <<<grid, TPB, 0, s>>>(bc, xc, xr, xb, br, bb, nx, ny, nz, ntx, ih2);
+    };
+    // 16 x 8 coarse cells per work-group where the grid is that wide (less halo and scalar work
+    // per cell), else 8 x 8
+    if (nxc >= 16)
+      go(std::integral_constant<int, 16>(), std::integral_constant<int, 8>());
+    else
+      go(std::integral_constant<int, 8>(), std::integral_constant<int, 8>());
+    return hipGetLastError();
   }
   if (br) launch_fold_residual0<T, true>(bc, xc, xr, xb, br, bb, nx, ny, nz, ncomp, ih2, s);
   else launch_fold_residual0<T, false>(bc, xc, xr, xb, br, bb, nx, ny, nz, ncomp, ih2, s);

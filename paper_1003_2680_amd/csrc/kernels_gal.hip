@@ -482,7 +482,7 @@ __global__ __launch_bounds__(TILE_I * TILE_J * 8) void k_block_tile_multi(BlockM
 // r = b - A x on a Galerkin level, LDS-tiled: a work-group owns GR_X x GR_Y x GR_Z cells and
 // stages the box within 2 of them; a thread takes a z-column of GR_Z cells and forms each of
 // the GR_Z + 4 staged planes' two partial sums once, adding them into every cell of the
-// column they reach (the per-cell order of the additions is that of gal_apply).
+// column they reach, plane by plane in index order.
 constexpr int GR_X = 16, GR_Y = 16, GR_Z = 4;
 constexpr int GR_SX = GR_X + 4, GR_SY = GR_Y + 4, GR_SZ = GR_Z + 4;
 
@@ -1060,12 +1060,11 @@ hipError_t launch_block_pass_multi(const BlockPassItem<T>* items, int n, int col
   return launch_block_multi_tiled<T, 4, 4>(items, n, colour, kind, s);
 }
 
-template <typename T>
-hipError_t launch_residual_gal(T* r, const T* x, const T* b, const T* s1d, const T* zt, int nx,
-                               int ny, int nz, int ncomp, hipStream_t s) {
+hipError_t launch_residual_gal(float* r, const float* x, const float* b, const float* s1d,
+                               const float* zt, int nx, int ny, int nz, int ncomp, hipStream_t s) {
   const int ntx = (nx + GR_X - 1) / GR_X, nty = (ny + GR_Y - 1) / GR_Y;
   dim3 grid(ntx * nty, (nz + GR_Z - 1) / GR_Z, ncomp);
-  k_residual_gal_tile<T><<<grid, TPB, 0, s>>>(r, x, b, s1d, zt, nx, ny, nz, ntx);
+  k_residual_gal_tile<float><<<grid, TPB, 0, s>>>(r, x, b, s1d, zt, nx, ny, nz, ntx);
   return hipGetLastError();
 }
 
@@ -1143,7 +1142,6 @@ hipError_t launch_coarsest(T* x, const T* b, const double* ainv, const double* w
 
 template <typename T>
 hipError_t launch_level_noise(const NoiseGenArgs& a, const NoiseArgs& na, hipStream_t s) {
-  if (a.total == 0 || a.nlev == 0) return hipSuccess;
   uint32_t maxblk = 0;
   int maxslot = 0;
   for (int e = 0; e < a.nlev; ++e) {
@@ -1151,6 +1149,7 @@ hipError_t launch_level_noise(const NoiseGenArgs& a, const NoiseArgs& na, hipStr
     maxblk = nb > maxblk ? nb : maxblk;
     maxslot = a.lv[e].nslot > maxslot ? a.lv[e].nslot : maxslot;
   }
+  if (maxblk == 0 || maxslot * a.nact == 0) return hipSuccess;
   dim3 grid(blocks_for(maxblk), a.nlev, maxslot * a.nact);
   k_level_noise<T><<<grid, TPB, 0, s>>>(a, na);
   return hipGetLastError();
@@ -1164,8 +1163,6 @@ hipError_t launch_level_noise(const NoiseGenArgs& a, const NoiseArgs& na, hipStr
   template hipError_t launch_block_pair<T>(const HalfPassItem<T>*, int, int, int, hipStream_t);   \
   template hipError_t launch_block_pass_multi<T>(const BlockPassItem<T>*, int, int, int, int,     \
                                                  hipStream_t);                                   \
-  template hipError_t launch_residual_gal<T>(T*, const T*, const T*, const T*, const T*, int,    \
-                                             int, int, int, hipStream_t);                        \
   template hipError_t launch_fold_residual<T>(T*, T*, const T*, const T*, const T*,             \
                                               const FoldTaps<T>&, int, int, int, int,          \
                                               hipStream_t);                                     \
