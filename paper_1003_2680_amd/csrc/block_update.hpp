@@ -103,9 +103,10 @@ struct BlockWeights<T, SPLIT, true> {
   T z0[5], z1[5], F[8];
 };
 // The device table of a block layer bz (kBlockRow values): A_BB^-1 with entry m of row k that of
-// cell k ^ m, cells k = kx + 2 ky + 4 kz; L_BB^-T; and at kBlockZ the packed z-factors of the two
-// cell layers kz, own0, own1, oth0, oth1 of planes m = 0 .. 2 and a zero each.
-constexpr int kBlockRow = 192, kBlockZ = 128;
+// cell k ^ m, cells k = kx + 2 ky + 4 kz; L_BB^-T; at kBlockZ the packed z-factors of the two
+// cell layers kz, own0, own1, oth0, oth1 of planes m = 0 .. 2 and a zero each; and for sums in index
+// order the layers' own z-rows, z0 and z1 eight apart (kBlockRows), and A_BB^-1 by cell (kBlockF).
+constexpr int kBlockRow = 256, kBlockZ = 128, kBlockRows = 160, kBlockF = 192;
 // Fp, Zp: a layer's A_BB^-1 part and its packed z-factors.
 template <typename T, int SPLIT, typename PT>
 __device__ __forceinline__ void block_weights(BlockWeights<T, SPLIT, true>& w, const PT Fp,
@@ -138,6 +139,26 @@ __device__ __forceinline__ void block_weights(BlockWeights<T, SPLIT, false>& w, 
   const PT F = Fp + (kx + 2 * ky + 4 * kz) * 8;
 #pragma unroll
   for (int m = 0; m < 8; ++m) w.F[m] = F[m];
+}
+
+// The same from a layer's row of the device table in memory, where the entries in index order lie
+// side by side: a lane's eight factors are two wide loads, where picking them out of the lane order
+// (in LDS, above) is a load each (FP32 single-colour pass of 256x256x128: 15.9 us, with those 18.3).
+template <typename T, bool INDEX>
+__device__ __forceinline__ void block_row_weights(BlockWeights<T, 1, INDEX>& w, const T* row, int kx,
+                                                  int ky, int kz) {
+  if constexpr (INDEX) {
+    const T *z = row + kBlockRows + kz * 16, *F = row + kBlockF + (kx + 2 * ky + 4 * kz) * 8;
+#pragma unroll
+    for (int d = 0; d < 5; ++d) {
+      w.z0[d] = z[d];
+      w.z1[d] = z[8 + d];
+    }
+#pragma unroll
+    for (int m = 0; m < 8; ++m) w.F[m] = F[m];
+  } else {
+    block_weights<T, 1>(w, row, row + kBlockZ, kx, ky, kz, 0);
+  }
 }
 
 // New value of the lane's cell: x_B + A_BB^-1 (b_B - (A x)_B) + noise, which equals A_BB^-1 (b_B -

@@ -941,7 +941,8 @@ int check_fp64(const Hierarchy& h) {
 }
 
 // The device form of a block level's factors (block_update.hpp): per block layer A_BB^-1 in lane
-// order, L_BB^-T, and the z-factors of the layer's planes packed for its two cell layers.
+// order, L_BB^-T, the z-factors of the layer's planes packed for its two cell layers, and the
+// layers' z-rows and A_BB^-1 in index order.
 std::vector<double> block_rows(const Level& v) {
   std::vector<double> out((size_t)(v.nz / 2) * kBlockRow, 0.0);
   for (int bz = 0; bz < v.nz / 2; ++bz) {
@@ -949,10 +950,17 @@ std::vector<double> block_rows(const Level& v) {
     double* dst = &out[(size_t)bz * kBlockRow];
     for (int k = 0; k < 8; ++k)
       for (int m = 0; m < 8; ++m) dst[k * 8 + m] = src[k * 8 + (k ^ m)];
-    for (int q = 0; q < 64; ++q) dst[64 + q] = src[64 + q];
+    for (int q = 0; q < 64; ++q) {
+      dst[64 + q] = src[64 + q];
+      dst[kBlockF + q] = src[q];
+    }
     for (int kz = 0; kz < 2; ++kz) {
       const double* zo = &v.zt[(size_t)(2 * bz + kz) * 10];
       const double* zp = &v.zt[(size_t)(2 * bz + 1 - kz) * 10];
+      for (int d = 0; d < 5; ++d) {
+        dst[kBlockRows + kz * 16 + d] = zo[d];
+        dst[kBlockRows + kz * 16 + 8 + d] = zo[5 + d];
+      }
       double* z = dst + kBlockZ + kz * 16;
       for (int m = 0; m < 3; ++m) {  // plane 3 kz + m of the layer's six
         const int own = 2 * kz + m, oth = kz ? 3 + m : m - 1;  // its dz + 2 from either cell

@@ -174,7 +174,7 @@ __device__ __forceinline__ void block_tile_body(T* __restrict__ xg, const T* __r
   __syncthreads();
   BlockWeights<T, 1, index_order<T, KIND>> w;
   const T* row = bfac + (size_t)bz * kBlockRow;
-  block_weights<T, 1>(w, row, row + kBlockZ, kx, ky, kz, 0);
+  block_row_weights<T>(w, row, kx, ky, kz);
 #pragma unroll
   for (int m = 0; m < 3; ++m) w.po[m] = (3 * kz + m) * TP;
   const Stencils<T> st = load_stencils(s1d);
@@ -281,7 +281,7 @@ __device__ __forceinline__ void block_half_body(const HalfItem<T>& h, int cz, bo
   __builtin_amdgcn_sched_barrier(0);
   BlockWeights<T, 1, index_order<T, KIND>> w;
   const T* row = h.bfac + (size_t)bz * kBlockRow;
-  block_weights<T, 1>(w, row, row + kBlockZ, kx, ky, kz, 0);
+  block_row_weights<T>(w, row, kx, ky, kz);
 #pragma unroll
   for (int m = 0; m < 3; ++m) w.po[m] = (3 * kz + m) * TP;
   __syncthreads();
@@ -410,7 +410,7 @@ __device__ __forceinline__ void block_pair_body(const HalfItem<T>& h, int c_firs
   __builtin_amdgcn_sched_barrier(0);
   BlockWeights<T, 1, index_order<T, KIND>> w;
   const T* row = h.bfac + (size_t)bz * kBlockRow;
-  block_weights<T, 1>(w, row, row + kBlockZ, kx, ky, kz, 0);
+  block_row_weights<T>(w, row, kx, ky, kz);
 #pragma unroll
   for (int m = 0; m < 3; ++m) w.po[m] = (3 * kz + m) * TP;
   __syncthreads();
