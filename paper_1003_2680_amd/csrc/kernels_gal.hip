@@ -39,7 +39,9 @@ __device__ __forceinline__ void colour_block_noise(const T* __restrict__ W, cons
   }
 }
 
-template <typename T>
+// POINT: some entry is a point level (with its branch the FP64 form has 78 registers, 68 without: one
+// wave a SIMD less, 2 % of the time of 128^3 x 24).
+template <typename T, bool POINT>
 __global__ __launch_bounds__(TPB) void k_level_noise(NoiseGenArgs a, NoiseArgs na) {
   using V2 = typename std::conditional<sizeof(T) == 8, double2, float2>::type;
   const NoiseLevel& L = a.lv[blockIdx.y];
@@ -47,7 +49,7 @@ __global__ __launch_bounds__(TPB) void k_level_noise(NoiseGenArgs a, NoiseArgs n
   const uint32_t bid = blockIdx.x * TPB + threadIdx.x;  // block within (slot, comp)
   const uint32_t s = blockIdx.z / (uint32_t)a.nact;
   const uint32_t comp = blockIdx.z - s * (uint32_t)a.nact;
-  if (!L.bfac) {
+  if (POINT && !L.bfac) {
     // a point level: N/4 calls a colour, four of the N/2 a thread, neighbours side by side
     const uint32_t per = (N / 2 + 3) / 4;
     if (bid >= per || (int)s >= L.nslot) return;
@@ -1144,14 +1146,17 @@ template <typename T>
 hipError_t launch_level_noise(const NoiseGenArgs& a, const NoiseArgs& na, hipStream_t s) {
   uint32_t maxblk = 0;
   int maxslot = 0;
+  bool point = false;
   for (int e = 0; e < a.nlev; ++e) {
+    point = point || !a.lv[e].bfac;
     const uint32_t nb = ((uint32_t)a.lv[e].nx * a.lv[e].ny * a.lv[e].nz + 7) / 8;
     maxblk = nb > maxblk ? nb : maxblk;
     maxslot = a.lv[e].nslot > maxslot ? a.lv[e].nslot : maxslot;
   }
   if (maxblk == 0 || maxslot * a.nact == 0) return hipSuccess;
   dim3 grid(blocks_for(maxblk), a.nlev, maxslot * a.nact);
-  k_level_noise<T><<<grid, TPB, 0, s>>>(a, na);
+  if (point) k_level_noise<T, true><<<grid, TPB, 0, s>>>(a, na);
+  else k_level_noise<T, false><<<grid, TPB, 0, s>>>(a, na);
   return hipGetLastError();
 }
 
