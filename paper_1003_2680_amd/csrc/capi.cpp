@@ -478,6 +478,10 @@ bool splits_bottom(const Hierarchy& h) {
   return h.wide_coarsest && h.lv[first_bottom(h)].kind != KIND_CHOL;
 }
 
+bool lone_draw(const Hierarchy& h) {
+  return h.wide_coarsest && h.lv[first_bottom(h)].kind == KIND_CHOL;
+}
+
 // The whole cycle, its point level included, runs in the bottom launch.
 bool point_bottom(const Hierarchy& h) {
   const int l = first_bottom(h);
@@ -489,8 +493,8 @@ int bottom_part(const Run& r, BotPart part) {
 }
 
 // Every level from h.bottom down: in one launch (LDS-resident, one work-group per component), or
-// in two around the coarsest draw's own where that level is large; a bottom that is the coarsest
-// level alone is that draw.
+// in two around the coarsest draw's own where that level is large; a bottom that is a large
+// coarsest level alone is that draw.
 template <typename T>
 int bottom_cycle(Run& r) {
   Hierarchy& h = *r.h;
@@ -504,7 +508,7 @@ int bottom_cycle(Run& r) {
                              bottom_part(r, part), na, r.s));
     return SMG_OK;
   };
-  if (h.lv[first_bottom(h)].kind == KIND_CHOL) {
+  if (lone_draw(h)) {
     SMG_TRY(coarsest_step<T>(r, last));
   } else if (splits_bottom(h)) {
     SMG_TRY(launch(BOT_DOWN));
@@ -824,7 +828,7 @@ int batch_bottoms(const std::vector<Run*>& runs) {
       for (Run* r : runs) {
         Hierarchy& h = *r->h;
         if (!split_bottom(h) || (int)refined(h) != f32 || kind_of(*r) != kind) continue;
-        if (r->nc > kBotMultiWG || h.lv[first_bottom(h)].kind == KIND_CHOL) {  // launches of its own
+        if (r->nc > kBotMultiWG || lone_draw(h)) {  // launches of its own
           Run ri = *r;
           ri.has_b0 = ri.has_b0 || refined(h);
           SMG_TRY(f32 ? bottom_cycle<float>(ri) : bottom_cycle<double>(ri));

@@ -456,8 +456,8 @@ __device__ __forceinline__ void point_sweeps(T* X, const T* B, bool has_b, const
                                              size_t slot_stride, int slot0, int nslot, bool post) {
   constexpr bool NOISE = KIND == CYCLE_NOISE;
   const int nsite = S.nsite;
-  // FP32: the order of the z-neighbours' sum in the colour-pass launches (launch_rb_pass)
-  const bool vec = !index_order<T, KIND> || (L.nx >> 1) % (16 / (int)sizeof(T)) == 0;
+  // the order of the sums in the colour-pass launches (launch_rb_pass), whose bits these are
+  const bool vec = (L.nx >> 1) % (16 / (int)sizeof(T)) == 0;
   T dg[10];
 #pragma unroll
   for (int e = 0; e < 10; ++e) dg[e] = (T)L.s1d[e];  // uniform: scalar registers
@@ -485,11 +485,12 @@ __device__ __forceinline__ void point_sweeps(T* X, const T* B, bool has_b, const
         sum = (sxy + (top ? T(0) : xo[S.u[k]])) + (low ? T(0) : xo[S.d[k]]);
       const int nw = (int)top + (int)low;
       auto by_walls = [&](T d6, T d7, T d8) { return nw == 0 ? d6 : (nw == 1 ? d7 : d8); };
-      const T rhs = has_b ? fma(sum, dg[9], bc[own]) : T(0), idg = by_walls(dg[0], dg[1], dg[2]);
-      T v = has_b ? rhs * idg : sum * by_walls(dg[6], dg[7], dg[8]);
+      const T rhs = has_b ? fma(sum, dg[9], bc[own]) : sum * dg[9];
+      const T idg = by_walls(dg[0], dg[1], dg[2]);
+      T v = has_b || !vec ? rhs * idg : sum * by_walls(dg[6], dg[7], dg[8]);
       if (NOISE) {
         const T sig = by_walls(dg[3], dg[4], dg[5]);
-        v = has_b && !vec ? fma(rhs, idg, sig * zn[k]) : fma(sig, zn[k], v);
+        v = vec ? fma(sig, zn[k], v) : fma(rhs, idg, sig * zn[k]);
       }
       if (S.p[k] < nsite) xc[own] = v;
     }
@@ -513,9 +514,8 @@ __device__ __forceinline__ void point_residual(T* R, const T* X, const T* B, boo
       T sn = (xo[S.p[k]] + xo[S.o[k][c]]) + (xo[S.s[k]] + xo[S.n[k]]);
       if (!top) sn += xo[S.u[k]];
       if (!low) sn += xo[S.d[k]];
-      T r = -(T(6 + (int)top + (int)low) * X[c * nsite + S.p[k]] - sn) * ih2;
-      if (has_b) r += B[c * nsite + S.p[k]];
-      R[S.nat[k][c]] = r;
+      const T t = fma(-T(6 + (int)top + (int)low), X[c * nsite + S.p[k]], sn);
+      R[S.nat[k][c]] = has_b ? fma(t, ih2, B[c * nsite + S.p[k]]) : t * ih2;
     }
   }
 }
@@ -549,6 +549,80 @@ __device__ __forceinline__ T point_restrict(const T* R, int nx, int ny, int nz, 
     acc = fma(wz, (cs[0] + cs[1]) + (cs[2] + cs[3]), acc);
   }
   return acc;
+}
+
+// b_1 = P^T (b - A x) axis by axis, the sums of k_fold_residual0 in its order: per fine row and
+// coarse column u = Px^T x and s = Px^T (b - a_x x), per coarse row p and q of them, then the six
+// planes of a layer.  R (n elements) holds first u, s on (nx/2, ny, nz), then p, q on (nx/2, ny/2, nz).
+template <typename T>
+__device__ __forceinline__ void point_fold(T* bc, T* R, const T* X, const T* B, bool has_b,
+                                           const BotLevel& L) {
+  const int nh = L.nx >> 1, ny = L.ny, nz = L.nz, nyc = ny >> 1, nzc = nz >> 1;
+  const int tid = (int)threadIdx.x, nsite = nh * ny * nz, half = nsite >> 1, col = nh * nyc;
+  const T ih2 = (T)L.s1d[9];
+  const T q1 = T(0.25), q3 = T(0.75), d1 = T(0.25) * ih2, d2 = T(0.5) * ih2;
+  for (int it = tid; it < nsite; it += BOT_TPB) {
+    int row, j, z, y;
+    divmod_uniform(it, nh, row, j);
+    divmod_uniform(row, ny, z, y);
+    const int odd = (y + z) & 1, l = j == 0 ? it + nh - 1 : it - 1, r = j + 1 == nh ? it - j : it + 1;
+    // even cells 2j of the row are entries of colour (y + z) & 1, odd ones of the other
+    const T *E = X + odd * nsite, *O = X + (1 - odd) * nsite;
+    const T m = E[it] + O[it], n = O[l] + E[r];
+    T s = fma(d1, n + (E[l] + O[r]), -d2 * m);
+    if (has_b) {
+      const T *Eb = B + odd * nsite, *Ob = B + (1 - odd) * nsite;
+      s += fma(q3, Eb[it] + Ob[it], q1 * (Ob[l] + Eb[r]));
+    }
+    R[it] = fma(q3, m, q1 * n);
+    R[nsite + it] = s;
+  }
+  __syncthreads();
+  constexpr int PER = 4096 / 4 / BOT_TPB;
+  T p[PER], q[PER];
+#pragma unroll
+  for (int k = 0; k < PER; ++k) {
+    const int it = tid + k * BOT_TPB;
+    if (it >= half) break;
+    int r, Xc, Y, z;
+    divmod_uniform(it, nh, r, Xc);
+    divmod_uniform(r, nyc, z, Y);
+    T u[6], s[6];
+#pragma unroll
+    for (int d = 0; d < 6; ++d) {
+      const int at = (z * ny + wrapm(2 * Y - 2 + d, ny)) * nh + Xc;
+      u[d] = R[at];
+      s[d] = R[nsite + at];
+    }
+    const T mid = u[2] + u[3], near = u[1] + u[4], far = u[0] + u[5];
+    p[k] = fma(q3, mid, q1 * near);
+    q[k] = fma(q3, s[2] + s[3], q1 * (s[1] + s[4])) + fma(d1, near + far, -d2 * mid);
+  }
+  __syncthreads();
+#pragma unroll
+  for (int k = 0; k < PER; ++k) {
+    const int it = tid + k * BOT_TPB;
+    if (it >= half) break;
+    R[it] = p[k];
+    R[half + it] = q[k];
+  }
+  __syncthreads();
+  for (int it = tid; it < col * nzc; it += BOT_TPB) {
+    int Z, c;
+    divmod_uniform(it, col, Z, c);
+    const T mid = d2 + (Z == 0 ? d1 : T(0)) + (Z == nzc - 1 ? d1 : T(0));
+    T acc = T(0);
+#pragma unroll
+    for (int d = 0; d < 6; ++d) {
+      const int f = 2 * Z - 2 + d;
+      if (f < 0 || f >= nz) continue;
+      acc = fma(d == 2 || d == 3 ? -mid : d1, R[f * col + c], acc);
+      T w = d == 1 || d == 4 ? q1 : q3;
+      if ((d == 2 && Z == 0) || (d == 3 && Z == nzc - 1)) w = T(0.5);
+      if (d > 0 && d < 5) acc = fma(w, R[half + f * col + c], acc);
+    }
+    bc[it] = acc;
+  }
 }
 
 // POINT: the first level may be a point level (level 0).
@@ -671,20 +745,23 @@ __device__ __forceinline__ void bottom_body(const BotArgs& a, const uint32_t com
       return;
     }
     if (part == BOT_DOWN) point_store(ps);
-    point_residual<T>(X + 2 * n0, X, X + n0, has_b, L0, ps);
-    __syncthreads();
-    // b_1 = P^T r, x_1 = 0
+    // b_1 = P^T (b - A x), x_1 = 0, added up as the launch of this restriction does
+    // (launch_restrict_residual0)
     const BotLevel& C = a.lv[1];
     T* xc = sm + a.lds_off[1];
+    T* bc = xc + C.nz * C.sz;
     for (int q = tid; q < C.nz * C.sz; q += BOT_TPB) xc[q] = T(0);
-    for (int q = tid; q < C.nx * C.ny * C.nz; q += BOT_TPB) {
-      int Xc, Y, Z, r;
-      divmod_uniform(q, C.nx, r, Xc);
-      divmod_uniform(r, C.ny, Z, Y);
-      xc[C.nz * C.sz + q] =
-          index_order<T, KIND>
-              ? point_restrict<T>(X + 2 * n0, L0.nx, L0.ny, L0.nz, Xc, Y, Z)
-              : restrict_at<T>(X + 2 * n0, L0.nx, L0.nx * L0.ny, L0.nx, L0.ny, L0.nz, Xc, Y, Z);
+    if (!index_order<T, KIND> && (L0.nx >> 1) % 2 == 0) {
+      point_fold<T>(bc, X + 2 * n0, X, X + n0, has_b, L0);
+    } else {
+      point_residual<T>(X + 2 * n0, X, X + n0, has_b, L0, ps);
+      __syncthreads();
+      for (int q = tid; q < C.nx * C.ny * C.nz; q += BOT_TPB) {
+        int Xc, Y, Z, r;
+        divmod_uniform(q, C.nx, r, Xc);
+        divmod_uniform(r, C.ny, Z, Y);
+        bc[q] = point_restrict<T>(X + 2 * n0, L0.nx, L0.ny, L0.nz, Xc, Y, Z);
+      }
     }
     __syncthreads();
   }

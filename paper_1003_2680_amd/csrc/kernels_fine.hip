@@ -276,11 +276,9 @@ __global__ __launch_bounds__(TPB) void k_rb_pass(T* __restrict__ xc, const T* __
     int nw = 0;
     if (z + 1 < nz) s += o[rb + j + plane]; else ++nw;
     if (z > 0) s += o[rb + j - plane]; else ++nw;
-    T v = s * inv_h2;
-    if (HAS_B) v += bc[base + p];
-    v *= dg.inv_d[nw];
-    if (NOISE) v += dg.sig[nw] * (t == 0 ? z0 : z1);
-    xc[base + p] = v;
+    // the roundings as in the bottom's passes (kernels_bottom.hip: point_sweeps)
+    const T v = HAS_B ? fma(s, inv_h2, bc[base + p]) : s * inv_h2;
+    xc[base + p] = NOISE ? fma(v, dg.inv_d[nw], dg.sig[nw] * (t == 0 ? z0 : z1)) : v * dg.inv_d[nw];
   }
 }
 
@@ -414,9 +412,9 @@ __global__ __launch_bounds__(TPB) void k_restrict_residual0(
         int nw = 0;
         if (f + 1 < nz) sn += Pp[rxo[p]]; else ++nw;
         if (f > 0) sn += Pm[rxo[p]]; else ++nw;
-        T rv = -(T(6 + nw) * c[0] - sn) * inv_h2;
-        if (HAS_B) rv += bcur[p];
-        R[roff[p]] = rv;
+        // the roundings as in the bottom's restriction (kernels_bottom.hip: point_residual)
+        const T t = fma(-T(6 + nw), c[0], sn);
+        R[roff[p]] = HAS_B ? fma(t, inv_h2, bcur[p]) : t * inv_h2;
       }
     }
     if (HAS_B && f + 2 <= f1) load_b(bcur, f + 2);
