@@ -68,7 +68,8 @@ TRAFFIC_FILE = os.path.join(ROOT, "profiles", "traffic_128cubed_3comp_fp64.json"
 KERNEL_SOURCES = {
     "fine_pass": ("kernels_fine.hip", "device_common.hpp", "philox.hpp", "kernels.hpp"),
     "fine_pass_fp32": ("kernels_fine.hip", "device_common.hpp", "philox.hpp", "kernels.hpp"),
-    "level1_block_pass": ("kernels_gal.hip", "device_common.hpp", "philox.hpp", "kernels.hpp"),
+    "level1_block_pass": ("kernels_gal.hip", "block_update.hpp", "device_common.hpp",
+                          "philox.hpp", "kernels.hpp"),
     "composite_base_pass": ("kernels_comp.hip", "composite.hpp", "device_common.hpp",
                             "philox.hpp", "kernels.hpp"),
 }

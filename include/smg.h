@@ -243,8 +243,8 @@ int smg_sample_field_static(smg_hierarchy* h, int64_t n, uint64_t seed, uint64_t
  *     rtol within max_cycles; infos (host, [max(nchains, 1)], or NULL) filled.
  * Sampling items run first, cycle by cycle in step (cycle k of every item before cycle k + 1 of
  * any); then the solve items cycle in step until each has converged or run out of cycles.  In
- * every cycle the levels that each hierarchy runs in its LDS-resident bottom launch (the levels
- * of at most 4096 cells and the coarsest draw: Sec. "Stochastic Multigrid Methods", Alg. 3,
+ * every cycle the levels that each hierarchy runs in its LDS-resident bottom (the levels
+ * of at most 4096 cells and a coarsest draw of fewer than 192 unknowns: Sec. "Stochastic Multigrid Methods", Alg. 3,
  * below the tiled levels) are run for all items in as few launches as possible (one per sweep
  * precision and noise setting, up to 16 hierarchies and 256 components each), instead of one
  * latency-bound launch per hierarchy.  With SMG_OPT_STREAM_GROUPS above 1 on any sampling
@@ -313,14 +313,18 @@ int smg_debug_coarsest(smg_hierarchy* h, void* x, const void* b, uint64_t seed, 
 int smg_debug_host_table(const smg_hierarchy* h, int32_t level, int32_t which, double* out,
                          size_t count);
 
-/* smg_set_option: execution switches that never change results.
- *   SMG_OPT_BOTTOM_KERNEL (default 1): run the levels with at most 4096 cells (and the
- *   coarsest draw) in one LDS-resident launch per cycle; 0 = one launch per colour pass.
+/* smg_set_option: execution switches that do not change results.
+ *   SMG_OPT_BOTTOM_KERNEL (default 1): run the levels with at most 4096 cells (level 0 included
+ *   where the whole hierarchy is that small) and the coarsest draw in one LDS-resident launch per
+ *   cycle, or in two around a launch for a draw of 192 unknowns and more; 0 = one launch per
+ *   colour pass (results agree to rounding).
  *   SMG_OPT_BLOCK_TILE (default SMG_TILE_AUTO): see below.
  *   SMG_OPT_TIMED_KERNEL (default SMG_TIMED_FINE_PASS): the kernel class that
  *   smg_kernel_timing brackets with events: the level-0 colour pass, the level-1 block
  *   colour passes (one, two or four colours per launch, see SMG_OPT_BLOCK_PAIRS), or the
- *   LDS-resident bottom launch. */
+ *   LDS-resident bottom (counted once a cycle, with the coarsest draw's own launch where it has
+ *   one).  While the level-0 passes are timed they are launches of their own, also where level 0
+ *   otherwise runs in the bottom (the same bits). */
 enum {
   SMG_OPT_BOTTOM_KERNEL = 1,
   SMG_OPT_TIMED_KERNEL = 2,

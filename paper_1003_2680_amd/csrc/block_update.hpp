@@ -353,9 +353,9 @@ __device__ __forceinline__ Stencils<T> load_stencils(const T* s1d) {
 // fall on different banks (32 of four bytes).  FP64 reads are served sixteen lanes at a time (two
 // neighbouring blocks: x steps 0, 1, 4, 5; the y-partners an odd number of rows apart, the
 // z-partners three planes), which need distinct elements mod 16: planes of 8 mod 16.  FP32 reads
-// are served 32 lanes at a time: planes of 16 mod 32.  (With 16 mod 32 for both, the z-partners of
-// FP64 share a bank: a third of the LDS time of the 16^3 .. 4^3 bottom, 109 against 92 us; FP32
-// with 8 mod 16: 82 against 77 us.)
+// are served 32 lanes at a time: planes of 16 mod 32.  (Bottom launches of a 16^3 level, half a
+// cycle: FP64 34.9 us, with 16 mod 32, where its z-partners share a bank, 40.9; FP32 32.1, with 8
+// mod 16 34.8.)
 __host__ __device__ constexpr int block_plane_stride(int plane, size_t elem) {
   return elem == 8 ? plane + (24 - plane % 16) % 16 : plane + (48 - plane % 32) % 32;
 }

@@ -56,7 +56,10 @@ struct Point2Args {
 };
 // Rows a work-group owns (even; 0: the window of a row strip does not fit): as many as leave the
 // launch two work-groups per compute unit, at least eight (fewer draw more rows again than they
-// own).
+// own) unless only four fit.  Wherever a window fits, strips are the faster form, also on chips
+// full of chains, whose launches are bound by the redrawn noise: four cycles, a launch a colour /
+// strips, us: 512x512 1 chain 1309 / 1230, 8 2195 / 1668, 64 9796 / 7069; 416x512 (four rows) 16
+// chains 2890 / 2168, 128 15 354 / 10 667; 256x256 255 chains 8976 / 5345; 64x64 255 792 / 443.
 inline int level0_rows(int nx, int nz, int ncomp, int npass, bool restricts) {
   const int halo = npass + (restricts ? 2 : 0);
   int rows = 32;

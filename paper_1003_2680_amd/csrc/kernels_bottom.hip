@@ -22,8 +22,8 @@ namespace {
 // two halo cells per side, so a row's five reads are one address with immediate offsets; the
 // z-factors and the block's A_BB^-1 row stay in registers over the four passes that share them;
 // and the noise of a pair of passes is loaded while the pair before runs.  The 16^3 .. 4^3 bottom
-// takes 81 us (FP64, inside the kernel): a 16^3 pass 1.3 us, an 8^3 pass 0.55 us.  With indexed
-// window reads, permutes and a noise load inside each pass it took 203 us.
+// takes 88 us a launch (FP64): a 16^3 pass 1.3 us, an 8^3 pass 0.55 us.  With indexed window
+// reads, permutes and a noise load inside each pass it took 203 us.
 constexpr int BOT_TPB = 512;
 
 // Pointers read from a level descriptor are taken into the global address space: a load through a
@@ -402,8 +402,9 @@ __device__ __forceinline__ void bot_restrict(T* bc, T* R, const T* X, const T* B
 // A thread owns the sites p = tid + k BOT_TPB of either colour, so a site's row, plane and wall
 // are found once, and the normals of a pass are loaded while the pass before runs.  A launch per
 // colour pass and transfer of such a grid is all latency: a 16^3 cycle took 75 us in 12 launches
-// and takes 55 in two (noise and this one), of which the point level 17: a pass 0.55 us, the
-// residual 1.8, its restriction 3.0, the prolongation 1.8.
+// and takes 50 in two (noise 4.6, this one 45.5; a sample's export is a third, 4.5), of which the
+// point level 17: a pass 0.55 us, the folded restriction 4.8 (as a residual and its window sums
+// did), the prolongation 1.8.
 constexpr int PT_PER = 4096 / 2 / BOT_TPB;
 template <typename T>
 struct PointSites {
