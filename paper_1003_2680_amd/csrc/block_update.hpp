@@ -102,11 +102,13 @@ struct BlockWeights<T, SPLIT, true> {
   int po[P];
   T z0[5], z1[5], F[8];
 };
-// The device table of a block layer bz (kBlockRow values): A_BB^-1 with entry m of row k that of
+// The device table of a block layer bz (kBlockRow<T> values): A_BB^-1 with entry m of row k that of
 // cell k ^ m, cells k = kx + 2 ky + 4 kz; L_BB^-T; at kBlockZ the packed z-factors of the two
-// cell layers kz, own0, own1, oth0, oth1 of planes m = 0 .. 2 and a zero each; and for sums in index
-// order the layers' own z-rows, z0 and z1 eight apart (kBlockRows), and A_BB^-1 by cell (kBlockF).
-constexpr int kBlockRow = 256, kBlockZ = 128, kBlockRows = 160, kBlockF = 192;
+// cell layers kz, own0, own1, oth0, oth1 of planes m = 0 .. 2 and a zero each; and in FP32, for sums in
+// index order, the layers' own z-rows, z0 and z1 eight apart (kBlockRows), and A_BB^-1 by cell (kBlockF).
+template <typename T>
+constexpr int kBlockRow = sizeof(T) == 4 ? 256 : 192;
+constexpr int kBlockZ = 128, kBlockRows = 160, kBlockF = 192;
 // Fp, Zp: a layer's A_BB^-1 part and its packed z-factors.
 template <typename T, int SPLIT, typename PT>
 __device__ __forceinline__ void block_weights(BlockWeights<T, SPLIT, true>& w, const PT Fp,

@@ -945,23 +945,25 @@ int check_fp64(const Hierarchy& h) {
 }
 
 // The device form of a block level's factors (block_update.hpp): per block layer A_BB^-1 in lane
-// order, L_BB^-T, the z-factors of the layer's planes packed for its two cell layers, and the
-// layers' z-rows and A_BB^-1 in index order.
+// order, L_BB^-T, the z-factors of the layer's planes packed for its two cell layers, and in
+// FP32 the layers' z-rows and A_BB^-1 in index order.
+template <typename T>
 std::vector<double> block_rows(const Level& v) {
-  std::vector<double> out((size_t)(v.nz / 2) * kBlockRow, 0.0);
+  constexpr bool index = sizeof(T) == 4;
+  std::vector<double> out((size_t)(v.nz / 2) * kBlockRow<T>, 0.0);
   for (int bz = 0; bz < v.nz / 2; ++bz) {
     const double* src = &v.bfac[(size_t)bz * 192];
-    double* dst = &out[(size_t)bz * kBlockRow];
+    double* dst = &out[(size_t)bz * kBlockRow<T>];
     for (int k = 0; k < 8; ++k)
       for (int m = 0; m < 8; ++m) dst[k * 8 + m] = src[k * 8 + (k ^ m)];
     for (int q = 0; q < 64; ++q) {
       dst[64 + q] = src[64 + q];
-      dst[kBlockF + q] = src[q];
+      if (index) dst[kBlockF + q] = src[q];
     }
     for (int kz = 0; kz < 2; ++kz) {
       const double* zo = &v.zt[(size_t)(2 * bz + kz) * 10];
       const double* zp = &v.zt[(size_t)(2 * bz + 1 - kz) * 10];
-      for (int d = 0; d < 5; ++d) {
+      for (int d = 0; index && d < 5; ++d) {
         dst[kBlockRows + kz * 16 + d] = zo[d];
         dst[kBlockRows + kz * 16 + 8 + d] = zo[5 + d];
       }
@@ -987,7 +989,7 @@ template <typename T>
 int upload_tables(Level& v, char* ws, hipStream_t s) {
   std::vector<T> g(v.s1d.begin(), v.s1d.end());
   std::vector<T> z(v.zt.begin(), v.zt.end());
-  const std::vector<double> rows = block_rows(v);
+  const std::vector<double> rows = block_rows<T>(v);
   std::vector<T> b(rows.begin(), rows.end());
   v.s1d_d = ws + v.off_s1d;
   v.zt_d = ws + v.off_zt;

@@ -27,7 +27,7 @@ struct NoiseLevel {
   int level, nx, ny, nz, nslot, slot0;
   int lg_bx, lg_bxy;      // log2 of nx/2 and of (nx/2)(ny/2) when powers of two, else -1
   void* out;              // T[nslot][ncomp][N]
-  const void* bfac;       // T[nz/2][kBlockRow]: the level's block factors (L_BB^-T at offset 64);
+  const void* bfac;       // T[nz/2][kBlockRow<T>]: the level's block factors (L_BB^-T at offset 64);
                           // null: a point level (split colours: colour c of a component begins
                           // at c N/2, call q is sites 2q, 2q + 1)
 };
@@ -47,7 +47,7 @@ struct BotLevel {
   double s1d[20];      // 1D stencils (m_x, a_x, m_y, a_y), offsets -2..2; a point level (level 0):
                        // h^2/d, sqrt(kT h^2/d) and 1/d for d = 6, 7, 8, then 1/h^2
   const void* zt;      // T: [nz][10]
-  const void* bfac;    // T: [nz/2][kBlockRow]
+  const void* bfac;    // T: [nz/2][kBlockRow<T>]
   void* xg;            // T [ncomp][n]: the level's x and b in memory, where the two parts of a
   void* bg;            // split bottom leave and find them; a point level: its split state and b
 };

@@ -712,7 +712,7 @@ __device__ __forceinline__ void bottom_body(const BotArgs& a, const uint32_t com
       for (int q = tid; q < nz * 10; q += BOT_TPB) t[q] = zt[q];
       for (int q = tid; q < (nz / 2) * kBotRow; q += BOT_TPB) {
         const int bz = q / kBotRow, e = q - bz * kBotRow;
-        t[nz * 10 + q] = bf[bz * kBlockRow + (e < 64 ? e : e - 64 + kBlockZ)];
+        t[nz * 10 + q] = bf[bz * kBlockRow<T> + (e < 64 ? e : e - 64 + kBlockZ)];
       }
     } else if (NOISE && part == BOT_WHOLE) {
       const int n = L.nx * L.ny * L.nz;

@@ -82,9 +82,9 @@ __global__ __launch_bounds__(TPB) void k_level_noise(NoiseGenArgs a, NoiseArgs n
   for (int m = 0; m < 4; ++m) normal_pair_t<T>(na, sid, comp, 4 * bid + m, n[2 * m], n[2 * m + 1]);
   if ((nbx * nby) % 64 == 0) {
     const uint32_t bzu = __builtin_amdgcn_readfirstlane(bz);
-    colour_block_noise<T, true>((const T*)L.bfac + (size_t)bzu * kBlockRow + 64, n, e);
+    colour_block_noise<T, true>((const T*)L.bfac + (size_t)bzu * kBlockRow<T> + 64, n, e);
   } else {
-    colour_block_noise<T, false>((const T*)L.bfac + (size_t)bz * kBlockRow + 64, n, e);
+    colour_block_noise<T, false>((const T*)L.bfac + (size_t)bz * kBlockRow<T> + 64, n, e);
   }
   const T sq = (T)na.sqkT;
   T* out = (T*)L.out + ((size_t)s * a.ncomp + comp) * N;
@@ -175,7 +175,7 @@ __device__ __forceinline__ void block_tile_body(T* __restrict__ xg, const T* __r
     for (int p = 0; p < PPT; ++p) Tl[sz * TP + loff[p]] = stage[sz][p];
   __syncthreads();
   BlockWeights<T, 1, index_order<T, KIND>> w;
-  const T* row = bfac + (size_t)bz * kBlockRow;
+  const T* row = bfac + (size_t)bz * kBlockRow<T>;
   block_row_weights<T>(w, row, kx, ky, kz);
 #pragma unroll
   for (int m = 0; m < 3; ++m) w.po[m] = (3 * kz + m) * TP;
@@ -282,7 +282,7 @@ __device__ __forceinline__ void block_half_body(const HalfItem<T>& h, int cz, bo
       }
   __builtin_amdgcn_sched_barrier(0);
   BlockWeights<T, 1, index_order<T, KIND>> w;
-  const T* row = h.bfac + (size_t)bz * kBlockRow;
+  const T* row = h.bfac + (size_t)bz * kBlockRow<T>;
   block_row_weights<T>(w, row, kx, ky, kz);
 #pragma unroll
   for (int m = 0; m < 3; ++m) w.po[m] = (3 * kz + m) * TP;
@@ -411,7 +411,7 @@ __device__ __forceinline__ void block_pair_body(const HalfItem<T>& h, int c_firs
       }
   __builtin_amdgcn_sched_barrier(0);
   BlockWeights<T, 1, index_order<T, KIND>> w;
-  const T* row = h.bfac + (size_t)bz * kBlockRow;
+  const T* row = h.bfac + (size_t)bz * kBlockRow<T>;
   block_row_weights<T>(w, row, kx, ky, kz);
 #pragma unroll
   for (int m = 0; m < 3; ++m) w.po[m] = (3 * kz + m) * TP;

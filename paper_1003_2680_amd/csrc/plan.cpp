@@ -416,7 +416,7 @@ int build_plan(const smg_grid_desc& d, const smg_cycle_params& p, Hierarchy& h, 
     if (v.kind == KIND_BLOCK) {
       v.off_s1d = take(v.s1d.size() * ts);
       v.off_zt = take(v.zt.size() * ts);
-      v.off_bfac = take((size_t)(v.nz / 2) * kBlockRow * ts);
+      v.off_bfac = take((size_t)(v.nz / 2) * (ts == sizeof(float) ? kBlockRow<float> : kBlockRow<double>) * ts);
       v.off_noise = take((size_t)(p.nu1 + p.nu2) * n * ts);
     }
   }
