@@ -402,9 +402,9 @@ __device__ __forceinline__ void bot_restrict(T* bc, T* R, const T* X, const T* B
 // A thread owns the sites p = tid + k BOT_TPB of either colour, so a site's row, plane and wall
 // are found once, and the normals of a pass are loaded while the pass before runs.  A launch per
 // colour pass and transfer of such a grid is all latency: a 16^3 cycle took 75 us in 12 launches
-// and takes 50 in two (noise 4.6, this one 45.5; a sample's export is a third, 4.5), of which the
-// point level 17: a pass 0.55 us, the folded restriction 4.8 (as a residual and its window sums
-// did), the prolongation 1.8.
+// and takes 49 in two (noise 4.6, this one 44.0; a sample's export is a third, 4.5), of which the
+// point level 16: a pass 0.55 us, the folded restriction 3.8 (a residual and its window sums 4.8),
+// the prolongation 1.8.
 constexpr int PT_PER = 4096 / 2 / BOT_TPB;
 template <typename T>
 struct PointSites {
@@ -450,15 +450,14 @@ __device__ __forceinline__ void point_noise(T (&z)[PT_PER], const PointSites<T>&
   for (int k = 0; k < PT_PER; ++k) z[k] = P[S.p[k] < S.nsite ? S.p[k] : 0];
 }
 
-// Sweeps slot0 .. slot0 + nslot - 1; z holds the normals of the first pass (point_noise).
-template <typename T, int KIND>
-__device__ __forceinline__ void point_sweeps(T* X, const T* B, bool has_b, const BotLevel& L,
+// Sweeps slot0 .. slot0 + nslot - 1; z holds the normals of the first pass (point_noise).  VEC: the
+// order of the sums in the colour-pass launches (launch_rb_pass), whose bits these are.
+template <typename T, int KIND, bool VEC>
+__device__ __forceinline__ void point_sweeps_as(T* X, const T* B, bool has_b, const BotLevel& L,
                                              const PointSites<T>& S, T (&z)[PT_PER], gptr<T> Z,
                                              size_t slot_stride, int slot0, int nslot, bool post) {
   constexpr bool NOISE = KIND == CYCLE_NOISE;
   const int nsite = S.nsite;
-  // the order of the sums in the colour-pass launches (launch_rb_pass), whose bits these are
-  const bool vec = (L.nx >> 1) % (16 / (int)sizeof(T)) == 0;
   T dg[10];
 #pragma unroll
   for (int e = 0; e < 10; ++e) dg[e] = (T)L.s1d[e];  // uniform: scalar registers
@@ -480,7 +479,7 @@ __device__ __forceinline__ void point_sweeps(T* X, const T* B, bool has_b, const
       const T sx = xo[own] + xo[ox];
       const T sxy = sx + (xo[S.n[k]] + xo[S.s[k]]);
       T sum;
-      if (vec)
+      if (VEC)
         sum = sxy + fma(xo[S.u[k]], top ? T(0) : T(1), xo[S.d[k]] * (low ? T(0) : T(1)));
       else
         sum = (sxy + (top ? T(0) : xo[S.u[k]])) + (low ? T(0) : xo[S.d[k]]);
@@ -488,15 +487,25 @@ __device__ __forceinline__ void point_sweeps(T* X, const T* B, bool has_b, const
       auto by_walls = [&](T d6, T d7, T d8) { return nw == 0 ? d6 : (nw == 1 ? d7 : d8); };
       const T rhs = has_b ? fma(sum, dg[9], bc[own]) : sum * dg[9];
       const T idg = by_walls(dg[0], dg[1], dg[2]);
-      T v = has_b || !vec ? rhs * idg : sum * by_walls(dg[6], dg[7], dg[8]);
+      T v = has_b || !VEC ? rhs * idg : sum * by_walls(dg[6], dg[7], dg[8]);
       if (NOISE) {
         const T sig = by_walls(dg[3], dg[4], dg[5]);
-        v = vec ? fma(sig, zn[k], v) : fma(rhs, idg, sig * zn[k]);
+        v = VEC ? fma(sig, zn[k], v) : fma(rhs, idg, sig * zn[k]);
       }
       if (S.p[k] < nsite) xc[own] = v;
     }
     __syncthreads();
   }
+}
+
+template <typename T, int KIND>
+__device__ __forceinline__ void point_sweeps(T* X, const T* B, bool has_b, const BotLevel& L,
+                                              const PointSites<T>& S, T (&z)[PT_PER], gptr<T> Z,
+                                              size_t slot_stride, int slot0, int nslot, bool post) {
+  if ((L.nx >> 1) % (16 / (int)sizeof(T)) == 0)
+    point_sweeps_as<T, KIND, true>(X, B, has_b, L, S, z, Z, slot_stride, slot0, nslot, post);
+  else
+    point_sweeps_as<T, KIND, false>(X, B, has_b, L, S, z, Z, slot_stride, slot0, nslot, post);
 }
 
 // R = b - A x in natural layout.
@@ -557,17 +566,18 @@ __device__ __forceinline__ T point_restrict(const T* R, int nx, int ny, int nz, 
 // planes of a layer.  R (n elements) holds first u, s on (nx/2, ny, nz), then p, q on (nx/2, ny/2, nz).
 template <typename T>
 __device__ __forceinline__ void point_fold(T* bc, T* R, const T* X, const T* B, bool has_b,
-                                           const BotLevel& L) {
+                                           const BotLevel& L, const PointSites<T>& S) {
   const int nh = L.nx >> 1, ny = L.ny, nz = L.nz, nyc = ny >> 1, nzc = nz >> 1;
-  const int tid = (int)threadIdx.x, nsite = nh * ny * nz, half = nsite >> 1, col = nh * nyc;
+  const int tid = (int)threadIdx.x, nsite = S.nsite, half = nsite >> 1, col = nh * nyc;
   const T ih2 = (T)L.s1d[9];
   const T q1 = T(0.25), q3 = T(0.75), d1 = T(0.25) * ih2, d2 = T(0.5) * ih2;
-  for (int it = tid; it < nsite; it += BOT_TPB) {
-    int row, j, z, y;
-    divmod_uniform(it, nh, row, j);
-    divmod_uniform(row, ny, z, y);
-    const int odd = (y + z) & 1, l = j == 0 ? it + nh - 1 : it - 1, r = j + 1 == nh ? it - j : it + 1;
+#pragma unroll
+  for (int k = 0; k < PT_PER; ++k) {
+    const int it = S.p[k];
+    if (it >= nsite) break;
     // even cells 2j of the row are entries of colour (y + z) & 1, odd ones of the other
+    const int odd = S.nat[k][0] & 1;
+    const int l = odd ? S.o[k][1] : S.o[k][0], r = odd ? S.o[k][0] : S.o[k][1];
     const T *E = X + odd * nsite, *O = X + (1 - odd) * nsite;
     const T m = E[it] + O[it], n = O[l] + E[r];
     T s = fma(d1, n + (E[l] + O[r]), -d2 * m);
@@ -753,7 +763,7 @@ __device__ __forceinline__ void bottom_body(const BotArgs& a, const uint32_t com
     T* bc = xc + C.nz * C.sz;
     for (int q = tid; q < C.nz * C.sz; q += BOT_TPB) xc[q] = T(0);
     if (!index_order<T, KIND> && (L0.nx >> 1) % 2 == 0) {
-      point_fold<T>(bc, X + 2 * n0, X, X + n0, has_b, L0);
+      point_fold<T>(bc, X + 2 * n0, X, X + n0, has_b, L0, ps);
     } else {
       point_residual<T>(X + 2 * n0, X, X + n0, has_b, L0, ps);
       __syncthreads();
